@@ -103,6 +103,8 @@ struct choco_ctx {
   bool multipart;         // long candidate lists: the select runs as three multi-block launches
   bool fallback_chain;    // long rows: a failed guess is repaired by the histogram passes, not a row scan
   bool nt;                // non-temporal loads/stores: the state does not fit in cache anyway
+  bool narrow_tile;       // the mix takes tiles of 64 columns (n > 8, rows on whole lines)
+  bool nt_tile;           // ... and streams past the caches
   int nlayers;            // > 0: the operator is applied layer by layer
   bool layers_generic;    // ... on a table that is not aligned (see layers_aligned): no pass carries the local update
   int nmid, nsmall;       // layers (by falling length, after the long ones) that take a 1024- / a 256-thread workgroup
@@ -693,10 +695,40 @@ void launch_apply_mix(choco_ctx* ctx, const Args& A) {
 #undef CALL
 }
 
+// The mix (with SPARSE: and the update of xhat) of more than eight workers whose rows start on whole
+// lines: tiles of 64 columns.  NT: streamed past the caches from 48 MB per array on, also where the
+// passes before it go through them: nothing of this step reads x or xhat again, and written through
+// the caches they push out what the next pass has to read (64 rows of 270,000, three contexts in
+// turn: top_a 109 -> 99 us per step, random_a 91 -> 70; one context alone, everything still cached
+// from the step before: 96 -> 100, 67 -> 70; at 33 MB 54 against 55).
+template <bool NT, bool SPARSE>
+void launch_tile_mix_narrow(choco_ctx* ctx, const Args& A, int kid) {
+  const dim3 grid((unsigned)((A.d + kNarrowCols - 1) / kNarrowCols));
+  const size_t lds = (size_t)A.n * kNarrowCols * sizeof(float) +
+                     (A.staged_nnz ? (size_t)A.staged_nnz * sizeof(float2) + (size_t)(A.n + 1) * sizeof(int) : 0);
+  // a 4-vector per thread up to 32 rows, two above; workgroups of no more than four idle rows up to
+  // 24, of eight above (half-idle workgroups of 512 threads at n = 20: 33.5 against 32.0 us per step)
+#define CALL(V, T) LAUNCH(ctx, kid, (k_tile_mix_narrow<V, T, NT, SPARSE>), grid, dim3(T), lds, A)
+  if (A.n <= 12) CALL(1, 192);
+  else if (A.n <= 16) CALL(1, 256);
+  else if (A.n <= 20) CALL(1, 320);
+  else if (A.n <= 24) CALL(1, 384);
+  else if (A.n <= 32) CALL(1, 512);
+  else if (A.n <= 40) CALL(2, 320);
+  else if (A.n <= 48) CALL(2, 384);
+  else CALL(2, 512);
+#undef CALL
+}
+
 template <int STAT, bool NT, bool SPARSE = false>
 void launch_tile_mix(choco_ctx* ctx, const Args& A, bool fused) {
-  const size_t lds = (size_t)A.n * kChunk * sizeof(float);
   const int kid = fused ? KID_TILE_MIX_SGD : KID_TILE_MIX;
+  if (STAT == Q_NONE && ctx->narrow_tile) {
+    if (ctx->nt_tile) launch_tile_mix_narrow<true, SPARSE>(ctx, A, kid);
+    else launch_tile_mix_narrow<false, SPARSE>(ctx, A, kid);
+    return;
+  }
+  const size_t lds = (size_t)A.n * kChunk * sizeof(float);
   const dim3 grid((unsigned)A.nchunks), block(A.n <= 8 ? 512 : A.n <= 16 ? 256 : 1024);
 #define CALL(R, W) LAUNCH(ctx, kid, (k_tile_mix<STAT, R, W, NT, SPARSE>), grid, block, lds, A)
   TILE_SWITCH(A.n, ctx->rpw, CALL)
@@ -1479,6 +1511,15 @@ int choco_init(const choco_config* cfg, float* x_dev, void* workspace_dev, size_
   const size_t state_bytes = (size_t)cfg->n * (size_t)resolve_ld(*cfg) * sizeof(float);
   const bool cache_resident = state_bytes >= ((size_t)12 << 20) && state_bytes <= ((size_t)96 << 20);
   ctx->nt = state_bytes >= ((size_t)4 << 20) && !cache_resident;
+  // narrow tiles want rows that start on whole 128-byte lines: off them a tile's 256-byte pieces touch
+  // three lines instead of two (64 rows of 2,000,001: 639 against 534 us; 32 rows of 540,001: 124
+  // against 121; aligned: 455 against 471).  One range stays with the wide tile: top_a through the
+  // caches from 24 MB on, whose candidate pass leaves x and xhat there in long pieces (33 MB: 51.6
+  // against 53.1; 16 MB: 34.9 against 33.4; random_a, no pass before it, 33 MB: 36.4 against 35.2).
+  ctx->nt_tile = ctx->nt || state_bytes >= ((size_t)48 << 20);
+  const bool warm = cfg->compressor == CHOCO_Q_TOPK && !ctx->nt_tile && state_bytes >= ((size_t)24 << 20);
+  ctx->narrow_tile = cfg->n > 8 && cfg->n <= kMaxTileRows && resolve_ld(*cfg) % 32 == 0 &&
+                     ((uintptr_t)x_dev & 127u) == 0 && !warm;
   ctx->t = 0;
   ctx->last_hip_error = 0;
   ctx->profiling = false;
@@ -1497,6 +1538,7 @@ int choco_init(const choco_config* cfg, float* x_dev, void* workspace_dev, size_
   A.row_ptr = (const int32_t*)(base + L.row_ptr);
   A.col = (const int32_t*)(base + L.col);
   A.w = (const float*)(base + L.w);
+  A.staged_nnz = nnz <= kStagedNnz ? nnz : 0;
   A.ctl = (WorkerCtl*)(base + L.ctl);
   // polls of about 2 us each: a tenth of a second before a workgroup of the fallback stops waiting
   // for its worker's others (CHOCO_FALLBACK_SPIN_LIMIT: for tests of that path, which scans the row)

@@ -125,6 +125,7 @@ struct Args {
   const int32_t* row_ptr;
   const int32_t* col;
   const float* w;
+  int32_t staged_nnz;   // entries of W when its rows fit beside the narrow tile in LDS, else 0
   WorkerCtl* ctl;
   float gamma;
   // fused local update (choco_step): when G is non-null the first pass over X of the step
@@ -1110,6 +1111,127 @@ __global__ __launch_bounds__(64 * NW) void k_tile_mix(Args A) {
         t = wave_tree_sum(t);
         if (lane == 0) A.chunk_sums[(int64_t)r * A.nchunks + blockIdx.x] = t;
       }
+    }
+  }
+}
+
+// The same pass for more than eight workers (no norm sums): a tile of 64 columns, sixteen lanes to
+// a row, four rows of a wave side by side.  What bounds the 256-column tile above at n = 64 is its
+// 1024-thread workgroups (two to a compute unit, each a load - barrier - mix - store sequence, four
+// rows of x in the registers of every thread); a quarter of the columns makes workgroups of 256 or
+// 512 threads with VPT = one or two 4-vectors per thread, all loads of a thread in flight at once,
+// and four of them to a unit whose phases overlap.  W's rows differ between the lanes of a wave, so
+// the CSR rows are staged in LDS beside the tile (up to kStagedNnz entries, else read from memory).
+//   stand-alone, 64 rows of 270,000, random 1 % kept, with the local update, three states in turn:
+//   256 columns x 1024 threads x 4: 82.8 us cached, 73.3 streamed;  128 x 1024 x 2: 60.1;
+//   64 x 512 x 2: 58.8;  64 x 1024 x 1: 59.7;  64 x 256 x 4: 62.1;  32 columns: 59.5
+//   16 rows of 1,080,000: 256 x 256 x 4: 67.4 cached, 59.4 streamed;  64 x 256 x 1: 51.6
+// A line of xhat that holds a kept entry is stored whole (the eight lanes that share a word of kept
+// bits store their 4-vectors; 128 bytes where rows are aligned) instead of the 4-vectors that
+// changed: partly written lines cost more than the bytes saved (58.8 -> 54.4 us).
+constexpr int kNarrowCols = 64;
+constexpr int kStagedNnz = 1024;
+
+// Sixteen neighbouring tiles (4 KiB of every row) on one die, one after the other (workgroups go to
+// the dies in turn); the last, partial group of 128 is left as it is.
+__device__ __forceinline__ int die_run_tile(int b, int ntiles) {
+  const int base = b & ~127;
+  if (base + 128 > ntiles) return b;
+  return base + ((b & 7) << 4) + ((b >> 3) & 15);
+}
+
+template <int VPT, int TH, bool NT, bool SPARSE>
+__global__ __launch_bounds__(TH) void k_tile_mix_narrow(Args A) {
+  extern __shared__ float tile[];
+  constexpr int LPR = kNarrowCols / 4, RS = TH / LPR;   // lanes per row, rows side by side
+  float2* nbr = reinterpret_cast<float2*>(tile + A.n * kNarrowCols);       // (tile row of the neighbour, weight)
+  int* rowp = reinterpret_cast<int*>(nbr + A.staged_nnz);                  // n + 1
+  const int lr = threadIdx.x % LPR, r0 = threadIdx.x / LPR;
+  const int e = die_run_tile((int)blockIdx.x, (int)gridDim.x) * kNarrowCols + lr * 4;
+  const bool valid = e < A.d;
+  const bool sgd = A.G != nullptr, mom = sgd && A.M != nullptr;
+  vf4 x[VPT], xhv[VPT], gv[VPT], mv[VPT];
+  uint32_t word[VPT];
+#pragma unroll
+  for (int u = 0; u < VPT; ++u) {
+    const int r = r0 + u * RS;
+    word[u] = 0u;
+    if (r < A.n && valid) {
+      const int64_t o = (int64_t)r * A.ld + e;
+      x[u] = load4<NT>(A.X + o);
+      xhv[u] = load4<NT>(A.Xhat + o);
+      if (sgd) gv[u] = load4<true>(A.G + o);   // a gradient is read once: always streamed
+      if (mom) mv[u] = load4<NT>(A.M + o);
+      if (SPARSE)
+        word[u] = A.bitmap_words ? A.bitmap[(int64_t)r * A.bitmap_words + ((uint32_t)e >> 5)]
+                                 : A.keptmap[(int64_t)r * A.map_words + ((uint32_t)e >> 5)];
+    }
+  }
+  if (A.staged_nnz) {
+    for (int p = threadIdx.x; p < A.staged_nnz; p += TH)
+      nbr[p] = make_float2(__int_as_float(A.col[p] * kNarrowCols), A.w[p]);
+    for (int r = threadIdx.x; r <= A.n; r += TH) rowp[r] = A.row_ptr[r];
+  }
+#pragma unroll
+  for (int u = 0; u < VPT; ++u) {
+    const int r = r0 + u * RS;
+    if (r < A.n) {
+      vf4 xh = {0.f, 0.f, 0.f, 0.f};
+      if (valid) {
+        const int64_t o = (int64_t)r * A.ld + e;
+        xh = xhv[u];
+        if (sgd) {
+          x[u] = local_update_regs(A, x[u], gv[u], mv[u]);
+          if (mom) store4<NT>(A.M + o, mv[u]);
+        }
+        if (SPARSE && word[u] != 0u) {
+          const uint32_t bits = (word[u] >> ((uint32_t)e & 31u)) & 0xFu;
+          if (bits) {
+            vf4 q = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+              if ((bits >> c) & 1u) {
+                q[c] = x[u][c] - xh[c];
+                if (A.randk_rescale) q[c] = randk_scale_at(A, e + c) * q[c];
+                xh[c] = xh[c] + q[c];
+              }
+            if (A.Qv) store4<false>(A.Qv + o, q);   // (only kept entries are ever read there)
+          }
+          store4<false>(A.Xhat + o, xh);
+          // eight lanes of the wave share the word; every one of them has loaded it by now
+          if (!A.bitmap_words && (lr & 7) == 0) A.keptmap[(int64_t)r * A.map_words + ((uint32_t)e >> 5)] = 0u;
+        }
+      }
+      lds_store4(tile + r * kNarrowCols + lr * 4, xh);
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < VPT; ++u) {
+    const int r = r0 + u * RS;
+    if (r < A.n && valid) {
+      const vf4 me = lds_load4(tile + r * kNarrowCols + lr * 4);
+      vf4 acc = {0.f, 0.f, 0.f, 0.f};
+      if (A.staged_nnz) {
+        const int pend = rowp[r + 1];
+        for (int p = rowp[r]; p < pend; ++p) {           // neighbours in the order of the CSR row
+          const float2 jw = nbr[p];
+          const vf4 o = lds_load4(tile + __float_as_int(jw.x) + lr * 4);
+#pragma unroll
+          for (int c = 0; c < 4; ++c) acc[c] = acc[c] + jw.y * (o[c] - me[c]);
+        }
+      } else {
+        const int pend = A.row_ptr[r + 1];
+        for (int p = A.row_ptr[r]; p < pend; ++p) {
+          const float wj = A.w[p];
+          const vf4 o = lds_load4(tile + A.col[p] * kNarrowCols + lr * 4);
+#pragma unroll
+          for (int c = 0; c < 4; ++c) acc[c] = acc[c] + wj * (o[c] - me[c]);
+        }
+      }
+#pragma unroll
+      for (int c = 0; c < 4; ++c) x[u][c] = x[u][c] + A.gamma * acc[c];
+      store4<NT>(A.X + (int64_t)r * A.ld + e, x[u]);
     }
   }
 }

@@ -1,0 +1,48 @@
+"""GPU parity of the mix's tile shapes at the edges of their ranges: worker counts at which the
+workgroup shape changes, columns around the end of a tile, rows of W beyond what a tile stages."""
+import numpy as np
+import pytest
+
+from paper_1907_09356_amd import binding as B
+from paper_1907_09356_amd import synth
+from tests.parity_util import Pair
+
+pytestmark = pytest.mark.gpu
+
+
+def walk(n, d, topo, comp, steps=3, momentum=False, ld_align=32, **kw):
+    """A few fused iterations, the state compared bit for bit after each."""
+    pair = Pair(synth.normal_state(n, d, seed=n + d), topo, 0.2, comp, seed=5, ld_align=ld_align, **kw)
+    grads = synth.GradientStream(n, d, seed=n)
+    for t in range(steps):
+        g = grads.next()
+        det = pair.step_momentum(g, 0.1, 0.9, 1e-3) if momentum else pair.step(g, 0.1)
+        pair.check(det, tag="n=%d d=%d step %d" % (n, d, t))
+    pair.close()
+
+
+@pytest.mark.parametrize("n", [9, 12, 13, 16, 17, 20, 21, 24, 25, 32, 33, 40, 41, 48, 49, 64])
+@pytest.mark.parametrize("comp", [B.Q_TOPK, B.Q_RANDK])
+def test_narrow_tile_by_number_of_workers(n, comp):
+    d = 64 * 9 + (n * 7) % 64           # the last tile is cut anywhere
+    walk(n, d, synth.ring_csr(n), comp, k=max(1, d // 20), momentum=n % 2 == 0, randk_rescale=int(comp == B.Q_RANDK and n % 3 == 0))
+
+
+@pytest.mark.parametrize("d", [1, 63, 64, 65, 127, 128, 129, 64 * 128 - 1, 64 * 128 + 1, 64 * 300 + 3])
+@pytest.mark.parametrize("comp,order", [(B.Q_TOPK, B.ORDER_COMPRESS_THEN_MIX), (B.Q_RANDK, B.ORDER_COMPRESS_THEN_MIX),
+                                        (B.Q_RANDK, B.ORDER_MIX_THEN_COMPRESS)])
+def test_narrow_tile_by_columns(d, comp, order):
+    """Around one tile, and around the 128 tiles that share out eight dies."""
+    walk(16, d, synth.torus_csr(4, 4), comp, k=max(1, d // 30), order=order)
+
+
+@pytest.mark.parametrize("n", [31, 33, 64])
+def test_narrow_tile_with_more_neighbours_than_it_stages(n):
+    """The complete graph: 961 entries of W (staged), 1,089 and 4,096 (read from memory)."""
+    walk(n, 300, synth.complete_csr(n), B.Q_TOPK, k=10)
+
+
+@pytest.mark.parametrize("n,d,align", [(64, 17_000, 32), (16, 66_000, 32), (12, 90_001, 4)])
+def test_mix_of_a_state_that_is_streamed(n, d, align):
+    """Past the caches (4 to 12 MB per array), on whole lines and off them (the wide tile)."""
+    walk(n, d, synth.ring_csr(n), B.Q_TOPK, steps=2, k=d // 100, ld_align=align)
