@@ -658,40 +658,58 @@ dim3 chunk_grid(int32_t nvec, int32_t n, int vecs) {
   return dim3((unsigned)(((int64_t)nvec + per_block - 1) / per_block), (unsigned)n, 1);
 }
 
-// Tile kernels: waves per block (8 up to 8 workers - a row per wave measured 4 % faster than
-// two -, 4 up to 16, else 16) and rows per wave.  (n = 64 with 8-wave workgroups of 8 rows per
-// wave, which leave half of a compute unit's wave slots free: the mix pass 55 against 43 us.)
-int pick_rpw(int n) {
-  if (n > kMaxTileRows) return 0;
-  const int nw = n <= 8 ? 8 : n <= 16 ? 4 : 16;
-  const int rows = (n + nw - 1) / nw;
-  return rows <= 1 ? 1 : rows <= 2 ? 2 : 4;
+// Tile kernels of 256 columns: a row per wave up to 16 workers (at 8 workers 4 % faster than two
+// rows; 16 rows of 1,080,000: 16 waves of one row 54.7 us, 4 waves of four 59.4), above that 16
+// waves of two or four rows.  Nine to twelve rows would leave a third of a compute unit's wave slots
+// free that way (768-thread workgroups): with tiles enough to fill the chip they take four waves of
+// up to four rows (9 rows of 270,000, sign: 21.2 against 21.8 us per step; 8 tiles, 9 rows of 2,000,
+// where a workgroup's own chain is all there is: 10.8 against 8.5).
+int pick_rpw(int n) { return n > kMaxTileRows ? 0 : n <= 16 ? 1 : n <= 32 ? 2 : 4; }
+bool four_by_four(const Args& A) { return A.n > 8 && A.n <= 12 && A.nchunks >= 512; }
+dim3 tile_block(const Args& A) { return dim3(A.n <= 8 ? 512 : four_by_four(A) ? 256 : A.n <= 12 ? 768 : 1024); }
+
+#define TILE_SWITCH(A, CALL)          \
+  if ((A).n <= 8) {                   \
+    CALL(1, 8);                       \
+  } else if (four_by_four(A)) {       \
+    CALL(4, 4);                       \
+  } else if ((A).n <= 12) {           \
+    CALL(1, 12);                      \
+  } else if ((A).n <= 16) {           \
+    CALL(1, 16);                      \
+  } else if ((A).n <= 32) {           \
+    CALL(2, 16);                      \
+  } else {                            \
+    CALL(4, 16);                      \
+  }
+
+size_t narrow_lds(const Args& A) {
+  return (size_t)A.n * kNarrowCols * sizeof(float) +
+         (A.staged_nnz ? (size_t)A.staged_nnz * sizeof(float2) + (size_t)(A.n + 1) * sizeof(int) : 0);
 }
 
-#define TILE_SWITCH(n, rpw, CALL)                      \
-  if ((n) <= 8) {                                      \
-    CALL(1, 8);                                        \
-  } else if ((n) <= 16) {                                     \
-    switch (rpw) {                                     \
-      case 1: CALL(1, 4); break;                       \
-      case 2: CALL(2, 4); break;                       \
-      default: CALL(4, 4); break;                      \
-    }                                                  \
-  } else {                                             \
-    switch (rpw) {                                     \
-      case 1: CALL(1, 16); break;                      \
-      case 2: CALL(2, 16); break;                      \
-      default: CALL(4, 16); break;                     \
-    }                                                  \
-  }
+template <int COMP, bool NT, bool LAYERED>
+void launch_apply_mix_narrow(choco_ctx* ctx, const Args& A) {
+  const dim3 grid((unsigned)((A.d + kNarrowCols - 1) / kNarrowCols));
+#define CALL(V, T) LAUNCH(ctx, KID_DENSE_APPLY_MIX, (k_dense_apply_mix_narrow<COMP, V, T, NT, LAYERED>), grid, dim3(T), narrow_lds(A), A)
+  if (A.n <= 16) CALL(1, 256);
+  else if (A.n <= 32) CALL(1, 512);
+  else CALL(2, 512);
+#undef CALL
+}
 
 template <int COMP, bool CAPTURE, bool NT, bool LAYERED = false>
 void launch_apply_mix(choco_ctx* ctx, const Args& A) {
-  const dim3 grid((unsigned)A.nchunks), block(A.n <= 8 ? 512 : A.n <= 16 ? 256 : 1024);
+  if (ctx->narrow_tile && (LAYERED || !A.fold_finalise)) {
+    if (ctx->nt_tile) launch_apply_mix_narrow<COMP, true, LAYERED>(ctx, A);
+    else launch_apply_mix_narrow<COMP, false, LAYERED>(ctx, A);
+    return;
+  }
+  const dim3 grid((unsigned)A.nchunks), block = tile_block(A);
   const size_t lds = (size_t)A.n * kChunk * sizeof(float);
 #define CALL(R, W) \
   LAUNCH(ctx, KID_DENSE_APPLY_MIX, (k_dense_apply_mix<COMP, R, W, CAPTURE, NT, LAYERED>), grid, block, lds, A)
-  TILE_SWITCH(A.n, ctx->rpw, CALL)
+  TILE_SWITCH(A, CALL)
 #undef CALL
 }
 
@@ -704,8 +722,7 @@ void launch_apply_mix(choco_ctx* ctx, const Args& A) {
 template <bool NT, bool SPARSE>
 void launch_tile_mix_narrow(choco_ctx* ctx, const Args& A, int kid) {
   const dim3 grid((unsigned)((A.d + kNarrowCols - 1) / kNarrowCols));
-  const size_t lds = (size_t)A.n * kNarrowCols * sizeof(float) +
-                     (A.staged_nnz ? (size_t)A.staged_nnz * sizeof(float2) + (size_t)(A.n + 1) * sizeof(int) : 0);
+  const size_t lds = narrow_lds(A);
   // a 4-vector per thread up to 32 rows, two above; workgroups of no more than four idle rows up to
   // 24, of eight above (half-idle workgroups of 512 threads at n = 20: 33.5 against 32.0 us per step)
 #define CALL(V, T) LAUNCH(ctx, kid, (k_tile_mix_narrow<V, T, NT, SPARSE>), grid, dim3(T), lds, A)
@@ -729,9 +746,9 @@ void launch_tile_mix(choco_ctx* ctx, const Args& A, bool fused) {
     return;
   }
   const size_t lds = (size_t)A.n * kChunk * sizeof(float);
-  const dim3 grid((unsigned)A.nchunks), block(A.n <= 8 ? 512 : A.n <= 16 ? 256 : 1024);
+  const dim3 grid((unsigned)A.nchunks), block = tile_block(A);
 #define CALL(R, W) LAUNCH(ctx, kid, (k_tile_mix<STAT, R, W, NT, SPARSE>), grid, block, lds, A)
-  TILE_SWITCH(A.n, ctx->rpw, CALL)
+  TILE_SWITCH(A, CALL)
 #undef CALL
 }
 
@@ -761,11 +778,24 @@ void launch_mix_direct_global(choco_ctx* ctx, const Args& A) {
 // in the step (it may carry the fused local update, F.G != nullptr) and `A` the block for
 // every later kernel (A.G == nullptr).
 
+// Will the apply pass of a fused step with plain SGD read g and form x - lr g a second time instead
+// of the norm pass storing it?  The bytes are the same, but a store costs the stream more than a load
+// (896 MB arrays: 3 reads 382 us, 3 reads and 1 write 577; 2 + 2 615, 3 + 2 745).  Where the state is
+// streamed past the caches: n = 8, d = 28 M sign 1171 -> 1141 us per step, gsgd 1248 -> 1234; d = 270 k
+// 18.5 -> 17.6.  Read through the caches the stored x is found there and g is not: n = 64, d = 270 k
+// sign 88.6 against 90.4, n = 16, d = 1.08 M gsgd 94.5 against 101.  With momentum m would be read twice too.
+bool redo_sgd(const choco_ctx* ctx, const Args& F) {
+  const int comp = ctx->cfg.compressor;
+  return ctx->nt && F.G != nullptr && F.M == nullptr && (comp == CHOCO_Q_SIGN || comp == CHOCO_Q_QSGD) &&
+         ctx->rpw != 0 && ctx->cfg.order == CHOCO_ORDER_COMPRESS_THEN_MIX;
+}
+
 // Dense operators (identity, sign, gsgd), direct mix form.
 template <int COMP, bool NT>
-int gossip_dense(choco_ctx* ctx, const Args& F) {
-  Args A = F;
+int gossip_dense(choco_ctx* ctx, const Args& F0) {
+  Args F = F0, A = F0;
   A.G = nullptr;
+  F.redo_sgd = redo_sgd(ctx, F) ? 1 : 0;
   const bool fused = F.G != nullptr;
   constexpr bool needs_stat = (COMP == Q_SIGN || COMP == Q_QSGD);
   constexpr int STAT = needs_stat ? COMP : Q_NONE;
@@ -779,6 +809,7 @@ int gossip_dense(choco_ctx* ctx, const Args& F) {
         LAUNCH(ctx, KID_DENSE_FINALISE, (k_dense_finalise<STATK>), dim3((unsigned)A.n), dim3(256), 0, A);
     }
     if (ctx->rpw) {
+      if (F.redo_sgd) A.G = F.G;
       if (A.codes) launch_apply_mix<COMP, true, NT>(ctx, A);
       else launch_apply_mix<COMP, false, NT>(ctx, A);
     } else {
@@ -1042,9 +1073,10 @@ int gossip_sparse(choco_ctx* ctx, const Args& F) {
 // Layer-wise sign / gsgd: the whole-row pipeline with per-layer norms (norm pass over
 // (layer, group) work items, per-layer scales, apply kernels that look the scale up by layer).
 template <int COMP, bool NT>
-int gossip_layers_dense(choco_ctx* ctx, const Args& F) {
-  Args A = F;
+int gossip_layers_dense(choco_ctx* ctx, const Args& F0) {
+  Args F = F0, A = F0;
   A.G = nullptr;
+  F.redo_sgd = redo_sgd(ctx, F) ? 1 : 0;
   const bool fused = F.G != nullptr;
   const bool mix_first = ctx->cfg.order == CHOCO_ORDER_MIX_THEN_COMPRESS;
   bool x_touched = false;
@@ -1058,6 +1090,7 @@ int gossip_layers_dense(choco_ctx* ctx, const Args& F) {
          dim3((unsigned)A.ngroup_items, (unsigned)A.n), dim3(stat_threads(NT)), 0, C);
   LAUNCH(ctx, KID_LAYER_FINALISE, (k_layer_finalise<COMP>), dim3((unsigned)A.nlayers, (unsigned)A.n), dim3(256), 0, A);
   if (!mix_first && ctx->rpw) {
+    if (F.redo_sgd) A.G = F.G;
     if (A.codes) launch_apply_mix<COMP, true, NT, true>(ctx, A);
     else launch_apply_mix<COMP, false, NT, true>(ctx, A);
   } else {
@@ -1556,8 +1589,10 @@ int choco_init(const choco_config* cfg, float* x_dev, void* workspace_dev, size_
     A.tau = 1.0 + std::min(dd / (s * s), std::sqrt(dd) / s);
   }
   A.codes = nullptr;
-  // with few group sums the fused apply kernel finishes the norm tree itself (one launch less)
-  A.fold_finalise = (ctx->rpw != 0 && cfg->order == CHOCO_ORDER_COMPRESS_THEN_MIX && L.ngroups <= 256) ? 1 : 0;
+  // with few group sums the fused apply kernel finishes the norm tree itself (one launch less), a row
+  // per wave; above 16 workers a wave would finish several rows one after the other in every tile
+  // (n = 64, d = 270 k sign: 137 against 90 us per step with the launch and the narrow tile)
+  A.fold_finalise = (ctx->rpw != 0 && cfg->order == CHOCO_ORDER_COMPRESS_THEN_MIX && L.ngroups <= 256 && cfg->n <= 16) ? 1 : 0;
   A.k = kept_per_worker(*cfg);
   A.hist16 = (uint32_t*)(base + L.hist16);
   A.cand = (uint2*)(base + L.cand);

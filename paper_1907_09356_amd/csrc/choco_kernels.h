@@ -135,6 +135,8 @@ struct Args {
   float* M;              // momentum memory (Algorithm 2) or null for plain SGD
   float beta, lambda;    // momentum factor and weight decay of Algorithm 2
   int32_t deferred_sgd;  // the local update is applied by the LAST kernel of the step (random_a)
+  int32_t redo_sgd;      // dense operators, plain SGD: the norm pass forms x - lr g without storing it and
+                         // the apply pass, which reads x anyway, forms it again
   // dense operators
   double* chunk_sums;  // n x nchunks first-level sums (only the printed-order tile kernel writes them)
   double* group_sums;  // n x ngroups second-level sums
@@ -783,7 +785,7 @@ __global__ __launch_bounds__(stat_threads(NT)) void k_dense_stat(Args A) {
         if (A.M) mm = load4<NT>(A.M + (int64_t)i * A.ld + e[u]);
         a[u] = local_update_regs(A, a[u], g[u], mm);
         if (A.M) store4<NT>(A.M + (int64_t)i * A.ld + e[u], mm);
-        store4<NT>(xw + e[u], a[u]);
+        if (!NT || !A.redo_sgd) store4<NT>(xw + e[u], a[u]);
       }
     }
   }
@@ -933,6 +935,55 @@ __device__ __forceinline__ void tile_mix_rows(const Args& A, const float* tile, 
   }
 }
 
+// ---- tiles of 64 columns: what their kernels share (k_tile_mix_narrow says why the shape) ----
+constexpr int kNarrowCols = 64;
+constexpr int kStagedNnz = 1024;
+
+// Sixteen neighbouring tiles (4 KiB of every row) on one die, one after the other (workgroups go to
+// the dies in turn); the last, partial group of 128 is left as it is.
+__device__ __forceinline__ int die_run_tile(int b, int ntiles) {
+  const int base = b & ~127;
+  if (base + 128 > ntiles) return b;
+  return base + ((b & 7) << 4) + ((b >> 3) & 15);
+}
+
+// The rows of W into LDS: (where the neighbour's row starts in the tile, its weight) per entry, and
+// the row pointers.  (Callers synchronise.)
+template <int TH>
+__device__ __forceinline__ void stage_rows_of_w(const Args& A, float2* nbr, int* rowp) {
+  if (A.staged_nnz) {
+    for (int p = threadIdx.x; p < A.staged_nnz; p += TH)
+      nbr[p] = make_float2(__int_as_float(A.col[p] * kNarrowCols), A.w[p]);
+    for (int r = threadIdx.x; r <= A.n; r += TH) rowp[r] = A.row_ptr[r];
+  }
+}
+
+// x += gamma sum_p w_p (xhat_j - xhat_i) on one 4-vector of row r, neighbours in the order of the CSR row.
+__device__ __forceinline__ void narrow_mix(const Args& A, const float* tile, const float2* nbr, const int* rowp, int r,
+                                           int lr, vf4& x) {
+  const vf4 me = lds_load4(tile + r * kNarrowCols + lr * 4);
+  vf4 acc = {0.f, 0.f, 0.f, 0.f};
+  if (A.staged_nnz) {
+    const int pend = rowp[r + 1];
+    for (int p = rowp[r]; p < pend; ++p) {
+      const float2 jw = nbr[p];
+      const vf4 o = lds_load4(tile + __float_as_int(jw.x) + lr * 4);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) acc[c] = acc[c] + jw.y * (o[c] - me[c]);
+    }
+  } else {
+    const int pend = A.row_ptr[r + 1];
+    for (int p = A.row_ptr[r]; p < pend; ++p) {
+      const float wj = A.w[p];
+      const vf4 o = lds_load4(tile + A.col[p] * kNarrowCols + lr * 4);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) acc[c] = acc[c] + wj * (o[c] - me[c]);
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < 4; ++c) x[c] = x[c] + A.gamma * acc[c];
+}
+
 // LAYERED: the operator is applied layer by layer; the scales come per (worker, layer) from
 // the layer-wise norm pass.
 template <int COMP, int RPW, int NW, bool CAPTURE, bool NT, bool LAYERED>
@@ -945,7 +996,7 @@ __global__ __launch_bounds__(64 * NW) void k_dense_apply_mix(Args A) {
   int lay = 0, nvalid = A.d - e < 4 ? A.d - e : 4;   // the last 4-vector of a row may end in pad columns
   const bool generic = LAYERED && A.layers_generic;   // a 4-vector may span layers and gaps: scales entry by entry
   if (LAYERED && valid && !generic) lay = layer_of_vector(A, e, nvalid);
-  vf4 xr[RPW], xh[RPW];
+  vf4 xr[RPW], xh[RPW], g[RPW];
 #pragma unroll
   for (int q = 0; q < RPW; ++q) {
     const int r = wave + NW * q;
@@ -953,6 +1004,7 @@ __global__ __launch_bounds__(64 * NW) void k_dense_apply_mix(Args A) {
       const int64_t o = (int64_t)r * A.ld + e;
       xr[q] = load4<NT>(A.X + o);
       xh[q] = load4<NT>(A.Xhat + o);
+      if (NT && A.G) g[q] = load4<true>(A.G + o);   // (redo_sgd; streamed states only)
     }
   }
   // scales of this wave's rows: read from the control block, or (few group sums) finished here
@@ -979,6 +1031,10 @@ __global__ __launch_bounds__(64 * NW) void k_dense_apply_mix(Args A) {
       vi4 code = {0, 0, 0, 0};
       if (valid) {
         const int64_t o = (int64_t)r * A.ld + e;
+        if (NT && A.G) {   // the local update that the norm pass formed and did not store
+#pragma unroll
+          for (int c = 0; c < 4; ++c) xr[q][c] = xr[q][c] - A.lr * g[q][c];
+        }
         uint4 words = make_uint4(0, 0, 0, 0);
         if (COMP == Q_QSGD) words = random_words(A, r, (uint32_t)(e >> 2), STREAM_DITHER);
         if (generic) {
@@ -1000,6 +1056,73 @@ __global__ __launch_bounds__(64 * NW) void k_dense_apply_mix(Args A) {
   for (int q = 0; q < RPW; ++q) {
     const int r = wave + NW * q;
     if (r < A.n && valid) store4<NT>(A.X + (int64_t)r * A.ld + e, xr[q]);
+  }
+}
+
+// The same pass in tiles of 64 columns (see k_tile_mix_narrow for the shape; the scales come from
+// memory: a wave holds four rows, so the tree's last level would be done for each of them in turn).
+template <int COMP, int VPT, int TH, bool NT, bool LAYERED>
+__global__ __launch_bounds__(TH) void k_dense_apply_mix_narrow(Args A) {
+  extern __shared__ float tile[];
+  constexpr int LPR = kNarrowCols / 4, RS = TH / LPR;   // lanes per row, rows side by side
+  float2* nbr = reinterpret_cast<float2*>(tile + A.n * kNarrowCols);
+  int* rowp = reinterpret_cast<int*>(nbr + A.staged_nnz);
+  const int lane = threadIdx.x & 63, lr = threadIdx.x % LPR, r0 = threadIdx.x / LPR;
+  const int e = die_run_tile((int)blockIdx.x, (int)gridDim.x) * kNarrowCols + lr * 4;
+  const bool valid = e < A.d;
+  int lay = 0, nvalid = A.d - e < 4 ? A.d - e : 4;
+  const bool generic = LAYERED && A.layers_generic;
+  if (LAYERED && valid && !generic) lay = layer_of_vector(A, e, nvalid);
+  vf4 x[VPT], xh[VPT], g[VPT];
+  RowScale<COMP> sc[VPT];
+#pragma unroll
+  for (int u = 0; u < VPT; ++u) {
+    const int r = r0 + u * RS;
+    if (r < A.n && valid) {
+      const int64_t o = (int64_t)r * A.ld + e;
+      x[u] = load4<NT>(A.X + o);
+      xh[u] = load4<NT>(A.Xhat + o);
+      if (NT && A.G) g[u] = load4<true>(A.G + o);   // (redo_sgd; streamed states only)
+      if (!LAYERED) sc[u].load(A.ctl + r);
+      else if (!generic) sc[u].load(A.layer_scale[(int64_t)r * A.nlayers + lay]);
+    }
+  }
+  stage_rows_of_w<TH>(A, nbr, rowp);
+#pragma unroll
+  for (int u = 0; u < VPT; ++u) {
+    const int r = r0 + u * RS;
+    const bool mine = r < A.n && valid;
+    vf4 nh = {0.f, 0.f, 0.f, 0.f};
+    vi4 code = {0, 0, 0, 0};
+    if (mine) {
+      const int64_t o = (int64_t)r * A.ld + e;
+      if (NT && A.G) {   // the local update that the norm pass formed and did not store
+#pragma unroll
+        for (int c = 0; c < 4; ++c) x[u][c] = x[u][c] - A.lr * g[u][c];
+      }
+      uint4 words = make_uint4(0, 0, 0, 0);
+      if (COMP == Q_QSGD) words = random_words(A, r, (uint32_t)(e >> 2), STREAM_DITHER);
+      if (generic) {
+        nh = absorb_by_entry<COMP>(A, r, e, x[u], xh[u], words, code);
+      } else {
+        nh = absorb<COMP>(x[u], xh[u], sc[u], words, code);
+        mask_padding(nvalid, xh[u], nh, code);
+      }
+      store4<NT>(A.Xhat + o, nh);
+      if (A.codes) *reinterpret_cast<vi4*>(A.codes + o) = code;
+    }
+    // (every lane of the wave takes part; one without entries writes nothing)
+    emit_code_planes<COMP>(A, r, mine ? e : A.d, lane, code, lay);
+    if (r < A.n) lds_store4(tile + r * kNarrowCols + lr * 4, nh);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < VPT; ++u) {
+    const int r = r0 + u * RS;
+    if (r < A.n && valid) {
+      narrow_mix(A, tile, nbr, rowp, r, lr, x[u]);
+      store4<NT>(A.X + (int64_t)r * A.ld + e, x[u]);
+    }
   }
 }
 
@@ -1129,16 +1252,6 @@ __global__ __launch_bounds__(64 * NW) void k_tile_mix(Args A) {
 // A line of xhat that holds a kept entry is stored whole (the eight lanes that share a word of kept
 // bits store their 4-vectors; 128 bytes where rows are aligned) instead of the 4-vectors that
 // changed: partly written lines cost more than the bytes saved (58.8 -> 54.4 us).
-constexpr int kNarrowCols = 64;
-constexpr int kStagedNnz = 1024;
-
-// Sixteen neighbouring tiles (4 KiB of every row) on one die, one after the other (workgroups go to
-// the dies in turn); the last, partial group of 128 is left as it is.
-__device__ __forceinline__ int die_run_tile(int b, int ntiles) {
-  const int base = b & ~127;
-  if (base + 128 > ntiles) return b;
-  return base + ((b & 7) << 4) + ((b >> 3) & 15);
-}
 
 template <int VPT, int TH, bool NT, bool SPARSE>
 __global__ __launch_bounds__(TH) void k_tile_mix_narrow(Args A) {
@@ -1167,11 +1280,7 @@ __global__ __launch_bounds__(TH) void k_tile_mix_narrow(Args A) {
                                  : A.keptmap[(int64_t)r * A.map_words + ((uint32_t)e >> 5)];
     }
   }
-  if (A.staged_nnz) {
-    for (int p = threadIdx.x; p < A.staged_nnz; p += TH)
-      nbr[p] = make_float2(__int_as_float(A.col[p] * kNarrowCols), A.w[p]);
-    for (int r = threadIdx.x; r <= A.n; r += TH) rowp[r] = A.row_ptr[r];
-  }
+  stage_rows_of_w<TH>(A, nbr, rowp);
 #pragma unroll
   for (int u = 0; u < VPT; ++u) {
     const int r = r0 + u * RS;
@@ -1210,27 +1319,7 @@ __global__ __launch_bounds__(TH) void k_tile_mix_narrow(Args A) {
   for (int u = 0; u < VPT; ++u) {
     const int r = r0 + u * RS;
     if (r < A.n && valid) {
-      const vf4 me = lds_load4(tile + r * kNarrowCols + lr * 4);
-      vf4 acc = {0.f, 0.f, 0.f, 0.f};
-      if (A.staged_nnz) {
-        const int pend = rowp[r + 1];
-        for (int p = rowp[r]; p < pend; ++p) {           // neighbours in the order of the CSR row
-          const float2 jw = nbr[p];
-          const vf4 o = lds_load4(tile + __float_as_int(jw.x) + lr * 4);
-#pragma unroll
-          for (int c = 0; c < 4; ++c) acc[c] = acc[c] + jw.y * (o[c] - me[c]);
-        }
-      } else {
-        const int pend = A.row_ptr[r + 1];
-        for (int p = A.row_ptr[r]; p < pend; ++p) {
-          const float wj = A.w[p];
-          const vf4 o = lds_load4(tile + A.col[p] * kNarrowCols + lr * 4);
-#pragma unroll
-          for (int c = 0; c < 4; ++c) acc[c] = acc[c] + wj * (o[c] - me[c]);
-        }
-      }
-#pragma unroll
-      for (int c = 0; c < 4; ++c) x[u][c] = x[u][c] + A.gamma * acc[c];
+      narrow_mix(A, tile, nbr, rowp, r, lr, x[u]);
       store4<NT>(A.X + (int64_t)r * A.ld + e, x[u]);
     }
   }

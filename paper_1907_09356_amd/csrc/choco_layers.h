@@ -484,7 +484,7 @@ __global__ __launch_bounds__(stat_threads(NT)) void k_layer_stat(Args A) {
         if (A.M) mm = load4<NT>(A.M + row + e[u]);
         a[u] = local_update_regs(A, a[u], g[u], mm);
         if (A.M) store4<NT>(A.M + row + e[u], mm);
-        store4<NT>(A.X + row + e[u], a[u]);
+        if (!NT || !A.redo_sgd) store4<NT>(A.X + row + e[u], a[u]);
       }
     }
   }

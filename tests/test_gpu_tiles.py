@@ -46,3 +46,24 @@ def test_narrow_tile_with_more_neighbours_than_it_stages(n):
 def test_mix_of_a_state_that_is_streamed(n, d, align):
     """Past the caches (4 to 12 MB per array), on whole lines and off them (the wide tile)."""
     walk(n, d, synth.ring_csr(n), B.Q_TOPK, steps=2, k=d // 100, ld_align=align)
+
+
+@pytest.mark.parametrize("n", [8, 9, 12, 13, 16, 17, 32, 33, 64])
+@pytest.mark.parametrize("comp", [B.Q_SIGN, B.Q_QSGD])
+@pytest.mark.parametrize("layered", [False, True])
+def test_dense_tiles_by_number_of_workers(n, comp, layered):
+    lengths = [700, 3, 64, 129, 5000 + n]
+    d = synth.layers_dim(synth.layer_table(lengths)) if layered else 64 * 9 + (n * 7) % 64
+    walk(n, d, synth.ring_csr(n), comp, levels=8, momentum=n % 2 == 0,
+         layers=synth.layer_table(lengths) if layered else None)
+
+
+@pytest.mark.parametrize("n,d,align", [(8, 140_001, 32), (16, 66_003, 4), (64, 17_000, 32)])
+@pytest.mark.parametrize("comp", [B.Q_SIGN, B.Q_QSGD])
+@pytest.mark.parametrize("layered", [False, True])
+def test_local_update_formed_twice(n, d, align, comp, layered):
+    """States streamed past the caches (4 to 12 MB per array): the norm pass does not store x - lr g."""
+    lengths = [d // 2, 37, d - d // 2 - 40 - 300, 255]
+    layers = synth.layer_table(lengths) if layered else None
+    walk(n, synth.layers_dim(layers) if layered else d, synth.ring_csr(n), comp, steps=2, levels=8, ld_align=align,
+         layers=layers)
