@@ -2048,7 +2048,7 @@ int choco_pack_messages(choco_ctx* ctx, void* msgs_dev) {
   uint32_t* msg = (uint32_t*)msgs_dev;
   const dim3 kgrid((unsigned)((Wa.k + 255) / 256), (unsigned)Wa.n);
   const dim3 lgrid((unsigned)((ctx->wire_plane_words + 255) / 256), (unsigned)Wa.n);
-  const dim3 pgrid((unsigned)((Wa.W + 255) / 256), (unsigned)(Wa.nplanes > 0 ? Wa.nplanes : 1), (unsigned)Wa.n);
+  const dim3 pgrid((unsigned)((Wa.W + 1023) / 1024), (unsigned)(Wa.nplanes > 0 ? Wa.nplanes : 1), (unsigned)Wa.n);
   switch (ctx->cfg.compressor) {
     case CHOCO_Q_SIGN:
       if (Wa.nlayers) LAUNCH(ctx, KID_WIRE, k_pack_dense_layers<false>, lgrid, dim3(256), 0, Wa, msg);
@@ -2088,6 +2088,7 @@ int choco_unpack_messages(choco_ctx* ctx, const void* msgs_dev, float* q_dev) {
   const dim3 wgrid((unsigned)((Wa.W + 255) / 256), (unsigned)Wa.n);
   const dim3 kgrid((unsigned)((Wa.k + 255) / 256), (unsigned)Wa.n);
   const dim3 lgrid((unsigned)((ctx->wire_plane_words + 255) / 256), (unsigned)Wa.n);
+  const size_t llds = (size_t)(3 + Wa.nplanes + (ctx->cfg.compressor == CHOCO_Q_QSGD ? kOverflowSlots : 0)) * 1024;
   // every entry of q is written: pad columns and entries not sent are zero (the dense decoders
   // write whole 4-vectors up to d themselves, so they need the fill only for a wider ld)
   if (ctx->sparse || Wa.nlayers || Wa.ld > ((int64_t)Wa.d + 3) / 4 * 4)
@@ -2095,11 +2096,11 @@ int choco_unpack_messages(choco_ctx* ctx, const void* msgs_dev, float* q_dev) {
            Wa.ld);
   switch (ctx->cfg.compressor) {
     case CHOCO_Q_SIGN:
-      if (Wa.nlayers) LAUNCH(ctx, KID_WIRE, k_unpack_dense_layers<false>, lgrid, dim3(256), 0, Wa, msg, q_dev);
+      if (Wa.nlayers) LAUNCH(ctx, KID_WIRE, k_unpack_dense_layers<false>, lgrid, dim3(256), llds, Wa, msg, q_dev);
       else LAUNCH(ctx, KID_WIRE, k_unpack_sign, wgrid, dim3(256), 0, Wa, msg, q_dev);
       break;
     case CHOCO_Q_QSGD:
-      if (Wa.nlayers) LAUNCH(ctx, KID_WIRE, k_unpack_dense_layers<true>, lgrid, dim3(256), 0, Wa, msg, q_dev);
+      if (Wa.nlayers) LAUNCH(ctx, KID_WIRE, k_unpack_dense_layers<true>, lgrid, dim3(256), llds, Wa, msg, q_dev);
       else if (Wa.levels < 256)
         LAUNCH(ctx, KID_WIRE, k_unpack_gsgd<true>, wgrid, dim3(256), (size_t)(1 + Wa.mb) * 1024, Wa, msg, q_dev);
       else

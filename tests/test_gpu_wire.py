@@ -69,6 +69,13 @@ def test_messages_match_the_oracle(name, q, d):
     pair.close()
 
 
+@pytest.mark.parametrize("d", [1, 33, 96, 32 * 1023 + 1, 32 * 1024, 32 * 1025 - 3])
+@pytest.mark.parametrize("name,q", [o for o in OPERATORS if o[0] in ("sign", "qsgd16")])
+def test_planes_around_what_a_workgroup_copies(name, q, d):
+    """Four words per thread, 1,024 per workgroup; the last words one by one."""
+    test_messages_match_the_oracle(name, q, d)
+
+
 def test_level_s_goes_through_the_index_slots():
     # one entry of every worker holds almost the whole norm
     n, d, s = 3, 500, 4
