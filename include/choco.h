@@ -14,7 +14,8 @@
  *     printed, nothing aborts, no exception crosses the boundary;
  *   - pointers named *_dev are device pointers, *_host are host pointers;
  *   - device buffers are owned by the caller (allocated e.g. with torch); the
- *     library allocates no device memory, it only carves up the workspace;
+ *     library allocates no device memory, it only carves up the workspace (and holds one
+ *     page of pinned host memory, into which choco_metrics has its figures written);
  *   - work is enqueued on the caller's stream (one documented exception: the look-ahead
  *     selection of RANDK, see choco_set_lookahead) and the calls return without
  *     synchronising, except choco_metrics, choco_last_scalars, choco_layer_scalars,
@@ -181,8 +182,8 @@ int choco_metrics(choco_ctx *ctx, double *consensus_host, double *mean_norm_host
    distance, ||xbar||_2, Psi}.  Same kernels as choco_metrics, but their partial sums go to an
    array that is part of the loaded library (CHOCO_NOALLOC_SCRATCH_BYTES of device memory on
    every GPU the library runs on, held until the process ends) instead of the workspace, the
-   result is not copied to the host and nothing is waited for: the call enqueues two kernels on
-   the context's stream and calls no allocating routine.  The address of the array on the
+   result is not copied to the host and nothing is waited for: the call enqueues one or two kernels
+   on the context's stream and calls no allocating routine.  The address of the array on the
    context's GPU is looked up once, by choco_init.  CHOCO_E_UNSUPPORTED for d above
    CHOCO_NOALLOC_MAX_D (or a GPU number above 63); CHOCO_E_INVAL if the GPU current at the call
    is not the one that was current in choco_init.  All contexts on one GPU share the array:

@@ -126,7 +126,8 @@ struct choco_ctx {
   int device;             // the GPU that was current in choco_init
   double* noalloc_scratch;   // address of `scratch` on that GPU (null: more GPUs than the table holds)
   double* metrics_part;   // device scratch of the metrics kernels
-  double* metrics_out;
+  double* metrics_host;   // the three figures in pinned host memory: a slot of the library's page ...
+  int metrics_slot;       // ... this one, or -1: an allocation of the context's own
   int metrics_blocks;
   int last_hip_error;
   // optional per-kernel timing with HIP events on the context's stream
@@ -147,7 +148,7 @@ size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 struct Layout {
   size_t xhat, s, row_ptr, col, w, ctl, chunk_sums, group_sums, hist16, cand, hist_parts, small_list, sel_idx, sel_val, keptmap, bitmap,
       layers, layer_work, long_tab, layer_guess, layer_scal, layer_groups, layer_group_first, layer_group_sums, layer_scale,
-      chunk_layer, planes, ovf_ring, ovf_pos, wire_rank, wire_word_off, wire_plane_off, sel_idx2, bitmap2, keptmap2, layer_scal2, qv, mpart, mout, total;
+      chunk_layer, planes, ovf_ring, ovf_pos, wire_rank, wire_word_off, wire_plane_off, sel_idx2, bitmap2, keptmap2, layer_scal2, qv, mpart, total;
   int64_t wire_words, wire_plane_words;   // layer by layer: words of a worker's message / of one bit plane
   int32_t ngroup_items;
   uint32_t cand_cap, seg_cap;
@@ -494,7 +495,6 @@ Layout make_layout(const choco_config& c, int32_t nnz) {
   // random_a whose update of xhat rides on the fused mix pass: the kept values by entry
   L.qv = take(fused_sparse_apply(c) && c.compressor == CHOCO_Q_RANDK ? state : 0);
   L.mpart = take((size_t)kMetricsBlocks * 3 * sizeof(double));
-  L.mout = take(3 * sizeof(double));
   L.total = off;
   return L;
 }
@@ -579,6 +579,45 @@ hipError_t resolve_scratch(int* device_out, double** addr_out) {
   return hipSuccess;
 }
 
+// choco_metrics has its figures written to pinned host memory.  Contexts share one page of it, made
+// by the first and held until the process ends (pinning memory for every context would cost each
+// choco_init some 100 us); beyond kHostSlots contexts at a time one gets an allocation of its own.
+constexpr int kHostSlots = 64;
+std::mutex g_slot_mutex;
+double* g_slot_page = nullptr;
+uint64_t g_slots_used = 0;
+
+hipError_t take_host_slot(choco_ctx* ctx) {
+  std::lock_guard<std::mutex> lock(g_slot_mutex);
+  ctx->metrics_slot = -1;
+  if (!g_slot_page) {
+    const hipError_t e = hipHostMalloc((void**)&g_slot_page, kHostSlots * 8 * sizeof(double), hipHostMallocPortable);
+    if (e != hipSuccess) {
+      g_slot_page = nullptr;
+      return e;
+    }
+  }
+  for (int s = 0; s < kHostSlots; ++s)
+    if (!((g_slots_used >> s) & 1u)) {
+      g_slots_used |= 1ull << s;
+      ctx->metrics_slot = s;
+      ctx->metrics_host = g_slot_page + 8 * s;
+      return hipSuccess;
+    }
+  return hipHostMalloc((void**)&ctx->metrics_host, 8 * sizeof(double), hipHostMallocPortable);
+}
+
+void give_host_slot(choco_ctx* ctx) {
+  if (!ctx->metrics_host) return;
+  if (ctx->metrics_slot < 0) {
+    (void)hipHostFree(ctx->metrics_host);
+  } else {
+    std::lock_guard<std::mutex> lock(g_slot_mutex);
+    g_slots_used &= ~(1ull << ctx->metrics_slot);
+  }
+  ctx->metrics_host = nullptr;
+}
+
 // Frees the host-side objects of a context (its own stream and events; never device memory).
 void release_ctx(choco_ctx* ctx) {
   if (ctx->aux_stream) {
@@ -593,6 +632,7 @@ void release_ctx(choco_ctx* ctx) {
   if (ctx->ev_join2) (void)hipEventDestroy(ctx->ev_join2);
   if (ctx->ev_fork) (void)hipEventDestroy(ctx->ev_fork);
   if (ctx->ev_ahead) (void)hipEventDestroy(ctx->ev_ahead);
+  give_host_slot(ctx);
   for (hipEvent_t e : ctx->ev_begin) (void)hipEventDestroy(e);
   for (hipEvent_t e : ctx->ev_end) (void)hipEventDestroy(e);
   delete ctx;
@@ -1405,6 +1445,18 @@ int fused_iteration(choco_ctx* ctx, const LocalUpdate& u) {
   return run_gossip(ctx, LocalUpdate());
 }
 
+// The figures of choco_metrics to `out` (three doubles), partial sums of up to max_blocks blocks to `part`.
+void launch_metrics(choco_ctx* ctx, double* part, int max_blocks, double* out) {
+  const Args& A = ctx->args;
+  if (A.d <= 4096) {
+    hipLaunchKernelGGL(k_metrics_small, dim3(1), dim3(1024), 0, ctx->stream, A, out);
+    return;
+  }
+  const int blocks = (int)std::min<int64_t>(max_blocks, ((int64_t)A.d + 1023) / 1024);
+  hipLaunchKernelGGL(k_metrics_partial, dim3((unsigned)blocks), dim3(256), 0, ctx->stream, A, part);
+  hipLaunchKernelGGL(k_metrics_final, dim3(1), dim3(256), 0, ctx->stream, part, blocks, A.n, out);
+}
+
 // Which configurations the message kernels cover.
 int wire_supported(const choco_ctx* ctx) {
   if (ctx->cfg.compressor == CHOCO_Q_IDENTITY) return CHOCO_E_UNSUPPORTED;
@@ -1505,6 +1557,8 @@ int choco_init(const choco_config* cfg, float* x_dev, void* workspace_dev, size_
   ctx->cfg.layer_len_host = nullptr;
   ctx->cfg.layer_k_host = nullptr;
   ctx->stream = (hipStream_t)cfg->stream;
+  ctx->metrics_host = nullptr;
+  ctx->metrics_slot = -1;
   ctx->aux_stream = nullptr;
   ctx->launch_stream = ctx->stream;
   ctx->ev_fork = ctx->ev_ahead = nullptr;
@@ -1775,7 +1829,10 @@ int choco_init(const choco_config* cfg, float* x_dev, void* workspace_dev, size_
     plane_off.push_back(po);
   }
   ctx->metrics_part = (double*)(base + L.mpart);
-  ctx->metrics_out = (double*)(base + L.mout);
+  if (take_host_slot(ctx) != hipSuccess) {
+    release_ctx(ctx);
+    return CHOCO_E_HIP;
+  }
   ctx->metrics_blocks = kMetricsBlocks;
 
   // the library's own scratch array on this GPU (used by choco_metrics_noalloc only)
@@ -1890,20 +1947,13 @@ int choco_step_momentum(choco_ctx* ctx, const float* g_dev, float* m_dev, float 
 
 int choco_metrics(choco_ctx* ctx, double* consensus_host, double* mean_norm_host, double* psi_host) {
   if (!ctx) return CHOCO_E_INVAL;
-  const Args& A = ctx->args;
-  int blocks = (A.d + 255) / 256;
-  if (blocks > ctx->metrics_blocks) blocks = ctx->metrics_blocks;
-  hipLaunchKernelGGL(k_metrics_partial, dim3((unsigned)blocks), dim3(256), 0, ctx->stream, A,
-                     ctx->metrics_part);
-  hipLaunchKernelGGL(k_metrics_final, dim3(1), dim3(64), 0, ctx->stream, ctx->metrics_part, blocks,
-                     ctx->metrics_out);
+  // the figures are written straight to pinned host memory: no copy to wait for after the kernels
+  launch_metrics(ctx, ctx->metrics_part, ctx->metrics_blocks, ctx->metrics_host);
   LAUNCH_CHECK(ctx);
-  double out[3];
-  HIP_TRY(ctx, hipMemcpyAsync(out, ctx->metrics_out, sizeof(out), hipMemcpyDeviceToHost, ctx->stream));
   HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
-  if (consensus_host) *consensus_host = out[0] / (double)A.n;
-  if (mean_norm_host) *mean_norm_host = std::sqrt(out[1]);
-  if (psi_host) *psi_host = out[0] + out[2];
+  if (consensus_host) *consensus_host = ctx->metrics_host[0];
+  if (mean_norm_host) *mean_norm_host = ctx->metrics_host[1];
+  if (psi_host) *psi_host = ctx->metrics_host[2];
   return CHOCO_OK;
 }
 
@@ -1915,14 +1965,9 @@ int choco_metrics_noalloc(choco_ctx* ctx, double* out_dev) {
   int dev = -1;
   HIP_TRY(ctx, hipGetDevice(&dev));
   if (dev != ctx->device) return CHOCO_E_INVAL;            // the address kept is that GPU's
-  int blocks = (A.d + 255) / 256;
-  if (blocks > kNoAllocBlocks) blocks = kNoAllocBlocks;
-  // every block writes its three partial sums and the last kernel reads exactly `blocks` of them,
-  // so what an earlier (larger) call left behind in the array is never read: nothing to clear
-  hipLaunchKernelGGL(k_metrics_partial, dim3((unsigned)blocks), dim3(256), 0, ctx->stream, A,
-                     ctx->noalloc_scratch);
-  hipLaunchKernelGGL(k_metrics_final_dev, dim3(1), dim3(64), 0, ctx->stream, ctx->noalloc_scratch, blocks,
-                     A.n, out_dev);
+  // every block writes its three partial sums and the last kernel reads exactly those, so what an
+  // earlier (larger) call left behind in the array is never read: nothing to clear
+  launch_metrics(ctx, ctx->noalloc_scratch, kNoAllocBlocks, out_dev);
   LAUNCH_CHECK(ctx);
   return CHOCO_OK;
 }
