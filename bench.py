@@ -128,6 +128,11 @@ KERNEL_BYTES_PER_ELEM = {
     # first pass of a fused choco_step: also reads g and writes x
     "k_dense_stat_sgd": 16,       # read x, g, xhat; write x
     "k_sel_compact_sgd": 16,      # read x, g, xhat; write x
+    # passes that form x - lr g without storing it, and the apply pass that forms it again
+    "k_dense_stat_redo": 12,      # read x, g, xhat
+    "k_layer_stat_redo": 12,
+    "k_sel_compact_redo": 12,
+    "k_dense_apply_mix_sgd": 20,  # read x, g, xhat; write x, xhat
     "k_tile_mix_sgd": 16,         # read x, g, xhat; write x
     "k_mix_incremental_sgd": 20,  # read x, g, s, xhat; write x
     # layer-wise sign / gsgd: the norm pass over (layer, group) work items

@@ -651,14 +651,14 @@ int join_lookahead(choco_ctx* ctx) {
 enum KernelId {
   KID_SGD, KID_MOMENTUM, KID_DENSE_STAT, KID_GROUP_REDUCE, KID_DENSE_FINALISE, KID_DENSE_APPLY_MIX, KID_TILE_MIX,
   KID_DENSE_APPLY, KID_MIX_DIRECT_GLOBAL, KID_MIX_INCREMENTAL, KID_SEL_COMPACT, KID_SEL_FALLBACK,
-  KID_SEL_REFINE, KID_SCATTER_S, KID_XHAT_UPDATE, KID_GATHER_VALUES, KID_SEL_VALUES, KID_SEL_HIST_PARTS, KID_SEL_EMIT_PARTS, KID_SEL_FINISH, KID_DENSE_STAT_SGD, KID_SEL_COMPACT_SGD, KID_TILE_MIX_SGD, KID_MIX_INCREMENTAL_SGD, KID_LAYER_COMPRESS, KID_LAYER_COMPRESS_SGD, KID_LAYER_STAT, KID_LAYER_STAT_SGD, KID_LAYER_FINALISE, KID_WIRE, KID_ZERO_WORDS, KID_COUNT
+  KID_SEL_REFINE, KID_SCATTER_S, KID_XHAT_UPDATE, KID_GATHER_VALUES, KID_SEL_VALUES, KID_SEL_HIST_PARTS, KID_SEL_EMIT_PARTS, KID_SEL_FINISH, KID_DENSE_STAT_SGD, KID_DENSE_STAT_REDO, KID_DENSE_APPLY_MIX_SGD, KID_SEL_COMPACT_SGD, KID_SEL_COMPACT_REDO, KID_TILE_MIX_SGD, KID_MIX_INCREMENTAL_SGD, KID_LAYER_COMPRESS, KID_LAYER_COMPRESS_SGD, KID_LAYER_STAT, KID_LAYER_STAT_SGD, KID_LAYER_STAT_REDO, KID_LAYER_FINALISE, KID_WIRE, KID_ZERO_WORDS, KID_COUNT
 };
 const char* const kKernelNames[KID_COUNT] = {
   "k_sgd", "k_momentum", "k_dense_stat", "k_group_reduce", "k_dense_finalise", "k_dense_apply_mix", "k_tile_mix",
   "k_dense_apply", "k_mix_direct_global", "k_mix_incremental", "k_sel_compact", "k_sel_fallback",
   "k_sel_refine", "k_scatter_s", "k_xhat_update", "k_gather_values", "k_sel_values", "k_sel_hist_parts", "k_sel_emit_parts", "k_sel_finish",
-  "k_dense_stat_sgd", "k_sel_compact_sgd", "k_tile_mix_sgd", "k_mix_incremental_sgd",
-  "k_layer_compress", "k_layer_compress_sgd", "k_layer_stat", "k_layer_stat_sgd", "k_layer_finalise", "k_wire",
+  "k_dense_stat_sgd", "k_dense_stat_redo", "k_dense_apply_mix_sgd", "k_sel_compact_sgd", "k_sel_compact_redo", "k_tile_mix_sgd", "k_mix_incremental_sgd",
+  "k_layer_compress", "k_layer_compress_sgd", "k_layer_stat", "k_layer_stat_sgd", "k_layer_stat_redo", "k_layer_finalise", "k_wire",
   "k_zero_words"};
 constexpr size_t kMaxProfiledLaunches = 16384;
 
@@ -731,7 +731,7 @@ size_t narrow_lds(const Args& A) {
 template <int COMP, bool NT, bool LAYERED>
 void launch_apply_mix_narrow(choco_ctx* ctx, const Args& A) {
   const dim3 grid((unsigned)((A.d + kNarrowCols - 1) / kNarrowCols));
-#define CALL(V, T) LAUNCH(ctx, KID_DENSE_APPLY_MIX, (k_dense_apply_mix_narrow<COMP, V, T, NT, LAYERED>), grid, dim3(T), narrow_lds(A), A)
+#define CALL(V, T) LAUNCH(ctx, A.G ? KID_DENSE_APPLY_MIX_SGD : KID_DENSE_APPLY_MIX, (k_dense_apply_mix_narrow<COMP, V, T, NT, LAYERED>), grid, dim3(T), narrow_lds(A), A)
   if (A.n <= 16) CALL(1, 256);
   else if (A.n <= 32) CALL(1, 512);
   else CALL(2, 512);
@@ -748,7 +748,7 @@ void launch_apply_mix(choco_ctx* ctx, const Args& A) {
   const dim3 grid((unsigned)A.nchunks), block = tile_block(A);
   const size_t lds = (size_t)A.n * kChunk * sizeof(float);
 #define CALL(R, W) \
-  LAUNCH(ctx, KID_DENSE_APPLY_MIX, (k_dense_apply_mix<COMP, R, W, CAPTURE, NT, LAYERED>), grid, block, lds, A)
+  LAUNCH(ctx, A.G ? KID_DENSE_APPLY_MIX_SGD : KID_DENSE_APPLY_MIX, (k_dense_apply_mix<COMP, R, W, CAPTURE, NT, LAYERED>), grid, block, lds, A)
   TILE_SWITCH(A, CALL)
 #undef CALL
 }
@@ -843,7 +843,7 @@ int gossip_dense(choco_ctx* ctx, const Args& F0) {
   const dim3 stat_grid((unsigned)A.ngroups, (unsigned)A.n);
   if (ctx->cfg.order == CHOCO_ORDER_COMPRESS_THEN_MIX) {
     if (needs_stat) {
-      LAUNCH(ctx, fused ? KID_DENSE_STAT_SGD : KID_DENSE_STAT, (k_dense_stat<STATK, NT>), stat_grid,
+      LAUNCH(ctx, F.redo_sgd ? KID_DENSE_STAT_REDO : fused ? KID_DENSE_STAT_SGD : KID_DENSE_STAT, (k_dense_stat<STATK, NT>), stat_grid,
              dim3(stat_threads(NT)), 0, F);
       if (!A.fold_finalise)
         LAUNCH(ctx, KID_DENSE_FINALISE, (k_dense_finalise<STATK>), dim3((unsigned)A.n), dim3(256), 0, A);
@@ -916,6 +916,8 @@ void launch_select(choco_ctx* ctx, const Args& C, const Args& A, int kid_compact
     else LAUNCH(ctx, kid_compact, (k_sel_compact<COMP, COMP == Q_TOPK, NT, kCompactVecs>), cgrid, dim3(256), 0, C);
   } else {
     if (cvecs == 2) LAUNCH(ctx, kid_compact, (k_sel_compact<COMP, false, NT, 2>), cgrid, dim3(256), pad, C);
+    else if (kWide && C.deferred_sgd)   // (1024 x 1 1066 us per step, 512 x 2 1035, 256 x 4 1030 at n = 8, d = 28 M)
+      LAUNCH(ctx, kid_compact, (k_sel_compact<COMP, false, NT, kCompactVecs, false, 256, COMP == Q_TOPK>), cgrid, dim3(256), 0, C);
     else if (kWide) LAUNCH(ctx, kid_compact, (k_sel_compact<COMP, false, NT, 1, false, 1024>), cgrid, dim3(1024), pad, C);
     else LAUNCH(ctx, kid_compact, (k_sel_compact<COMP, false, NT, kCompactVecs>), cgrid, dim3(256), pad, C);
   }
@@ -1051,7 +1053,8 @@ int gossip_sparse(choco_ctx* ctx, const Args& F) {
   }
   // select: one pass over the rows; histogram fallback and rebuild are no-ops unless a guess failed
   const Args& C = x_touched ? A : F;
-  const int kid_compact = (!x_touched && fused) ? KID_SEL_COMPACT_SGD : KID_SEL_COMPACT;
+  const int kid_compact = (!x_touched && fused) ? KID_SEL_COMPACT_SGD
+                          : (COMP == Q_TOPK && F.deferred_sgd) ? KID_SEL_COMPACT_REDO : KID_SEL_COMPACT;
   // random_a: this step's selection may already have been made (or be under way) on the second
   // stream; then it is only waited for
   const bool ahead = COMP == Q_RANDK && ctx->lookahead && !ctx->profiling;
@@ -1126,7 +1129,7 @@ int gossip_layers_dense(choco_ctx* ctx, const Args& F0) {
     x_touched = true;
   }
   const Args& C = x_touched ? A : F;
-  LAUNCH(ctx, C.G ? KID_LAYER_STAT_SGD : KID_LAYER_STAT, (k_layer_stat<COMP, NT>),
+  LAUNCH(ctx, C.redo_sgd ? KID_LAYER_STAT_REDO : C.G ? KID_LAYER_STAT_SGD : KID_LAYER_STAT, (k_layer_stat<COMP, NT>),
          dim3((unsigned)A.ngroup_items, (unsigned)A.n), dim3(stat_threads(NT)), 0, C);
   LAUNCH(ctx, KID_LAYER_FINALISE, (k_layer_finalise<COMP>), dim3((unsigned)A.nlayers, (unsigned)A.n), dim3(256), 0, A);
   if (!mix_first && ctx->rpw) {
@@ -1435,9 +1438,20 @@ int launch_momentum(choco_ctx* ctx, const float* g_dev, float* m_dev, float lr, 
   return CHOCO_OK;
 }
 
+// top_a, plain SGD, the fused pass of the direct form on a streamed state: the candidate pass forms
+// x - lr g for its keys without storing it, and the last pass applies the update (as redo_sgd above).
+// Rows above 2^21 entries: n = 8, d = 28 M 1066 -> 1030 us per step, d = 4 M 178 -> 171, n = 16, d = 6.25 M
+// 499 -> 490, n = 64, d = 2 M 638 -> 631; shorter ones lose (n = 64, d = 520 k, whose arrays the last-level
+// cache still holds in part: 204 -> 213).
+bool redo_topk(const choco_ctx* ctx, const LocalUpdate& u) {
+  return ctx->cfg.compressor == CHOCO_Q_TOPK && ctx->nlayers == 0 && ctx->fused_sparse_apply && ctx->nt &&
+         ctx->long_rows && u.m == nullptr;
+}
+
 // One whole iteration: the local update (plain or momentum), then the gossip step; fused
 // into the first (or, for random_a, the last) dense pass where the configuration has one.
 int fused_iteration(choco_ctx* ctx, const LocalUpdate& u) {
+  if (redo_topk(ctx, u)) return run_gossip(ctx, u, true);
   if (first_pass_can_carry_sgd(ctx)) return run_gossip(ctx, u);
   if (last_pass_carries_sgd(ctx)) return run_gossip(ctx, u, true);
   const int rc = u.m ? launch_momentum(ctx, u.g, u.m, u.lr, u.beta, u.lambda) : launch_sgd(ctx, u.g, u.lr);
@@ -1625,6 +1639,8 @@ int choco_init(const choco_config* cfg, float* x_dev, void* workspace_dev, size_
   A.row_ptr = (const int32_t*)(base + L.row_ptr);
   A.col = (const int32_t*)(base + L.col);
   A.w = (const float*)(base + L.w);
+  // (in turn at 4 M entries per row: no gain; more rows than 8 at once: 64 rows of 2 M 631 -> 643 us)
+  A.rows_in_turn = (cfg->n <= 8 && cfg->d >= ((int64_t)1 << 24)) ? 1 : 0;
   A.staged_nnz = nnz <= kStagedNnz ? nnz : 0;
   A.ctl = (WorkerCtl*)(base + L.ctl);
   // polls of about 2 us each: a tenth of a second before a workgroup of the fallback stops waiting

@@ -47,6 +47,7 @@ constexpr int stat_threads(bool nt) { return 64 * (16 / stat_cpw(nt)); }
 constexpr int kFallbackBlocks = 64; // blocks per worker of the (normally idle) fallback passes
 constexpr int kRefineParts = 16;    // blocks per worker of the select when the candidate lists are long
 constexpr int kSegs = 32;         // candidate sub-lists per worker (spreads the append counter)
+constexpr int kSegPad = 32;       // words from one sub-list counter to the next
 constexpr int kOvfRing = 8;       // gsgd: remembered entries at the top level per worker (and layer); a step adds at most 4
 
 // Per-worker control block in device memory (written by small "finalise" code,
@@ -63,7 +64,7 @@ struct WorkerCtl {
   uint32_t guess_key;   // entries with key32 >= this are appended to the candidate list
   uint32_t bin_shift;   // the select bins candidates by min((key32 - guess_key) >> bin_shift, 2047)
   uint32_t mode;        // 0: candidate list is complete, 1: rebuild it, 2: scan the row
-  uint32_t seg_count[kSegs];  // entries with key32 >= guess_key appended per sub-list (may exceed seg_cap)
+  alignas(128) uint32_t seg_count[kSegs * kSegPad];  // entries with key32 >= guess_key appended per sub-list (may exceed seg_cap)
   uint32_t kept;        // number of entries emitted by the last selection
   uint32_t fallbacks;   // how many steps needed a fallback (histogram rebuild or row scan)
   uint32_t last_candidates;  // length of the candidate list the last select worked on
@@ -134,7 +135,9 @@ struct Args {
   float lr;
   float* M;              // momentum memory (Algorithm 2) or null for plain SGD
   float beta, lambda;    // momentum factor and weight decay of Algorithm 2
-  int32_t deferred_sgd;  // the local update is applied by the LAST kernel of the step (random_a)
+  int32_t deferred_sgd;  // the local update is applied by the LAST kernel of the step (random_a; top_a on
+                         // streamed states, whose select forms x - lr g for its keys and stores nothing)
+  int32_t rows_in_turn;  // ... whose candidate pass goes through the rows in turn
   int32_t redo_sgd;      // dense operators, plain SGD: the norm pass forms x - lr g without storing it and
                          // the apply pass, which reads x anyway, forms it again
   // dense operators
@@ -372,6 +375,14 @@ __device__ __forceinline__ float x_entry(const ArgsT& A, int64_t o) {
   }
   return x - A.lr * A.G[o];
 }
+// A 4-vector of x with a deferred plain local update (top_a on streamed states; never with momentum).
+template <class ArgsT>
+__device__ __forceinline__ vf4 x_redone(const ArgsT& A, int64_t o, vf4 x) {
+  const vf4 g = load4<true>(A.G + o);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) x[c] = x[c] - A.lr * g[c];
+  return x;
+}
 __device__ __forceinline__ vf4 lds_load4(const float* p) { return *reinterpret_cast<const vf4*>(p); }
 __device__ __forceinline__ void lds_store4(float* p, vf4 v) { *reinterpret_cast<vf4*>(p) = v; }
 
@@ -379,6 +390,11 @@ __device__ __forceinline__ void lds_store4(float* p, vf4 v) { *reinterpret_cast<
 // Philox4x32, 10 rounds (Salmon et al., SC'11): counter-based, so the word for
 // (seed, step, worker, index) is the same in whatever order entries are visited.
 // ---------------------------------------------------------------------------
+// a ^ b ^ c in one instruction (any function of three bits by its truth table; 0x96 is the parity).
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+  return (uint32_t)__builtin_amdgcn_bitop3_b32((int)a, (int)b, (int)c, 0x96);
+}
+
 __device__ __forceinline__ uint4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
                                                uint32_t k0, uint32_t k1) {
 #pragma unroll
@@ -393,8 +409,8 @@ __device__ __forceinline__ uint4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_
     const uint64_t p1 = (uint64_t)0xCD9E8D57u * (uint64_t)c2;
     const uint32_t hi0 = (uint32_t)(p0 >> 32), lo0 = (uint32_t)p0;
     const uint32_t hi1 = (uint32_t)(p1 >> 32), lo1 = (uint32_t)p1;
-    const uint32_t n0 = hi1 ^ c1 ^ k0;
-    const uint32_t n2 = hi0 ^ c3 ^ k1;
+    const uint32_t n0 = xor3(hi1, c1, k0);
+    const uint32_t n2 = xor3(hi0, c3, k1);
     c0 = n0; c1 = lo1; c2 = n2; c3 = lo0;
   }
   return make_uint4(c0, c1, c2, c3);
@@ -1498,7 +1514,7 @@ __device__ __forceinline__ bool list_is_good(const WorkerCtl* ctl, const Args& A
   bool fits = true;
 #pragma unroll
   for (int s = 0; s < kSegs; ++s) {
-    const uint32_t c = ctl->seg_count[s];
+    const uint32_t c = ctl->seg_count[s * kSegPad];
     total += c;
     fits = fits && (c <= A.seg_cap);
   }
@@ -1518,6 +1534,7 @@ __device__ __forceinline__ void entry_bits(const Args& A, int i, int m, uint32_t
     const vf4 xh = load4<NT>(A.Xhat + o);
     const bool sgd = FIRST && A.G != nullptr;
     if (sgd) x = local_update4<NT>(A, o, x);
+    else if (A.deferred_sgd && A.G != nullptr) x = x_redone(A, o, x);
     if (DO_MIX) {
       const vf4 s = load4<NT>(A.S + o);
 #pragma unroll
@@ -1535,9 +1552,9 @@ __device__ __forceinline__ void entry_bits(const Args& A, int i, int m, uint32_t
 // Append the candidates (key32 >= guess) among the 256 * VECS 4-vectors of
 // one chunk of worker i to sub-list chunk % kSegs.  Hits are staged in LDS and
 // flushed with one global atomic per block.
-template <int COMP, bool DO_MIX, bool NT, bool FIRST, int VECS, int THREADS = 256>
+template <int COMP, bool DO_MIX, bool NT, bool FIRST, int VECS, int THREADS = 256, bool REDO = false>
 __device__ __forceinline__ void compact_chunk(const Args& A, int i, int chunk, uint2* stage,
-                                              uint32_t* s_count, uint32_t* s_base) {
+                                              uint32_t* s_count) {
   WorkerCtl* ctl = A.ctl + i;
   const uint32_t guess = ctl->guess_key;
   const int seg = chunk % kSegs;
@@ -1550,8 +1567,8 @@ __device__ __forceinline__ void compact_chunk(const Args& A, int i, int chunk, u
     // all loads of the chunk first, then the arithmetic and the stores: a store to X between
     // two groups of loads would hold the later loads back (the compiler must assume that the
     // arrays overlap)
-    const bool sgd = FIRST && A.G != nullptr;
-    const bool mom = sgd && A.M != nullptr;
+    const bool sgd = REDO || (FIRST && A.G != nullptr);   // (REDO: for the keys only)
+    const bool mom = !REDO && sgd && A.M != nullptr;
     vf4 x[VECS], xh[VECS], g[VECS], sm[VECS];   // sm: S (DO_MIX) or the momentum
 #pragma unroll
     for (int u = 0; u < VECS; ++u) {
@@ -1585,7 +1602,7 @@ __device__ __forceinline__ void compact_chunk(const Args& A, int i, int chunk, u
 #pragma unroll
           for (int c = 0; c < 4; ++c) x[u][c] = x[u][c] + A.gamma * (sm[u][c] - xh[u][c]);
         }
-        if (DO_MIX || sgd) store4<NT>(A.X + o, x[u]);
+        if (DO_MIX || (sgd && !REDO)) store4<NT>(A.X + o, x[u]);
 #pragma unroll
         for (int c = 0; c < 4; ++c) a[u][c] = __float_as_uint(x[u][c] - xh[u][c]);
       }
@@ -1610,7 +1627,7 @@ __device__ __forceinline__ void compact_chunk(const Args& A, int i, int chunk, u
           if (slot < (uint32_t)kStageCap) {
             stage[slot] = make_uint2(a[u][c], (uint32_t)e);
           } else {   // more hits than the stage holds: append one by one
-            const uint32_t pos = atomicAdd(&ctl->seg_count[seg], 1u);
+            const uint32_t pos = atomicAdd(&ctl->seg_count[seg * kSegPad], 1u);
             if (pos < A.seg_cap) cand[pos] = make_uint2(a[u][c], (uint32_t)e);
           }
         }
@@ -1618,12 +1635,15 @@ __device__ __forceinline__ void compact_chunk(const Args& A, int i, int chunk, u
     }
   }
   __syncthreads();
+  // the first wave alone appends: the others leave their slots to the next workgroup instead of
+  // waiting for the counter's round trip
+  if (threadIdx.x >= 64) return;
   const uint32_t count = *s_count < (uint32_t)kStageCap ? *s_count : (uint32_t)kStageCap;
   if (count != 0) {
-    if (threadIdx.x == 0) *s_base = atomicAdd(&ctl->seg_count[seg], count);
-    __syncthreads();
-    const uint32_t base = *s_base;
-    for (uint32_t t = threadIdx.x; t < count; t += THREADS)
+    uint32_t base = 0;
+    if (threadIdx.x == 0) base = atomicAdd(&ctl->seg_count[seg * kSegPad], count);
+    base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+    for (uint32_t t = threadIdx.x; t < count; t += 64)
       if (base + t < A.seg_cap) cand[base + t] = stage[t];
   }
 }
@@ -1636,15 +1656,26 @@ __device__ __forceinline__ void compact_chunk(const Args& A, int i, int chunk, u
 // 256 threads (its pass draws Philox words beside another pass and should get in its way little).
 // BATCH: grid.z counts the long layers of A.long_tab, grid.x covers the longest of them (the
 // workgroups past a shorter layer's end leave at once).
-template <int COMP, bool DO_MIX, bool NT, int VECS, bool BATCH = false, int THREADS = 256>
+// REDO: x - lr g is formed for the keys and not stored (the last pass of the step forms it again);
+// such a pass only reads, and on very long rows what bounds it is the sub-list counters, 8.6 ns per
+// append to one cache line (n = 8, d = 28 M: all 32 counters of a row on one line 474 us, on lines of
+// their own 417); there the workgroups take the rows in turn, so that the counters of all rows are
+// in use at once (403 us; the loads alone would take 382).
+template <int COMP, bool DO_MIX, bool NT, int VECS, bool BATCH = false, int THREADS = 256, bool REDO = false>
 __global__ __launch_bounds__(THREADS) void k_sel_compact(Args A0) {
   __shared__ uint2 stage[kStageCap];
-  __shared__ uint32_t s_count, s_base;
+  __shared__ uint32_t s_count;
   const Args A = BATCH ? long_view(A0, A0.long_tab[blockIdx.z]) : A0;
   if (BATCH && (int64_t)blockIdx.x * (THREADS * VECS) >= (int64_t)((A.d + 3) >> 2)) return;
   if (threadIdx.x == 0) s_count = 0;
   __syncthreads();
-  compact_chunk<COMP, DO_MIX, NT, true, VECS, THREADS>(A, blockIdx.y, blockIdx.x, stage, &s_count, &s_base);
+  int row = blockIdx.y, chunk = blockIdx.x;
+  if (REDO && A.rows_in_turn) {
+    const uint32_t lin = blockIdx.y * gridDim.x + blockIdx.x;
+    chunk = (int)(lin / gridDim.y);
+    row = (int)(lin - (uint32_t)chunk * gridDim.y);
+  }
+  compact_chunk<COMP, DO_MIX, NT, true, VECS, THREADS, REDO>(A, row, chunk, stage, &s_count);
 }
 
 // The fallback of a failed guess on a long row, one launch.  A workgroup whose worker's list is
@@ -1744,7 +1775,7 @@ __global__ __launch_bounds__(256) void k_sel_fallback(Args A) {
       ctl->mode = mode;
       if (mode == 1u) {
         ctl->fallbacks += 1;
-        for (int sg = 0; sg < kSegs; ++sg) ctl->seg_count[sg] = 0;
+        for (int sg = 0; sg < kSegs; ++sg) ctl->seg_count[sg * kSegPad] = 0;
       }
     }
     if (t == 0) {
@@ -1777,7 +1808,10 @@ __global__ __launch_bounds__(256) void k_sel_fallback(Args A) {
     __syncthreads();
     if (t == 0) s_count = 0;
     __syncthreads();
-    compact_chunk<COMP, false, false, false, kCompactVecs>(A, i, chunk, stage, &s_count, &s_base);
+    if (COMP == Q_TOPK && A.deferred_sgd && A.G != nullptr)
+      compact_chunk<COMP, false, false, false, kCompactVecs, 256, true>(A, i, chunk, stage, &s_count);
+    else
+      compact_chunk<COMP, false, false, false, kCompactVecs>(A, i, chunk, stage, &s_count);
   }
 }
 
@@ -1795,7 +1829,7 @@ __device__ __forceinline__ void list_layout_wave(const Args& A, const WorkerCtl*
                                                  uint32_t* total_out, uint32_t* good_out,
                                                  uint32_t* short_out = nullptr) {
   const int lane = threadIdx.x & 63;
-  const uint32_t raw = lane < kSegs ? ctl->seg_count[lane] : 0u;
+  const uint32_t raw = lane < kSegs ? ctl->seg_count[lane * kSegPad] : 0u;
   const uint32_t len = raw < A.seg_cap ? raw : A.seg_cap;
   uint32_t incl = len;
   unsigned long long rawsum = raw;
@@ -1835,7 +1869,7 @@ __device__ __forceinline__ void row_entry(const Args& A, int i, uint32_t t, uint
   idx = t;
   if (COMP == Q_TOPK) {
     const int64_t o = (int64_t)i * A.ld + t;
-    a = __float_as_uint(A.X[o] - A.Xhat[o]);   // top_a never defers the local update
+    a = __float_as_uint(x_entry(A, o) - A.Xhat[o]);
   } else {
     const uint4 wds = random_words(A, i, A.vec_base + (t >> 2), STREAM_RANDK);
     a = ~pick(wds, (int)(t & 3u));
@@ -1974,7 +2008,7 @@ __device__ __forceinline__ void emit_entry(const Args& A, int i, bool keep, uint
 // Place the guess (and the bin width) for the next step below this step's
 // threshold key T: by the distance that, at the key density seen between the old
 // guess and T, holds `want` entries (for top_a the k entries kept now leave the
-// race, so want includes k).  Also resets the per-step counters.
+// race, so want includes k).  Also resets the per-step counters (the lists': reset_lists).
 __device__ __forceinline__ void next_guess(const Args& A, WorkerCtl* ctl, uint64_t kstar, uint32_t total,
                                            bool from_list, uint32_t emitted, uint32_t mode,
                                            bool have_floor = false, uint32_t floor_key = 0) {
@@ -2000,7 +2034,11 @@ __device__ __forceinline__ void next_guess(const Args& A, WorkerCtl* ctl, uint64
   ctl->small_count = 0;
   ctl->fb_abort = 0;
   if (mode == 2u) ctl->fallbacks += 1;
-  for (int s = 0; s < kSegs; ++s) ctl->seg_count[s] = 0;
+}
+
+// ... by thread 0; and the sub-list counters, each on a line of its own, by the first kSegs threads.
+__device__ __forceinline__ void reset_lists(WorkerCtl* ctl) {
+  if (threadIdx.x < (unsigned)kSegs) ctl->seg_count[threadIdx.x * kSegPad] = 0;
 }
 
 // Digit-by-digit radix select over the composite keys of the candidate list (ROW = false)
@@ -2065,6 +2103,7 @@ __device__ void refine_and_emit(const Args& A, int i, const uint32_t* pre, uint3
   __syncthreads();
   publish_bitmap(A, i, lbits);
   __syncthreads();
+  reset_lists(ctl);
   if (threadIdx.x == 0) next_guess(A, ctl, kstar, total, !ROW, *s_emit, ROW ? 2u : 0u, ROW, floor_key);
 }
 
@@ -2237,6 +2276,7 @@ __global__ __launch_bounds__(1024) void k_sel_refine(Args A0) {
   }
   __syncthreads();
   publish_bitmap(A, i, lbits);
+  reset_lists(ctl);
   if (threadIdx.x == 0) next_guess(A, ctl, s_kstar, total, true, s_emit, 0u);
 }
 
@@ -2421,6 +2461,7 @@ __global__ __launch_bounds__(1024) void k_sel_finish(Args A) {
     if (rank + 1u == need_in_bin) s_kstar = K;
   }
   __syncthreads();
+  reset_lists(ctl);
   if (threadIdx.x == 0) next_guess(A, ctl, s_kstar, total, true, above + need_in_bin, 0u);
 }
 

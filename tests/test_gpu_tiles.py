@@ -67,3 +67,14 @@ def test_local_update_formed_twice(n, d, align, comp, layered):
     layers = synth.layer_table(lengths) if layered else None
     walk(n, synth.layers_dim(layers) if layered else d, synth.ring_csr(n), comp, steps=2, levels=8, ld_align=align,
          layers=layers)
+
+
+@pytest.mark.parametrize("n,d", [(2, (1 << 21) + 1), (9, (1 << 21) + 130)])
+def test_topk_update_formed_for_the_keys_only(n, d):
+    """Rows above 2^21 entries: the candidate pass stores no x, neither does the repair of a failed
+    guess (the first step, and the one after the state has been scaled)."""
+    pair = Pair(synth.normal_state(n, d, seed=3), synth.ring_csr(n), 0.2, B.Q_TOPK, k=d // 1000, ld_align=32)
+    grads = synth.GradientStream(n, d, seed=4)
+    for t in range(4):
+        pair.check(pair.step(grads.next(), 0.1 if t != 2 else 50.0), tag="step %d" % t)
+    pair.close()
