@@ -325,7 +325,7 @@ def run_gpu(w, steps, warmup, profile=True, fused=True, mix_form=None, order=Non
                 bpe += 4 if name.endswith("_sgd") else 8   # the mix rides on this pass: + read s (+ write x)
             if bpe is not None and momentum and name.endswith("_sgd"):
                 bpe += 8                                   # + read and write the momentum memory
-            if bpe is not None and name in ("k_dense_apply_mix", "k_dense_apply"):
+            if bpe is not None and name in ("k_dense_apply_mix", "k_dense_apply_mix_sgd", "k_dense_apply"):
                 # + the message itself: one sign bit per entry (sign), b bits per entry (gsgd)
                 bpe += message_bits_per_entry(w) / 8.0
             if bpe is not None and not (w["comp"] == "randk" and name == "k_sel_compact"):

@@ -728,27 +728,35 @@ size_t narrow_lds(const Args& A) {
          (A.staged_nnz ? (size_t)A.staged_nnz * sizeof(float2) + (size_t)(A.n + 1) * sizeof(int) : 0);
 }
 
-template <int COMP, bool NT, bool LAYERED>
+template <int COMP, bool NT, int LAYERED>
 void launch_apply_mix_narrow(choco_ctx* ctx, const Args& A) {
   const dim3 grid((unsigned)((A.d + kNarrowCols - 1) / kNarrowCols));
 #define CALL(V, T) LAUNCH(ctx, A.G ? KID_DENSE_APPLY_MIX_SGD : KID_DENSE_APPLY_MIX, (k_dense_apply_mix_narrow<COMP, V, T, NT, LAYERED>), grid, dim3(T), narrow_lds(A), A)
   if (A.n <= 16) CALL(1, 256);
   else if (A.n <= 32) CALL(1, 512);
-  else CALL(2, 512);
+  else if constexpr (LAYERED != 2) CALL(2, 512);
 #undef CALL
 }
 
-template <int COMP, bool CAPTURE, bool NT, bool LAYERED = false>
+template <int COMP, bool CAPTURE, bool NT, int LAYERED = 0>
 void launch_apply_mix(choco_ctx* ctx, const Args& A) {
   if (ctx->narrow_tile && (LAYERED || !A.fold_finalise)) {
-    if (ctx->nt_tile) launch_apply_mix_narrow<COMP, true, LAYERED>(ctx, A);
+    constexpr int FOLDED = LAYERED && COMP == Q_SIGN ? 2 : LAYERED;
+    if (A.fold_layers && ctx->nt_tile) launch_apply_mix_narrow<COMP, true, FOLDED>(ctx, A);
+    else if (A.fold_layers) launch_apply_mix_narrow<COMP, false, FOLDED>(ctx, A);
+    else if (ctx->nt_tile) launch_apply_mix_narrow<COMP, true, LAYERED>(ctx, A);
     else launch_apply_mix_narrow<COMP, false, LAYERED>(ctx, A);
     return;
   }
   const dim3 grid((unsigned)A.nchunks), block = tile_block(A);
   const size_t lds = (size_t)A.n * kChunk * sizeof(float);
-#define CALL(R, W) \
-  LAUNCH(ctx, A.G ? KID_DENSE_APPLY_MIX_SGD : KID_DENSE_APPLY_MIX, (k_dense_apply_mix<COMP, R, W, CAPTURE, NT, LAYERED>), grid, block, lds, A)
+#define CALL(R, W)                                                                                       \
+  do {                                                                                                   \
+    constexpr int FOLDED = LAYERED && COMP == Q_SIGN && R == 1 ? 2 : LAYERED;                            \
+    const int kid = A.G ? KID_DENSE_APPLY_MIX_SGD : KID_DENSE_APPLY_MIX;                                 \
+    if (A.fold_layers) LAUNCH(ctx, kid, (k_dense_apply_mix<COMP, R, W, CAPTURE, NT, FOLDED>), grid, block, lds, A); \
+    else LAUNCH(ctx, kid, (k_dense_apply_mix<COMP, R, W, CAPTURE, NT, LAYERED>), grid, block, lds, A);   \
+  } while (0)
   TILE_SWITCH(A, CALL)
 #undef CALL
 }
@@ -1131,11 +1139,12 @@ int gossip_layers_dense(choco_ctx* ctx, const Args& F0) {
   const Args& C = x_touched ? A : F;
   LAUNCH(ctx, C.redo_sgd ? KID_LAYER_STAT_REDO : C.G ? KID_LAYER_STAT_SGD : KID_LAYER_STAT, (k_layer_stat<COMP, NT>),
          dim3((unsigned)A.ngroup_items, (unsigned)A.n), dim3(stat_threads(NT)), 0, C);
-  LAUNCH(ctx, KID_LAYER_FINALISE, (k_layer_finalise<COMP>), dim3((unsigned)A.nlayers, (unsigned)A.n), dim3(256), 0, A);
+  if (!A.fold_layers)
+    LAUNCH(ctx, KID_LAYER_FINALISE, (k_layer_finalise<COMP>), dim3((unsigned)A.nlayers, (unsigned)A.n), dim3(256), 0, A);
   if (!mix_first && ctx->rpw) {
     if (F.redo_sgd) A.G = F.G;
-    if (A.codes) launch_apply_mix<COMP, true, NT, true>(ctx, A);
-    else launch_apply_mix<COMP, false, NT, true>(ctx, A);
+    if (A.codes) launch_apply_mix<COMP, true, NT, 1>(ctx, A);
+    else launch_apply_mix<COMP, false, NT, 1>(ctx, A);
   } else {
     launch_dense_apply<COMP, NT, true>(ctx, A);
     if (!mix_first) launch_mix_direct_global(ctx, A);
@@ -1809,6 +1818,12 @@ int choco_init(const choco_config* cfg, float* x_dev, void* workspace_dev, size_
       for (int32_t off = 0; off < D.len; off += span) groups.push_back(LayerGroup{D.start + off, D.len - off, D.id, 0});
     }
     group_first.push_back((int32_t)groups.size());
+    int32_t most = 0;
+    for (size_t l = 0; l + 1 < group_first.size(); ++l) most = std::max(most, group_first[l + 1] - group_first[l]);
+    // (one row per thread or wave only: see layer_scales_here)
+    A.fold_layers = (cfg->compressor == CHOCO_Q_SIGN && most <= kGroup && !ctx->layers_generic && ctx->rpw != 0 &&
+                     cfg->order == CHOCO_ORDER_COMPRESS_THEN_MIX &&
+                     (ctx->narrow_tile ? cfg->n <= 32 : cfg->n <= 16 && !four_by_four(A))) ? 1 : 0;
     chunk_layer.resize((size_t)L.nchunks);
     int32_t lay = 0;
     for (int32_t ch = 0; ch < L.nchunks && !ctx->layers_generic; ++ch) {

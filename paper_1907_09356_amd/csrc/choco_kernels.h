@@ -210,6 +210,7 @@ struct Args {
   uint32_t* layer_guess;     // n x nlayers: top_a threshold key of the last step (all ones: none yet)
   const LayerGroup* layer_groups;   // ngroup_items work items of the layer-wise norm pass, layer after layer
   const int32_t* layer_group_first; // nlayers + 1: where each layer's items start
+  int32_t fold_layers;       // the apply kernel does level 3 of the layers' norm trees itself (see layer_scales_here)
   int32_t ngroup_items;
   double* layer_group_sums;  // n x ngroup_items second-level norm sums
   LayerScale* layer_scale;   // n x nlayers: scales of the last step (sign, gsgd)
@@ -951,6 +952,65 @@ __device__ __forceinline__ void tile_mix_rows(const Args& A, const float* tile, 
   }
 }
 
+// Scales of a layer from its finished norm sum (Appendix C with the layer's length in the place of d);
+// fp64 sqrt and divisions, rounded once to fp32.
+template <int COMP>
+__device__ __forceinline__ LayerScale layer_scale_from(const Args& A, double total, int len, double& nrm) {
+  LayerScale ls;
+  ls.c = ls.r = ls.step = 0.0f;
+  ls.nonzero = 0;
+  nrm = 0.0;
+  if (COMP == Q_SIGN) {
+    ls.c = (float)(total / (double)len);
+  } else {
+    nrm = sqrt(total);
+    const double s = (double)A.levels, dl = (double)len;
+    const double tau = A.qsgd_biased ? 1.0 + fmin(dl / (s * s), sqrt(dl) / s) : 1.0;
+    ls.nonzero = nrm > 0.0 ? 1 : 0;
+    ls.r = nrm > 0.0 ? (float)(s / nrm) : 0.0f;
+    ls.step = nrm > 0.0 ? (float)(nrm / (tau * s)) : 0.0f;
+  }
+  return ls;
+}
+
+template <int COMP>
+__device__ __forceinline__ void record_layer_scale(const Args& A, int i, int lay, const LayerScale& ls, double total,
+                                                   double nrm) {
+  A.layer_scale[(int64_t)i * A.nlayers + lay] = ls;
+  double* scal = A.layer_scal + ((int64_t)i * A.nlayers + lay) * 4;
+  scal[0] = total;
+  scal[1] = COMP == Q_SIGN ? (double)ls.c : nrm;
+  scal[2] = COMP == Q_SIGN ? 0.0 : (double)ls.r;
+  scal[3] = COMP == Q_SIGN ? 0.0 : (double)ls.step;
+}
+
+// Layer-wise sign / gsgd on a table whose layers have at most kGroup = 16 group sums (65,536 entries)
+// each: level 3 of the norm tree and the layer's scales inside the apply kernel, instead of in a
+// launch of their own (sign on 65 layers: n = 8 21.9 -> 20.7 us per step, n = 16 33.2 -> 32.3, with
+// momentum 38.6 -> 37.6).  Not for gsgd, whose square root and divisions for every layer of a tile cost
+// more than the launch (n = 8, 65 layers 23.9 -> 26.0), nor with two rows per thread (more than the
+// 64 registers that fill a compute unit; n = 64 125 -> 127).  Sixteen lanes hold a layer's group sums;
+// the tree over 256 lanes of which the rest are +0.0 is the tree over these sixteen.  Sixteen lanes
+// of one row call it together, `lay` the layer of the lane's own entries (ascending over the lanes);
+// the layers first .. last of the sixteen lanes are gone through in turn.  The lane whose tile holds a
+// layer's first entry records its scales.
+template <int COMP>
+__device__ __forceinline__ void layer_scales_here(const Args& A, int r, int lay, int first, int last, int tile_lo,
+                                                  int tile_hi, RowScale<COMP>& sc) {
+  const int l16 = threadIdx.x & (kGroup - 1);
+  for (int L = first; L <= last; ++L) {
+    const int g0 = A.layer_group_first[L], ng = A.layer_group_first[L + 1] - g0;
+    const LayerDesc D = A.layers[L];
+    const double total =
+        group_tree_sum(l16 < ng ? A.layer_group_sums[(int64_t)r * A.ngroup_items + g0 + l16] : 0.0);
+    double nrm;
+    const LayerScale ls = layer_scale_from<COMP>(A, total, D.len, nrm);
+    if (L == lay) sc.load(ls);
+    if (D.start >= tile_lo && D.start < tile_hi && (threadIdx.x & 63) % kGroup == 0)
+      record_layer_scale<COMP>(A, r, L, ls, total, nrm);
+  }
+}
+
 // ---- tiles of 64 columns: what their kernels share (k_tile_mix_narrow says why the shape) ----
 constexpr int kNarrowCols = 64;
 constexpr int kStagedNnz = 1024;
@@ -1000,9 +1060,9 @@ __device__ __forceinline__ void narrow_mix(const Args& A, const float* tile, con
   for (int c = 0; c < 4; ++c) x[c] = x[c] + A.gamma * acc[c];
 }
 
-// LAYERED: the operator is applied layer by layer; the scales come per (worker, layer) from
-// the layer-wise norm pass.
-template <int COMP, int RPW, int NW, bool CAPTURE, bool NT, bool LAYERED>
+// LAYERED: the operator is applied layer by layer; 1: the scales come per (worker, layer) from
+// k_layer_finalise, 2: they are made here (layer_scales_here).
+template <int COMP, int RPW, int NW, bool CAPTURE, bool NT, int LAYERED>
 __global__ __launch_bounds__(64 * NW) void k_dense_apply_mix(Args A) {
   extern __shared__ float tile[];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -1010,7 +1070,7 @@ __global__ __launch_bounds__(64 * NW) void k_dense_apply_mix(Args A) {
   const int e = tile_no * kChunk + lane * 4;
   const bool valid = e < A.d;
   int lay = 0, nvalid = A.d - e < 4 ? A.d - e : 4;   // the last 4-vector of a row may end in pad columns
-  const bool generic = LAYERED && A.layers_generic;   // a 4-vector may span layers and gaps: scales entry by entry
+  const bool generic = LAYERED == 1 && A.layers_generic;   // a 4-vector may span layers and gaps: scales entry by entry
   if (LAYERED && valid && !generic) lay = layer_of_vector(A, e, nvalid);
   vf4 xr[RPW], xh[RPW], g[RPW];
 #pragma unroll
@@ -1029,7 +1089,12 @@ __global__ __launch_bounds__(64 * NW) void k_dense_apply_mix(Args A) {
   for (int q = 0; q < RPW; ++q) {
     const int r = wave + NW * q;
     if (LAYERED) {
-      if (r < A.n && valid && !generic) sc[q].load(A.layer_scale[(int64_t)r * A.nlayers + lay]);
+      if (LAYERED == 2 && r < A.n) {
+        const int l0 = __shfl(valid ? lay : A.nlayers - 1, 0, 64), l1 = __shfl(valid ? lay : A.nlayers - 1, 63, 64);
+        layer_scales_here<COMP>(A, r, lay, l0, l1, tile_no * kChunk, tile_no * kChunk + kChunk, sc[q]);
+      } else if (LAYERED == 1 && r < A.n && valid && !generic) {
+        sc[q].load(A.layer_scale[(int64_t)r * A.nlayers + lay]);
+      }
     } else if (r < A.n) {
       if ((COMP == Q_SIGN || COMP == Q_QSGD) && A.fold_finalise) {
         const double total = wave_level3(A, r, lane);
@@ -1077,7 +1142,7 @@ __global__ __launch_bounds__(64 * NW) void k_dense_apply_mix(Args A) {
 
 // The same pass in tiles of 64 columns (see k_tile_mix_narrow for the shape; the scales come from
 // memory: a wave holds four rows, so the tree's last level would be done for each of them in turn).
-template <int COMP, int VPT, int TH, bool NT, bool LAYERED>
+template <int COMP, int VPT, int TH, bool NT, int LAYERED>
 __global__ __launch_bounds__(TH) void k_dense_apply_mix_narrow(Args A) {
   extern __shared__ float tile[];
   constexpr int LPR = kNarrowCols / 4, RS = TH / LPR;   // lanes per row, rows side by side
@@ -1087,7 +1152,7 @@ __global__ __launch_bounds__(TH) void k_dense_apply_mix_narrow(Args A) {
   const int e = die_run_tile((int)blockIdx.x, (int)gridDim.x) * kNarrowCols + lr * 4;
   const bool valid = e < A.d;
   int lay = 0, nvalid = A.d - e < 4 ? A.d - e : 4;
-  const bool generic = LAYERED && A.layers_generic;
+  const bool generic = LAYERED == 1 && A.layers_generic;
   if (LAYERED && valid && !generic) lay = layer_of_vector(A, e, nvalid);
   vf4 x[VPT], xh[VPT], g[VPT];
   RowScale<COMP> sc[VPT];
@@ -1100,8 +1165,15 @@ __global__ __launch_bounds__(TH) void k_dense_apply_mix_narrow(Args A) {
       xh[u] = load4<NT>(A.Xhat + o);
       if (NT && A.G) g[u] = load4<true>(A.G + o);   // (redo_sgd; streamed states only)
       if (!LAYERED) sc[u].load(A.ctl + r);
-      else if (!generic) sc[u].load(A.layer_scale[(int64_t)r * A.nlayers + lay]);
+      else if (LAYERED == 1 && !generic) sc[u].load(A.layer_scale[(int64_t)r * A.nlayers + lay]);
     }
+  }
+  if (LAYERED == 2) {
+    const int l0 = __shfl(valid ? lay : A.nlayers - 1, 0, LPR), l1 = __shfl(valid ? lay : A.nlayers - 1, LPR - 1, LPR);
+    const int lo = e - lr * 4;
+#pragma unroll
+    for (int u = 0; u < VPT; ++u)
+      if (r0 + u * RS < A.n) layer_scales_here<COMP>(A, r0 + u * RS, lay, l0, l1, lo, lo + kNarrowCols, sc[u]);
   }
   stage_rows_of_w<TH>(A, nbr, rowp);
 #pragma unroll

@@ -540,27 +540,9 @@ __global__ __launch_bounds__(256) void k_layer_finalise(Args A) {
   }
   if (l != 0) return;
   const double total = sh[0];
-  const int len = A.layers[lay].len;
-  LayerScale ls;
-  ls.c = ls.r = ls.step = 0.0f;
-  ls.nonzero = 0;
-  double nrm = 0.0;
-  if (COMP == Q_SIGN) {
-    ls.c = (float)(total / (double)len);
-  } else {
-    nrm = sqrt(total);
-    const double s = (double)A.levels, dl = (double)len;
-    const double tau = A.qsgd_biased ? 1.0 + fmin(dl / (s * s), sqrt(dl) / s) : 1.0;
-    ls.nonzero = nrm > 0.0 ? 1 : 0;
-    ls.r = nrm > 0.0 ? (float)(s / nrm) : 0.0f;
-    ls.step = nrm > 0.0 ? (float)(nrm / (tau * s)) : 0.0f;
-  }
-  A.layer_scale[(int64_t)i * A.nlayers + lay] = ls;
-  double* scal = A.layer_scal + ((int64_t)i * A.nlayers + lay) * 4;
-  scal[0] = total;
-  scal[1] = COMP == Q_SIGN ? (double)ls.c : nrm;
-  scal[2] = COMP == Q_SIGN ? 0.0 : (double)ls.r;
-  scal[3] = COMP == Q_SIGN ? 0.0 : (double)ls.step;
+  double nrm;
+  const LayerScale ls = layer_scale_from<COMP>(A, total, A.layers[lay].len, nrm);
+  record_layer_scale<COMP>(A, i, lay, ls, total, nrm);
 }
 
 }  // namespace choco
