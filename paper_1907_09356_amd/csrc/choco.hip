@@ -923,7 +923,8 @@ void launch_select(choco_ctx* ctx, const Args& C, const Args& A, int kid_compact
     else if (kWide) LAUNCH(ctx, kid_compact, (k_sel_compact<COMP, COMP == Q_TOPK, NT, 1, false, 1024>), cgrid, dim3(1024), 0, C);
     else LAUNCH(ctx, kid_compact, (k_sel_compact<COMP, COMP == Q_TOPK, NT, kCompactVecs>), cgrid, dim3(256), 0, C);
   } else {
-    if (cvecs == 2) LAUNCH(ctx, kid_compact, (k_sel_compact<COMP, false, NT, 2>), cgrid, dim3(256), pad, C);
+    if (cvecs == 2)   // (top_a: one 4-vector per thread, n = 64, d = 65 k 33.8 -> 32.3 us per step, d = 270 k 96.0 -> 95.6)
+      LAUNCH(ctx, kid_compact, (k_sel_compact<COMP, false, NT, COMP == Q_TOPK ? 1 : 2>), chunk_grid(nvec, A.n, COMP == Q_TOPK ? 1 : 2), dim3(256), pad, C);
     else if (kWide && C.deferred_sgd)   // (1024 x 1 1066 us per step, 512 x 2 1035, 256 x 4 1030 at n = 8, d = 28 M)
       LAUNCH(ctx, kid_compact, (k_sel_compact<COMP, false, NT, kCompactVecs, false, 256, COMP == Q_TOPK>), cgrid, dim3(256), 0, C);
     else if (kWide) LAUNCH(ctx, kid_compact, (k_sel_compact<COMP, false, NT, 1, false, 1024>), cgrid, dim3(1024), pad, C);
@@ -1251,8 +1252,9 @@ int gossip_layers_sparse(choco_ctx* ctx, const Args& F) {
       LAUNCH(ctx, S.G ? KID_SEL_COMPACT_SGD : KID_SEL_COMPACT, (k_sel_compact<COMP, false, NT, 1, true, 1024>), cgrid,
              dim3(1024), 0, S);
     } else if (ctx->nbatched > 0) {
-      const dim3 cgrid((unsigned)((ctx->batched_nvec + 511) / 512), (unsigned)A.n, (unsigned)ctx->nbatched);
-      LAUNCH(ctx, S.G ? KID_SEL_COMPACT_SGD : KID_SEL_COMPACT, (k_sel_compact<COMP, false, NT, 2, true>), cgrid,
+      constexpr int V = COMP == Q_TOPK ? 1 : 2;   // (as for whole vectors of that length)
+      const dim3 cgrid((unsigned)((ctx->batched_nvec + 256 * V - 1) / (256 * V)), (unsigned)A.n, (unsigned)ctx->nbatched);
+      LAUNCH(ctx, S.G ? KID_SEL_COMPACT_SGD : KID_SEL_COMPACT, (k_sel_compact<COMP, false, NT, V, true>), cgrid,
              dim3(256), 0, S);
     }
     if (ctx->nbatched > 0) {
@@ -1670,8 +1672,11 @@ int choco_init(const choco_config* cfg, float* x_dev, void* workspace_dev, size_
   A.codes = nullptr;
   // with few group sums the fused apply kernel finishes the norm tree itself (one launch less), a row
   // per wave; above 16 workers a wave would finish several rows one after the other in every tile
-  // (n = 64, d = 270 k sign: 137 against 90 us per step with the launch and the narrow tile)
-  A.fold_finalise = (ctx->rpw != 0 && cfg->order == CHOCO_ORDER_COMPRESS_THEN_MIX && L.ngroups <= 256 && cfg->n <= 16) ? 1 : 0;
+  // (n = 64, d = 270 k sign: 137 against 90 us per step with the launch and the narrow tile), which
+  // up to 32 workers pays only when the tiles fill the chip (n = 24: d = 1,000 9.5 against 12.8, d = 40 k
+  // 14.4 against 14.9; n = 20, d = 100 k 21.9 against 19.9; n = 64, d = 16 k 19.0 against 15)
+  A.fold_finalise = (ctx->rpw != 0 && cfg->order == CHOCO_ORDER_COMPRESS_THEN_MIX && L.ngroups <= 256 &&
+                     (cfg->n <= 16 || (cfg->n <= 32 && L.nchunks <= 256))) ? 1 : 0;
   A.k = kept_per_worker(*cfg);
   A.hist16 = (uint32_t*)(base + L.hist16);
   A.cand = (uint2*)(base + L.cand);

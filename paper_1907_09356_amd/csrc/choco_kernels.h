@@ -558,6 +558,13 @@ __device__ __forceinline__ void emit_code_planes(const Args& A, int r, int e, in
     y |= y >> 14;
     return y & 0xFu;
   };
+  // gsgd on a long vector: nearly all levels are 0 (|v| s / ||v|| is a few thousandths), and in every
+  // second wave all of them are
+  if (COMP == Q_QSGD && __ballot((code[0] | code[1] | code[2] | code[3]) != 0) == 0ull) {
+    if (writer)
+      for (int p = 0; p < A.nplanes; ++p) P[(int64_t)p * A.plane_words] = 0u;
+    return;
+  }
   // one byte per entry: bit 7 = negative, bits 0..6 = min(level, 2^mb - 1) (levels above 127 are
   // handled plane by plane below)
   const uint32_t negs = ((uint32_t)code[0] >> 31) | (((uint32_t)code[1] >> 31) << 8) |
@@ -1122,7 +1129,7 @@ __global__ __launch_bounds__(64 * NW) void k_dense_apply_mix(Args A) {
           nh = absorb_by_entry<COMP>(A, r, e, xr[q], xh[q], words, code);
         } else {
           nh = absorb<COMP>(xr[q], xh[q], sc[q], words, code);
-          mask_padding(nvalid, xh[q], nh, code);
+          if (nvalid < 4) mask_padding(nvalid, xh[q], nh, code);
         }
         store4<NT>(A.Xhat + o, nh);
         if (CAPTURE) *reinterpret_cast<vi4*>(A.codes + o) = code;
@@ -1194,7 +1201,7 @@ __global__ __launch_bounds__(TH) void k_dense_apply_mix_narrow(Args A) {
         nh = absorb_by_entry<COMP>(A, r, e, x[u], xh[u], words, code);
       } else {
         nh = absorb<COMP>(x[u], xh[u], sc[u], words, code);
-        mask_padding(nvalid, xh[u], nh, code);
+        if (nvalid < 4) mask_padding(nvalid, xh[u], nh, code);
       }
       store4<NT>(A.Xhat + o, nh);
       if (A.codes) *reinterpret_cast<vi4*>(A.codes + o) = code;

@@ -78,3 +78,9 @@ def test_topk_update_formed_for_the_keys_only(n, d):
     for t in range(4):
         pair.check(pair.step(grads.next(), 0.1 if t != 2 else 50.0), tag="step %d" % t)
     pair.close()
+
+
+@pytest.mark.parametrize("n,d", [(24, 256 * 256), (24, 256 * 256 + 1), (64, 250)])
+def test_norm_finished_in_the_apply_pass_or_before_it(n, d):
+    """17 to 32 workers: up to 256 tiles of 256 columns the apply pass finishes the norms itself."""
+    walk(n, d, synth.ring_csr(n), B.Q_SIGN, steps=2)
