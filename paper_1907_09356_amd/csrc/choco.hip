@@ -146,7 +146,7 @@ constexpr int kMaxTileRows = 64;  // n * 1 KiB of LDS for the tile of all rows
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 struct Layout {
-  size_t xhat, s, row_ptr, col, w, ctl, chunk_sums, group_sums, hist16, cand, hist_parts, small_list, sel_idx, sel_val, keptmap, bitmap,
+  size_t xhat, s, row_ptr, col, w, ctl, seg_counts, chunk_sums, group_sums, hist16, cand, hist_parts, small_list, sel_idx, sel_val, keptmap, bitmap,
       layers, layer_work, long_tab, layer_guess, layer_scal, layer_groups, layer_group_first, layer_group_sums, layer_scale,
       chunk_layer, planes, ovf_ring, ovf_pos, wire_rank, wire_word_off, wire_plane_off, sel_idx2, bitmap2, keptmap2, layer_scal2, qv, mpart, total;
   int64_t wire_words, wire_plane_words;   // layer by layer: words of a worker's message / of one bit plane
@@ -408,6 +408,7 @@ Layout make_layout(const choco_config& c, int32_t nnz) {
   L.col = take((size_t)nnz * sizeof(int32_t));
   L.w = take((size_t)nnz * sizeof(float));
   L.ctl = take((size_t)c.n * std::max<size_t>(1, longs.size()) * sizeof(WorkerCtl));
+  L.seg_counts = take(guessed ? (size_t)c.n * std::max<size_t>(1, longs.size()) * kSegs * kSegPad * sizeof(uint32_t) : 0);
   L.nchunks = (int32_t)((c.d + kChunk - 1) / kChunk);
   L.ngroups = (L.nchunks + kGroup - 1) / kGroup;
   const bool dense_stat = c.compressor == CHOCO_Q_SIGN || c.compressor == CHOCO_Q_QSGD;
@@ -1654,6 +1655,7 @@ int choco_init(const choco_config* cfg, float* x_dev, void* workspace_dev, size_
   A.rows_in_turn = (cfg->n <= 8 && cfg->d >= ((int64_t)1 << 24)) ? 1 : 0;
   A.staged_nnz = nnz <= kStagedNnz ? nnz : 0;
   A.ctl = (WorkerCtl*)(base + L.ctl);
+  A.seg_counts = (uint32_t*)(base + L.seg_counts);
   // polls of about 2 us each: a tenth of a second before a workgroup of the fallback stops waiting
   // for its worker's others (CHOCO_FALLBACK_SPIN_LIMIT: for tests of that path, which scans the row)
   A.spin_limit = 1u << 16;

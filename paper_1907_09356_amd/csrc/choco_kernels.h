@@ -64,7 +64,6 @@ struct WorkerCtl {
   uint32_t guess_key;   // entries with key32 >= this are appended to the candidate list
   uint32_t bin_shift;   // the select bins candidates by min((key32 - guess_key) >> bin_shift, 2047)
   uint32_t mode;        // 0: candidate list is complete, 1: rebuild it, 2: scan the row
-  alignas(128) uint32_t seg_count[kSegs * kSegPad];  // entries with key32 >= guess_key appended per sub-list (may exceed seg_cap)
   uint32_t kept;        // number of entries emitted by the last selection
   uint32_t fallbacks;   // how many steps needed a fallback (histogram rebuild or row scan)
   uint32_t last_candidates;  // length of the candidate list the last select worked on
@@ -167,6 +166,8 @@ struct Args {
   uint2* cand;         // n x kSegs x seg_cap  (a, index)
   uint32_t* hist_parts; // n x kRefineParts x kBins: per-block candidate histograms (multi-block select)
   uint2* small_list;   // n x kSmallCap: entries of the threshold bin (multi-block select)
+  uint32_t* seg_counts;  // n x kSegs x kSegPad: entries with key32 >= guess_key appended per sub-list (may exceed
+                         // seg_cap), a cache line per counter
   uint32_t seg_cap;    // capacity of one sub-list
   uint32_t cand_cap;   // largest total the fallback aims to stay under
   uint32_t sample_stride;  // the fallback histogram looks at every sample_stride-th 4-vector
@@ -235,6 +236,7 @@ __host__ __device__ __forceinline__ Args long_view(const Args& src, const LongSe
   R.e_lo = L.e_lo;
   R.k = L.k;
   R.ctl = src.ctl + (int64_t)L.set * src.n;
+  R.seg_counts = src.seg_counts + (int64_t)L.set * src.n * (kSegs * kSegPad);
   R.sel_idx += L.sel_base;     // sel_stride stays the worker's whole list
   R.sel_val += L.sel_base;
   R.idx_base = L.base;
@@ -1586,14 +1588,19 @@ struct Digits {
   }
 };
 
+// The counter of sub-list s of worker i.
+__device__ __forceinline__ uint32_t* seg_counter(const Args& A, int i, int s) {
+  return A.seg_counts + ((int64_t)i * kSegs + s) * kSegPad;
+}
+
 // The candidate list of a worker holds the k largest entries iff at least k
 // entries qualified in total and no sub-list overflowed.
-__device__ __forceinline__ bool list_is_good(const WorkerCtl* ctl, const Args& A) {
+__device__ __forceinline__ bool list_is_good(const Args& A, int i) {
   uint64_t total = 0;
   bool fits = true;
 #pragma unroll
   for (int s = 0; s < kSegs; ++s) {
-    const uint32_t c = ctl->seg_count[s * kSegPad];
+    const uint32_t c = *seg_counter(A, i, s);
     total += c;
     fits = fits && (c <= A.seg_cap);
   }
@@ -1706,7 +1713,7 @@ __device__ __forceinline__ void compact_chunk(const Args& A, int i, int chunk, u
           if (slot < (uint32_t)kStageCap) {
             stage[slot] = make_uint2(a[u][c], (uint32_t)e);
           } else {   // more hits than the stage holds: append one by one
-            const uint32_t pos = atomicAdd(&ctl->seg_count[seg * kSegPad], 1u);
+            const uint32_t pos = atomicAdd(seg_counter(A, i, seg), 1u);
             if (pos < A.seg_cap) cand[pos] = make_uint2(a[u][c], (uint32_t)e);
           }
         }
@@ -1720,7 +1727,7 @@ __device__ __forceinline__ void compact_chunk(const Args& A, int i, int chunk, u
   const uint32_t count = *s_count < (uint32_t)kStageCap ? *s_count : (uint32_t)kStageCap;
   if (count != 0) {
     uint32_t base = 0;
-    if (threadIdx.x == 0) base = atomicAdd(&ctl->seg_count[seg * kSegPad], count);
+    if (threadIdx.x == 0) base = atomicAdd(seg_counter(A, i, seg), count);
     base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
     for (uint32_t t = threadIdx.x; t < count; t += 64)
       if (base + t < A.seg_cap) cand[base + t] = stage[t];
@@ -1781,7 +1788,7 @@ __global__ __launch_bounds__(256) void k_sel_fallback(Args A) {
   __shared__ uint32_t s_grp, s_above, s_last, s_gen, s_go;
   const int i = blockIdx.y;
   WorkerCtl* ctl = A.ctl + i;
-  if (list_is_good(ctl, A)) {
+  if (list_is_good(A, i)) {
     if (blockIdx.x == 0 && threadIdx.x == 0) ctl->mode = 0;
     return;
   }
@@ -1854,7 +1861,7 @@ __global__ __launch_bounds__(256) void k_sel_fallback(Args A) {
       ctl->mode = mode;
       if (mode == 1u) {
         ctl->fallbacks += 1;
-        for (int sg = 0; sg < kSegs; ++sg) ctl->seg_count[sg * kSegPad] = 0;
+        for (int sg = 0; sg < kSegs; ++sg) *seg_counter(A, i, sg) = 0;
       }
     }
     if (t == 0) {
@@ -1904,11 +1911,11 @@ __global__ __launch_bounds__(256) void k_sel_fallback(Args A) {
 // a wave scan - one round trip to memory instead of a thread's 32 loads in turn.
 constexpr uint32_t kSpecPerSeg = 256;   // entries of a sub-list that k_sel_refine fetches before it knows the lengths
 
-__device__ __forceinline__ void list_layout_wave(const Args& A, const WorkerCtl* ctl, uint32_t* lens, uint32_t* pre,
+__device__ __forceinline__ void list_layout_wave(const Args& A, int i, const WorkerCtl* ctl, uint32_t* lens, uint32_t* pre,
                                                  uint32_t* total_out, uint32_t* good_out,
                                                  uint32_t* short_out = nullptr) {
   const int lane = threadIdx.x & 63;
-  const uint32_t raw = lane < kSegs ? ctl->seg_count[lane * kSegPad] : 0u;
+  const uint32_t raw = lane < kSegs ? *seg_counter(A, i, lane) : 0u;
   const uint32_t len = raw < A.seg_cap ? raw : A.seg_cap;
   uint32_t incl = len;
   unsigned long long rawsum = raw;
@@ -2116,8 +2123,8 @@ __device__ __forceinline__ void next_guess(const Args& A, WorkerCtl* ctl, uint64
 }
 
 // ... by thread 0; and the sub-list counters, each on a line of its own, by the first kSegs threads.
-__device__ __forceinline__ void reset_lists(WorkerCtl* ctl) {
-  if (threadIdx.x < (unsigned)kSegs) ctl->seg_count[threadIdx.x * kSegPad] = 0;
+__device__ __forceinline__ void reset_lists(const Args& A, int i) {
+  if (threadIdx.x < (unsigned)kSegs) *seg_counter(A, i, (int)threadIdx.x) = 0;
 }
 
 // Digit-by-digit radix select over the composite keys of the candidate list (ROW = false)
@@ -2182,7 +2189,7 @@ __device__ void refine_and_emit(const Args& A, int i, const uint32_t* pre, uint3
   __syncthreads();
   publish_bitmap(A, i, lbits);
   __syncthreads();
-  reset_lists(ctl);
+  reset_lists(A, i);
   if (threadIdx.x == 0) next_guess(A, ctl, kstar, total, !ROW, *s_emit, ROW ? 2u : 0u, ROW, floor_key);
 }
 
@@ -2233,7 +2240,7 @@ __global__ __launch_bounds__(1024) void k_sel_refine(Args A0) {
     s_emit = 0;
     s_small = 0;
   }
-  if (threadIdx.x < 64) list_layout_wave(A, ctl, lens, pre, &s_total, &s_good, &s_short);
+  if (threadIdx.x < 64) list_layout_wave(A, i, ctl, lens, pre, &s_total, &s_good, &s_short);
   __syncthreads();
   const uint32_t total = s_total;
   if (!s_good) {
@@ -2355,7 +2362,7 @@ __global__ __launch_bounds__(1024) void k_sel_refine(Args A0) {
   }
   __syncthreads();
   publish_bitmap(A, i, lbits);
-  reset_lists(ctl);
+  reset_lists(A, i);
   if (threadIdx.x == 0) next_guess(A, ctl, s_kstar, total, true, s_emit, 0u);
 }
 
@@ -2386,7 +2393,7 @@ __global__ __launch_bounds__(1024) void k_sel_hist_parts(Args A) {
   const int i = blockIdx.y;
   const WorkerCtl* ctl = A.ctl + i;
   for (int b = threadIdx.x; b < kBins; b += 1024) h[b] = 0;
-  if (threadIdx.x < 64) list_layout_wave(A, ctl, lens, pre, &s_total, &s_good);
+  if (threadIdx.x < 64) list_layout_wave(A, i, ctl, lens, pre, &s_total, &s_good);
   __syncthreads();
   if (!s_good) return;
   uint32_t lo, hi;
@@ -2429,7 +2436,7 @@ __global__ __launch_bounds__(1024) void k_sel_emit_parts(Args A) {
   __shared__ uint32_t s_total, s_good, s_digit, s_above, s_count, s_base;
   const int i = blockIdx.y;
   WorkerCtl* ctl = A.ctl + i;
-  if (threadIdx.x < 64) list_layout_wave(A, ctl, lens, pre, &s_total, &s_good);
+  if (threadIdx.x < 64) list_layout_wave(A, i, ctl, lens, pre, &s_total, &s_good);
   __syncthreads();
   if (!s_good) return;
   sum_hist_parts(A, i, h);
@@ -2505,7 +2512,7 @@ __global__ __launch_bounds__(1024) void k_sel_finish(Args A) {
     s_need = (uint32_t)A.k;
     s_emit = 0;
   }
-  if (threadIdx.x < 64) list_layout_wave(A, ctl, lens, pre, &s_total, &s_good);
+  if (threadIdx.x < 64) list_layout_wave(A, i, ctl, lens, pre, &s_total, &s_good);
   __syncthreads();
   const uint32_t total = s_total;
   if (!s_good) {
@@ -2540,7 +2547,7 @@ __global__ __launch_bounds__(1024) void k_sel_finish(Args A) {
     if (rank + 1u == need_in_bin) s_kstar = K;
   }
   __syncthreads();
-  reset_lists(ctl);
+  reset_lists(A, i);
   if (threadIdx.x == 0) next_guess(A, ctl, s_kstar, total, true, above + need_in_bin, 0u);
 }
 
