@@ -288,7 +288,7 @@ SelectPlan plan_select(int compressor, int64_t d, int64_t k) {
   P.cand_cap = (uint32_t)cap;
   // sub-lists: block b of a worker appends to sub-list b % kSegs; each gets twice its even
   // share of the capacity, but never more than the blocks feeding it can produce
-  const int64_t per_block = 256 * kCompactVecs * 4;   // (short rows use half-size blocks: the bound below still holds)
+  const int64_t per_block = 256 * kCompactVecs * 4;   // (short rows use blocks of a quarter of that: the bound below still holds)
   const int64_t nblocks = (d + per_block - 1) / per_block;
   const int64_t feeders = (nblocks + kSegs - 1) / kSegs;
   int64_t seg_cap = std::max<int64_t>((2 * cap + kSegs - 1) / kSegs, 1024);
@@ -908,7 +908,7 @@ size_t ahead_lds_pad(const choco_ctx* ctx, int64_t row_len) {
 template <int COMP, bool NT>
 void launch_select(choco_ctx* ctx, const Args& C, const Args& A, int kid_compact, bool fuse_mix) {
   const int32_t nvec = (A.d + 3) >> 2;
-  // long rows: 4 four-vectors per thread, short ones 2; random_a 4 at any length (its pass draws
+  // long rows: 4 four-vectors per thread, short ones 1 (2 where the mix rides on the pass); random_a 4 at any length (its pass draws
   // Philox words beside the step's bandwidth-bound pass: half as many workgroups get in that pass's
   // way less, n = 64, d = 270 k: 79.4 -> 75.3 us per step; 8 per thread: 76.3; one per thread of a
   // 1024-thread workgroup, the shape top_a's long rows take: 73.7 against 66.4 us as the step stands now)

@@ -34,7 +34,7 @@ constexpr int kBins16 = 65536;    // first digit of the fallback histogram (16 b
 constexpr int kChunk = 256;       // entries per first-level norm chunk / tile width
 constexpr int kGroup = 16;        // chunks per second-level group (4096 entries)
 constexpr int kStreamVecs = 2;    // 4-vectors per thread in the streaming kernels
-constexpr int kCompactVecs = 4;   // 4-vectors per thread in the select pass (long rows; short rows take 2)
+constexpr int kCompactVecs = 4;   // 4-vectors per thread in the select pass of long rows and of random_a
 constexpr int kStageCap = 1024;   // candidates one block stages in LDS before its single append
 constexpr int kSmallCap = 1024;   // entries of the threshold bin the select ranks directly in LDS
 // Chunks per wave in the norm passes (a workgroup takes a group of 16 chunks): one, in
@@ -1736,8 +1736,8 @@ __device__ __forceinline__ void compact_chunk(const Args& A, int i, int chunk, u
 
 // The one pass of the fast path: every worker, one block per chunk.
 // grid (ceil(nvec / (THREADS * VECS)), n), block THREADS.  Chunks of 4096 entries for long rows,
-// of 2048 for short ones (twice the blocks and the occupancy: 49 against 57 us at n = 64,
-// d = 270 k).  A long row's chunk: top_a one 4-vector per thread of 1024 threads (6.2 TB/s at
+// of 1024 for short ones (more blocks and occupancy: n = 64, d = 270 k, 57 us with 4096, 49 with 2048;
+// per step 96.0 with 2048, 95.6 with 1024, d = 65 k 33.8 and 32.3).  A long row's chunk: top_a one 4-vector per thread of 1024 threads (6.2 TB/s at
 // d = 28 M; four per thread of 256 threads 6.0; two per thread 5.5), random_a four per thread of
 // 256 threads (its pass draws Philox words beside another pass and should get in its way little).
 // BATCH: grid.z counts the long layers of A.long_tab, grid.x covers the longest of them (the
