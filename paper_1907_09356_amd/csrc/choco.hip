@@ -1472,10 +1472,17 @@ int fused_iteration(choco_ctx* ctx, const LocalUpdate& u) {
 }
 
 // The figures of choco_metrics to `out` (three doubles), partial sums of up to max_blocks blocks to `part`.
+// One launch instead of two where the pass would have one block anyway (up to 1,024 entries), or two
+// (up to 2,048, n = 8: 5.0 against 6.3 us per call of choco_metrics_noalloc); with four, one
+// compute unit reads what four could (d = 4,096 in one launch and in two: n = 64 25.6 and 14.7, n = 1,000 356 and 158).
 void launch_metrics(choco_ctx* ctx, double* part, int max_blocks, double* out) {
   const Args& A = ctx->args;
-  if (A.d <= 4096) {
-    hipLaunchKernelGGL(k_metrics_small, dim3(1), dim3(1024), 0, ctx->stream, A, out);
+  if (A.d <= 1024) {
+    hipLaunchKernelGGL(k_metrics_small<256>, dim3(1), dim3(256), 0, ctx->stream, A, out);
+    return;
+  }
+  if (A.d <= 2048 && A.n <= 64) {
+    hipLaunchKernelGGL(k_metrics_small<512>, dim3(1), dim3(512), 0, ctx->stream, A, out);
     return;
   }
   const int blocks = (int)std::min<int64_t>(max_blocks, ((int64_t)A.d + 1023) / 1024);

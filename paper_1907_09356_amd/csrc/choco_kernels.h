@@ -2741,12 +2741,13 @@ __global__ __launch_bounds__(256) void k_metrics_final(const double* part, int n
   if (threadIdx.x == 0) metrics_figures(s, n, out);
 }
 
-// Short vectors (up to 4,096 entries): both in one launch of one block.
-__global__ __launch_bounds__(1024) void k_metrics_small(Args A, double* out) {
+// Short vectors: both in one launch of one block, a 4-vector per thread.
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void k_metrics_small(Args A, double* out) {
   MetricSums s{0.0, 0.0, 0.0};
   const int m = threadIdx.x;
   if (4 * m < A.d) metrics_column(A, 4 * (int64_t)m, A.d - 4 * m, s);
-  s = metrics_block_sum<1024>(s);
+  s = metrics_block_sum<THREADS>(s);
   if (threadIdx.x == 0) metrics_figures(s, A.n, out);
 }
 

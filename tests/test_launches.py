@@ -1,0 +1,27 @@
+"""Which kernels a configuration runs, and in what shape: the rules of the dispatch, on the CPU."""
+import pytest
+
+from tests.launches import recorded
+
+pytestmark = pytest.mark.timeout(300)
+
+
+def names(launches):
+    return [l[0].split("<")[0] for l in launches]
+
+
+def test_metrics_in_one_launch_only_where_one_workgroup_is_enough():
+    out = recorded("""
+out = {}
+for n, d in ((1000, 1024), (64, 1025), (64, 2048), (65, 2048), (8, 2049), (8, 4096), (1000, 4096)):
+    c = Context(n, d, B.Q_SIGN)
+    out["%d %d" % (n, d)] = c.metrics()
+    c.close()
+""")
+    one = {k for k, v in out.items() if len(v) == 1}
+    assert one == {"1000 1024", "64 1025", "64 2048"}
+    assert out["1000 1024"][0][:3] == ["k_metrics_small<256>", "1x1x1", "256x1x1"]
+    assert out["64 2048"][0][:3] == ["k_metrics_small<512>", "1x1x1", "512x1x1"]
+    for k, blocks in (("8 4096", 4), ("1000 4096", 4), ("65 2048", 2), ("8 2049", 3)):
+        assert names(out[k]) == ["k_metrics_partial", "k_metrics_final"]
+        assert out[k][0][1:3] == ["%dx1x1" % blocks, "256x1x1"]
