@@ -1473,8 +1473,9 @@ int fused_iteration(choco_ctx* ctx, const LocalUpdate& u) {
 
 // The figures of choco_metrics to `out` (three doubles), partial sums of up to max_blocks blocks to `part`.
 // One launch instead of two where the pass would have one block anyway (up to 1,024 entries), or two
-// (up to 2,048, n = 8: 5.0 against 6.3 us per call of choco_metrics_noalloc); with four, one
-// compute unit reads what four could (d = 4,096 in one launch and in two: n = 64 25.6 and 14.7, n = 1,000 356 and 158).
+// (up to 2,048; us per call of choco_metrics_noalloc, one launch and two: n = 8 5.0 and 6.3, n = 64 16.4
+// and 17.6, n = 256 55.1 and 53.6); with four, one compute unit reads what four could (d = 4,096, 1,024
+// threads: n = 8 6.9 and 6.5, n = 64 25.9 and 17.8, n = 1,000 358 and 206).
 void launch_metrics(choco_ctx* ctx, double* part, int max_blocks, double* out) {
   const Args& A = ctx->args;
   if (A.d <= 1024) {
