@@ -15,7 +15,8 @@
  *   - pointers named *_dev are device pointers, *_host are host pointers;
  *   - device buffers are owned by the caller (allocated e.g. with torch); the
  *     library allocates no device memory, it only carves up the workspace (and holds one
- *     page of pinned host memory, into which choco_metrics has its figures written);
+ *     page of pinned host memory, into which choco_metrics has its figures written; where
+ *     there is none to be had they are copied from the device);
  *   - work is enqueued on the caller's stream (one documented exception: the look-ahead
  *     selection of RANDK, see choco_set_lookahead) and the calls return without
  *     synchronising, except choco_metrics, choco_last_scalars, choco_layer_scalars,

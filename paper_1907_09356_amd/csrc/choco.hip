@@ -128,6 +128,7 @@ struct choco_ctx {
   double* metrics_part;   // device scratch of the metrics kernels
   double* metrics_host;   // the three figures in pinned host memory: a slot of the library's page ...
   int metrics_slot;       // ... this one, or -1: an allocation of the context's own
+  double* metrics_out;    // the three figures in device memory, where no pinned memory was to be had
   int metrics_blocks;
   int last_hip_error;
   // optional per-kernel timing with HIP events on the context's stream
@@ -495,7 +496,7 @@ Layout make_layout(const choco_config& c, int32_t nnz) {
     }
   // random_a whose update of xhat rides on the fused mix pass: the kept values by entry
   L.qv = take(fused_sparse_apply(c) && c.compressor == CHOCO_Q_RANDK ? state : 0);
-  L.mpart = take((size_t)kMetricsBlocks * 3 * sizeof(double));
+  L.mpart = take(((size_t)kMetricsBlocks + 1) * 3 * sizeof(double));   // the blocks' sums, then the figures
   L.total = off;
   return L;
 }
@@ -583,29 +584,31 @@ hipError_t resolve_scratch(int* device_out, double** addr_out) {
 // choco_metrics has its figures written to pinned host memory.  Contexts share one page of it, made
 // by the first and held until the process ends (pinning memory for every context would cost each
 // choco_init some 100 us); beyond kHostSlots contexts at a time one gets an allocation of its own.
+// A context for which there is no pinned memory has metrics_host null: its figures are copied.
 constexpr int kHostSlots = 64;
 std::mutex g_slot_mutex;
 double* g_slot_page = nullptr;
 uint64_t g_slots_used = 0;
 
-hipError_t take_host_slot(choco_ctx* ctx) {
+double* pinned_doubles(size_t count) {
+  double* p = nullptr;
+  if (hipHostMalloc((void**)&p, count * sizeof(double), hipHostMallocPortable) == hipSuccess) return p;
+  (void)hipGetLastError();   // (not for the next call to report)
+  return nullptr;
+}
+
+void take_host_slot(choco_ctx* ctx) {
   std::lock_guard<std::mutex> lock(g_slot_mutex);
   ctx->metrics_slot = -1;
-  if (!g_slot_page) {
-    const hipError_t e = hipHostMalloc((void**)&g_slot_page, kHostSlots * 8 * sizeof(double), hipHostMallocPortable);
-    if (e != hipSuccess) {
-      g_slot_page = nullptr;
-      return e;
-    }
-  }
-  for (int s = 0; s < kHostSlots; ++s)
+  if (!g_slot_page) g_slot_page = pinned_doubles(kHostSlots * 8);
+  for (int s = 0; g_slot_page && s < kHostSlots; ++s)
     if (!((g_slots_used >> s) & 1u)) {
       g_slots_used |= 1ull << s;
       ctx->metrics_slot = s;
       ctx->metrics_host = g_slot_page + 8 * s;
-      return hipSuccess;
+      return;
     }
-  return hipHostMalloc((void**)&ctx->metrics_host, 8 * sizeof(double), hipHostMallocPortable);
+  ctx->metrics_host = g_slot_page ? pinned_doubles(8) : nullptr;
 }
 
 void give_host_slot(choco_ctx* ctx) {
@@ -1875,10 +1878,8 @@ int choco_init(const choco_config* cfg, float* x_dev, void* workspace_dev, size_
     plane_off.push_back(po);
   }
   ctx->metrics_part = (double*)(base + L.mpart);
-  if (take_host_slot(ctx) != hipSuccess) {
-    release_ctx(ctx);
-    return CHOCO_E_HIP;
-  }
+  ctx->metrics_out = ctx->metrics_part + 3 * (size_t)kMetricsBlocks;
+  take_host_slot(ctx);
   ctx->metrics_blocks = kMetricsBlocks;
 
   // the library's own scratch array on this GPU (used by choco_metrics_noalloc only)
@@ -1994,12 +1995,16 @@ int choco_step_momentum(choco_ctx* ctx, const float* g_dev, float* m_dev, float 
 int choco_metrics(choco_ctx* ctx, double* consensus_host, double* mean_norm_host, double* psi_host) {
   if (!ctx) return CHOCO_E_INVAL;
   // the figures are written straight to pinned host memory: no copy to wait for after the kernels
-  launch_metrics(ctx, ctx->metrics_part, ctx->metrics_blocks, ctx->metrics_host);
+  launch_metrics(ctx, ctx->metrics_part, ctx->metrics_blocks, ctx->metrics_host ? ctx->metrics_host : ctx->metrics_out);
   LAUNCH_CHECK(ctx);
+  double copied[3];
+  if (!ctx->metrics_host)
+    HIP_TRY(ctx, hipMemcpyAsync(copied, ctx->metrics_out, sizeof(copied), hipMemcpyDeviceToHost, ctx->stream));
   HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
-  if (consensus_host) *consensus_host = ctx->metrics_host[0];
-  if (mean_norm_host) *mean_norm_host = ctx->metrics_host[1];
-  if (psi_host) *psi_host = ctx->metrics_host[2];
+  const double* out = ctx->metrics_host ? ctx->metrics_host : copied;
+  if (consensus_host) *consensus_host = out[0];
+  if (mean_norm_host) *mean_norm_host = out[1];
+  if (psi_host) *psi_host = out[2];
   return CHOCO_OK;
 }
 

@@ -75,7 +75,9 @@ class Context:
     def metrics(self):
         _stub.stub_clear()
         a = [ctypes.c_double(-1.0) for _ in range(3)]
-        return self._launches(self.B.lib().choco_metrics(self.ctx, *map(ctypes.byref, a)))
+        launches = self._launches(self.B.lib().choco_metrics(self.ctx, *map(ctypes.byref, a)))
+        self.figures = [v.value for v in a]
+        return launches
 
     def close(self):
         self.B.lib().choco_destroy(self.ctx)

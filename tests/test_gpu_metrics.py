@@ -69,3 +69,17 @@ def test_no_digits_are_lost(n, d, kind):
     ctx = open_ctx(X, H)
     check(ctx, X, H)
     ctx.close()
+
+
+def test_more_contexts_at_once_than_share_the_pinned_page():
+    states = [state(2, 50, "plain", seed=s) for s in range(70)]
+    ctxs = [open_ctx(*s) for s in states]
+    for ctx, s in zip(ctxs[::-1], states[::-1]):
+        check(ctx, *s)
+    for ctx in ctxs[::2]:
+        ctx.close()
+    again = [open_ctx(*s) for s in states[:10]]
+    for ctx, s in list(zip(ctxs[1::2], states[1::2])) + list(zip(again, states)):
+        check(ctx, *s)
+    for ctx in ctxs + again:
+        ctx.close()

@@ -25,3 +25,29 @@ for n, d in ((1000, 1024), (64, 1025), (64, 2048), (65, 2048), (8, 2049), (8, 40
     for k, blocks in (("8 4096", 4), ("1000 4096", 4), ("65 2048", 2), ("8 2049", 3)):
         assert names(out[k]) == ["k_metrics_partial", "k_metrics_final"]
         assert out[k][0][1:3] == ["%dx1x1" % blocks, "256x1x1"]
+
+
+def test_a_context_needs_no_pinned_memory():
+    """... not even for its metrics: they are copied then (a kernel that does not run leaves zeros)."""
+    out = recorded("""
+stub.stub_fail_pinned(1)
+c = Context(8, 5000, B.Q_SIGN)
+out = [c.rc, len(c.step()), len(c.metrics()), c.figures]
+stub.stub_fail_pinned(0)
+d = Context(8, 5000, B.Q_SIGN)
+out += [d.rc, len(d.metrics()), len(c.metrics()), c.figures]
+""")
+    assert out == [0, 2, 2, [0.0, 0.0, 0.0], 0, 2, 2, [0.0, 0.0, 0.0]]
+
+
+def test_sixty_four_contexts_share_a_page_of_pinned_memory():
+    out = recorded("""
+cs = [Context(3, 64, B.Q_SIGN) for _ in range(64)]
+out = [stub.stub_pinned_calls()]
+more = [Context(3, 64, B.Q_SIGN) for _ in range(2)]       # no slot left: an allocation each
+out += [stub.stub_pinned_calls(), [m.rc for m in more], [len(m.metrics()) for m in more]]
+more[0].close(); cs[5].close(); cs[63].close()
+again = [Context(3, 64, B.Q_SIGN) for _ in range(3)]      # the two slots given back, then one allocation
+out += [stub.stub_pinned_calls(), [len(c.metrics()) for c in again]]
+""")
+    assert out == [1, 3, [0, 0], [1, 1], 4, [1, 1, 1]]
