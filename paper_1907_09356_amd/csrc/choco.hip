@@ -104,7 +104,8 @@ struct choco_ctx {
   bool fallback_chain;    // long rows: a failed guess is repaired by the histogram passes, not a row scan
   bool nt;                // non-temporal loads/stores: the state does not fit in cache anyway
   bool narrow_tile;       // the mix takes tiles of 64 columns (n > 8, rows on whole lines)
-  bool nt_tile;           // ... and streams past the caches
+  bool nt_tile;           // ... and streams x (and xhat, unless hat_cached) past the caches
+  bool hat_cached;        // ... but reads xhat through them
   int nlayers;            // > 0: the operator is applied layer by layer
   bool layers_generic;    // ... on a table that is not aligned (see layers_aligned): no pass carries the local update
   int nmid, nsmall;       // layers (by falling length, after the long ones) that take a 1024- / a 256-thread workgroup
@@ -769,15 +770,23 @@ void launch_apply_mix(choco_ctx* ctx, const Args& A) {
 // lines: tiles of 64 columns.  NT: streamed past the caches from 48 MB per array on, also where the
 // passes before it go through them: nothing of this step reads x or xhat again, and written through
 // the caches they push out what the next pass has to read (64 rows of 270,000, three contexts in
-// turn: top_a 109 -> 99 us per step, random_a 91 -> 70; one context alone, everything still cached
-// from the step before: 96 -> 100, 67 -> 70; at 33 MB 54 against 55).
-template <bool NT, bool SPARSE>
+// turn: top_a 107 -> 92 us per step; one context alone, everything still cached from the step before,
+// 96 -> 95).  random_a has no pass that has just read x and xhat: it reads xhat through the caches, where
+// the lines that its own update stored are found again, and streams x from 12 MB on (up to 96 MB; in the
+// printed order from 48 MB): what the caches keep is then xhat, which nothing else pushes out.
+//   us per step, 64 rows, one context alone | three in turn:   both streamed     xhat cached    wide tile, both cached
+//   69 MB                                                     67.9 | 67.4       64.3 | 63.5       65.4 | 88
+//   69 MB with momentum                                       90.9 | 93         83.6 | 88         86.5 | 123
+//   12 rows of 40 MB with momentum  (cached: 72.5 | 70)          -              65.8 | 52         65.1 | 71
+//   65 layers of 270 k                                        87.4 | 80.8       83.5 | 78.2       85.9 | 97
+//   above 96 MB in turn the cached xhat loses: 64 rows, 130 MB 1.05 against 0.97 of the wide tile's time
+template <bool NT, bool SPARSE, bool NTHAT = NT>
 void launch_tile_mix_narrow(choco_ctx* ctx, const Args& A, int kid) {
   const dim3 grid((unsigned)((A.d + kNarrowCols - 1) / kNarrowCols));
   const size_t lds = narrow_lds(A);
   // a 4-vector per thread up to 32 rows, two above; workgroups of no more than four idle rows up to
   // 24, of eight above (half-idle workgroups of 512 threads at n = 20: 33.5 against 32.0 us per step)
-#define CALL(V, T) LAUNCH(ctx, kid, (k_tile_mix_narrow<V, T, NT, SPARSE>), grid, dim3(T), lds, A)
+#define CALL(V, T) LAUNCH(ctx, kid, (k_tile_mix_narrow<V, T, NT, SPARSE, NTHAT>), grid, dim3(T), lds, A)
   if (A.n <= 12) CALL(1, 192);
   else if (A.n <= 16) CALL(1, 256);
   else if (A.n <= 20) CALL(1, 320);
@@ -793,7 +802,8 @@ template <int STAT, bool NT, bool SPARSE = false>
 void launch_tile_mix(choco_ctx* ctx, const Args& A, bool fused) {
   const int kid = fused ? KID_TILE_MIX_SGD : KID_TILE_MIX;
   if (STAT == Q_NONE && ctx->narrow_tile) {
-    if (ctx->nt_tile) launch_tile_mix_narrow<true, SPARSE>(ctx, A, kid);
+    if (ctx->hat_cached) launch_tile_mix_narrow<true, SPARSE, false>(ctx, A, kid);
+    else if (ctx->nt_tile) launch_tile_mix_narrow<true, SPARSE>(ctx, A, kid);
     else launch_tile_mix_narrow<false, SPARSE>(ctx, A, kid);
     return;
   }
@@ -1640,7 +1650,9 @@ int choco_init(const choco_config* cfg, float* x_dev, void* workspace_dev, size_
   // against 121; aligned: 455 against 471).  One range stays with the wide tile: top_a through the
   // caches from 24 MB on, whose candidate pass leaves x and xhat there in long pieces (33 MB: 51.6
   // against 53.1; 16 MB: 34.9 against 33.4; random_a, no pass before it, 33 MB: 36.4 against 35.2).
-  ctx->nt_tile = ctx->nt || state_bytes >= ((size_t)48 << 20);
+  const bool past_caches = state_bytes >= ((size_t)48 << 20);
+  ctx->hat_cached = cfg->compressor == CHOCO_Q_RANDK && cache_resident && (past_caches || ctx->fused_sparse_apply);
+  ctx->nt_tile = ctx->nt || past_caches || ctx->hat_cached;
   const bool warm = cfg->compressor == CHOCO_Q_TOPK && !ctx->nt_tile && state_bytes >= ((size_t)24 << 20);
   ctx->narrow_tile = cfg->n > 8 && cfg->n <= kMaxTileRows && resolve_ld(*cfg) % 32 == 0 &&
                      ((uintptr_t)x_dev & 127u) == 0 && !warm;

@@ -1350,7 +1350,7 @@ __global__ __launch_bounds__(64 * NW) void k_tile_mix(Args A) {
 // bits store their 4-vectors; 128 bytes where rows are aligned) instead of the 4-vectors that
 // changed: partly written lines cost more than the bytes saved (58.8 -> 54.4 us).
 
-template <int VPT, int TH, bool NT, bool SPARSE>
+template <int VPT, int TH, bool NT, bool SPARSE, bool NTHAT>
 __global__ __launch_bounds__(TH) void k_tile_mix_narrow(Args A) {
   extern __shared__ float tile[];
   constexpr int LPR = kNarrowCols / 4, RS = TH / LPR;   // lanes per row, rows side by side
@@ -1369,7 +1369,7 @@ __global__ __launch_bounds__(TH) void k_tile_mix_narrow(Args A) {
     if (r < A.n && valid) {
       const int64_t o = (int64_t)r * A.ld + e;
       x[u] = load4<NT>(A.X + o);
-      xhv[u] = load4<NT>(A.Xhat + o);
+      xhv[u] = load4<NTHAT>(A.Xhat + o);
       if (sgd) gv[u] = load4<true>(A.G + o);   // a gradient is read once: always streamed
       if (mom) mv[u] = load4<NT>(A.M + o);
       if (SPARSE)

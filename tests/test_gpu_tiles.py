@@ -84,3 +84,10 @@ def test_topk_update_formed_for_the_keys_only(n, d):
 def test_norm_finished_in_the_apply_pass_or_before_it(n, d):
     """17 to 32 workers: up to 256 tiles of 256 columns the apply pass finishes the norms itself."""
     walk(n, d, synth.ring_csr(n), B.Q_SIGN, steps=2)
+
+
+@pytest.mark.parametrize("n", [9, 13, 20, 24, 32, 40, 48, 64])
+def test_random_a_with_x_streamed_and_xhat_cached(n):
+    """12 to 96 MB per array, every shape of the narrow tile."""
+    d = (13 << 18) // n + n % 5
+    walk(n, d, synth.ring_csr(n), B.Q_RANDK, steps=2, k=d // 50, momentum=n % 2 == 0)

@@ -51,3 +51,22 @@ again = [Context(3, 64, B.Q_SIGN) for _ in range(3)]      # the two slots given 
 out += [stub.stub_pinned_calls(), [len(c.metrics()) for c in again]]
 """)
     assert out == [1, 3, [0, 0], [1, 1], 4, [1, 1, 1]]
+
+
+def test_what_the_narrow_tile_streams():
+    """<.., x past the caches, update of xhat, xhat past the caches>"""
+    out = recorded("""
+out = {}
+for n, d in ((64, 40_000), (64, 65_000), (64, 270_000), (64, 400_000)):
+    for op, comp in (("topk", B.Q_TOPK), ("randk", B.Q_RANDK)):
+        for order in (0, 1):
+            c = Context(n, d, comp, k=d // 100, align=64, order=order)
+            tiles = [l[0] for l in c.step() if l[0].startswith("k_tile_mix")]
+            out["%s %d %d" % (op, d, order)] = tiles[0].split("<")[1].split(",", 2)[2][:-1] if tiles else ""
+            c.close()
+""")
+    streamed, cached, hat = "true,true,true", "false,true,false", "true,true,false"
+    assert [out["topk %d 0" % d] for d in (40_000, 65_000, 270_000, 400_000)] == [streamed, cached, streamed, streamed]
+    assert [out["randk %d 0" % d] for d in (40_000, 65_000, 270_000, 400_000)] == [streamed, hat, hat, streamed]
+    assert [out["randk %d 1" % d] for d in (40_000, 65_000, 270_000, 400_000)] == [
+        "true,false,true", "false,false,false", "true,false,false", "true,false,true"]
