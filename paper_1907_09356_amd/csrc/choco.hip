@@ -852,6 +852,34 @@ bool redo_sgd(const choco_ctx* ctx, const Args& F) {
          ctx->rpw != 0 && ctx->cfg.order == CHOCO_ORDER_COMPRESS_THEN_MIX;
 }
 
+// Does the apply pass finish the norm tree itself, in the wide tile, instead of reading scales that a
+// launch of its own has made, in the narrow tile if the rows allow it?  A row per wave (up to 16
+// workers): always.  Above, a wave finishes two or four rows one after the other in every tile, and the
+// wide tile holds one or two workgroups per compute unit: it pays while the tiles are few.
+// us per step, finished in the pass | by the launch (n, d, tiles of 256 columns):
+//   sign  20, 100 k, 391, streamed 15.1 | 18.8   17, 176 k, 690, streamed 21.5 | 24.1
+//         28, 125 k, 489, cached   24.2 | 26.0   32, 133 k, 519, cached   29.7 | 28.5
+//         40, 50 k, 196            15.8 | 19.7   40, 125 k, 489, cached   30.8 | 33.0
+//         48, 52 k, 204            18.4 | 21.5   48, 73 k, 285, cached    28.1 | 26.2
+//         64, 17.6 k, 69           18.0 | 16.7   64, 46.9 k, 184          21.9 | 22.7
+//   gsgd  24, 83 k, 326            21.3 | 19.4   40, 50 k, 196            19.5 | 23.1    48, 31 k, 123  20.4 | 18.0
+//   off whole lines, where there is no narrow tile:
+//   sign  64, 2,001, 8             15.1 | 16.7   24, 100 k, 391           18.3 | 21.5    24, 177 k, 692, cached 30.0 | 31.0
+//   gsgd  64, 2,001, 8             19.8 | 21.2   24, 100 k, 391           24.4 | 25.6    24, 270 k, 1,055  56.4 | 53.8
+bool folds_norms(const choco_config& c, bool narrow, bool nt, int32_t tiles) {
+  if (c.n <= 16) return true;
+  if (c.compressor == CHOCO_Q_SIGN) {
+    if (c.n <= 32) return tiles <= (nt ? 768 : narrow ? 512 : 1024);
+    if (c.n <= 48) return tiles <= (!nt && c.n <= 40 ? 512 : 256);
+    return tiles <= 256 && (!narrow || (nt && tiles > 128));
+  }
+  if (c.compressor == CHOCO_Q_QSGD) {
+    if (c.n <= 32) return tiles <= (narrow ? 256 : 512);
+    return tiles <= 256 && (!narrow || c.n <= 40);
+  }
+  return c.n <= 32 && tiles <= 256;   // identity has no norms: the tile it takes
+}
+
 // Dense operators (identity, sign, gsgd), direct mix form.
 template <int COMP, bool NT>
 int gossip_dense(choco_ctx* ctx, const Args& F0) {
@@ -1695,13 +1723,9 @@ int choco_init(const choco_config* cfg, float* x_dev, void* workspace_dev, size_
     A.tau = 1.0 + std::min(dd / (s * s), std::sqrt(dd) / s);
   }
   A.codes = nullptr;
-  // with few group sums the fused apply kernel finishes the norm tree itself (one launch less), a row
-  // per wave; above 16 workers a wave would finish several rows one after the other in every tile
-  // (n = 64, d = 270 k sign: 137 against 90 us per step with the launch and the narrow tile), which
-  // up to 32 workers pays only when the tiles fill the chip (n = 24: d = 1,000 9.5 against 12.8, d = 40 k
-  // 14.4 against 14.9; n = 20, d = 100 k 21.9 against 19.9; n = 64, d = 16 k 19.0 against 15)
+  // with few group sums the fused apply kernel finishes the norm tree itself (one launch less)
   A.fold_finalise = (ctx->rpw != 0 && cfg->order == CHOCO_ORDER_COMPRESS_THEN_MIX && L.ngroups <= 256 &&
-                     (cfg->n <= 16 || (cfg->n <= 32 && L.nchunks <= 256))) ? 1 : 0;
+                     folds_norms(*cfg, ctx->narrow_tile, ctx->nt, L.nchunks)) ? 1 : 0;
   A.k = kept_per_worker(*cfg);
   A.hist16 = (uint32_t*)(base + L.hist16);
   A.cand = (uint2*)(base + L.cand);

@@ -91,3 +91,10 @@ def test_random_a_with_x_streamed_and_xhat_cached(n):
     """12 to 96 MB per array, every shape of the narrow tile."""
     d = (13 << 18) // n + n % 5
     walk(n, d, synth.ring_csr(n), B.Q_RANDK, steps=2, k=d // 50, momentum=n % 2 == 0)
+
+
+@pytest.mark.parametrize("n,d,align", [(20, 256 * 391, 32), (40, 256 * 200 - 3, 32), (40, 256 * 350, 32), (48, 52_001, 32),
+                                       (64, 256 * 180, 32), (64, 2001, 4), (24, 256 * 300 + 1, 4)])
+@pytest.mark.parametrize("comp", [B.Q_SIGN, B.Q_QSGD])
+def test_norms_finished_in_the_apply_pass_of_more_than_sixteen_workers(n, d, align, comp):
+    walk(n, d, synth.ring_csr(n), comp, steps=2, levels=16, ld_align=align, momentum=n == 48)

@@ -70,3 +70,25 @@ for n, d in ((64, 40_000), (64, 65_000), (64, 270_000), (64, 400_000)):
     assert [out["randk %d 0" % d] for d in (40_000, 65_000, 270_000, 400_000)] == [streamed, hat, hat, streamed]
     assert [out["randk %d 1" % d] for d in (40_000, 65_000, 270_000, 400_000)] == [
         "true,false,true", "false,false,false", "true,false,false", "true,false,true"]
+
+
+def test_where_the_apply_pass_finishes_the_norms():
+    """A launch of k_dense_finalise or none; above 16 workers the latter is for few tiles."""
+    out = recorded("""
+out = {}
+for op, comp in (("sign", B.Q_SIGN), ("gsgd", B.Q_QSGD)):
+    for n, tiles, align in ((8, 4096, 64), (16, 4096, 64), (20, 391, 64), (20, 586, 64), (20, 700, 64), (24, 300, 64),
+                            (24, 300, 4), (24, 700, 4), (24, 1030, 4), (32, 513, 64), (40, 200, 64), (40, 500, 64), (40, 513, 64), (48, 200, 64), (48, 285, 64),
+                            (64, 100, 64), (64, 180, 64), (64, 220, 64), (64, 100, 4), (64, 260, 4)):
+        d = 256 * tiles - 64
+        c = Context(n, d - (align == 4) * 5, comp, levels=16, align=align)
+        l = c.step()
+        assert len(l) == (3 if "k_dense_finalise" in names(l) else 2)
+        out["%s %d %d %d" % (op, n, tiles, align)] = "k_dense_finalise" not in names(l)
+        c.close()
+""".replace("out = {}", "names = lambda l: [x[0].split('<')[0] for x in l]\nout = {}"))
+    folded = {k for k, v in out.items() if v}
+    assert folded == {
+        "sign 8 4096 64", "sign 16 4096 64", "sign 20 391 64", "sign 20 586 64", "sign 24 300 64", "sign 24 300 4", "sign 24 700 4",
+        "sign 40 200 64", "sign 40 500 64", "sign 48 200 64", "sign 64 180 64", "sign 64 100 4",
+        "gsgd 8 4096 64", "gsgd 16 4096 64", "gsgd 24 300 4", "gsgd 40 200 64", "gsgd 64 100 4"}
