@@ -707,16 +707,23 @@ dim3 chunk_grid(int32_t nvec, int32_t n, int vecs) {
 // rows; 16 rows of 1,080,000: 16 waves of one row 54.7 us, 4 waves of four 59.4), above that 16
 // waves of two or four rows.  Nine to twelve rows would leave a third of a compute unit's wave slots
 // free that way (768-thread workgroups): with tiles enough to fill the chip they take four waves of
-// up to four rows (9 rows of 270,000, sign: 21.2 against 21.8 us per step; 8 tiles, 9 rows of 2,000,
-// where a workgroup's own chain is all there is: 10.8 against 8.5).
+// up to four rows.  us per step, four by four | a row per wave: n = 9, sign, d = 140 k 14.2 | 13.9, 270 k
+// 18.1 | 20.4, 1 M 52.4 | 53.5; gsgd 140 k 16.9 | 16.0, 270 k 22.7 | 24.0, 540 k 41.0 | 39.7; top_a off whole
+// lines 270 k 29.9 | 31.0; 8 tiles, n = 9, d = 2,000, where a workgroup's own chain is all there is: 10.9 | 8.8.
+// The mix of the printed order, which has no xhat to update and may add up norms, takes them up to 16
+// rows: n = 16, sign, d = 270 k 29.6 | 30.4, 1 M 75.2 | 81.8; n = 13, gsgd, 1 M 67.4 | 73.7; random_a off
+// whole lines, n = 16, 540 k, contexts in turn 38.9 | 43.2.
 int pick_rpw(int n) { return n > kMaxTileRows ? 0 : n <= 16 ? 1 : n <= 32 ? 2 : 4; }
-bool four_by_four(const Args& A) { return A.n > 8 && A.n <= 12 && A.nchunks >= 512; }
-dim3 tile_block(const Args& A) { return dim3(A.n <= 8 ? 512 : four_by_four(A) ? 256 : A.n <= 12 ? 768 : 1024); }
+constexpr int kFourRows = 12, kFourRowsPrinted = 16;   // `most` below
+bool four_by_four(const Args& A, int most) { return A.n > 8 && A.n <= most && A.nchunks >= 512; }
+dim3 tile_block(const Args& A, int most) {
+  return dim3(A.n <= 8 ? 512 : four_by_four(A, most) ? 256 : A.n <= 12 ? 768 : 1024);
+}
 
-#define TILE_SWITCH(A, CALL)          \
+#define TILE_SWITCH(A, most, CALL)    \
   if ((A).n <= 8) {                   \
     CALL(1, 8);                       \
-  } else if (four_by_four(A)) {       \
+  } else if (four_by_four(A, most)) { \
     CALL(4, 4);                       \
   } else if ((A).n <= 12) {           \
     CALL(1, 12);                      \
@@ -753,7 +760,7 @@ void launch_apply_mix(choco_ctx* ctx, const Args& A) {
     else launch_apply_mix_narrow<COMP, false, LAYERED>(ctx, A);
     return;
   }
-  const dim3 grid((unsigned)A.nchunks), block = tile_block(A);
+  const dim3 grid((unsigned)A.nchunks), block = tile_block(A, kFourRows);
   const size_t lds = (size_t)A.n * kChunk * sizeof(float);
 #define CALL(R, W)                                                                                       \
   do {                                                                                                   \
@@ -762,7 +769,7 @@ void launch_apply_mix(choco_ctx* ctx, const Args& A) {
     if (A.fold_layers) LAUNCH(ctx, kid, (k_dense_apply_mix<COMP, R, W, CAPTURE, NT, FOLDED>), grid, block, lds, A); \
     else LAUNCH(ctx, kid, (k_dense_apply_mix<COMP, R, W, CAPTURE, NT, LAYERED>), grid, block, lds, A);   \
   } while (0)
-  TILE_SWITCH(A, CALL)
+  TILE_SWITCH(A, kFourRows, CALL)
 #undef CALL
 }
 
@@ -808,9 +815,10 @@ void launch_tile_mix(choco_ctx* ctx, const Args& A, bool fused) {
     return;
   }
   const size_t lds = (size_t)A.n * kChunk * sizeof(float);
-  const dim3 grid((unsigned)A.nchunks), block = tile_block(A);
+  constexpr int most = SPARSE ? kFourRows : kFourRowsPrinted;
+  const dim3 grid((unsigned)A.nchunks), block = tile_block(A, most);
 #define CALL(R, W) LAUNCH(ctx, kid, (k_tile_mix<STAT, R, W, NT, SPARSE>), grid, block, lds, A)
-  TILE_SWITCH(A, CALL)
+  TILE_SWITCH(A, most, CALL)
 #undef CALL
 }
 
@@ -1877,7 +1885,7 @@ int choco_init(const choco_config* cfg, float* x_dev, void* workspace_dev, size_
     // (one row per thread or wave only: see layer_scales_here)
     A.fold_layers = (cfg->compressor == CHOCO_Q_SIGN && most <= kGroup && !ctx->layers_generic && ctx->rpw != 0 &&
                      cfg->order == CHOCO_ORDER_COMPRESS_THEN_MIX &&
-                     (ctx->narrow_tile ? cfg->n <= 32 : cfg->n <= 16 && !four_by_four(A))) ? 1 : 0;
+                     (ctx->narrow_tile ? cfg->n <= 32 : cfg->n <= 16 && !four_by_four(A, kFourRows))) ? 1 : 0;
     chunk_layer.resize((size_t)L.nchunks);
     int32_t lay = 0;
     for (int32_t ch = 0; ch < L.nchunks && !ctx->layers_generic; ++ch) {

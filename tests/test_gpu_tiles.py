@@ -98,3 +98,13 @@ def test_random_a_with_x_streamed_and_xhat_cached(n):
 @pytest.mark.parametrize("comp", [B.Q_SIGN, B.Q_QSGD])
 def test_norms_finished_in_the_apply_pass_of_more_than_sixteen_workers(n, d, align, comp):
     walk(n, d, synth.ring_csr(n), comp, steps=2, levels=16, ld_align=align, momentum=n == 48)
+
+
+@pytest.mark.parametrize("n", [9, 12, 13, 16])
+@pytest.mark.parametrize("d", [256 * 511 - 4, 256 * 511 + 1])
+@pytest.mark.parametrize("comp,order", [(B.Q_SIGN, B.ORDER_COMPRESS_THEN_MIX), (B.Q_QSGD, B.ORDER_COMPRESS_THEN_MIX),
+                                        (B.Q_TOPK, B.ORDER_COMPRESS_THEN_MIX), (B.Q_SIGN, B.ORDER_MIX_THEN_COMPRESS),
+                                        (B.Q_QSGD, B.ORDER_MIX_THEN_COMPRESS), (B.Q_RANDK, B.ORDER_MIX_THEN_COMPRESS)])
+def test_wide_tile_around_512_tiles(n, d, comp, order):
+    """Four waves of four rows or a row per wave; rows off whole lines, where there is no narrow tile."""
+    walk(n, d, synth.ring_csr(n), comp, steps=2, levels=16, k=500, order=order, ld_align=4)

@@ -92,3 +92,25 @@ for op, comp in (("sign", B.Q_SIGN), ("gsgd", B.Q_QSGD)):
         "sign 8 4096 64", "sign 16 4096 64", "sign 20 391 64", "sign 20 586 64", "sign 24 300 64", "sign 24 300 4", "sign 24 700 4",
         "sign 40 200 64", "sign 40 500 64", "sign 48 200 64", "sign 64 180 64", "sign 64 100 4",
         "gsgd 8 4096 64", "gsgd 16 4096 64", "gsgd 24 300 4", "gsgd 40 200 64", "gsgd 64 100 4"}
+
+
+def test_waves_and_rows_of_the_wide_tile():
+    """Four waves of four rows for 9 to 12 workers, in the printed order's mix for 9 to 16, from 512 tiles on."""
+    out = recorded("""
+out = {}
+for n in (8, 9, 12, 13, 16, 17):
+    for tiles in (511, 512):
+        for order in (0, 1):
+            c = Context(n, 256 * tiles - 5, B.Q_SIGN, order=order)
+            l = [x for x in c.step() if x[0].startswith("k_tile_mix" if order else "k_dense_apply_mix")]
+            assert len(l) == 1
+            rows, waves = map(int, l[0][0].split("<")[1].split(",")[1:3])
+            assert l[0][2] == "%dx1x1" % (64 * waves) and rows * waves >= n
+            out["%d %d %d" % (n, tiles, order)] = [rows, waves]
+            c.close()
+""")
+    one = {8: [1, 8], 9: [1, 12], 12: [1, 12], 13: [1, 16], 16: [1, 16], 17: [2, 16]}
+    for n in one:
+        for order in (0, 1):
+            assert out["%d 511 %d" % (n, order)] == one[n]
+            assert out["%d 512 %d" % (n, order)] == ([4, 4] if 9 <= n <= (16 if order else 12) else one[n])
