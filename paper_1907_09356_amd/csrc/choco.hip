@@ -720,20 +720,27 @@ dim3 tile_block(const Args& A, int most) {
   return dim3(A.n <= 8 ? 512 : four_by_four(A, most) ? 256 : A.n <= 12 ? 768 : 1024);
 }
 
-#define TILE_SWITCH(A, most, CALL)    \
-  if ((A).n <= 8) {                   \
-    CALL(1, 8);                       \
-  } else if (four_by_four(A, most)) { \
-    CALL(4, 4);                       \
-  } else if ((A).n <= 12) {           \
-    CALL(1, 12);                      \
-  } else if ((A).n <= 16) {           \
-    CALL(1, 16);                      \
-  } else if ((A).n <= 32) {           \
-    CALL(2, 16);                      \
-  } else {                            \
-    CALL(4, 16);                      \
+int rows_per_wave(const Args& A, int most) {
+  return A.n <= 8 ? 1 : four_by_four(A, most) ? 4 : A.n <= 16 ? 1 : A.n <= 32 ? 2 : 4;
+}
+
+#define TILE_SWITCH(A, most, CALL)              \
+  switch (rows_per_wave(A, most)) {             \
+    case 1:                                     \
+      if ((A).n <= 8) CALL(1, 8);               \
+      else if ((A).n <= 12) CALL(1, 12);        \
+      else CALL(1, 16);                         \
+      break;                                    \
+    case 2: CALL(2, 16); break;                 \
+    default:                                    \
+      if (four_by_four(A, most)) CALL(4, 4);    \
+      else CALL(4, 16);                         \
   }
+
+// Can the apply pass finish the layers' norm trees?  With one row per wave or, in the narrow tile, thread
+// (see layer_scales_here).  What decides whether k_layer_finalise is launched and which form of the apply
+// kernel runs.
+bool one_row_each(const Args& A, bool narrow) { return narrow ? A.n <= 32 : rows_per_wave(A, kFourRows) == 1; }
 
 size_t narrow_lds(const Args& A) {
   return (size_t)A.n * kNarrowCols * sizeof(float) +
@@ -1882,10 +1889,8 @@ int choco_init(const choco_config* cfg, float* x_dev, void* workspace_dev, size_
     group_first.push_back((int32_t)groups.size());
     int32_t most = 0;
     for (size_t l = 0; l + 1 < group_first.size(); ++l) most = std::max(most, group_first[l + 1] - group_first[l]);
-    // (one row per thread or wave only: see layer_scales_here)
     A.fold_layers = (cfg->compressor == CHOCO_Q_SIGN && most <= kGroup && !ctx->layers_generic && ctx->rpw != 0 &&
-                     cfg->order == CHOCO_ORDER_COMPRESS_THEN_MIX &&
-                     (ctx->narrow_tile ? cfg->n <= 32 : cfg->n <= 16 && !four_by_four(A, kFourRows))) ? 1 : 0;
+                     cfg->order == CHOCO_ORDER_COMPRESS_THEN_MIX && one_row_each(A, ctx->narrow_tile)) ? 1 : 0;
     chunk_layer.resize((size_t)L.nchunks);
     int32_t lay = 0;
     for (int32_t ch = 0; ch < L.nchunks && !ctx->layers_generic; ++ch) {

@@ -108,3 +108,14 @@ def test_norms_finished_in_the_apply_pass_of_more_than_sixteen_workers(n, d, ali
 def test_wide_tile_around_512_tiles(n, d, comp, order):
     """Four waves of four rows or a row per wave; rows off whole lines, where there is no narrow tile."""
     walk(n, d, synth.ring_csr(n), comp, steps=2, levels=16, k=500, order=order, ld_align=4)
+
+
+@pytest.mark.parametrize("n", [9, 12, 13, 16])
+@pytest.mark.parametrize("tiles", [511, 512])
+@pytest.mark.parametrize("comp", [B.Q_SIGN, B.Q_QSGD])
+def test_layers_around_512_tiles(n, tiles, comp):
+    """The layers' norms come from the apply pass (sign, a row per wave) or from a launch of their own."""
+    layers = synth.layer_table([60_000, 7, 256 * tiles - 60_000 - 12 - 30_001, 29_989])
+    d = synth.layers_dim(layers)
+    assert (d + 255) // 256 == tiles
+    walk(n, d, synth.ring_csr(n), comp, steps=2, levels=16, ld_align=4, layers=layers, momentum=n == 12)

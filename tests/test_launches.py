@@ -114,3 +114,30 @@ for n in (8, 9, 12, 13, 16, 17):
         for order in (0, 1):
             assert out["%d 511 %d" % (n, order)] == one[n]
             assert out["%d 512 %d" % (n, order)] == ([4, 4] if 9 <= n <= (16 if order else 12) else one[n])
+
+
+def test_layer_scales_are_made_exactly_once():
+    """Either by a launch of k_layer_finalise or by the form of the apply kernel that makes them (its
+    last parameter 2), whatever the tile; never by the apply pass where it takes several rows at a time."""
+    out = recorded("""
+out = {}
+for n in (2, 8, 9, 12, 13, 16, 17, 32, 33, 64):
+    for lengths in ([700, 65536, 3], [65537, 700], [256 * 511 // 2 - 40] * 2, [256 * 512 // 2 - 4] * 2, [60000] * 3):
+        for align in (4, 32):
+            t = synth.layer_table(lengths)
+            for op, comp in (("sign", B.Q_SIGN), ("gsgd", B.Q_QSGD)):
+                c = Context(n, synth.layers_dim(t), comp, layers=t, align=align, levels=16)
+                l = [x[0] for x in c.step()]
+                apply = [x for x in l if x.startswith("k_dense_apply_mix")]
+                assert len(apply) == 1, l
+                out["%s %d %s %d" % (op, n, lengths[:2], align)] = [
+                    sum(x.startswith("k_layer_finalise") for x in l), int(apply[0].rstrip(">").split(",")[-1]), apply[0]]
+                c.close()
+""")
+    assert len(out) == 200
+    for key, (launches, layered, kernel) in out.items():
+        assert (launches, layered) in ((1, 1), (0, 2)), key
+        args = kernel.split("<")[1].split(",")
+        if layered == 2:
+            assert key.startswith("sign") and "65537" not in key and args[1] == "1", (key, kernel)
+    assert sum(v[1] == 2 for v in out.values()) > 40
