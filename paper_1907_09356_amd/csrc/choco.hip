@@ -98,7 +98,7 @@ struct choco_ctx {
   bool fused_sparse_apply;   // ... whose update of xhat rides on the tile mix pass (direct form, compress-then-mix)
   bool values_in_qv;      // random_a after such a step: the kept values are in Qv, not yet in the list
   int mix_form;           // resolved: CHOCO_MIX_INCREMENTAL_S or CHOCO_MIX_DIRECT
-  int rpw;                // rows per wave of the tile kernels, 0 = tile does not fit
+  bool tile_fits;         // the LDS tile of all rows exists (up to kMaxTileRows workers)
   bool fused;             // the step being enqueued carries the local update in its first pass
   bool multipart;         // long candidate lists: the select runs as three multi-block launches
   bool fallback_chain;    // long rows: a failed guess is repaired by the histogram passes, not a row scan
@@ -713,7 +713,6 @@ dim3 chunk_grid(int32_t nvec, int32_t n, int vecs) {
 // The mix of the printed order, which has no xhat to update and may add up norms, takes them up to 16
 // rows: n = 16, sign, d = 270 k 29.6 | 30.4, 1 M 75.2 | 81.8; n = 13, gsgd, 1 M 67.4 | 73.7; random_a off
 // whole lines, n = 16, 540 k, contexts in turn 38.9 | 43.2.
-int pick_rpw(int n) { return n > kMaxTileRows ? 0 : n <= 16 ? 1 : n <= 32 ? 2 : 4; }
 constexpr int kFourRows = 12, kFourRowsPrinted = 16;   // `most` below
 bool four_by_four(const Args& A, int most) { return A.n > 8 && A.n <= most && A.nchunks >= 512; }
 dim3 tile_block(const Args& A, int most) {
@@ -864,7 +863,7 @@ void launch_mix_direct_global(choco_ctx* ctx, const Args& A) {
 bool redo_sgd(const choco_ctx* ctx, const Args& F) {
   const int comp = ctx->cfg.compressor;
   return ctx->nt && F.G != nullptr && F.M == nullptr && (comp == CHOCO_Q_SIGN || comp == CHOCO_Q_QSGD) &&
-         ctx->rpw != 0 && ctx->cfg.order == CHOCO_ORDER_COMPRESS_THEN_MIX;
+         ctx->tile_fits && ctx->cfg.order == CHOCO_ORDER_COMPRESS_THEN_MIX;
 }
 
 // Does the apply pass finish the norm tree itself, in the wide tile, instead of reading scales that a
@@ -913,7 +912,7 @@ int gossip_dense(choco_ctx* ctx, const Args& F0) {
       if (!A.fold_finalise)
         LAUNCH(ctx, KID_DENSE_FINALISE, (k_dense_finalise<STATK>), dim3((unsigned)A.n), dim3(256), 0, A);
     }
-    if (ctx->rpw) {
+    if (ctx->tile_fits) {
       if (F.redo_sgd) A.G = F.G;
       if (A.codes) launch_apply_mix<COMP, true, NT>(ctx, A);
       else launch_apply_mix<COMP, false, NT>(ctx, A);
@@ -922,7 +921,7 @@ int gossip_dense(choco_ctx* ctx, const Args& F0) {
       launch_mix_direct_global(ctx, A);
     }
   } else {
-    if (ctx->rpw) {
+    if (ctx->tile_fits) {
       launch_tile_mix<STAT, NT>(ctx, F, fused);
       if (needs_stat)
         LAUNCH(ctx, KID_GROUP_REDUCE, k_group_reduce, dim3((unsigned)((A.ngroups + 15) / 16), (unsigned)A.n),
@@ -982,8 +981,8 @@ void launch_select(choco_ctx* ctx, const Args& C, const Args& A, int kid_compact
   } else {
     if (cvecs == 2)   // (top_a: one 4-vector per thread, n = 64, d = 65 k 33.8 -> 32.3 us per step, d = 270 k 96.0 -> 95.6)
       LAUNCH(ctx, kid_compact, (k_sel_compact<COMP, false, NT, COMP == Q_TOPK ? 1 : 2>), chunk_grid(nvec, A.n, COMP == Q_TOPK ? 1 : 2), dim3(256), pad, C);
-    else if (kWide && C.deferred_sgd)   // (1024 x 1 1066 us per step, 512 x 2 1035, 256 x 4 1030 at n = 8, d = 28 M)
-      LAUNCH(ctx, kid_compact, (k_sel_compact<COMP, false, NT, kCompactVecs, false, 256, COMP == Q_TOPK>), cgrid, dim3(256), 0, C);
+    else if (kWide && NT && C.deferred_sgd)   // (1024 x 1 1066 us per step, 512 x 2 1035, 256 x 4 1030 at n = 8, d = 28 M)
+      LAUNCH(ctx, kid_compact, (k_sel_compact<COMP, false, NT, kCompactVecs, false, 256, COMP == Q_TOPK && NT>), cgrid, dim3(256), 0, C);
     else if (kWide) LAUNCH(ctx, kid_compact, (k_sel_compact<COMP, false, NT, 1, false, 1024>), cgrid, dim3(1024), pad, C);
     else LAUNCH(ctx, kid_compact, (k_sel_compact<COMP, false, NT, kCompactVecs>), cgrid, dim3(256), pad, C);
   }
@@ -1112,7 +1111,7 @@ int gossip_sparse(choco_ctx* ctx, const Args& F) {
       fuse_mix = true;
     } else {
       if (incremental) launch_mix_incremental<NT>(ctx, F, fused);
-      else if (ctx->rpw) launch_tile_mix<Q_NONE, NT>(ctx, F, fused);
+      else if (ctx->tile_fits) launch_tile_mix<Q_NONE, NT>(ctx, F, fused);
       else launch_mix_direct_global(ctx, A);
       x_touched = true;
     }
@@ -1158,7 +1157,7 @@ int gossip_sparse(choco_ctx* ctx, const Args& F) {
     L.fold_xhat = fold_xhat ? 1 : 0;
     if (incremental) launch_mix_incremental<NT>(ctx, L, last_carries);
     else if (fused_apply) launch_tile_mix<Q_NONE, NT, true>(ctx, L, last_carries);
-    else if (ctx->rpw) launch_tile_mix<Q_NONE, NT>(ctx, L, last_carries);
+    else if (ctx->tile_fits) launch_tile_mix<Q_NONE, NT>(ctx, L, last_carries);
     else launch_mix_direct_global(ctx, A);
   }
   ctx->values_in_qv = fused_apply && COMP == Q_RANDK;
@@ -1190,7 +1189,7 @@ int gossip_layers_dense(choco_ctx* ctx, const Args& F0) {
   const bool mix_first = ctx->cfg.order == CHOCO_ORDER_MIX_THEN_COMPRESS;
   bool x_touched = false;
   if (mix_first) {
-    if (ctx->rpw) launch_tile_mix<Q_NONE, NT>(ctx, F, fused);   // carries the local update if there is one
+    if (ctx->tile_fits) launch_tile_mix<Q_NONE, NT>(ctx, F, fused);   // carries the local update if there is one
     else launch_mix_direct_global(ctx, A);                     // (never handed one: see first_pass_can_carry_sgd)
     x_touched = true;
   }
@@ -1199,7 +1198,7 @@ int gossip_layers_dense(choco_ctx* ctx, const Args& F0) {
          dim3((unsigned)A.ngroup_items, (unsigned)A.n), dim3(stat_threads(NT)), 0, C);
   if (!A.fold_layers)
     LAUNCH(ctx, KID_LAYER_FINALISE, (k_layer_finalise<COMP>), dim3((unsigned)A.nlayers, (unsigned)A.n), dim3(256), 0, A);
-  if (!mix_first && ctx->rpw) {
+  if (!mix_first && ctx->tile_fits) {
     if (F.redo_sgd) A.G = F.G;
     if (A.codes) launch_apply_mix<COMP, true, NT, 1>(ctx, A);
     else launch_apply_mix<COMP, false, NT, 1>(ctx, A);
@@ -1440,8 +1439,8 @@ bool first_pass_can_carry_sgd(const choco_ctx* ctx) {
   if (ctx->cfg.order == CHOCO_ORDER_COMPRESS_THEN_MIX)
     return comp == CHOCO_Q_SIGN || comp == CHOCO_Q_QSGD || comp == CHOCO_Q_TOPK;
   // printed order: the first kernel is the mix
-  if (ctx->sparse) return incremental || ctx->rpw != 0;   // k_sel_compact(+mix) / k_mix_incremental / k_tile_mix
-  return ctx->rpw != 0;                                    // k_tile_mix
+  if (ctx->sparse) return incremental || ctx->tile_fits;   // k_sel_compact(+mix) / k_mix_incremental / k_tile_mix
+  return ctx->tile_fits;                                    // k_tile_mix
 }
 
 int launch_sgd(choco_ctx* ctx, const float* g_dev, float lr) {
@@ -1458,7 +1457,7 @@ int launch_sgd(choco_ctx* ctx, const float* g_dev, float lr) {
 // before the final mix, so the local update is deferred into that mix.
 bool last_pass_carries_sgd(const choco_ctx* ctx) {
   return !ctx->layers_generic && ctx->cfg.compressor == CHOCO_Q_RANDK && ctx->cfg.order == CHOCO_ORDER_COMPRESS_THEN_MIX &&
-         (ctx->mix_form == CHOCO_MIX_INCREMENTAL_S || ctx->rpw != 0);
+         (ctx->mix_form == CHOCO_MIX_INCREMENTAL_S || ctx->tile_fits);
 }
 
 struct LocalUpdate {      // the local update a fused step carries (g == nullptr: none)
@@ -1666,7 +1665,7 @@ int choco_init(const choco_config* cfg, float* x_dev, void* workspace_dev, size_
   ctx->mix_form = resolve_mix_form(*cfg);
   ctx->fused_sparse_apply = fused_sparse_apply(*cfg);
   ctx->values_in_qv = false;
-  ctx->rpw = pick_rpw(cfg->n);
+  ctx->tile_fits = cfg->n <= kMaxTileRows;
   ctx->plan = SelectPlan{};
   ctx->plan.guess0 = 0xFFFFFFFFu;
   if (ctx->sparse && cfg->nlayers == 0) ctx->plan = plan_select(cfg->compressor, cfg->d, cfg->k);
@@ -1739,7 +1738,7 @@ int choco_init(const choco_config* cfg, float* x_dev, void* workspace_dev, size_
   }
   A.codes = nullptr;
   // with few group sums the fused apply kernel finishes the norm tree itself (one launch less)
-  A.fold_finalise = (ctx->rpw != 0 && cfg->order == CHOCO_ORDER_COMPRESS_THEN_MIX && L.ngroups <= 256 &&
+  A.fold_finalise = (ctx->tile_fits && cfg->order == CHOCO_ORDER_COMPRESS_THEN_MIX && L.ngroups <= 256 &&
                      folds_norms(*cfg, ctx->narrow_tile, ctx->nt, L.nchunks)) ? 1 : 0;
   A.k = kept_per_worker(*cfg);
   A.hist16 = (uint32_t*)(base + L.hist16);
@@ -1889,7 +1888,7 @@ int choco_init(const choco_config* cfg, float* x_dev, void* workspace_dev, size_
     group_first.push_back((int32_t)groups.size());
     int32_t most = 0;
     for (size_t l = 0; l + 1 < group_first.size(); ++l) most = std::max(most, group_first[l + 1] - group_first[l]);
-    A.fold_layers = (cfg->compressor == CHOCO_Q_SIGN && most <= kGroup && !ctx->layers_generic && ctx->rpw != 0 &&
+    A.fold_layers = (cfg->compressor == CHOCO_Q_SIGN && most <= kGroup && !ctx->layers_generic && ctx->tile_fits &&
                      cfg->order == CHOCO_ORDER_COMPRESS_THEN_MIX && one_row_each(A, ctx->narrow_tile)) ? 1 : 0;
     chunk_layer.resize((size_t)L.nchunks);
     int32_t lay = 0;

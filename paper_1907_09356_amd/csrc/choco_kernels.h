@@ -1783,7 +1783,7 @@ __global__ __launch_bounds__(THREADS) void k_sel_compact(Args A0) {
 template <int COMP>
 __global__ __launch_bounds__(256) void k_sel_fallback(Args A) {
   __shared__ uint2 stage[kStageCap];
-  __shared__ uint32_t s_count, s_base;
+  __shared__ uint32_t s_count;
   __shared__ uint32_t part[256];
   __shared__ uint32_t s_grp, s_above, s_last, s_gen, s_go;
   const int i = blockIdx.y;
