@@ -1689,15 +1689,14 @@ int choco_init(const choco_config* cfg, float* x_dev, void* workspace_dev, size_
   ctx->nt = state_bytes >= ((size_t)4 << 20) && !cache_resident;
   // narrow tiles want rows that start on whole 128-byte lines: off them a tile's 256-byte pieces touch
   // three lines instead of two (64 rows of 2,000,001: 639 against 534 us; 32 rows of 540,001: 124
-  // against 121; aligned: 455 against 471).  One range stays with the wide tile: top_a through the
-  // caches from 24 MB on, whose candidate pass leaves x and xhat there in long pieces (33 MB: 51.6
-  // against 53.1; 16 MB: 34.9 against 33.4; random_a, no pass before it, 33 MB: 36.4 against 35.2).
+  // against 121; aligned: 455 against 471).  top_a through the caches, wide and narrow: 16 rows, 24 MB
+  // 52.7 and 49.9, 40 MB 75.7 and 72.5; 32 rows, 33 MB 57.5 and 53.7; 48 rows, 28 MB 49.2 and 49.0, 40 MB
+  // 63.2 and 63.5; 64 rows, 28 MB 46.7 and 46.6, 40 MB 62.2 and 60.4.
   const bool past_caches = state_bytes >= ((size_t)48 << 20);
   ctx->hat_cached = cfg->compressor == CHOCO_Q_RANDK && cache_resident && (past_caches || ctx->fused_sparse_apply);
   ctx->nt_tile = ctx->nt || past_caches || ctx->hat_cached;
-  const bool warm = cfg->compressor == CHOCO_Q_TOPK && !ctx->nt_tile && state_bytes >= ((size_t)24 << 20);
   ctx->narrow_tile = cfg->n > 8 && cfg->n <= kMaxTileRows && resolve_ld(*cfg) % 32 == 0 &&
-                     ((uintptr_t)x_dev & 127u) == 0 && !warm;
+                     ((uintptr_t)x_dev & 127u) == 0;
   ctx->t = 0;
   ctx->last_hip_error = 0;
   ctx->profiling = false;
@@ -1716,7 +1715,10 @@ int choco_init(const choco_config* cfg, float* x_dev, void* workspace_dev, size_
   A.row_ptr = (const int32_t*)(base + L.row_ptr);
   A.col = (const int32_t*)(base + L.col);
   A.w = (const float*)(base + L.w);
-  // (in turn at 4 M entries per row: no gain; more rows than 8 at once: 64 rows of 2 M 631 -> 643 us)
+  // us per step of top_a, rows in turn and one after the other: n = 8 28 M 1041 | 1051, 24 M 889 | 903, 16 M
+  // 604 | 613, 12 M 460 | 465, 8 M 319 | 319, 4 M 171 | 170; n = 4 28 M 548 | 564, 24 M 479 | 482, 16 M 327 | 327;
+  // n = 6 24 M 677 | 686; n = 2 28 M 358 | 360; n = 12 16 M 914 | 929, 8 M 482 | 472, 4 M 248 | 245; n = 16 8 M 620 | 633,
+  // 3 M 248 | 251; 64 rows of 2 M 643 | 631: up to 8 rows it pays from 12 M to 16 M on, more rows gain and lose
   A.rows_in_turn = (cfg->n <= 8 && cfg->d >= ((int64_t)1 << 24)) ? 1 : 0;
   A.staged_nnz = nnz <= kStagedNnz ? nnz : 0;
   A.ctl = (WorkerCtl*)(base + L.ctl);

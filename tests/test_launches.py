@@ -141,3 +141,21 @@ for n in (2, 8, 9, 12, 13, 16, 17, 32, 33, 64):
         if layered == 2:
             assert key.startswith("sign") and "65537" not in key and args[1] == "1", (key, kernel)
     assert sum(v[1] == 2 for v in out.values()) > 40
+
+
+def test_narrow_tile_on_whole_lines_whatever_the_size():
+    """Above 8 workers, rows and X on 128 bytes; otherwise the tile of 256 columns."""
+    out = recorded("""
+out = {}
+for op, comp in (("topk", B.Q_TOPK), ("randk", B.Q_RANDK)):
+    for n, d, align, off in ((16, 1000, 32, 0), (16, 400_000, 32, 0), (16, 540_000, 32, 0), (16, 1_000_000, 32, 0), (64, 120_000, 32, 0),
+                             (64, 1000, 4, 0), (64, 1000, 32, 64), (8, 1000, 32, 0), (65, 1000, 32, 0)):
+        c = Context(n, d, comp, k=10, align=align, x_off=off)
+        l = [x[0].split("<")[0] for x in c.step()]
+        out["%s %d %d %d %d" % (op, n, d, align, off)] = [x for x in l if "mix" in x]
+        c.close()
+""")
+    for key, tile in out.items():
+        n, d, align, off = map(int, key.split()[1:])
+        want = "k_mix_incremental" if n > 64 else "k_tile_mix_narrow" if n > 8 and align == 32 and not off else "k_tile_mix"
+        assert tile == [want], key
