@@ -79,5 +79,9 @@ class Context:
         self.figures = [v.value for v in a]
         return launches
 
+    def metrics_noalloc(self):
+        _stub.stub_clear()
+        return self._launches(self.B.lib().choco_metrics_noalloc(self.ctx, self.mp))
+
     def close(self):
         self.B.lib().choco_destroy(self.ctx)

@@ -69,20 +69,32 @@ def test_local_update_formed_twice(n, d, align, comp, layered):
          layers=layers)
 
 
-@pytest.mark.parametrize("n,d", [(2, (1 << 21) + 1), (9, (1 << 21) + 130)])
-def test_topk_update_formed_for_the_keys_only(n, d):
-    """Rows above 2^21 entries: the candidate pass stores no x, neither does the repair of a failed
-    guess (the first step, and the one after the state has been scaled)."""
+@pytest.mark.parametrize("n,d", [(1, (1 << 21) + 1), (12, (1 << 21) + 1), (13, (1 << 21) + 131)])
+@pytest.mark.parametrize("polls", [None, "0"])
+def test_topk_update_formed_for_the_keys_only(n, d, polls, monkeypatch):
+    """Rows above 2^21 entries of a state that is streamed (below 12 MB or above 96 MB per array): the
+    candidate pass stores no x, neither does the repair of a failed guess (the first step, and the one
+    after the state has been scaled), nor the row scan that is left when the repair's bounded wait is
+    over at once (polls = 0)."""
+    if polls is not None:
+        monkeypatch.setenv("CHOCO_FALLBACK_SPIN_LIMIT", polls)
     pair = Pair(synth.normal_state(n, d, seed=3), synth.ring_csr(n), 0.2, B.Q_TOPK, k=d // 1000, ld_align=32)
+    pair.gpu.set_profiling(True)
     grads = synth.GradientStream(n, d, seed=4)
+    modes = []
     for t in range(4):
         pair.check(pair.step(grads.next(), 0.1 if t != 2 else 50.0), tag="step %d" % t)
+        modes.append(set(pair.gpu.last_scalars()[:, 3]))
+    assert pair.gpu.profile_report()["k_sel_compact_redo"][0] == 4
+    assert modes[0] == {2.0 if polls else 0.0}       # (rebuilt: the select then takes the list)
+    assert np.all(pair.gpu.last_scalars()[:, 4] >= 2)   # steps whose guess failed
     pair.close()
 
 
-@pytest.mark.parametrize("n,d", [(24, 256 * 256), (24, 256 * 256 + 1), (64, 250)])
+@pytest.mark.parametrize("n,d", [(24, 256 * 256), (24, 256 * 256 + 1), (64, 250), (24, 256 * 512), (24, 256 * 512 + 1)])
 def test_norm_finished_in_the_apply_pass_or_before_it(n, d):
-    """17 to 32 workers: up to 256 tiles of 256 columns the apply pass finishes the norms itself."""
+    """sign with 17 to 32 workers, a state of 12 MB or more: up to 512 tiles of 256 columns the apply pass
+    finishes the norms itself (in the test of the launches: which does)."""
     walk(n, d, synth.ring_csr(n), B.Q_SIGN, steps=2)
 
 

@@ -79,7 +79,7 @@ out = {}
 for op, comp in (("sign", B.Q_SIGN), ("gsgd", B.Q_QSGD)):
     for n, tiles, align in ((8, 4096, 64), (16, 4096, 64), (20, 391, 64), (20, 586, 64), (20, 700, 64), (24, 300, 64),
                             (24, 300, 4), (24, 700, 4), (24, 1030, 4), (32, 513, 64), (40, 200, 64), (40, 500, 64), (40, 513, 64), (48, 200, 64), (48, 285, 64),
-                            (64, 100, 64), (64, 180, 64), (64, 220, 64), (64, 100, 4), (64, 260, 4)):
+                            (24, 512, 64), (24, 513, 64), (64, 100, 64), (64, 180, 64), (64, 220, 64), (64, 100, 4), (64, 260, 4)):
         d = 256 * tiles - 64
         c = Context(n, d - (align == 4) * 5, comp, levels=16, align=align)
         l = c.step()
@@ -89,7 +89,7 @@ for op, comp in (("sign", B.Q_SIGN), ("gsgd", B.Q_QSGD)):
 """.replace("out = {}", "names = lambda l: [x[0].split('<')[0] for x in l]\nout = {}"))
     folded = {k for k, v in out.items() if v}
     assert folded == {
-        "sign 8 4096 64", "sign 16 4096 64", "sign 20 391 64", "sign 20 586 64", "sign 24 300 64", "sign 24 300 4", "sign 24 700 4",
+        "sign 8 4096 64", "sign 16 4096 64", "sign 20 391 64", "sign 20 586 64", "sign 24 300 64", "sign 24 300 4", "sign 24 700 4", "sign 24 512 64",
         "sign 40 200 64", "sign 40 500 64", "sign 48 200 64", "sign 64 180 64", "sign 64 100 4",
         "gsgd 8 4096 64", "gsgd 16 4096 64", "gsgd 24 300 4", "gsgd 40 200 64", "gsgd 64 100 4"}
 
@@ -159,3 +159,29 @@ for op, comp in (("topk", B.Q_TOPK), ("randk", B.Q_RANDK)):
         n, d, align, off = map(int, key.split()[1:])
         want = "k_mix_incremental" if n > 64 else "k_tile_mix_narrow" if n > 8 and align == 32 and not off else "k_tile_mix"
         assert tile == [want], key
+
+
+def test_where_the_update_is_formed_twice():
+    """Streamed states (4 to 12 MB per array, above 96 MB), plain SGD; top_a on rows above 2^21 entries."""
+    out = recorded("""
+redo = lambda l: [x[0].rstrip(">").split(",")[-1] == "true" for x in l if x[0].startswith("k_sel_compact")]
+out = {}
+for n, d in ((1, 1 << 21), (1, (1 << 21) + 1), (2, (1 << 21) + 1), (9, (1 << 21) + 130), (12, (1 << 21) + 1)):
+    c = Context(n, d, B.Q_TOPK, k=100, align=32)
+    out["%d %d" % (n, d)] = redo(c.step()) + redo(c.step_momentum())
+    c.close()
+""")
+    assert out == {"1 2097152": [False, False], "1 2097153": [True, False], "2 2097153": [False, False],
+                   "9 2097282": [False, False], "12 2097153": [True, False]}
+
+
+def test_metrics_blocks_fill_the_scratch_of_the_call_without_allocations():
+    """1,024 blocks write all of it, five a small part (what the test of two calls in a row relies on)."""
+    out = recorded("""
+out = []
+for n, d in ((2, 1_050_001), (5, 4100)):
+    c = Context(n, d, B.Q_SIGN)
+    out.append(c.metrics_noalloc())
+    c.close()
+""")
+    assert [l[0][:2] for l in out] == [["k_metrics_partial", "1024x1x1"], ["k_metrics_partial", "5x1x1"]]

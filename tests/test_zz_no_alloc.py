@@ -45,8 +45,8 @@ def check(ctx, out):
 def test_noalloc_metrics_match_on_two_calls_the_second_smaller():
     import torch
     out = torch.empty(3, dtype=torch.float64, device="cuda:0")
-    big, Xb = make_ctx(8, 300_001, seed=3, steps=2)      # 1024 blocks: every slot of the array is written
-    small, Xs = make_ctx(5, 1000, seed=4, steps=3)        # 4 blocks: most of the array keeps the first call's sums
+    big, Xb = make_ctx(2, 1_050_001, seed=3, steps=2)    # 1024 blocks: every slot of the array is written
+    small, Xs = make_ctx(5, 4100, seed=4, steps=3)        # 5 blocks: most of the array keeps the first call's sums
     try:
         check(big, out)
         check(small, out)
