@@ -880,8 +880,11 @@ bool redo_sgd(const choco_ctx* ctx, const Args& F) {
 //   off whole lines, where there is no narrow tile:
 //   sign  64, 2,001, 8             15.1 | 16.7   24, 100 k, 391           18.3 | 21.5    24, 177 k, 692, cached 30.0 | 31.0
 //   gsgd  64, 2,001, 8             19.8 | 21.2   24, 100 k, 391           24.4 | 25.6    24, 270 k, 1,055  56.4 | 53.8
-bool folds_norms(const choco_config& c, bool narrow, bool nt, int32_t tiles) {
+//   more than 16 neighbours (the complete graph), which the narrow tile mixes faster (d = 20 k):
+//   sign  48  33.1 | 26.4   33  23.5 | 21.1      gsgd  48  37.8 | 28.6   33  26.9 | 23.2
+bool folds_norms(const choco_config& c, bool narrow, bool nt, int32_t tiles, int32_t maxdeg) {
   if (c.n <= 16) return true;
+  if (narrow && maxdeg > 16) return c.n <= 32 && tiles <= 256;
   if (c.compressor == CHOCO_Q_SIGN) {
     if (c.n <= 32) return tiles <= (nt ? 768 : narrow ? 512 : 1024);
     if (c.n <= 48) return tiles <= (!nt && c.n <= 40 ? 512 : 256);
@@ -1741,7 +1744,7 @@ int choco_init(const choco_config* cfg, float* x_dev, void* workspace_dev, size_
   A.codes = nullptr;
   // with few group sums the fused apply kernel finishes the norm tree itself (one launch less)
   A.fold_finalise = (ctx->tile_fits && cfg->order == CHOCO_ORDER_COMPRESS_THEN_MIX && L.ngroups <= 256 &&
-                     folds_norms(*cfg, ctx->narrow_tile, ctx->nt, L.nchunks)) ? 1 : 0;
+                     folds_norms(*cfg, ctx->narrow_tile, ctx->nt, L.nchunks, maxdeg)) ? 1 : 0;
   A.k = kept_per_worker(*cfg);
   A.hist16 = (uint32_t*)(base + L.hist16);
   A.cand = (uint2*)(base + L.cand);

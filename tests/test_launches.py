@@ -185,3 +185,18 @@ for n, d in ((2, 1_050_001), (5, 4100)):
     c.close()
 """)
     assert [l[0][:2] for l in out] == [["k_metrics_partial", "1024x1x1"], ["k_metrics_partial", "5x1x1"]]
+
+
+def test_many_neighbours_keep_the_narrow_tile():
+    """Above 32 workers, or 256 tiles, the norms get a launch of their own on dense graphs."""
+    out = recorded("""
+out = {}
+for n, d in ((24, 60_000), (24, 100_000), (33, 20_000), (48, 20_000)):
+    for topo in ("ring", "complete"):
+        c = Context(n, d, B.Q_SIGN, topo=synth.ring_csr(n) if topo == "ring" else synth.complete_csr(n), align=64)
+        out["%d %d %s" % (n, d, topo)] = [x[0].split("<")[0] for x in c.step()]
+        c.close()
+""")
+    folded = {k for k, v in out.items() if len(v) == 2}
+    assert folded == {"24 60000 ring", "24 100000 ring", "33 20000 ring", "48 20000 ring", "24 60000 complete"}
+    assert all(v[-1] == ("k_dense_apply_mix" if k in folded else "k_dense_apply_mix_narrow") for k, v in out.items())
