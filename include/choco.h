@@ -267,7 +267,7 @@ int choco_last_message(choco_ctx *ctx, int32_t worker, int32_t *idx_dev, float *
    and its own padding to whole words; TOPK pairs carry positions in the whole vector.
    RANDK layer by layer: the kept values in ascending position in the whole vector (which
    is layer after layer).  IDENTITY has no message format (CHOCO_E_UNSUPPORTED).  These
-   calls are not part of the timed path. */
+   calls are not part of a step. */
 int choco_paper_message_bits(int32_t compressor, int64_t d, int64_t k, int32_t levels,
                              int64_t *bits_host);
 int choco_message_bytes(choco_ctx *ctx, size_t *bytes_host);

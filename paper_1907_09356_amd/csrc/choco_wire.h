@@ -1,7 +1,7 @@
 // Messages on the wire (Appendix C states a size with each operator: d + 32 bits for
 // sign, 2*32*k for top_a, 32*k for random_a, b bits per entry for gsgd_b).  These kernels
 // encode the q of the last gossip step into those sizes and decode them again; they are
-// not on the timed path (on one GPU "sending" is memory traffic), they are what a
+// not part of a step (on one GPU "sending" is memory traffic), they are what a
 // worker-per-GPU mapping would put on the links.  For sign and gsgd the bits of the message
 // are written by the compress pass itself (the bit planes of choco_kernels.h); packing is a
 // copy of those planes behind the header (whole vector) or their re-alignment layer by layer.
