@@ -134,6 +134,9 @@ KERNEL_BYTES_PER_ELEM = {
     "k_sel_compact_redo": 12,
     "k_dense_apply_mix_sgd": 20,  # read x, g, xhat; write x, xhat
     "k_tile_mix_sgd": 16,         # read x, g, xhat; write x
+    # top-k in one pass: candidates, update of xhat and mix (the records are not counted)
+    "k_onepass_mix": 12,
+    "k_onepass_mix_sgd": 16,
     "k_mix_incremental_sgd": 20,  # read x, g, s, xhat; write x
     # layer-wise sign / gsgd: the norm pass over (layer, group) work items
     "k_layer_stat": 8,            # read x, xhat

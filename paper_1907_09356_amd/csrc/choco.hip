@@ -17,6 +17,7 @@
 #include "choco.h"
 #include "choco_kernels.h"
 #include "choco_layers.h"
+#include "choco_onepass.h"
 #include "choco_wire.h"
 
 using namespace choco;
@@ -96,6 +97,8 @@ struct choco_ctx {
   int32_t nnz;
   bool sparse;            // top_a / random_a
   bool fused_sparse_apply;   // ... whose update of xhat rides on the tile mix pass (direct form, compress-then-mix)
+  bool one_pass;          // top_a: one pass over the state (choco_onepass.h)
+  bool one_pass_begun;    // ... and has taken a step (later ones have a threshold to go by)
   bool values_in_qv;      // random_a after such a step: the kept values are in Qv, not yet in the list
   int mix_form;           // resolved: CHOCO_MIX_INCREMENTAL_S or CHOCO_MIX_DIRECT
   bool tile_fits;         // the LDS tile of all rows exists (up to kMaxTileRows workers)
@@ -150,7 +153,7 @@ size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 struct Layout {
   size_t xhat, s, row_ptr, col, w, ctl, seg_counts, chunk_sums, group_sums, hist16, cand, hist_parts, small_list, sel_idx, sel_val, keptmap, bitmap,
       layers, layer_work, long_tab, layer_guess, layer_scal, layer_groups, layer_group_first, layer_group_sums, layer_scale,
-      chunk_layer, planes, ovf_ring, ovf_pos, wire_rank, wire_word_off, wire_plane_off, sel_idx2, bitmap2, keptmap2, layer_scal2, qv, mpart, total;
+      chunk_layer, planes, ovf_ring, ovf_pos, wire_rank, wire_word_off, wire_plane_off, sel_idx2, bitmap2, keptmap2, layer_scal2, qv, recs, rec_cols, onepass, mpart, total;
   int64_t wire_words, wire_plane_words;   // layer by layer: words of a worker's message / of one bit plane
   int32_t ngroup_items;
   uint32_t cand_cap, seg_cap;
@@ -335,6 +338,24 @@ SelectPlan plan_select(int compressor, int64_t d, int64_t k) {
   return P;
 }
 
+// top_a in one pass over the state (choco_onepass.h)?  It reads and writes 16 bytes per entry instead of 28
+// and launches two kernels more, so it is for states that do not stay in the caches; and what it records
+// must be little: `marked` is the number of a tile's 256 columns in which some worker is expected to list
+// a candidate.  us per step, two passes | one (three contexts in turn, k / d = 0.001 unless said):
+//   n = 8  28 M 1036 | 667   9.4 M 374 | 260   4.4 M 183 | 142   2.2 M (70 MB) 109 | 96   1 M 49 | 57
+//   n = 4  18.8 M 380 | 252   6 M (96 MB) 165 | 125     n = 2  37.5 M 471 | 259   17.5 M 236 | 144
+//   n = 8, d = 12 M by marked columns   6 467 | 317   14 488 | 347   18 498 | 360   24 508 | 384
+//   n = 8, d = 3.5 M (112 MB)           6 152 | 125   10 158 | 136   18 162 | 152   24 166 | 185
+//   ... with gradients that move x more in a step than it has moved so far, so that the expected
+//   thresholds are poor: d = 3.5 M 6 155 | 132, 10 159 | 167; d = 28 M 5 1049 | 699, 10 1104 | 805
+bool one_pass_topk(const choco_config& c) {
+  if (c.compressor != CHOCO_Q_TOPK || c.nlayers > 0 || !fused_sparse_apply(c) || c.randk_rescale) return false;
+  if (c.n < 2 || c.n > kOnePassRows) return false;
+  const double mib = (double)c.n * (double)resolve_ld(c) * sizeof(float) / 1048576.0;
+  const double marked = (double)kChunk * c.n * expected_candidates(c.compressor, c.k) / (double)c.d;
+  return mib > 96.0 && marked <= (mib < 160.0 ? 8.0 : 16.0);
+}
+
 // The layers of a top_a / random_a configuration that are too long for the layer kernel.
 std::vector<LongLayer> long_layers_of(const choco_config& c) {
   std::vector<LongLayer> out;
@@ -448,7 +469,8 @@ Layout make_layout(const choco_config& c, int32_t nnz) {
   // beside its other arrays), else a bit per entry in global memory
   L.bitmap_words = (guessed && !layered && !L.multipart && c.d <= 40 * 1024 * 8) ? (c.d + 31) / 32 : 0;
   const size_t map_bytes = (size_t)c.n * (size_t)((ld + 31) / 32) * sizeof(uint32_t);   // a bit per entry
-  L.keptmap = take(sparse && !L.bitmap_words ? map_bytes : 0);
+  const bool one_pass = one_pass_topk(c);
+  L.keptmap = take(sparse && !L.bitmap_words && !one_pass ? map_bytes : 0);
   L.bitmap = take((size_t)c.n * (size_t)L.bitmap_words * sizeof(uint32_t));
   // further copies for the selections random_a makes ahead: the kept-index lists, the bitmap
   // (short rows in whole-vector mode) or the bit map in global memory, the per-layer scalars
@@ -497,6 +519,9 @@ Layout make_layout(const choco_config& c, int32_t nnz) {
     }
   // random_a whose update of xhat rides on the fused mix pass: the kept values by entry
   L.qv = take(fused_sparse_apply(c) && c.compressor == CHOCO_Q_RANDK ? state : 0);
+  L.recs = take(one_pass ? (size_t)L.nchunks * kRecSlots * (size_t)c.n * sizeof(float2) : 0);
+  L.rec_cols = take(one_pass ? (size_t)L.nchunks * 8 * sizeof(uint32_t) : 0);
+  L.onepass = take(one_pass ? sizeof(OnePassState) : 0);
   L.mpart = take(((size_t)kMetricsBlocks + 1) * 3 * sizeof(double));   // the blocks' sums, then the figures
   L.total = off;
   return L;
@@ -656,7 +681,7 @@ int join_lookahead(choco_ctx* ctx) {
 enum KernelId {
   KID_SGD, KID_MOMENTUM, KID_DENSE_STAT, KID_GROUP_REDUCE, KID_DENSE_FINALISE, KID_DENSE_APPLY_MIX, KID_TILE_MIX,
   KID_DENSE_APPLY, KID_MIX_DIRECT_GLOBAL, KID_MIX_INCREMENTAL, KID_SEL_COMPACT, KID_SEL_FALLBACK,
-  KID_SEL_REFINE, KID_SCATTER_S, KID_XHAT_UPDATE, KID_GATHER_VALUES, KID_SEL_VALUES, KID_SEL_HIST_PARTS, KID_SEL_EMIT_PARTS, KID_SEL_FINISH, KID_DENSE_STAT_SGD, KID_DENSE_STAT_REDO, KID_DENSE_APPLY_MIX_SGD, KID_SEL_COMPACT_SGD, KID_SEL_COMPACT_REDO, KID_TILE_MIX_SGD, KID_MIX_INCREMENTAL_SGD, KID_LAYER_COMPRESS, KID_LAYER_COMPRESS_SGD, KID_LAYER_STAT, KID_LAYER_STAT_SGD, KID_LAYER_STAT_REDO, KID_LAYER_FINALISE, KID_WIRE, KID_ZERO_WORDS, KID_COUNT
+  KID_SEL_REFINE, KID_SCATTER_S, KID_XHAT_UPDATE, KID_GATHER_VALUES, KID_SEL_VALUES, KID_SEL_HIST_PARTS, KID_SEL_EMIT_PARTS, KID_SEL_FINISH, KID_DENSE_STAT_SGD, KID_DENSE_STAT_REDO, KID_DENSE_APPLY_MIX_SGD, KID_SEL_COMPACT_SGD, KID_SEL_COMPACT_REDO, KID_TILE_MIX_SGD, KID_MIX_INCREMENTAL_SGD, KID_LAYER_COMPRESS, KID_LAYER_COMPRESS_SGD, KID_LAYER_STAT, KID_LAYER_STAT_SGD, KID_LAYER_STAT_REDO, KID_LAYER_FINALISE, KID_WIRE, KID_ZERO_WORDS, KID_ONEPASS_MIX, KID_ONEPASS_MIX_SGD, KID_ONEPASS_LIST, KID_ONEPASS_RESTORE, KID_ONEPASS_FINISH, KID_COUNT
 };
 const char* const kKernelNames[KID_COUNT] = {
   "k_sgd", "k_momentum", "k_dense_stat", "k_group_reduce", "k_dense_finalise", "k_dense_apply_mix", "k_tile_mix",
@@ -664,7 +689,7 @@ const char* const kKernelNames[KID_COUNT] = {
   "k_sel_refine", "k_scatter_s", "k_xhat_update", "k_gather_values", "k_sel_values", "k_sel_hist_parts", "k_sel_emit_parts", "k_sel_finish",
   "k_dense_stat_sgd", "k_dense_stat_redo", "k_dense_apply_mix_sgd", "k_sel_compact_sgd", "k_sel_compact_redo", "k_tile_mix_sgd", "k_mix_incremental_sgd",
   "k_layer_compress", "k_layer_compress_sgd", "k_layer_stat", "k_layer_stat_sgd", "k_layer_stat_redo", "k_layer_finalise", "k_wire",
-  "k_zero_words"};
+  "k_zero_words", "k_onepass_mix", "k_onepass_mix_sgd", "k_onepass_list", "k_onepass_restore", "k_onepass_finish"};
 constexpr size_t kMaxProfiledLaunches = 16384;
 
 // Brackets one launch with two events when profiling is on (no-op otherwise).
@@ -959,6 +984,23 @@ size_t ahead_lds_pad(const choco_ctx* ctx, int64_t row_len) {
   return (ctx->launch_stream != ctx->stream && row_len > ((int64_t)1 << 21)) ? (size_t)48 << 10 : 0;
 }
 
+// The exact select on the candidate lists of whole rows.
+template <int COMP>
+void launch_exact_select(choco_ctx* ctx, const Args& A) {
+  if (ctx->fallback_chain) {
+    LAUNCH(ctx, KID_SEL_FALLBACK, (k_sel_fallback<COMP>), fallback_grid(A.n), dim3(256), 0, A);
+  }
+  if (ctx->multipart) {
+    const dim3 pgrid((unsigned)kRefineParts, (unsigned)A.n);
+    LAUNCH(ctx, KID_SEL_HIST_PARTS, (k_sel_hist_parts<COMP>), pgrid, dim3(1024), 0, A);
+    LAUNCH(ctx, KID_SEL_EMIT_PARTS, (k_sel_emit_parts<COMP>), pgrid, dim3(1024), 0, A);
+    LAUNCH(ctx, KID_SEL_FINISH, (k_sel_finish<COMP>), dim3((unsigned)A.n), dim3(1024), 0, A);
+  } else {
+    LAUNCH(ctx, KID_SEL_REFINE, (k_sel_refine<COMP>), dim3((unsigned)A.n), dim3(1024),
+           (size_t)A.bitmap_words * sizeof(uint32_t), A);
+  }
+}
+
 // The select of the whole-vector path: one pass over the rows appends the candidates, the
 // histogram fallback and the rebuild are no-ops unless a guess failed, then the exact select
 // on the lists.  C is the argument block for the pass over the rows (it may carry the local
@@ -989,18 +1031,7 @@ void launch_select(choco_ctx* ctx, const Args& C, const Args& A, int kid_compact
     else if (kWide) LAUNCH(ctx, kid_compact, (k_sel_compact<COMP, false, NT, 1, false, 1024>), cgrid, dim3(1024), pad, C);
     else LAUNCH(ctx, kid_compact, (k_sel_compact<COMP, false, NT, kCompactVecs>), cgrid, dim3(256), pad, C);
   }
-  if (ctx->fallback_chain) {
-    LAUNCH(ctx, KID_SEL_FALLBACK, (k_sel_fallback<COMP>), fallback_grid(A.n), dim3(256), 0, A);
-  }
-  if (ctx->multipart) {
-    const dim3 pgrid((unsigned)kRefineParts, (unsigned)A.n);
-    LAUNCH(ctx, KID_SEL_HIST_PARTS, (k_sel_hist_parts<COMP>), pgrid, dim3(1024), 0, A);
-    LAUNCH(ctx, KID_SEL_EMIT_PARTS, (k_sel_emit_parts<COMP>), pgrid, dim3(1024), 0, A);
-    LAUNCH(ctx, KID_SEL_FINISH, (k_sel_finish<COMP>), dim3((unsigned)A.n), dim3(1024), 0, A);
-  } else {
-    LAUNCH(ctx, KID_SEL_REFINE, (k_sel_refine<COMP>), dim3((unsigned)A.n), dim3(1024),
-           (size_t)A.bitmap_words * sizeof(uint32_t), A);
-  }
+  launch_exact_select<COMP>(ctx, A);
 }
 
 // random_a selects ahead: the mask of a step depends on (seed, step, worker) only, so the
@@ -1097,9 +1128,35 @@ int look_ahead_end(choco_ctx* ctx, const Args& A, uint64_t base) {
   return CHOCO_OK;
 }
 
+// top_a in one pass (choco_onepass.h).  The kernels behind the pass have little or nothing to do as a
+// rule: workgroups to fill the chip once, which go through the tiles in turn.
+template <bool NT>
+int gossip_one_pass(choco_ctx* ctx, const Args& F0) {
+  Args F = F0;
+  F.onepass_first = ctx->one_pass_begun ? 0 : 1;
+  Args A = F;
+  A.G = nullptr;
+  const size_t lds = (size_t)A.n * kChunk * sizeof(float);
+  const dim3 block(64u * (unsigned)A.n);
+  const int waves = (A.nchunks + kRecTiles - 1) / kRecTiles;
+  LAUNCH(ctx, F.G ? KID_ONEPASS_MIX_SGD : KID_ONEPASS_MIX, (k_onepass_mix<NT>), dim3((unsigned)A.nchunks), block, lds, F);
+  if (!F.onepass_first) {
+    LAUNCH(ctx, KID_ONEPASS_LIST, k_onepass_list, dim3((unsigned)std::min((waves + 3) / 4, 2048)), dim3(256), 0, A, A.nchunks);
+    LAUNCH(ctx, KID_ONEPASS_RESTORE, (k_onepass_restore<NT>), dim3((unsigned)std::min(A.nchunks, 512)), block, lds, A, A.nchunks);
+  }
+  launch_exact_select<Q_TOPK>(ctx, A);
+  LAUNCH(ctx, KID_ONEPASS_FINISH, (k_onepass_finish<NT>), dim3((unsigned)std::min((waves + A.n - 1) / A.n, 1024)), block, lds,
+         A, A.nchunks);
+  LAUNCH_CHECK(ctx);
+  ctx->one_pass_begun = true;
+  return CHOCO_OK;
+}
+
 // Sparsifying operators (top_a, random_a).
 template <int COMP, bool NT>
 int gossip_sparse(choco_ctx* ctx, const Args& F) {
+  if constexpr (COMP == Q_TOPK)
+    if (ctx->one_pass) return gossip_one_pass<NT>(ctx, F);
   Args A = F;
   // a deferred local update (random_a) keeps G visible to the kernels that gather single
   // entries of x; otherwise only the first pass may see it
@@ -1514,8 +1571,8 @@ int launch_momentum(choco_ctx* ctx, const float* g_dev, float* m_dev, float lr, 
 // 499 -> 490, n = 64, d = 2 M 638 -> 631; shorter ones lose (n = 64, d = 520 k, whose arrays the last-level
 // cache still holds in part: 204 -> 213).
 bool redo_topk(const choco_ctx* ctx, const LocalUpdate& u) {
-  return ctx->cfg.compressor == CHOCO_Q_TOPK && ctx->nlayers == 0 && ctx->fused_sparse_apply && ctx->nt &&
-         ctx->long_rows && u.m == nullptr;
+  return ctx->cfg.compressor == CHOCO_Q_TOPK && ctx->nlayers == 0 && ctx->fused_sparse_apply && !ctx->one_pass &&
+         ctx->nt && ctx->long_rows && u.m == nullptr;
 }
 
 // One whole iteration: the local update (plain or momentum), then the gossip step; fused
@@ -1667,6 +1724,8 @@ int choco_init(const choco_config* cfg, float* x_dev, void* workspace_dev, size_
   ctx->sparse = is_sparse(cfg->compressor);
   ctx->mix_form = resolve_mix_form(*cfg);
   ctx->fused_sparse_apply = fused_sparse_apply(*cfg);
+  ctx->one_pass = one_pass_topk(*cfg);
+  ctx->one_pass_begun = false;
   ctx->values_in_qv = false;
   ctx->tile_fits = cfg->n <= kMaxTileRows;
   ctx->plan = SelectPlan{};
@@ -1758,7 +1817,10 @@ int choco_init(const choco_config* cfg, float* x_dev, void* workspace_dev, size_
   A.vec_base = 0;
   A.sel_idx = (int32_t*)(base + L.sel_idx);
   A.sel_val = (float*)(base + L.sel_val);
-  A.keptmap = (uint32_t*)(base + L.keptmap);
+  A.keptmap = ctx->one_pass ? nullptr : (uint32_t*)(base + L.keptmap);
+  A.recs = ctx->one_pass ? (float2*)(base + L.recs) : nullptr;
+  A.rec_cols = (uint32_t*)(base + L.rec_cols);
+  A.onepass = (OnePassState*)(base + L.onepass);
   A.Qv = (ctx->fused_sparse_apply && cfg->compressor == CHOCO_Q_RANDK) ? (float*)(base + L.qv) : nullptr;
   A.map_words = (A.ld + 31) / 32;
   A.bitmap = (uint32_t*)(base + L.bitmap);

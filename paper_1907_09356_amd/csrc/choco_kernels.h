@@ -74,6 +74,15 @@ struct WorkerCtl {
   // 'a workgroup gave up waiting: do not trust the list' (cleared when the next guess is placed)
   uint32_t fb_arrive, fb_go, fb_abort;
   uint64_t kstar;       // composite key of the k-th largest entry: kept <=> key >= kstar
+  // one-pass top_a: the threshold key that the next step's pass goes by, the one that this step's pass
+  // went by, and the rank among this step's entries at which the former was put
+  uint32_t expect_key, expected_key, expect_rank;
+};
+
+// What the kernels of one-pass top_a tell each other about a step (choco_onepass.h).
+struct OnePassState {
+  uint32_t redo_all;    // X holds x - lr g everywhere: every tile is mixed by the last kernel
+  uint32_t open_step;   // (low word of the) last step in which a tile was left unmixed
 };
 
 // One layer of a worker's vector when the operator is applied layer by layer.
@@ -218,6 +227,11 @@ struct Args {
   const int4* chunk_layer;   // per 256-entry chunk of a row: layer of its first entry, that layer's end, next layer's start
   double* layer_scal;        // n x nlayers x 4: norms and scales / threshold of the last step
   int32_t qsgd_biased;
+  // one-pass top_a (choco_onepass.h); recs is null elsewhere
+  float2* recs;            // tiles x kRecSlots x n: x' and xhat of all workers in the recorded columns
+  uint32_t* rec_cols;      // tiles x 8: which columns of the tile are recorded; all bits: the tile was left unmixed
+  OnePassState* onepass;
+  int32_t onepass_first;   // a context's first step
   // randomness
   uint32_t seed_lo, seed_hi, t_lo, t_hi;
 };
@@ -901,39 +915,44 @@ __device__ __forceinline__ RowNbrs nbr_fetch(const Args& A, const RowSpan& sp, i
   return nb;
 }
 
-template <int RPW, int NW>
-__device__ __forceinline__ void tile_mix_rows_staged(const Args& A, const float* tile, int wave, int lane,
-                                                     bool valid, vf4 (&xr)[RPW], const RowNbrs& nb) {
+// sum_p w_p (xhat_j - xhat_r) on the lane's 4-vector of row r, the wave's Q-th row.
+template <int Q>
+__device__ __forceinline__ vf4 mix_sum_staged(const Args& A, const float* tile, int r, int lane, const RowNbrs& nb) {
+  const vf4 me = lds_load4(tile + r * kChunk + lane * 4);
+  vf4 acc = {0.f, 0.f, 0.f, 0.f};
+  const int deg = __builtin_amdgcn_readlane(nb.col_deg, Q * kNbrLanes) >> 8;
+  if (deg <= kNbrLanes) {                        // neighbours in the order of the CSR row
+    for (int j = 0; j < deg; ++j) {
+      const int cj = __builtin_amdgcn_readlane(nb.col_deg, Q * kNbrLanes + j) & 0xFF;
+      const float wj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(nb.w), Q * kNbrLanes + j));
+      const vf4 o = lds_load4(tile + cj * kChunk + lane * 4);
 #pragma unroll
-  for (int q = 0; q < RPW; ++q) {
-    const int r = wave + NW * q;
-    if (r < A.n) {                                   // uniform over the wave (readlane takes every lane)
-      const vf4 me = lds_load4(tile + r * kChunk + lane * 4);
-      vf4 acc = {0.f, 0.f, 0.f, 0.f};
-      const int deg = __builtin_amdgcn_readlane(nb.col_deg, q * kNbrLanes) >> 8;
-      if (deg <= kNbrLanes) {                        // neighbours in the order of the CSR row
-        for (int j = 0; j < deg; ++j) {
-          const int cj = __builtin_amdgcn_readlane(nb.col_deg, q * kNbrLanes + j) & 0xFF;
-          const float wj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(nb.w), q * kNbrLanes + j));
-          const vf4 o = lds_load4(tile + cj * kChunk + lane * 4);
+      for (int c = 0; c < 4; ++c) acc[c] = acc[c] + wj * (o[c] - me[c]);
+    }
+  } else {
+    const int pbeg = A.row_ptr[r];
+    for (int p = pbeg; p < pbeg + deg; ++p) {
+      const float wj = A.w[p];
+      const vf4 o = lds_load4(tile + A.col[p] * kChunk + lane * 4);
 #pragma unroll
-          for (int c = 0; c < 4; ++c) acc[c] = acc[c] + wj * (o[c] - me[c]);
-        }
-      } else {
-        const int pbeg = A.row_ptr[r];
-        for (int p = pbeg; p < pbeg + deg; ++p) {
-          const float wj = A.w[p];
-          const vf4 o = lds_load4(tile + A.col[p] * kChunk + lane * 4);
-#pragma unroll
-          for (int c = 0; c < 4; ++c) acc[c] = acc[c] + wj * (o[c] - me[c]);
-        }
-      }
-      if (valid) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) xr[q][c] = xr[q][c] + A.gamma * acc[c];
-      }
+      for (int c = 0; c < 4; ++c) acc[c] = acc[c] + wj * (o[c] - me[c]);
     }
   }
+  return acc;
+}
+
+template <int Q, int RPW, int NW>
+__device__ __forceinline__ void tile_mix_rows_staged(const Args& A, const float* tile, int wave, int lane,
+                                                     bool valid, vf4 (&xr)[RPW], const RowNbrs& nb) {
+  const int r = wave + NW * Q;
+  if (r < A.n) {                                   // uniform over the wave (readlane takes every lane)
+    const vf4 acc = mix_sum_staged<Q>(A, tile, r, lane, nb);
+    if (valid) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) xr[Q][c] = xr[Q][c] + A.gamma * acc[c];
+    }
+  }
+  if constexpr (Q + 1 < RPW) tile_mix_rows_staged<Q + 1, RPW, NW>(A, tile, wave, lane, valid, xr, nb);
 }
 
 // The same with every row of W read from memory in the loop (k_dense_apply_mix, whose registers
@@ -1314,7 +1333,7 @@ __global__ __launch_bounds__(64 * NW) void k_tile_mix(Args A) {
     }
   }
   __syncthreads();
-  tile_mix_rows_staged<RPW, NW>(A, tile, wave, lane, valid, xr, nb);
+  tile_mix_rows_staged<0, RPW, NW>(A, tile, wave, lane, valid, xr, nb);
 #pragma unroll
   for (int q = 0; q < RPW; ++q) {
     const int r = wave + NW * q;
@@ -2042,7 +2061,7 @@ __device__ __forceinline__ void find_digit(const uint32_t* h, uint32_t* grp, uin
 __device__ __forceinline__ void mark_kept(const Args& A, int i, uint32_t idx, uint32_t* lbits) {
   // (lbits is null in the kernels that never see a row with an LDS bitmap)
   if (lbits != nullptr && A.bitmap_words) atomicOr(&lbits[idx >> 5], 1u << (idx & 31u));
-  else atomicOr(&A.keptmap[(int64_t)i * A.map_words + ((idx + (uint32_t)A.idx_base) >> 5)], 1u << ((idx + (uint32_t)A.idx_base) & 31u));
+  else if (A.keptmap != nullptr) atomicOr(&A.keptmap[(int64_t)i * A.map_words + ((idx + (uint32_t)A.idx_base) >> 5)], 1u << ((idx + (uint32_t)A.idx_base) & 31u));
 }
 
 // Did worker j keep entry e in this step?
@@ -2091,6 +2110,29 @@ __device__ __forceinline__ void emit_entry(const Args& A, int i, bool keep, uint
   }
 }
 
+// One-pass top_a: the threshold to expect in the next step.  The k entries kept now leave the race, and
+// some come in: the entries above the next threshold have about rank 2k - (those that come in) now, and
+// that rank is carried from step to step - with the rank at which this step's expectation was put and
+// the number c of entries that turned out above it, it moves by k - c.  Ranks become keys by the density
+// seen between the guess and the threshold T (total - k entries over `gap` keys).
+__device__ __forceinline__ void expect_threshold(const Args& A, WorkerCtl* ctl, uint32_t T, bool density, uint32_t gap,
+                                                 uint32_t total, uint32_t guess) {
+  const double k = (double)A.k;
+  double key = (double)T, rank = 2.0 * k;
+  if (density) {
+    const double per = (double)(total - (uint32_t)A.k) / (double)gap;
+    if (ctl->expect_rank != 0u) {
+      const double c = k + ((double)T - (double)ctl->expect_key) * per;
+      rank = fmin(fmax((double)ctl->expect_rank + k - c, 0.5 * k), 4.0 * k);
+    }
+    key = (double)T - (rank - k) / per;
+  }
+  key = fmin(fmax(key, (double)guess), 2147483647.0);
+  ctl->expected_key = ctl->expect_key;
+  ctl->expect_key = (uint32_t)key;
+  ctl->expect_rank = density ? (uint32_t)rank : 0u;
+}
+
 // Place the guess (and the bin width) for the next step below this step's
 // threshold key T: by the distance that, at the key density seen between the old
 // guess and T, holds `want` entries (for top_a the k entries kept now leave the
@@ -2107,7 +2149,9 @@ __device__ __forceinline__ void next_guess(const Args& A, WorkerCtl* ctl, uint64
     delta = (uint64_t)(T - floor_key);   // row scan: the first-digit histogram located rank k + want
   if (delta < 1) delta = 1;
   if (delta > 0xFFFFFFFFull) delta = 0xFFFFFFFFull;
-  ctl->guess_key = delta >= (uint64_t)T ? 0u : T - (uint32_t)delta;
+  const uint32_t guess = delta >= (uint64_t)T ? 0u : T - (uint32_t)delta;
+  if (A.recs != nullptr) expect_threshold(A, ctl, T, from_list && total > (uint32_t)A.k && T > G, T - G, total, guess);
+  ctl->guess_key = guess;
   // 256-511 bins between the guess and where the threshold is expected: the 2048 bins then
   // still resolve a threshold that lands 4-8 times further above the guess than predicted
   const int lg = 63 - __clzll((unsigned long long)delta);

@@ -1,0 +1,403 @@
+// top_a of a few workers on long rows in ONE pass over the state (compress-then-mix order, direct form).
+//
+// The two-pass form reads x, xhat and g for the candidates and, when the threshold of every row is
+// known, reads all three again for the update of xhat and the mix: 28 bytes per entry.  Here one pass
+// does the local update and mixes at once with the kept set that it expects (|v| at or above a threshold
+// predicted from the steps before): 16 bytes per entry.  A column in which some worker has a candidate is
+// recorded (x' after the local update and xhat of all workers); the candidate lists are made from the
+// records, and after the exact select the few columns whose kept set was not the expected one are done
+// again from them:
+//   k_onepass_mix      the pass
+//   k_onepass_list     the candidate lists of the rows out of the records
+//   k_onepass_restore  normally idle; where a row's list turns out not to hold its k largest entries:
+//                      x' and xhat back as they were before the mix, for the fallback and its row scans
+//   (the fallback and the exact select of the two-pass form, on the lists)
+//   k_onepass_finish   the recorded columns against the thresholds; tiles left unmixed as a whole
+// Every bit of the result is that of the two-pass form.  x' = x_mixed - gamma acc is exact for nearly all
+// entries (acc is formed again from the same xhat); the pass tries it, and records the columns where it
+// is not.  A tile with more than kRecSlots columns to record is left unmixed and done by the last kernel
+// (its candidates go to the lists one by one).
+#pragma once
+
+#include "choco_kernels.h"
+
+namespace choco {
+
+// Slots per tile of 256 columns.  A slot is 8 n bytes, so the records are a quarter of an array of the
+// state; at 5 expected columns per tile (n = 8, k / d = 0.001) no tile in 10^6 has more than 20.
+constexpr int kRecSlots = 32;
+constexpr int kOnePassRows = 8;     // a row per wave; n lanes of a group of eight where records are read
+constexpr int kRecTiles = 16;       // tiles whose records a wave goes through together
+
+// Columns of the lane's 4-vector that some wave marked (a byte per wave).
+__device__ __forceinline__ uint32_t fold_marks(uint64_t m) {
+  m |= m >> 32;
+  m |= m >> 16;
+  m |= m >> 8;
+  return (uint32_t)m & 0xFu;
+}
+
+// Bits `nibble` of the lane's 4-vector among the 256 columns of the tile: word lane / 8 of the tile's mask.
+__device__ __forceinline__ uint32_t mask_word(uint32_t nibble, int lane) {
+  uint32_t w = nibble << (4 * (lane & 7));
+  w |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0xB1, 0xF, 0xF, true);    // quad_perm [1,0,3,2]
+  w |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0x4E, 0xF, 0xF, true);    // quad_perm [2,3,0,1]
+  w |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0x141, 0xF, 0xF, true);   // row_half_mirror
+  return w;
+}
+
+// (x', xhat) of worker 0 in a slot; worker i's is i further on.
+__device__ __forceinline__ float2* record_of(const Args& A, int64_t tile, int slot) {
+  return A.recs + (tile * kRecSlots + slot) * A.n;
+}
+
+// A tile that was left unmixed has all bits of its mask set (a recorded one no more than kRecSlots).
+__device__ __forceinline__ bool left_open(uint2 w) { return (w.x & w.y) == 0xFFFFFFFFu; }
+static_assert(kRecSlots < 64, "two full words of a mask mean an open tile");
+
+// grid ceil(d / 256), block 64 n (wave r: row r), dynamic LDS n x 256 floats.
+template <bool NT>
+__global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_mix(Args A) {
+  extern __shared__ float tile[];
+  __shared__ uint64_t marks[64];   // a byte per lane and wave
+  const int r = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int tile_no = (int)blockIdx.x;   // (line_sharing_tile: 612 against 604 us at n = 8, d = 28 M)
+  const int e = tile_no * kChunk + lane * 4;
+  const bool mine = e < A.d;
+  const int64_t o = (int64_t)r * A.ld + e;
+  const bool mom = A.G != nullptr && A.M != nullptr;
+  vf4 x = {0.f, 0.f, 0.f, 0.f}, h = x, g = x, m = x;
+  if (mine) {
+    x = load4<NT>(A.X + o);
+    h = load4<NT>(A.Xhat + o);
+    if (A.G) g = load4<true>(A.G + o);
+    if (mom) m = load4<NT>(A.M + o);
+  }
+  const RowSpan span = nbr_span<1, kOnePassRows>(A, r, lane);
+  const uint32_t guess = A.ctl[r].guess_key, expect = A.ctl[r].expect_key;
+  if (r == 0) marks[lane] = 0u;    // (bytes of rows that there are not)
+  const RowNbrs nb = nbr_fetch(A, span, lane);
+  if (mine && A.G) {
+    x = local_update_regs(A, x, g, m);
+    if (mom) store4<NT>(A.M + o, m);
+  }
+  if (A.onepass_first) {           // no threshold to go by: the last kernel does all tiles
+    if (mine && A.G) store4<NT>(A.X + o, x);
+    return;
+  }
+  vf4 hn = h;
+  uint32_t cand = 0u, kept = 0u;
+  if (mine) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const float q = x[c] - h[c];
+      const uint32_t key = __float_as_uint(q) & 0x7fffffffu;
+      if (e + c < A.d && key >= guess) {
+        cand |= 1u << c;
+        if (key >= expect) {
+          kept |= 1u << c;
+          hn[c] = h[c] + q;
+        }
+      }
+    }
+  }
+  lds_store4(tile + r * kChunk + lane * 4, hn);
+  __syncthreads();
+  vf4 xm = x;
+  uint32_t lost = 0u;
+  const vf4 acc = mix_sum_staged<0>(A, tile, r, lane, nb);
+  if (mine) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const float step = A.gamma * acc[c];
+      xm[c] = x[c] + step;
+      const float back = xm[c] - step;
+      if (__float_as_uint(back) != __float_as_uint(x[c])) lost |= 1u << c;
+    }
+  }
+  reinterpret_cast<uint8_t*>(marks)[lane * 8 + r] = (uint8_t)(cand | lost);
+  __syncthreads();
+  const uint32_t dirty = fold_marks(marks[lane]);
+  uint64_t db[4];
+  int total = 0;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    db[c] = __ballot((dirty >> c) & 1u);
+    total += __popcll(db[c]);
+  }
+  const bool open = total > kRecSlots;     // the same in every wave
+  if (mine) {
+    store4<NT>(A.X + o, open ? x : xm);
+    if (kept && !open) store4<false>(A.Xhat + o, hn);
+  }
+  if (r == 0) {
+    const uint32_t w = mask_word(open ? 0xFu : dirty, lane);
+    if ((lane & 7) == 0) A.rec_cols[(int64_t)tile_no * 8 + (lane >> 3)] = w;
+    if (open && lane == 0) A.onepass->open_step = A.t_lo;
+  }
+  if (open) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+      if ((cand >> c) & 1u) {
+        const int seg = tile_no % kSegs;
+        const uint32_t at = atomicAdd(seg_counter(A, r, seg), 1u);
+        if (at < A.seg_cap)
+          A.cand[((int64_t)r * kSegs + seg) * A.seg_cap + at] = make_uint2(__float_as_uint(x[c] - h[c]), (uint32_t)(e + c));
+      }
+  } else if (mine && dirty != 0u) {
+    const uint64_t below = (1ull << lane) - 1ull;
+    int slot = 0;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) slot += __popcll(db[c] & below);
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+      if ((dirty >> c) & 1u) record_of(A, tile_no, slot++)[r] = make_float2(x[c], h[c]);
+  }
+}
+
+// The marked columns of the kRecTiles tiles from t0 on, to LDS as (tile of the sixteen x slots + slot,
+// column in the tile); returns how many.  A whole wave calls it: four lanes to a tile, two words of its
+// mask each.
+__device__ __forceinline__ uint32_t list_marked(const Args& A, int t0, int ntiles, ushort2* out) {
+  const int lane = threadIdx.x & 63;
+  const int t = t0 + (lane >> 2);
+  uint2 w = make_uint2(0u, 0u);
+  if (t < ntiles) w = *reinterpret_cast<const uint2*>(A.rec_cols + (int64_t)t * 8 + 2 * (lane & 3));
+  if (left_open(w)) w = make_uint2(0u, 0u);
+  const uint32_t cnt = (uint32_t)(__popc(w.x) + __popc(w.y));
+  uint32_t incl = cnt;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint32_t up = __shfl_up(incl, off, 64);
+    if (lane >= off) incl += up;
+  }
+  uint32_t at = incl - cnt;
+  uint32_t slot = at - __shfl(at, lane & ~3, 64);
+  uint64_t bits = ((uint64_t)w.y << 32) | w.x;
+  while (bits) {
+    const int b = __ffsll((unsigned long long)bits) - 1;
+    bits &= bits - 1;
+    out[at++] = make_ushort2((unsigned short)((lane >> 2) * kRecSlots + slot++), (unsigned short)(64 * (lane & 3) + b));
+  }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  return __shfl(incl, 63, 64);
+}
+
+// Record f of the listed ones, as lane i of its group sees it.
+struct Recorded {
+  float x, h;
+  int col;
+  bool have;    // there is such a record, and the lane stands for a worker in it
+};
+__device__ __forceinline__ Recorded recorded(const Args& A, int t0, const ushort2* list, uint32_t f, uint32_t total, int i) {
+  Recorded R{0.0f, 0.0f, 0, false};
+  if (f < total) {
+    const int ts = list[f].x, t = t0 + ts / kRecSlots;
+    R.col = t * kChunk + list[f].y;
+    R.have = i < A.n && R.col < A.d;
+    if (R.have) {
+      const float2 v = record_of(A, t, ts % kRecSlots)[i];
+      R.x = v.x;
+      R.h = v.y;
+    }
+  }
+  return R;
+}
+
+// The candidates among the recorded entries, to the rows' lists: each wave counts those of its sixteen
+// tiles row by row, takes room with one addition per row and writes them.  grid any, block 256.
+__global__ __launch_bounds__(256) void k_onepass_list(Args A, int32_t ntiles) {
+  __shared__ ushort2 lists[4][kRecTiles * kRecSlots];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, i = lane & 7, grp = lane >> 3;
+  ushort2* list = lists[wave];
+  const uint32_t guess = A.ctl[i < A.n ? i : 0].guess_key;
+  const int w0 = (int)blockIdx.x * 4 + wave, nwaves = (int)gridDim.x * 4;
+  for (int t0 = w0 * kRecTiles; t0 < ntiles; t0 += nwaves * kRecTiles) {
+    const uint32_t total = list_marked(A, t0, ntiles, list);
+    auto is_candidate = [&](const Recorded& R) {
+      return R.have && (__float_as_uint(R.x - R.h) & 0x7fffffffu) >= guess;
+    };
+    uint32_t mine = 0;
+#pragma unroll 4
+    for (uint32_t f = (uint32_t)grp; f < total; f += 8) mine += is_candidate(recorded(A, t0, list, f, total, i)) ? 1u : 0u;
+    uint32_t incl = mine;     // over the eight lanes of a row
+#pragma unroll
+    for (int off = 8; off < 64; off <<= 1) {
+      const uint32_t up = __shfl_up(incl, off, 64);
+      if (lane >= off) incl += up;
+    }
+    const int seg = (t0 / kRecTiles) % kSegs;
+    uint32_t base = 0;
+    if (grp == 7 && incl != 0u) base = atomicAdd(seg_counter(A, i, seg), incl);
+    base = __shfl(base, 56 + i, 64) + incl - mine;
+    if (mine != 0u) {
+      uint2* out = A.cand + ((int64_t)i * kSegs + seg) * A.seg_cap;
+#pragma unroll 4
+      for (uint32_t f = (uint32_t)grp; f < total; f += 8) {
+        const Recorded R = recorded(A, t0, list, f, total, i);
+        if (is_candidate(R)) {
+          if (base < A.seg_cap) out[base] = make_uint2(__float_as_uint(R.x - R.h), (uint32_t)R.col);
+          ++base;
+        }
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+
+// Do all lists hold their row's k largest entries?  If not, what k_onepass_mix did to x and xhat is
+// undone, tile by tile, so that X is x' everywhere.  Normally a launch of workgroups that read the
+// lists' lengths and leave.  grid any, block 64 n, dynamic LDS n x 256 floats.
+template <bool NT>
+__global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_restore(Args A, int32_t ntiles) {
+  extern __shared__ float tile[];
+  __shared__ uint32_t s_bad;
+  const int r = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  if (threadIdx.x == 0) s_bad = 0u;
+  __syncthreads();
+  const uint32_t raw = lane < kSegs ? *seg_counter(A, r, lane) : 0u;
+  unsigned long long sum = raw;
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off, 64);
+  const bool fits = __ballot(raw > A.seg_cap) == 0ull;
+  if (lane == 0 && (!fits || sum < (unsigned long long)A.k)) s_bad = 1u;
+  __syncthreads();
+  if (blockIdx.x == 0 && threadIdx.x == 0) A.onepass->redo_all = s_bad;
+  if (s_bad == 0u) return;
+  const RowNbrs nb = nbr_fetch(A, nbr_span<1, kOnePassRows>(A, r, lane), lane);
+  for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
+    const uint32_t* cols = A.rec_cols + (int64_t)t * 8;
+    if (left_open(make_uint2(cols[0], cols[1]))) continue;
+    const int e = t * kChunk + lane * 4;
+    const bool mine = e < A.d;
+    const int64_t o = (int64_t)r * A.ld + e;
+    vf4 x = {0.f, 0.f, 0.f, 0.f}, h = x, xr = x;
+    const uint32_t dirty = (cols[lane >> 3] >> (4 * (lane & 7))) & 0xFu;
+    int slot = 0;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) slot += __popcll(__ballot((dirty >> c) & 1u) & ((1ull << lane) - 1ull));
+    if (mine) {
+      x = load4<NT>(A.X + o);
+      h = load4<NT>(A.Xhat + o);
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        if ((dirty >> c) & 1u) {
+          const float2 v = record_of(A, t, slot++)[r];
+          xr[c] = v.x;
+          h[c] = v.y;
+        }
+      if (dirty) store4<false>(A.Xhat + o, h);
+    }
+    __syncthreads();                       // the tile of the round before has been read
+    lds_store4(tile + r * kChunk + lane * 4, h);
+    __syncthreads();
+    const vf4 acc = mix_sum_staged<0>(A, tile, r, lane, nb);
+    if (mine) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const float step = A.gamma * acc[c];
+        x[c] = ((dirty >> c) & 1u) ? xr[c] : x[c] - step;
+      }
+      store4<NT>(A.X + o, x);
+    }
+  }
+}
+
+// The k kept entries of every row are known (composite key >= kstar).  Tiles that hold x' as a whole
+// (all of them in a first step or after k_onepass_restore) get the update of xhat and the mix here; of
+// the others the recorded columns whose kept set is not the one that k_onepass_mix went by.
+// grid any, block 64 n, dynamic LDS n x 256 floats.
+template <bool NT>
+__global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_finish(Args A, int32_t ntiles) {
+  extern __shared__ float tile[];
+  __shared__ ushort2 lists[kOnePassRows][kRecTiles * kRecSlots];
+  const int r = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const bool all = A.onepass_first || A.onepass->redo_all != 0u;
+  if (all || A.onepass->open_step == A.t_lo) {
+    const RowNbrs nb = nbr_fetch(A, nbr_span<1, kOnePassRows>(A, r, lane), lane);
+    const uint64_t kstar = A.ctl[r].kstar;
+    for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
+      const uint32_t* cols = A.rec_cols + (int64_t)t * 8;
+      if (!all && !left_open(make_uint2(cols[0], cols[1]))) continue;
+      const int e = t * kChunk + lane * 4;
+      const bool mine = e < A.d;
+      const int64_t o = (int64_t)r * A.ld + e;
+      vf4 x = {0.f, 0.f, 0.f, 0.f}, h = x;
+      if (mine) {
+        x = load4<NT>(A.X + o);
+        h = load4<NT>(A.Xhat + o);
+        bool kept = false;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const float q = x[c] - h[c];
+          if (e + c < A.d && Digits<Q_TOPK>::composite(__float_as_uint(q), (uint32_t)(e + c)) >= kstar) {
+            h[c] = h[c] + q;
+            kept = true;
+          }
+        }
+        if (kept) store4<false>(A.Xhat + o, h);
+      }
+      __syncthreads();
+      lds_store4(tile + r * kChunk + lane * 4, h);
+      __syncthreads();
+      const vf4 acc = mix_sum_staged<0>(A, tile, r, lane, nb);
+      if (mine) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) x[c] = x[c] + A.gamma * acc[c];
+        store4<NT>(A.X + o, x);
+      }
+    }
+    if (all) return;
+  }
+  // eight lanes to a record, lane i of them for worker i; W's row in registers
+  const int i = lane & 7, grp = lane >> 3;
+  const bool row = i < A.n;
+  const uint64_t kstar = A.ctl[row ? i : 0].kstar;
+  const uint32_t expected = A.ctl[row ? i : 0].expected_key;
+  const int pbeg = row ? A.row_ptr[i] : 0, deg = row ? A.row_ptr[i + 1] - pbeg : 0;
+  int nc[kOnePassRows];
+  float nw[kOnePassRows];
+#pragma unroll
+  for (int j = 0; j < kOnePassRows; ++j) {
+    nc[j] = j < deg ? A.col[pbeg + j] : 0;
+    nw[j] = j < deg ? A.w[pbeg + j] : 0.0f;
+  }
+  const int waves = (int)(blockDim.x >> 6), nwaves = (int)gridDim.x * waves;
+  for (int t0 = ((int)blockIdx.x * waves + r) * kRecTiles; t0 < ntiles; t0 += nwaves * kRecTiles) {
+    const uint32_t total = list_marked(A, t0, ntiles, lists[r]);
+    constexpr int U = 4;       // records of a group in flight
+    for (uint32_t f0 = 0; f0 < total; f0 += 8 * U) {
+      Recorded R[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) R[u] = recorded(A, t0, lists[r], f0 + 8u * u + (uint32_t)grp, total, i);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const float q = R[u].x - R[u].h;
+        const uint32_t a = __float_as_uint(q);
+        const bool now = R[u].have && Digits<Q_TOPK>::composite(a, (uint32_t)R[u].col) >= kstar;
+        const bool was = R[u].have && Digits<Q_TOPK>::key32(a) >= expected;
+        const uint64_t wrong = __ballot(now != was);
+        if (wrong != 0ull) {                                    // (every lane takes part in the exchange)
+          const float hn = now ? R[u].h + q : R[u].h;
+          float acc = 0.0f;
+#pragma unroll
+          for (int j = 0; j < kOnePassRows; ++j) {
+            const float oth = __shfl(hn, (lane & ~7) + nc[j], 64);
+            if (j < deg) acc = acc + nw[j] * (oth - hn);
+          }
+          if (R[u].have && ((wrong >> (lane & ~7)) & 0xFFull) != 0ull) {
+            const int64_t o = (int64_t)i * A.ld + R[u].col;
+            A.X[o] = R[u].x + A.gamma * acc;
+            if (now != was) A.Xhat[o] = hn;
+          }
+        }
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+
+}  // namespace choco

@@ -1,0 +1,110 @@
+"""top_a in one pass over the state: every bit as the oracle has it, also where the pass went by a wrong
+threshold, left tiles unmixed, could not take its mix back without the records, or has to be undone."""
+import numpy as np
+import pytest
+
+from paper_1907_09356_amd import binding as B
+from paper_1907_09356_amd import synth
+from tests.launches import recorded
+from tests.parity_util import Pair
+
+
+def test_where_top_a_takes_one_pass():
+    """Two to eight workers, whole vectors in the default order, more than 96 MiB per array, few marked columns."""
+    out = recorded("""
+out = {}
+D = 3_200_000
+for name, n, d, kw in (
+        ("n8", 8, D, {}), ("n8 momentum", 8, D, {}), ("n2", 2, 4 * D, {}), ("n9", 9, D, {}), ("n1", 1, 8 * D, {}),
+        ("96 MiB", 8, 96 * 2**20 // 32, {}), ("printed", 8, D, dict(order=1)), ("sums", 8, D, dict(mix_form=B.MIX_INCREMENTAL_S)),
+        ("many kept", 8, D, dict(k=D // 500)), ("many kept, large", 8, 2 * D, dict(k=2 * D // 500)),
+        ("more kept, large", 8, 2 * D, dict(k=2 * D // 300)), ("rescale", 8, D, dict(randk_rescale=1)), ("odd", 8, D + 1, {})):
+    c = Context(n, d, B.Q_TOPK, **{"k": d // 1000, **kw})
+    first = c.step()
+    l = c.step_momentum() if "momentum" in name else c.step()
+    out[name] = [[x[0].split("<")[0] for x in y] for y in (first, l)] + [l[0][1:3]]
+    c.close()
+""")
+    # choco_init gives the first step no threshold to go by: nothing to list or to take back
+    select = ["k_sel_fallback", "k_sel_refine"]
+    first = ["k_onepass_mix"] + select + ["k_onepass_finish"]
+    later = ["k_onepass_mix", "k_onepass_list", "k_onepass_restore"] + select + ["k_onepass_finish"]
+    one = {"n8", "n8 momentum", "n2", "many kept, large", "odd"}
+    for name, (a, b, shape) in out.items():
+        if name in one:
+            drop = {"k_sel_hist_parts", "k_sel_emit_parts"}
+            norm = lambda l: ["k_sel_refine" if x == "k_sel_finish" else x for x in l if x not in drop]  # noqa: E731
+            assert (norm(a), norm(b)) == (first, later), name
+        else:
+            assert not any(x.startswith("k_onepass") for x in a + b), name
+    assert out["odd"][2] == ["12501x1x1", "512x1x1"] and out["n2"][2][1] == "128x1x1"
+
+
+def graph(name, n):
+    return synth.complete_csr(n) if name == "complete" else synth.ring_csr(n)
+
+
+def steps(pair, grads, lr, mode, count, tag):
+    for t in range(count):
+        g = grads.next()
+        if mode == "momentum":
+            det = pair.step_momentum(g, lr, 0.9, 1e-3)
+        elif mode == "halves":
+            pair.sgd_step(g, lr)
+            det = pair.gossip_step()
+        else:
+            det = pair.step(g, lr)
+        pair.check(det, tag="%s step %d" % (tag, t))
+
+
+@pytest.mark.gpu
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("n,d,k,topo,mode,align", [
+    (8, 3_150_001, 2000, "ring", "step", 4),        # a last tile of one column, rows off whole lines
+    (7, 3_600_255, 900, "complete", "momentum", 4),
+    (3, 8_400_300, 12_000, "ring", "halves", 64),   # (multi-block select)
+    (2, 12_600_000, 1, "ring", "step", 4),
+])
+def test_one_pass_steps(n, d, k, topo, mode, align):
+    X0 = synth.normal_state(n, d, seed=n)
+    X0[:, 5000:5400] *= 30.0                        # tiles with more candidates than there are slots
+    pair = Pair(X0, graph(topo, n) if n > 2 else synth.complete_csr(2), 0.3, compressor=B.Q_TOPK, k=k, ld_align=align)
+    try:
+        steps(pair, synth.GradientStream(n, d, seed=2), 0.05, mode, 4, mode)
+    finally:
+        pair.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.timeout(300)
+def test_one_pass_taken_back():
+    """Thresholds that fall by a factor between two steps (no list holds its k largest entries), with columns
+    whose mix has no exact inverse, tiles of such columns only, ties at the threshold, and NaN-free extremes."""
+    n, d, k = 8, 3_150_336, 1500
+    rng = np.random.default_rng(5)
+    X0 = synth.normal_state(n, d, seed=3)
+    pair = Pair(X0, synth.ring_csr(n), 0.7, compressor=B.Q_TOPK, k=k)
+    grads = synth.GradientStream(n, d, seed=4)
+    try:
+        steps(pair, grads, 0.05, "step", 2, "start")
+        # xhat of its own at three columns of every tile, and everywhere in the tiles from column 100,000 to
+        # 120,000: where the workers' xhat differ by as much as x, x' cannot be found again from the mixed x
+        for where in (slice(7, d, 256), slice(100, d, 256), slice(255, d, 256), slice(100_000, 120_000)):
+            pair.ref.Xhat[:, where] = pair.ref.X[:, where] + 1e-3 * rng.standard_normal(pair.ref.X[:, where].shape).astype(np.float32)
+        pair.force_state()
+        steps(pair, grads, 0.05, "step", 2, "lost")
+        # a thousandth of the distance: every guess is too high
+        pair.ref.X[:] = pair.ref.Xhat + (pair.ref.X - pair.ref.Xhat) * np.float32(1e-3)
+        pair.force_state()
+        steps(pair, grads, 1e-6, "step", 3, "fallen")
+        assert np.all(pair.gpu.last_scalars()[:, 4] >= 2), "the thresholds were to be missed"
+        # one worker's threshold only
+        pair.ref.X[3] = pair.ref.Xhat[3] + (pair.ref.X[3] - pair.ref.Xhat[3]) * np.float32(0.01)
+        pair.force_state()
+        steps(pair, grads, 1e-6, "step", 2, "one row")
+        # values on a grid: thousands of equal magnitudes around the threshold, lists that overflow
+        pair.ref.X[:] = pair.ref.Xhat + np.round(X0 * 4) / np.float32(4)
+        pair.force_state()
+        steps(pair, grads, 0.0, "step", 2, "ties")
+    finally:
+        pair.close()
