@@ -462,7 +462,7 @@ Layout make_layout(const choco_config& c, int32_t nnz) {
   L.sel_val = take(sparse ? (size_t)c.n * (size_t)kept * sizeof(float) : 0);
   L.multipart = guessed && multipart;
   L.hist_parts_bytes = align_up(L.multipart ? (size_t)c.n * kRefineParts * kBins * sizeof(uint32_t) : 0);
-  L.small_list_bytes = align_up(L.multipart ? (size_t)c.n * kSmallCap * sizeof(uint2) : 0);
+  L.small_list_bytes = align_up(L.multipart ? (size_t)c.n * kBinCap * sizeof(uint2) : 0);
   L.hist_parts = take(L.hist_parts_bytes * (size_t)L.select_sets);
   L.small_list = take(L.small_list_bytes * (size_t)L.select_sets);
   // kept entries: a bitmap per worker if it fits in the (single-block) select's LDS (40 KiB

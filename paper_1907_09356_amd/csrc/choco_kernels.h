@@ -37,6 +37,7 @@ constexpr int kStreamVecs = 2;    // 4-vectors per thread in the streaming kerne
 constexpr int kCompactVecs = 4;   // 4-vectors per thread in the select pass of long rows and of random_a
 constexpr int kStageCap = 1024;   // candidates one block stages in LDS before its single append
 constexpr int kSmallCap = 1024;   // entries of the threshold bin the select ranks directly in LDS
+constexpr int kBinCap = 32768;    // entries of the threshold bin the multi-block select takes apart by a second histogram
 // Chunks per wave in the norm passes (a workgroup takes a group of 16 chunks): one, in
 // 1024-thread workgroups, where the state is streamed past the caches (large states, and the
 // small ones that are latency-bound), two, in 512-thread workgroups, where it is read through
@@ -174,7 +175,7 @@ struct Args {
   uint32_t* hist16;    // n x kBins16 (fallback histogram)
   uint2* cand;         // n x kSegs x seg_cap  (a, index)
   uint32_t* hist_parts; // n x kRefineParts x kBins: per-block candidate histograms (multi-block select)
-  uint2* small_list;   // n x kSmallCap: entries of the threshold bin (multi-block select)
+  uint2* small_list;   // n x kBinCap: entries of the threshold bin (multi-block select)
   uint32_t* seg_counts;  // n x kSegs x kSegPad: entries with key32 >= guess_key appended per sub-list (may exceed
                          // seg_cap), a cache line per counter
   uint32_t seg_cap;    // capacity of one sub-list
@@ -2426,6 +2427,11 @@ __global__ __launch_bounds__(1024) void k_sel_refine(Args A0) {
 //   k_sel_finish      one block per worker ranks that short list, emits the rest, places
 //                     the next guess; also takes the digit-by-digit and row-scan paths when
 //                     the threshold bin is crowded or the list is not good
+// The bins are 256 to 511 between the guess and the expected threshold, so the threshold's holds up to
+// 0.6 % of k: above kSmallCap entries (k of some 175,000 on) k_sel_finish spreads them over 2048 bins of
+// their own first.  (One block that selects digit by digit out of the whole list instead, us per step:
+// n = 2, d = 28 M, k = 280,000 1122 against 281, 560,000 3249 against 477, 1,400,000 9270 against 730;
+// n = 8, d = 12 M, k = 600,000 4854 against 826.)
 // grid (kRefineParts, n) for the first two, n for the last; block 1024.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void part_slice(uint32_t total, uint32_t part, uint32_t* lo, uint32_t* hi) {
@@ -2483,7 +2489,7 @@ __global__ __launch_bounds__(1024) void k_sel_emit_parts(Args A) {
   __shared__ uint32_t grp[256];
   __shared__ uint32_t lens[kSegs];
   __shared__ uint32_t pre[kSegs + 1];
-  __shared__ uint32_t s_total, s_good, s_digit, s_above, s_count, s_base;
+  __shared__ uint32_t s_total, s_good, s_digit, s_above, s_count, s_base, s_in, s_in_base;
   const int i = blockIdx.y;
   WorkerCtl* ctl = A.ctl + i;
   if (threadIdx.x < 64) list_layout_wave(A, i, ctl, lens, pre, &s_total, &s_good);
@@ -2493,14 +2499,14 @@ __global__ __launch_bounds__(1024) void k_sel_emit_parts(Args A) {
   __syncthreads();
   find_digit(h, grp, (uint32_t)A.k, &s_digit, &s_above);
   const uint32_t tbin = s_digit;
-  if (h[tbin] > (uint32_t)kSmallCap) return;   // crowded threshold bin: k_sel_finish selects digit by digit
+  if (h[tbin] > (uint32_t)kBinCap) return;   // crowded threshold bin: k_sel_finish selects digit by digit
   uint32_t lo, hi;
   part_slice(s_total, blockIdx.x, &lo, &hi);
   const uint32_t guess = ctl->guess_key, shift = ctl->bin_shift;
   const int lane = threadIdx.x & 63;
   for (uint32_t base = lo; base < hi; base += 1024u * 8u) {
     __syncthreads();
-    if (threadIdx.x == 0) s_count = 0;
+    if (threadIdx.x == 0) s_count = s_in = 0;
     __syncthreads();
     uint2 c[8];
     bool have[8];
@@ -2511,37 +2517,36 @@ __global__ __launch_bounds__(1024) void k_sel_emit_parts(Args A) {
       if (have[u]) c[u] = list_entry(A, i, pre, f);
     }
     // which of my entries lie above the threshold bin; the bin's own entries go to the short list
-    uint64_t masks[8];
-    uint32_t wave_total = 0;
+    uint64_t masks[8], inside[8];
+    uint32_t wave_total = 0, wave_in = 0;
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      bool above = false;
-      if (have[u]) {
-        const uint32_t bin = cand_bin<COMP>(c[u].x, guess, shift);
-        above = bin > tbin;
-        if (bin == tbin) {
-          const uint32_t pos = atomicAdd(&ctl->small_count, 1u);
-          if (pos < (uint32_t)kSmallCap) A.small_list[(int64_t)i * kSmallCap + pos] = c[u];
-        }
-      }
-      masks[u] = __ballot(above);
+      const uint32_t bin = have[u] ? cand_bin<COMP>(c[u].x, guess, shift) : 0u;
+      masks[u] = __ballot(have[u] && bin > tbin);
+      inside[u] = __ballot(have[u] && bin == tbin);
       wave_total += (uint32_t)__popcll(masks[u]);
+      wave_in += (uint32_t)__popcll(inside[u]);
     }
     // slots: wave offset inside the block through LDS, block offset through one global atomic
-    uint32_t wave_base = 0;
+    uint32_t wave_base = 0, wave_in_base = 0;
     if (lane == 0 && wave_total) wave_base = atomicAdd(&s_count, wave_total);
+    if (lane == 0 && wave_in) wave_in_base = atomicAdd(&s_in, wave_in);
     wave_base = __shfl(wave_base, 0, 64);
+    wave_in_base = __shfl(wave_in_base, 0, 64);
     __syncthreads();
     if (threadIdx.x == 0 && s_count) s_base = atomicAdd(&ctl->emit_count, s_count);
+    if (threadIdx.x == 64 && s_in) s_in_base = atomicAdd(&ctl->small_count, s_in);
     __syncthreads();
-    uint32_t running = s_base + wave_base;
+    uint32_t running = s_base + wave_base, pos = s_in_base + wave_in_base;
+    const uint64_t below = (1ull << lane) - 1ull;
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      if ((masks[u] >> lane) & 1ull) {
-        const uint32_t slot = running + (uint32_t)__popcll(masks[u] & ((1ull << lane) - 1ull));
-        store_kept<COMP>(A, i, slot, c[u].x, c[u].y, nullptr);
-      }
+      if ((masks[u] >> lane) & 1ull)
+        store_kept<COMP>(A, i, running + (uint32_t)__popcll(masks[u] & below), c[u].x, c[u].y, nullptr);
+      else if ((inside[u] >> lane) & 1ull)
+        A.small_list[(int64_t)i * kBinCap + pos + (uint32_t)__popcll(inside[u] & below)] = c[u];
       running += (uint32_t)__popcll(masks[u]);
+      pos += (uint32_t)__popcll(inside[u]);
     }
   }
 }
@@ -2554,7 +2559,7 @@ __global__ __launch_bounds__(1024) void k_sel_finish(Args A) {
   __shared__ uint32_t pre[kSegs + 1];
   __shared__ uint2 small[kSmallCap];
   __shared__ uint64_t s_prefix, s_kstar;
-  __shared__ uint32_t s_need, s_digit, s_above, s_emit, s_total, s_good;
+  __shared__ uint32_t s_need, s_digit, s_above, s_emit, s_total, s_good, s_small;
   const int i = blockIdx.x;
   WorkerCtl* ctl = A.ctl + i;
   if (threadIdx.x == 0) {
@@ -2575,16 +2580,46 @@ __global__ __launch_bounds__(1024) void k_sel_finish(Args A) {
   const uint32_t tbin = s_digit, above = s_above;
   const uint32_t need_in_bin = (uint32_t)A.k - above;
   const uint32_t in_bin = h[tbin];
-  if (in_bin > (uint32_t)kSmallCap) {
+  // the blocks of k_sel_emit_parts emitted `above` entries into slots 0..above-1 and collected
+  // the in_bin entries of the threshold bin; rank those and emit the need_in_bin largest
+  const uint2* bin_list = A.small_list + (int64_t)i * kBinCap;
+  bool crowded = in_bin > (uint32_t)kBinCap;
+  uint32_t first = above, need = need_in_bin, m = in_bin;   // (slot of the best of `small`, kept of it, entries in it)
+  if (!crowded && in_bin > (uint32_t)kSmallCap) {
+    // more than can be ranked against each other: by the same steps again, one level down
+    const uint32_t guess = ctl->guess_key, shift = ctl->bin_shift, floor_key = guess + (tbin << shift);
+    const uint32_t top = COMP == Q_TOPK ? 0x7fffffffu : 0xffffffffu;
+    const uint32_t span = tbin < (uint32_t)kBins - 1u ? (1u << shift) - 1u : top - floor_key;   // (the last bin is open above)
+    const int sub_shift = span < (uint32_t)kBins ? 0 : 32 - __clz((int)span) - 11;
+    auto sub_bin = [&](uint32_t a) { return (Digits<COMP>::key32(a) - floor_key) >> sub_shift; };
     __syncthreads();
+    for (int b = threadIdx.x; b < kBins; b += 1024) h[b] = 0;
+    if (threadIdx.x == 0) s_small = 0;
+    __syncthreads();
+    for (uint32_t t = threadIdx.x; t < in_bin; t += 1024) atomicAdd(&h[sub_bin(bin_list[t].x)], 1u);
+    __syncthreads();
+    find_digit(h, grp, need_in_bin, &s_digit, &s_above);
+    const uint32_t sub = s_digit;
+    m = h[sub];
+    crowded = m > (uint32_t)kSmallCap;
+    if (!crowded) {
+      for (uint32_t t = threadIdx.x; t < in_bin; t += 1024) {
+        const uint2 c = bin_list[t];
+        const uint32_t b = sub_bin(c.x);
+        if (b > sub) store_kept<COMP>(A, i, above + atomicAdd(&s_emit, 1u), c.x, c.y, nullptr);
+        else if (b == sub) small[atomicAdd(&s_small, 1u)] = c;
+      }
+      first = above + s_above;
+      need = need_in_bin - s_above;
+    }
+  } else if (!crowded) {
+    for (uint32_t t = threadIdx.x; t < m; t += 1024) small[t] = bin_list[t];
+  }
+  __syncthreads();
+  if (crowded) {
     refine_and_emit<COMP, false>(A, i, pre, total, h, grp, &s_prefix, &s_need, &s_digit, &s_above, &s_emit, nullptr);
     return;
   }
-  // the blocks of k_sel_emit_parts emitted `above` entries into slots 0..above-1 and collected
-  // the in_bin entries of the threshold bin; rank those and emit the need_in_bin largest
-  const uint32_t m = in_bin;
-  for (uint32_t t = threadIdx.x; t < m; t += 1024) small[t] = A.small_list[(int64_t)i * kSmallCap + t];
-  __syncthreads();
   if (threadIdx.x < m) {
     const uint2 mine = small[threadIdx.x];
     const uint64_t K = Digits<COMP>::composite(mine.x, mine.y);
@@ -2593,8 +2628,8 @@ __global__ __launch_bounds__(1024) void k_sel_finish(Args A) {
       const uint2 o = small[u];
       rank += Digits<COMP>::composite(o.x, o.y) > K ? 1u : 0u;
     }
-    if (rank < need_in_bin) store_kept<COMP>(A, i, above + rank, mine.x, mine.y, nullptr);
-    if (rank + 1u == need_in_bin) s_kstar = K;
+    if (rank < need) store_kept<COMP>(A, i, first + rank, mine.x, mine.y, nullptr);
+    if (rank + 1u == need) s_kstar = K;
   }
   __syncthreads();
   reset_lists(A, i);
