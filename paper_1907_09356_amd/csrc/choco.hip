@@ -985,7 +985,7 @@ size_t ahead_lds_pad(const choco_ctx* ctx, int64_t row_len) {
 }
 
 // The exact select on the candidate lists of whole rows.
-template <int COMP>
+template <int COMP, bool ONEPASS = false>
 void launch_exact_select(choco_ctx* ctx, const Args& A) {
   if (ctx->fallback_chain) {
     LAUNCH(ctx, KID_SEL_FALLBACK, (k_sel_fallback<COMP>), fallback_grid(A.n), dim3(256), 0, A);
@@ -993,10 +993,10 @@ void launch_exact_select(choco_ctx* ctx, const Args& A) {
   if (ctx->multipart) {
     const dim3 pgrid((unsigned)kRefineParts, (unsigned)A.n);
     LAUNCH(ctx, KID_SEL_HIST_PARTS, (k_sel_hist_parts<COMP>), pgrid, dim3(1024), 0, A);
-    LAUNCH(ctx, KID_SEL_EMIT_PARTS, (k_sel_emit_parts<COMP>), pgrid, dim3(1024), 0, A);
-    LAUNCH(ctx, KID_SEL_FINISH, (k_sel_finish<COMP>), dim3((unsigned)A.n), dim3(1024), 0, A);
+    LAUNCH(ctx, KID_SEL_EMIT_PARTS, (k_sel_emit_parts<COMP, ONEPASS>), pgrid, dim3(1024), 0, A);
+    LAUNCH(ctx, KID_SEL_FINISH, (k_sel_finish<COMP, ONEPASS>), dim3((unsigned)A.n), dim3(1024), 0, A);
   } else {
-    LAUNCH(ctx, KID_SEL_REFINE, (k_sel_refine<COMP>), dim3((unsigned)A.n), dim3(1024),
+    LAUNCH(ctx, KID_SEL_REFINE, (k_sel_refine<COMP, false, ONEPASS>), dim3((unsigned)A.n), dim3(1024),
            (size_t)A.bitmap_words * sizeof(uint32_t), A);
   }
 }
@@ -1130,7 +1130,6 @@ int look_ahead_end(choco_ctx* ctx, const Args& A, uint64_t base) {
 
 // top_a in one pass (choco_onepass.h).  The kernels behind the pass have little or nothing to do as a
 // rule: workgroups to fill the chip once, which go through the tiles in turn.
-template <bool NT>
 int gossip_one_pass(choco_ctx* ctx, const Args& F0) {
   Args F = F0;
   F.onepass_first = ctx->one_pass_begun ? 0 : 1;
@@ -1139,13 +1138,13 @@ int gossip_one_pass(choco_ctx* ctx, const Args& F0) {
   const size_t lds = (size_t)A.n * kChunk * sizeof(float);
   const dim3 block(64u * (unsigned)A.n);
   const int waves = (A.nchunks + kRecTiles - 1) / kRecTiles;
-  LAUNCH(ctx, F.G ? KID_ONEPASS_MIX_SGD : KID_ONEPASS_MIX, (k_onepass_mix<NT>), dim3((unsigned)A.nchunks), block, lds, F);
+  LAUNCH(ctx, F.G ? KID_ONEPASS_MIX_SGD : KID_ONEPASS_MIX, k_onepass_mix, dim3((unsigned)A.nchunks), block, lds, F);
   if (!F.onepass_first) {
     LAUNCH(ctx, KID_ONEPASS_LIST, k_onepass_list, dim3((unsigned)std::min((waves + 3) / 4, 2048)), dim3(256), 0, A, A.nchunks);
-    LAUNCH(ctx, KID_ONEPASS_RESTORE, (k_onepass_restore<NT>), dim3((unsigned)std::min(A.nchunks, 512)), block, lds, A, A.nchunks);
+    LAUNCH(ctx, KID_ONEPASS_RESTORE, k_onepass_restore, dim3((unsigned)std::min(A.nchunks, 512)), block, lds, A, A.nchunks);
   }
-  launch_exact_select<Q_TOPK>(ctx, A);
-  LAUNCH(ctx, KID_ONEPASS_FINISH, (k_onepass_finish<NT>), dim3((unsigned)std::min((waves + A.n - 1) / A.n, 1024)), block, lds,
+  launch_exact_select<Q_TOPK, true>(ctx, A);
+  LAUNCH(ctx, KID_ONEPASS_FINISH, k_onepass_finish, dim3((unsigned)std::min((waves + A.n - 1) / A.n, 1024)), block, lds,
          A, A.nchunks);
   LAUNCH_CHECK(ctx);
   ctx->one_pass_begun = true;
@@ -1155,8 +1154,8 @@ int gossip_one_pass(choco_ctx* ctx, const Args& F0) {
 // Sparsifying operators (top_a, random_a).
 template <int COMP, bool NT>
 int gossip_sparse(choco_ctx* ctx, const Args& F) {
-  if constexpr (COMP == Q_TOPK)
-    if (ctx->one_pass) return gossip_one_pass<NT>(ctx, F);
+  if constexpr (COMP == Q_TOPK && NT)
+    if (ctx->one_pass) return gossip_one_pass(ctx, F);
   Args A = F;
   // a deferred local update (random_a) keeps G visible to the kernels that gather single
   // entries of x; otherwise only the first pass may see it

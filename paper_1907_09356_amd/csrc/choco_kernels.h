@@ -2062,7 +2062,7 @@ __device__ __forceinline__ void find_digit(const uint32_t* h, uint32_t* grp, uin
 __device__ __forceinline__ void mark_kept(const Args& A, int i, uint32_t idx, uint32_t* lbits) {
   // (lbits is null in the kernels that never see a row with an LDS bitmap)
   if (lbits != nullptr && A.bitmap_words) atomicOr(&lbits[idx >> 5], 1u << (idx & 31u));
-  else if (A.keptmap != nullptr) atomicOr(&A.keptmap[(int64_t)i * A.map_words + ((idx + (uint32_t)A.idx_base) >> 5)], 1u << ((idx + (uint32_t)A.idx_base) & 31u));
+  else atomicOr(&A.keptmap[(int64_t)i * A.map_words + ((idx + (uint32_t)A.idx_base) >> 5)], 1u << ((idx + (uint32_t)A.idx_base) & 31u));
 }
 
 // Did worker j keep entry e in this step?
@@ -2085,17 +2085,18 @@ __device__ __forceinline__ uint32_t cand_bin(uint32_t a, uint32_t guess, uint32_
 }
 
 // Store one kept entry at a known slot of worker i's message list and mark it.
-template <int COMP>
+// ONEPASS (choco_onepass.h): nobody asks for the mark.
+template <int COMP, bool ONEPASS = false>
 __device__ __forceinline__ void store_kept(const Args& A, int i, uint32_t slot, uint32_t a, uint32_t idx,
                                            uint32_t* lbits) {
   if (slot >= (uint32_t)A.k) return;
   // top_a carries the value in the entry; random_a gathers it afterwards (k_sel_values)
   A.sel_idx[(int64_t)i * A.sel_stride + slot] = A.idx_base + (int32_t)idx;
   if (COMP == Q_TOPK) A.sel_val[(int64_t)i * A.sel_stride + slot] = __uint_as_float(a);
-  mark_kept(A, i, idx, lbits);
+  if (!ONEPASS) mark_kept(A, i, idx, lbits);
 }
 
-template <int COMP>
+template <int COMP, bool ONEPASS>
 __device__ __forceinline__ void emit_entry(const Args& A, int i, bool keep, uint32_t a, uint32_t idx,
                                            uint32_t* s_emit, uint32_t* lbits) {
   const uint64_t mask = __ballot(keep);
@@ -2107,7 +2108,7 @@ __device__ __forceinline__ void emit_entry(const Args& A, int i, bool keep, uint
   base = __shfl(base, leader, 64);
   if (keep) {
     const uint32_t slot = base + (uint32_t)__popcll(mask & ((1ull << lane) - 1ull));
-    store_kept<COMP>(A, i, slot, a, idx, lbits);
+    store_kept<COMP, ONEPASS>(A, i, slot, a, idx, lbits);
   }
 }
 
@@ -2138,6 +2139,7 @@ __device__ __forceinline__ void expect_threshold(const Args& A, WorkerCtl* ctl, 
 // threshold key T: by the distance that, at the key density seen between the old
 // guess and T, holds `want` entries (for top_a the k entries kept now leave the
 // race, so want includes k).  Also resets the per-step counters (the lists': reset_lists).
+template <bool ONEPASS>
 __device__ __forceinline__ void next_guess(const Args& A, WorkerCtl* ctl, uint64_t kstar, uint32_t total,
                                            bool from_list, uint32_t emitted, uint32_t mode,
                                            bool have_floor = false, uint32_t floor_key = 0) {
@@ -2151,7 +2153,7 @@ __device__ __forceinline__ void next_guess(const Args& A, WorkerCtl* ctl, uint64
   if (delta < 1) delta = 1;
   if (delta > 0xFFFFFFFFull) delta = 0xFFFFFFFFull;
   const uint32_t guess = delta >= (uint64_t)T ? 0u : T - (uint32_t)delta;
-  if (A.recs != nullptr) expect_threshold(A, ctl, T, from_list && total > (uint32_t)A.k && T > G, T - G, total, guess);
+  if (ONEPASS) expect_threshold(A, ctl, T, from_list && total > (uint32_t)A.k && T > G, T - G, total, guess);
   ctl->guess_key = guess;
   // 256-511 bins between the guess and where the threshold is expected: the 2048 bins then
   // still resolve a threshold that lands 4-8 times further above the guess than predicted
@@ -2178,7 +2180,7 @@ __device__ __forceinline__ void reset_lists(const Args& A, int i) {
 // Digit-by-digit radix select over the composite keys of the candidate list (ROW = false)
 // or of the row itself (ROW = true: the list is not good); emits the kept entries, marks
 // them and places the next guess.  All threads of a 1024-thread block.
-template <int COMP, bool ROW>
+template <int COMP, bool ROW, bool ONEPASS>
 __device__ void refine_and_emit(const Args& A, int i, const uint32_t* pre, uint32_t total, uint32_t* h,
                                 uint32_t* grp, uint64_t* s_prefix, uint32_t* s_need, uint32_t* s_digit,
                                 uint32_t* s_above, uint32_t* s_emit, uint32_t* lbits) {
@@ -2230,7 +2232,7 @@ __device__ void refine_and_emit(const Args& A, int i, const uint32_t* pre, uint3
       if (slot < (uint32_t)A.k) {
         A.sel_idx[(int64_t)i * A.sel_stride + slot] = A.idx_base + (int32_t)idx;
         if (COMP == Q_TOPK) A.sel_val[(int64_t)i * A.sel_stride + slot] = __uint_as_float(a);
-        mark_kept(A, i, idx, lbits);
+        if (!ONEPASS) mark_kept(A, i, idx, lbits);
       }
     }
   });
@@ -2238,7 +2240,7 @@ __device__ void refine_and_emit(const Args& A, int i, const uint32_t* pre, uint3
   publish_bitmap(A, i, lbits);
   __syncthreads();
   reset_lists(A, i);
-  if (threadIdx.x == 0) next_guess(A, ctl, kstar, total, !ROW, *s_emit, ROW ? 2u : 0u, ROW, floor_key);
+  if (threadIdx.x == 0) next_guess<ONEPASS>(A, ctl, kstar, total, !ROW, *s_emit, ROW ? 2u : 0u, ROW, floor_key);
 }
 
 // Exact selection from the candidates by one block per worker: emission of the kept
@@ -2250,7 +2252,7 @@ __device__ void refine_and_emit(const Args& A, int i, const uint32_t* pre, uint3
 // digit-by-digit select runs on the list; if the list itself is not good, on the row.
 // grid n, block 1024, dynamic LDS = the worker's bitmap (short rows) or nothing.
 // BATCH: grid (n, long layers of A.long_tab).
-template <int COMP, bool BATCH = false>
+template <int COMP, bool BATCH = false, bool ONEPASS = false>
 __global__ __launch_bounds__(1024) void k_sel_refine(Args A0) {
   const Args A = BATCH ? long_view(A0, A0.long_tab[blockIdx.y]) : A0;
   __shared__ uint32_t h[kBins];
@@ -2295,7 +2297,7 @@ __global__ __launch_bounds__(1024) void k_sel_refine(Args A0) {
   __syncthreads();
   const uint32_t total = s_total;
   if (!s_good) {
-    refine_and_emit<COMP, true>(A, i, pre, total, h, grp, &s_prefix, &s_need, &s_digit, &s_above, &s_emit, lbits);
+    refine_and_emit<COMP, true, ONEPASS>(A, i, pre, total, h, grp, &s_prefix, &s_need, &s_digit, &s_above, &s_emit, lbits);
     return;
   }
   const uint32_t guess = ctl->guess_key, shift = ctl->bin_shift;
@@ -2332,7 +2334,7 @@ __global__ __launch_bounds__(1024) void k_sel_refine(Args A0) {
   const uint32_t in_bin = h[tbin];
   if (in_bin > (uint32_t)kSmallCap) {
     __syncthreads();
-    refine_and_emit<COMP, false>(A, i, pre, total, h, grp, &s_prefix, &s_need, &s_digit, &s_above, &s_emit, lbits);
+    refine_and_emit<COMP, false, ONEPASS>(A, i, pre, total, h, grp, &s_prefix, &s_need, &s_digit, &s_above, &s_emit, lbits);
     return;
   }
   // sweep 2: emit everything above the threshold bin, collect the bin itself
@@ -2367,7 +2369,7 @@ __global__ __launch_bounds__(1024) void k_sel_refine(Args A0) {
     uint32_t slot = wave_base + incl - mine;
 #pragma unroll
     for (int u = 0; u < 8; ++u)
-      if (above[u]) store_kept<COMP>(A, i, slot++, c[u].x, c[u].y, lbits);
+      if (above[u]) store_kept<COMP, ONEPASS>(A, i, slot++, c[u].x, c[u].y, lbits);
   } else
   for (uint32_t base = 0; base < total; base += 1024u * 8u) {
     if (!resident) {
@@ -2389,7 +2391,7 @@ __global__ __launch_bounds__(1024) void k_sel_refine(Args A0) {
           if (pos < (uint32_t)kSmallCap) small[pos] = c[u];
         }
       }
-      emit_entry<COMP>(A, i, above, c[u].x, c[u].y, &s_emit, lbits);
+      emit_entry<COMP, ONEPASS>(A, i, above, c[u].x, c[u].y, &s_emit, lbits);
     }
   }
   __syncthreads();
@@ -2409,12 +2411,12 @@ __global__ __launch_bounds__(1024) void k_sel_refine(Args A0) {
       keep = rank < need_in_bin;
       if (rank + 1u == need_in_bin) s_kstar = K;
     }
-    emit_entry<COMP>(A, i, keep, mine.x, mine.y, &s_emit, lbits);
+    emit_entry<COMP, ONEPASS>(A, i, keep, mine.x, mine.y, &s_emit, lbits);
   }
   __syncthreads();
   publish_bitmap(A, i, lbits);
   if (BATCH) reset_lists(A, i);
-  if (threadIdx.x == 0) next_guess(A, ctl, s_kstar, total, true, s_emit, 0u);
+  if (threadIdx.x == 0) next_guess<ONEPASS>(A, ctl, s_kstar, total, true, s_emit, 0u);
 }
 
 // ---------------------------------------------------------------------------
@@ -2483,7 +2485,7 @@ __device__ __forceinline__ void sum_hist_parts(const Args& A, int i, uint32_t* h
   }
 }
 
-template <int COMP>
+template <int COMP, bool ONEPASS = false>
 __global__ __launch_bounds__(1024) void k_sel_emit_parts(Args A) {
   __shared__ uint32_t h[kBins];
   __shared__ uint32_t grp[256];
@@ -2542,7 +2544,7 @@ __global__ __launch_bounds__(1024) void k_sel_emit_parts(Args A) {
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
       if ((masks[u] >> lane) & 1ull)
-        store_kept<COMP>(A, i, running + (uint32_t)__popcll(masks[u] & below), c[u].x, c[u].y, nullptr);
+        store_kept<COMP, ONEPASS>(A, i, running + (uint32_t)__popcll(masks[u] & below), c[u].x, c[u].y, nullptr);
       else if ((inside[u] >> lane) & 1ull)
         A.small_list[(int64_t)i * kBinCap + pos + (uint32_t)__popcll(inside[u] & below)] = c[u];
       running += (uint32_t)__popcll(masks[u]);
@@ -2551,7 +2553,7 @@ __global__ __launch_bounds__(1024) void k_sel_emit_parts(Args A) {
   }
 }
 
-template <int COMP>
+template <int COMP, bool ONEPASS = false>
 __global__ __launch_bounds__(1024) void k_sel_finish(Args A) {
   __shared__ uint32_t h[kBins];
   __shared__ uint32_t grp[256];
@@ -2571,7 +2573,7 @@ __global__ __launch_bounds__(1024) void k_sel_finish(Args A) {
   __syncthreads();
   const uint32_t total = s_total;
   if (!s_good) {
-    refine_and_emit<COMP, true>(A, i, pre, total, h, grp, &s_prefix, &s_need, &s_digit, &s_above, &s_emit, nullptr);
+    refine_and_emit<COMP, true, ONEPASS>(A, i, pre, total, h, grp, &s_prefix, &s_need, &s_digit, &s_above, &s_emit, nullptr);
     return;
   }
   sum_hist_parts(A, i, h);
@@ -2606,7 +2608,7 @@ __global__ __launch_bounds__(1024) void k_sel_finish(Args A) {
       for (uint32_t t = threadIdx.x; t < in_bin; t += 1024) {
         const uint2 c = bin_list[t];
         const uint32_t b = sub_bin(c.x);
-        if (b > sub) store_kept<COMP>(A, i, above + atomicAdd(&s_emit, 1u), c.x, c.y, nullptr);
+        if (b > sub) store_kept<COMP, ONEPASS>(A, i, above + atomicAdd(&s_emit, 1u), c.x, c.y, nullptr);
         else if (b == sub) small[atomicAdd(&s_small, 1u)] = c;
       }
       first = above + s_above;
@@ -2617,7 +2619,7 @@ __global__ __launch_bounds__(1024) void k_sel_finish(Args A) {
   }
   __syncthreads();
   if (crowded) {
-    refine_and_emit<COMP, false>(A, i, pre, total, h, grp, &s_prefix, &s_need, &s_digit, &s_above, &s_emit, nullptr);
+    refine_and_emit<COMP, false, ONEPASS>(A, i, pre, total, h, grp, &s_prefix, &s_need, &s_digit, &s_above, &s_emit, nullptr);
     return;
   }
   if (threadIdx.x < m) {
@@ -2628,12 +2630,12 @@ __global__ __launch_bounds__(1024) void k_sel_finish(Args A) {
       const uint2 o = small[u];
       rank += Digits<COMP>::composite(o.x, o.y) > K ? 1u : 0u;
     }
-    if (rank < need) store_kept<COMP>(A, i, first + rank, mine.x, mine.y, nullptr);
+    if (rank < need) store_kept<COMP, ONEPASS>(A, i, first + rank, mine.x, mine.y, nullptr);
     if (rank + 1u == need) s_kstar = K;
   }
   __syncthreads();
   reset_lists(A, i);
-  if (threadIdx.x == 0) next_guess(A, ctl, s_kstar, total, true, above + need_in_bin, 0u);
+  if (threadIdx.x == 0) next_guess<ONEPASS>(A, ctl, s_kstar, total, true, above + need_in_bin, 0u);
 }
 
 // random_a with the fused update-and-mix pass: the kept values were left at their entries of Qv;

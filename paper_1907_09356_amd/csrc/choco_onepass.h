@@ -56,7 +56,6 @@ __device__ __forceinline__ bool left_open(uint2 w) { return (w.x & w.y) == 0xFFF
 static_assert(kRecSlots < 64, "two full words of a mask mean an open tile");
 
 // grid ceil(d / 256), block 64 n (wave r: row r), dynamic LDS n x 256 floats.
-template <bool NT>
 __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_mix(Args A) {
   extern __shared__ float tile[];
   __shared__ uint64_t marks[64];   // a byte per lane and wave
@@ -68,10 +67,10 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_mix(Args A) {
   const bool mom = A.G != nullptr && A.M != nullptr;
   vf4 x = {0.f, 0.f, 0.f, 0.f}, h = x, g = x, m = x;
   if (mine) {
-    x = load4<NT>(A.X + o);
-    h = load4<NT>(A.Xhat + o);
+    x = load4<true>(A.X + o);
+    h = load4<true>(A.Xhat + o);
     if (A.G) g = load4<true>(A.G + o);
-    if (mom) m = load4<NT>(A.M + o);
+    if (mom) m = load4<true>(A.M + o);
   }
   const RowSpan span = nbr_span<1, kOnePassRows>(A, r, lane);
   const uint32_t guess = A.ctl[r].guess_key, expect = A.ctl[r].expect_key;
@@ -79,10 +78,10 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_mix(Args A) {
   const RowNbrs nb = nbr_fetch(A, span, lane);
   if (mine && A.G) {
     x = local_update_regs(A, x, g, m);
-    if (mom) store4<NT>(A.M + o, m);
+    if (mom) store4<true>(A.M + o, m);
   }
   if (A.onepass_first) {           // no threshold to go by: the last kernel does all tiles
-    if (mine && A.G) store4<NT>(A.X + o, x);
+    if (mine && A.G) store4<true>(A.X + o, x);
     return;
   }
   vf4 hn = h;
@@ -127,7 +126,7 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_mix(Args A) {
   }
   const bool open = total > kRecSlots;     // the same in every wave
   if (mine) {
-    store4<NT>(A.X + o, open ? x : xm);
+    store4<true>(A.X + o, open ? x : xm);
     if (kept && !open) store4<false>(A.Xhat + o, hn);
   }
   if (r == 0) {
@@ -250,7 +249,6 @@ __global__ __launch_bounds__(256) void k_onepass_list(Args A, int32_t ntiles) {
 // Do all lists hold their row's k largest entries?  If not, what k_onepass_mix did to x and xhat is
 // undone, tile by tile, so that X is x' everywhere.  Normally a launch of workgroups that read the
 // lists' lengths and leave.  grid any, block 64 n, dynamic LDS n x 256 floats.
-template <bool NT>
 __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_restore(Args A, int32_t ntiles) {
   extern __shared__ float tile[];
   __shared__ uint32_t s_bad;
@@ -279,8 +277,8 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_restore(Args A, i
 #pragma unroll
     for (int c = 0; c < 4; ++c) slot += __popcll(__ballot((dirty >> c) & 1u) & ((1ull << lane) - 1ull));
     if (mine) {
-      x = load4<NT>(A.X + o);
-      h = load4<NT>(A.Xhat + o);
+      x = load4<true>(A.X + o);
+      h = load4<true>(A.Xhat + o);
 #pragma unroll
       for (int c = 0; c < 4; ++c)
         if ((dirty >> c) & 1u) {
@@ -300,7 +298,7 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_restore(Args A, i
         const float step = A.gamma * acc[c];
         x[c] = ((dirty >> c) & 1u) ? xr[c] : x[c] - step;
       }
-      store4<NT>(A.X + o, x);
+      store4<true>(A.X + o, x);
     }
   }
 }
@@ -309,7 +307,6 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_restore(Args A, i
 // (all of them in a first step or after k_onepass_restore) get the update of xhat and the mix here; of
 // the others the recorded columns whose kept set is not the one that k_onepass_mix went by.
 // grid any, block 64 n, dynamic LDS n x 256 floats.
-template <bool NT>
 __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_finish(Args A, int32_t ntiles) {
   extern __shared__ float tile[];
   __shared__ ushort2 lists[kOnePassRows][kRecTiles * kRecSlots];
@@ -326,8 +323,8 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_finish(Args A, in
       const int64_t o = (int64_t)r * A.ld + e;
       vf4 x = {0.f, 0.f, 0.f, 0.f}, h = x;
       if (mine) {
-        x = load4<NT>(A.X + o);
-        h = load4<NT>(A.Xhat + o);
+        x = load4<true>(A.X + o);
+        h = load4<true>(A.Xhat + o);
         bool kept = false;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
@@ -346,7 +343,7 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_finish(Args A, in
       if (mine) {
 #pragma unroll
         for (int c = 0; c < 4; ++c) x[c] = x[c] + A.gamma * acc[c];
-        store4<NT>(A.X + o, x);
+        store4<true>(A.X + o, x);
       }
     }
     if (all) return;
