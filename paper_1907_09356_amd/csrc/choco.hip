@@ -97,8 +97,8 @@ struct choco_ctx {
   int32_t nnz;
   bool sparse;            // top_a / random_a
   bool fused_sparse_apply;   // ... whose update of xhat rides on the tile mix pass (direct form, compress-then-mix)
-  bool one_pass;          // top_a: one pass over the state (choco_onepass.h)
-  bool one_pass_begun;    // ... and has taken a step (later ones have a threshold to go by)
+  bool one_pass;          // top_a, gsgd: one pass over the state (choco_onepass.h)
+  bool one_pass_begun;    // ... and has taken a step (later ones have a threshold or a norm to go by)
   bool values_in_qv;      // random_a after such a step: the kept values are in Qv, not yet in the list
   int mix_form;           // resolved: CHOCO_MIX_INCREMENTAL_S or CHOCO_MIX_DIRECT
   bool tile_fits;         // the LDS tile of all rows exists (up to kMaxTileRows workers)
@@ -356,6 +356,22 @@ bool one_pass_topk(const choco_config& c) {
   return mib > 96.0 && marked <= (mib < 160.0 ? 8.0 : 16.0);
 }
 
+// gsgd in one pass over the state?  The entries whose level is not zero must be few: s ||v||_1 / ||v||_2 of a
+// row, 0.8 s sqrt(d) of a Gaussian one (at most a quarter more).  us per step, two passes | one (marked
+// columns of a tile expected):
+//   n = 8, ring         28 M s = 16 (5) 1255 | 789   32 (10) 1281 | 906   64 (20) 1305 | 1156
+//                       12 M s = 16 (8) 510 | 369    32 (15) 518 | 463    4.4 M s = 16 (13) 193 | 153   32 (25) 196 | 240
+//   n = 4, ring         25 M s = 64 (10) 606 | 487   7 M s = 32 (10) 175 | 127   64 (20) 176 | 188
+//   n = 2               28 M s = 16 (1) 451 | 184    14 M s = 64 (7) 248 | 132
+//   n = 8, 5.5 neighbours on average   12 M s = 16 (8) 544 | 401   3.3 M s = 16 (14) 160 | 140
+bool one_pass_qsgd(const choco_config& c) {
+  if (c.compressor != CHOCO_Q_QSGD || c.nlayers > 0 || c.order != CHOCO_ORDER_COMPRESS_THEN_MIX) return false;
+  if (c.n < 2 || c.n > kOnePassRows) return false;
+  const double mib = (double)c.n * (double)resolve_ld(c) * sizeof(float) / 1048576.0;
+  const double marked = (double)kChunk * c.n * 0.8 * (double)c.levels / std::sqrt((double)c.d);
+  return mib > 96.0 && marked <= 14.0;
+}
+
 // The layers of a top_a / random_a configuration that are too long for the layer kernel.
 std::vector<LongLayer> long_layers_of(const choco_config& c) {
   std::vector<LongLayer> out;
@@ -435,8 +451,8 @@ Layout make_layout(const choco_config& c, int32_t nnz) {
   L.nchunks = (int32_t)((c.d + kChunk - 1) / kChunk);
   L.ngroups = (L.nchunks + kGroup - 1) / kGroup;
   const bool dense_stat = c.compressor == CHOCO_Q_SIGN || c.compressor == CHOCO_Q_QSGD;
-  // chunk sums are only materialised by the tile kernel of the printed order
-  L.chunk_sums = take(dense_stat && c.order == CHOCO_ORDER_MIX_THEN_COMPRESS
+  // chunk sums are only materialised by the tile kernel of the printed order and by the one pass of gsgd
+  L.chunk_sums = take((dense_stat && c.order == CHOCO_ORDER_MIX_THEN_COMPRESS) || one_pass_qsgd(c)
                           ? (size_t)c.n * (size_t)L.nchunks * sizeof(double) : 0);
   L.group_sums = take(dense_stat ? (size_t)c.n * (size_t)L.ngroups * sizeof(double) : 0);
   int64_t cap = 0, seg_cap = 0;
@@ -469,7 +485,7 @@ Layout make_layout(const choco_config& c, int32_t nnz) {
   // beside its other arrays), else a bit per entry in global memory
   L.bitmap_words = (guessed && !layered && !L.multipart && c.d <= 40 * 1024 * 8) ? (c.d + 31) / 32 : 0;
   const size_t map_bytes = (size_t)c.n * (size_t)((ld + 31) / 32) * sizeof(uint32_t);   // a bit per entry
-  const bool one_pass = one_pass_topk(c);
+  const bool one_pass = one_pass_topk(c) || one_pass_qsgd(c);
   L.keptmap = take(sparse && !L.bitmap_words && !one_pass ? map_bytes : 0);
   L.bitmap = take((size_t)c.n * (size_t)L.bitmap_words * sizeof(uint32_t));
   // further copies for the selections random_a makes ahead: the kept-index lists, the bitmap
@@ -681,7 +697,7 @@ int join_lookahead(choco_ctx* ctx) {
 enum KernelId {
   KID_SGD, KID_MOMENTUM, KID_DENSE_STAT, KID_GROUP_REDUCE, KID_DENSE_FINALISE, KID_DENSE_APPLY_MIX, KID_TILE_MIX,
   KID_DENSE_APPLY, KID_MIX_DIRECT_GLOBAL, KID_MIX_INCREMENTAL, KID_SEL_COMPACT, KID_SEL_FALLBACK,
-  KID_SEL_REFINE, KID_SCATTER_S, KID_XHAT_UPDATE, KID_GATHER_VALUES, KID_SEL_VALUES, KID_SEL_HIST_PARTS, KID_SEL_EMIT_PARTS, KID_SEL_FINISH, KID_DENSE_STAT_SGD, KID_DENSE_STAT_REDO, KID_DENSE_APPLY_MIX_SGD, KID_SEL_COMPACT_SGD, KID_SEL_COMPACT_REDO, KID_TILE_MIX_SGD, KID_MIX_INCREMENTAL_SGD, KID_LAYER_COMPRESS, KID_LAYER_COMPRESS_SGD, KID_LAYER_STAT, KID_LAYER_STAT_SGD, KID_LAYER_STAT_REDO, KID_LAYER_FINALISE, KID_WIRE, KID_ZERO_WORDS, KID_ONEPASS_MIX, KID_ONEPASS_MIX_SGD, KID_ONEPASS_LIST, KID_ONEPASS_RESTORE, KID_ONEPASS_FINISH, KID_COUNT
+  KID_SEL_REFINE, KID_SCATTER_S, KID_XHAT_UPDATE, KID_GATHER_VALUES, KID_SEL_VALUES, KID_SEL_HIST_PARTS, KID_SEL_EMIT_PARTS, KID_SEL_FINISH, KID_DENSE_STAT_SGD, KID_DENSE_STAT_REDO, KID_DENSE_APPLY_MIX_SGD, KID_SEL_COMPACT_SGD, KID_SEL_COMPACT_REDO, KID_TILE_MIX_SGD, KID_MIX_INCREMENTAL_SGD, KID_LAYER_COMPRESS, KID_LAYER_COMPRESS_SGD, KID_LAYER_STAT, KID_LAYER_STAT_SGD, KID_LAYER_STAT_REDO, KID_LAYER_FINALISE, KID_WIRE, KID_ZERO_WORDS, KID_ONEPASS_MIX, KID_ONEPASS_MIX_SGD, KID_ONEPASS_LIST, KID_ONEPASS_RESTORE, KID_ONEPASS_FINISH, KID_ONEPASS_ENCODE, KID_COUNT
 };
 const char* const kKernelNames[KID_COUNT] = {
   "k_sgd", "k_momentum", "k_dense_stat", "k_group_reduce", "k_dense_finalise", "k_dense_apply_mix", "k_tile_mix",
@@ -689,7 +705,7 @@ const char* const kKernelNames[KID_COUNT] = {
   "k_sel_refine", "k_scatter_s", "k_xhat_update", "k_gather_values", "k_sel_values", "k_sel_hist_parts", "k_sel_emit_parts", "k_sel_finish",
   "k_dense_stat_sgd", "k_dense_stat_redo", "k_dense_apply_mix_sgd", "k_sel_compact_sgd", "k_sel_compact_redo", "k_tile_mix_sgd", "k_mix_incremental_sgd",
   "k_layer_compress", "k_layer_compress_sgd", "k_layer_stat", "k_layer_stat_sgd", "k_layer_stat_redo", "k_layer_finalise", "k_wire",
-  "k_zero_words", "k_onepass_mix", "k_onepass_mix_sgd", "k_onepass_list", "k_onepass_restore", "k_onepass_finish"};
+  "k_zero_words", "k_onepass_mix", "k_onepass_mix_sgd", "k_onepass_list", "k_onepass_restore", "k_onepass_finish", "k_onepass_encode"};
 constexpr size_t kMaxProfiledLaunches = 16384;
 
 // Brackets one launch with two events when profiling is on (no-op otherwise).
@@ -922,9 +938,27 @@ bool folds_norms(const choco_config& c, bool narrow, bool nt, int32_t tiles, int
   return c.n <= 32 && tiles <= 256;   // identity has no norms: the tile it takes
 }
 
+// gsgd in one pass (choco_onepass.h), from a context's second step on: the first has no norms to go by and
+// takes the two-pass form.
+int gossip_one_pass_qsgd(choco_ctx* ctx, const Args& F) {
+  Args A = F;
+  A.G = nullptr;
+  const size_t lds = (size_t)A.n * kChunk * sizeof(float);
+  const dim3 block(64u * (unsigned)A.n);
+  const int waves = (A.nchunks + kRecTiles - 1) / kRecTiles;
+  LAUNCH(ctx, F.G ? KID_ONEPASS_MIX_SGD : KID_ONEPASS_MIX, k_onepass_mix<Q_QSGD>, dim3((unsigned)A.nchunks), block, lds, F);
+  LAUNCH(ctx, KID_GROUP_REDUCE, k_group_reduce, dim3((unsigned)((A.ngroups + 15) / 16), (unsigned)A.n), dim3(256), 0, A);
+  LAUNCH(ctx, KID_DENSE_FINALISE, (k_dense_finalise<Q_QSGD, true>), dim3((unsigned)A.n), dim3(256), 0, A);
+  LAUNCH(ctx, KID_ONEPASS_ENCODE, k_onepass_encode, dim3((unsigned)std::min((waves + A.n - 1) / A.n, 1024)), block, lds, A, A.nchunks);
+  LAUNCH_CHECK(ctx);
+  return CHOCO_OK;
+}
+
 // Dense operators (identity, sign, gsgd), direct mix form.
 template <int COMP, bool NT>
 int gossip_dense(choco_ctx* ctx, const Args& F0) {
+  if constexpr (COMP == Q_QSGD && NT)
+    if (ctx->one_pass && ctx->one_pass_begun) return gossip_one_pass_qsgd(ctx, F0);
   Args F = F0, A = F0;
   A.G = nullptr;
   F.redo_sgd = redo_sgd(ctx, F) ? 1 : 0;
@@ -937,8 +971,11 @@ int gossip_dense(choco_ctx* ctx, const Args& F0) {
     if (needs_stat) {
       LAUNCH(ctx, F.redo_sgd ? KID_DENSE_STAT_REDO : fused ? KID_DENSE_STAT_SGD : KID_DENSE_STAT, (k_dense_stat<STATK, NT>), stat_grid,
              dim3(stat_threads(NT)), 0, F);
-      if (!A.fold_finalise)
+      if (ctx->one_pass)   // (gsgd's first step; its later ones go by the bounds made here)
+        LAUNCH(ctx, KID_DENSE_FINALISE, (k_dense_finalise<STATK, COMP == Q_QSGD>), dim3((unsigned)A.n), dim3(256), 0, A);
+      else if (!A.fold_finalise)
         LAUNCH(ctx, KID_DENSE_FINALISE, (k_dense_finalise<STATK>), dim3((unsigned)A.n), dim3(256), 0, A);
+      ctx->one_pass_begun = ctx->one_pass;
     }
     if (ctx->tile_fits) {
       if (F.redo_sgd) A.G = F.G;
@@ -1130,7 +1167,7 @@ int look_ahead_end(choco_ctx* ctx, const Args& A, uint64_t base) {
 
 // top_a in one pass (choco_onepass.h).  The kernels behind the pass have little or nothing to do as a
 // rule: workgroups to fill the chip once, which go through the tiles in turn.
-int gossip_one_pass(choco_ctx* ctx, const Args& F0) {
+int gossip_one_pass_topk(choco_ctx* ctx, const Args& F0) {
   Args F = F0;
   F.onepass_first = ctx->one_pass_begun ? 0 : 1;
   Args A = F;
@@ -1138,7 +1175,7 @@ int gossip_one_pass(choco_ctx* ctx, const Args& F0) {
   const size_t lds = (size_t)A.n * kChunk * sizeof(float);
   const dim3 block(64u * (unsigned)A.n);
   const int waves = (A.nchunks + kRecTiles - 1) / kRecTiles;
-  LAUNCH(ctx, F.G ? KID_ONEPASS_MIX_SGD : KID_ONEPASS_MIX, k_onepass_mix, dim3((unsigned)A.nchunks), block, lds, F);
+  LAUNCH(ctx, F.G ? KID_ONEPASS_MIX_SGD : KID_ONEPASS_MIX, k_onepass_mix<Q_TOPK>, dim3((unsigned)A.nchunks), block, lds, F);
   if (!F.onepass_first) {
     LAUNCH(ctx, KID_ONEPASS_LIST, k_onepass_list, dim3((unsigned)std::min((waves + 3) / 4, 2048)), dim3(256), 0, A, A.nchunks);
     LAUNCH(ctx, KID_ONEPASS_RESTORE, k_onepass_restore, dim3((unsigned)std::min(A.nchunks, 512)), block, lds, A, A.nchunks);
@@ -1155,7 +1192,7 @@ int gossip_one_pass(choco_ctx* ctx, const Args& F0) {
 template <int COMP, bool NT>
 int gossip_sparse(choco_ctx* ctx, const Args& F) {
   if constexpr (COMP == Q_TOPK && NT)
-    if (ctx->one_pass) return gossip_one_pass(ctx, F);
+    if (ctx->one_pass) return gossip_one_pass_topk(ctx, F);
   Args A = F;
   // a deferred local update (random_a) keeps G visible to the kernels that gather single
   // entries of x; otherwise only the first pass may see it
@@ -1723,7 +1760,7 @@ int choco_init(const choco_config* cfg, float* x_dev, void* workspace_dev, size_
   ctx->sparse = is_sparse(cfg->compressor);
   ctx->mix_form = resolve_mix_form(*cfg);
   ctx->fused_sparse_apply = fused_sparse_apply(*cfg);
-  ctx->one_pass = one_pass_topk(*cfg);
+  ctx->one_pass = one_pass_topk(*cfg) || one_pass_qsgd(*cfg);
   ctx->one_pass_begun = false;
   ctx->values_in_qv = false;
   ctx->tile_fits = cfg->n <= kMaxTileRows;

@@ -78,6 +78,8 @@ struct WorkerCtl {
   // one-pass top_a: the threshold key that the next step's pass goes by, the one that this step's pass
   // went by, and the rank among this step's entries at which the former was put
   uint32_t expect_key, expected_key, expect_rank;
+  // one-pass gsgd: the bound on s / ||v||_2 that the next step's pass goes by, and the one that this step's did
+  float bound_r, bounded_r;
 };
 
 // What the kernels of one-pass top_a tell each other about a step (choco_onepass.h).
@@ -228,7 +230,7 @@ struct Args {
   const int4* chunk_layer;   // per 256-entry chunk of a row: layer of its first entry, that layer's end, next layer's start
   double* layer_scal;        // n x nlayers x 4: norms and scales / threshold of the last step
   int32_t qsgd_biased;
-  // one-pass top_a (choco_onepass.h); recs is null elsewhere
+  // one-pass top_a and gsgd (choco_onepass.h)
   float2* recs;            // tiles x kRecSlots x n: x' and xhat of all workers in the recorded columns
   uint32_t* rec_cols;      // tiles x 8: which columns of the tile are recorded; all bits: the tile was left unmixed
   OnePassState* onepass;
@@ -476,6 +478,9 @@ struct RowScale {
   }
 };
 
+// The dither u in [0, 1) of gsgd_b.
+__device__ __forceinline__ float dither_of(uint32_t word) { return (float)(word >> 8) * (1.0f / 16777216.0f); }
+
 template <int COMP>
 __device__ __forceinline__ float encode(float v, const RowScale<COMP>& sc, uint32_t word, int32_t& code) {
   if (COMP == Q_IDENTITY) { code = 0; return v; }
@@ -487,9 +492,8 @@ __device__ __forceinline__ float encode(float v, const RowScale<COMP>& sc, uint3
   // gsgd_b: level = floor(s |v| / ||v||_2 + u), value = sig(v) * level * ||v||_2 / (tau s)
   int32_t level = 0;
   if (sc.nonzero) {
-    const float u = (float)(word >> 8) * (1.0f / 16777216.0f);
     const float a = fabsf(v) * sc.r;
-    level = (int32_t)floorf(a + u);
+    level = (int32_t)floorf(a + dither_of(word));
   }
   const float mag = (float)level * sc.step;
   code = neg ? -level : level;
@@ -548,6 +552,20 @@ __device__ __forceinline__ int line_sharing_tile(int b, int ntiles) {
   return base + ((b & 7) << 2) + ((b >> 3) & 3);
 }
 
+// gsgd: the magnitude of entry e's code as its bit planes hold it.  The level s itself may not fit them (at
+// most four entries of a vector can reach it): such an entry is remembered in the ring beside them.
+__device__ __forceinline__ int32_t magnitude_sent(const Args& A, int r, int e, int lay, int32_t code) {
+  const int32_t maxmag = (1 << A.mb) - 1;
+  const int32_t mag = code < 0 ? -code : code;
+  if (mag <= maxmag) return mag;
+  const int lay_e = (A.nlayers && A.layers_generic) ? layer_holding(A, e) : lay;
+  const int64_t unit = A.nlayers ? (int64_t)r * A.nlayers + lay_e : (int64_t)r;
+  const int32_t base = A.nlayers ? A.layers[lay_e].start : 0;
+  const uint32_t pos = atomicAdd(A.ovf_pos + unit, 1u);
+  A.ovf_ring[unit * kOvfRing + (pos & (uint32_t)(kOvfRing - 1))] = make_uint4(A.t_lo, A.t_hi + 1u, (uint32_t)(e - base), 0u);
+  return maxmag;
+}
+
 // The bits of a wave's 256 codes (four per lane, entries e..e+3 of row r) go to the row's bit
 // planes: eight lanes share a 32-bit word, their nibbles are combined with three lane moves and
 // the first of the eight stores the word.  Every lane of the wave calls this (lanes without
@@ -595,20 +613,10 @@ __device__ __forceinline__ void emit_code_planes(const Args& A, int r, int e, in
     if (writer) P[0] = sw;
   }
   if (COMP == Q_QSGD) {
-    const int32_t maxmag = (1 << A.mb) - 1;
     int32_t mag[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-      mag[c] = code[c] < 0 ? -code[c] : code[c];
-      if (mag[c] > maxmag) {   // the level s itself: at most four entries of a vector can reach it
-        const int lay_c = (A.nlayers && A.layers_generic) ? layer_holding(A, e + c) : lay;
-        const int64_t unit = A.nlayers ? (int64_t)r * A.nlayers + lay_c : (int64_t)r;
-        const int32_t base = A.nlayers ? A.layers[lay_c].start : 0;
-        const uint32_t pos = atomicAdd(A.ovf_pos + unit, 1u);
-        A.ovf_ring[unit * kOvfRing + (pos & (uint32_t)(kOvfRing - 1))] =
-            make_uint4(A.t_lo, A.t_hi + 1u, (uint32_t)(e + c - base), 0u);
-        mag[c] = maxmag;
-      }
+      mag[c] = magnitude_sent(A, r, e + c, lay, code[c]);
     }
     for (int p0 = 0; p0 < A.mb; p0 += 8) {   // eight planes at a time out of one byte per entry
       const uint32_t M = ((uint32_t)(mag[0] >> p0) & 0xFFu) | (((uint32_t)(mag[1] >> p0) & 0xFFu) << 8) |
@@ -752,7 +760,9 @@ __device__ __forceinline__ double wave_level3(const Args& A, int i, int lane) {
 // grid n, block 256.  (A separate launch on purpose: handing the group sums to a
 // "last block" of the producing kernel needs a device-scope fence per block,
 // which on this multi-die part writes back the L2 and cost 8x the pass itself.)
-template <int COMP>
+// ONEPASS (gsgd, choco_onepass.h): also the bound on s / ||v|| for the next step, above this step's value by
+// 2 % and twice the change since the step before.
+template <int COMP, bool ONEPASS = false>
 __global__ __launch_bounds__(256) void k_dense_finalise(Args A) {
   __shared__ double sh[256];
   const int i = blockIdx.x, l = threadIdx.x;
@@ -783,7 +793,14 @@ __global__ __launch_bounds__(256) void k_dense_finalise(Args A) {
   }
   if (l == 0) {
     RowScale<COMP> sc;
-    scales_from_total<COMP>(A, sh[0], sc, A.ctl + i);
+    WorkerCtl* ctl = A.ctl + i;
+    const float before = ctl->scale_r;
+    scales_from_total<COMP>(A, sh[0], sc, ctl);
+    if (ONEPASS) {
+      const float change = before > 0.0f ? fminf(fabsf(sc.r / before - 1.0f), 1.0f) : 0.0f;
+      ctl->bounded_r = ctl->bound_r;
+      ctl->bound_r = sc.r * (1.02f + 2.0f * change);
+    }
   }
 }
 

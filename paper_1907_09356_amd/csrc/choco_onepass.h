@@ -1,22 +1,27 @@
-// top_a of a few workers on long rows in ONE pass over the state (compress-then-mix order, direct form).
+// top_a and gsgd of a few workers on long rows in ONE pass over the state (compress-then-mix order, direct
+// form).
 //
-// The two-pass form reads x, xhat and g for the candidates and, when the threshold of every row is
-// known, reads all three again for the update of xhat and the mix: 28 bytes per entry.  Here one pass
-// does the local update and mixes at once with the kept set that it expects (|v| at or above a threshold
-// predicted from the steps before): 16 bytes per entry.  A column in which some worker has a candidate is
-// recorded (x' after the local update and xhat of all workers); the candidate lists are made from the
-// records, and after the exact select the few columns whose kept set was not the expected one are done
-// again from them:
-//   k_onepass_mix      the pass
-//   k_onepass_list     the candidate lists of the rows out of the records
-//   k_onepass_restore  normally idle; where a row's list turns out not to hold its k largest entries:
+// The two-pass forms read x, xhat and g for the candidates or the norms and, when the threshold or the
+// norm of every row is known, read all three again for the update of xhat and the mix.  But where few
+// entries are sent - the k largest, or those of a long vector whose level is not zero - xhat does not
+// change in most columns, and these can be mixed at once: 16 bytes per entry instead of 28 (top_a) or 32
+// (gsgd).  A column in which some worker may have something to send is recorded (x' after the local
+// update and xhat of all workers) and done again from its record when the row's figure is known.
+//   k_onepass_mix      the pass.  top_a: lists as candidates the entries at or above the guess and mixes
+//                      with those kept that it expects to be (|v| at or above a threshold predicted from
+//                      the steps before).  gsgd: adds up the norms, marks the entries whose level is not
+//                      zero by a bound on s / ||v||
+//   k_onepass_list     top_a: the candidate lists of the rows out of the records
+//   k_onepass_restore  top_a, normally idle; where a row's list turns out not to hold its k largest entries:
 //                      x' and xhat back as they were before the mix, for the fallback and its row scans
-//   (the fallback and the exact select of the two-pass form, on the lists)
-//   k_onepass_finish   the recorded columns against the thresholds; tiles left unmixed as a whole
+//   (top_a: the fallback and the exact select of the two-pass form, on the lists; gsgd: the upper levels of
+//   the norm trees)
+//   k_onepass_finish   top_a: the recorded columns whose kept set is not the expected one; tiles left unmixed
+//   k_onepass_encode   gsgd: the recorded columns; tiles left unmixed; everything where a bound did not hold
 // Every bit of the result is that of the two-pass form.  x' = x_mixed - gamma acc is exact for nearly all
 // entries (acc is formed again from the same xhat); the pass tries it, and records the columns where it
 // is not.  A tile with more than kRecSlots columns to record is left unmixed and done by the last kernel
-// (its candidates go to the lists one by one).
+// (top_a: its candidates go to the lists one by one).
 #pragma once
 
 #include "choco_kernels.h"
@@ -56,11 +61,13 @@ __device__ __forceinline__ bool left_open(uint2 w) { return (w.x & w.y) == 0xFFF
 static_assert(kRecSlots < 64, "two full words of a mask mean an open tile");
 
 // grid ceil(d / 256), block 64 n (wave r: row r), dynamic LDS n x 256 floats.
+template <int COMP>
 __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_mix(Args A) {
   extern __shared__ float tile[];
   __shared__ uint64_t marks[64];   // a byte per lane and wave
+  __shared__ float2 recs[kRecSlots * kOnePassRows];
   const int r = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int tile_no = (int)blockIdx.x;   // (line_sharing_tile: 612 against 604 us at n = 8, d = 28 M)
+  const int tile_no = (int)blockIdx.x;   // (line_sharing_tile: top_a 612 against 604 us at n = 8, d = 28 M)
   const int e = tile_no * kChunk + lane * 4;
   const bool mine = e < A.d;
   const int64_t o = (int64_t)r * A.ld + e;
@@ -74,13 +81,16 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_mix(Args A) {
   }
   const RowSpan span = nbr_span<1, kOnePassRows>(A, r, lane);
   const uint32_t guess = A.ctl[r].guess_key, expect = A.ctl[r].expect_key;
+  const float bound = A.ctl[r].bound_r;
   if (r == 0) marks[lane] = 0u;    // (bytes of rows that there are not)
+  uint4 words = make_uint4(0, 0, 0, 0);
+  if (COMP == Q_QSGD) words = random_words(A, r, (uint32_t)(e >> 2), STREAM_DITHER);
   const RowNbrs nb = nbr_fetch(A, span, lane);
   if (mine && A.G) {
     x = local_update_regs(A, x, g, m);
     if (mom) store4<true>(A.M + o, m);
   }
-  if (A.onepass_first) {           // no threshold to go by: the last kernel does all tiles
+  if (COMP == Q_TOPK && A.onepass_first) {   // no threshold to go by: the last kernel does all tiles
     if (mine && A.G) store4<true>(A.X + o, x);
     return;
   }
@@ -90,15 +100,26 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_mix(Args A) {
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       const float q = x[c] - h[c];
-      const uint32_t key = __float_as_uint(q) & 0x7fffffffu;
-      if (e + c < A.d && key >= guess) {
-        cand |= 1u << c;
-        if (key >= expect) {
-          kept |= 1u << c;
-          hn[c] = h[c] + q;
+      if (COMP == Q_TOPK) {
+        const uint32_t key = __float_as_uint(q) & 0x7fffffffu;
+        if (e + c < A.d && key >= guess) {
+          cand |= 1u << c;
+          if (key >= expect) {
+            kept |= 1u << c;
+            hn[c] = h[c] + q;
+          }
         }
+      } else {
+        // (rounding is monotonic: no level is above zero that is not by the larger factor; and adding
+        // the zero that a level of zero stands for changes an xhat of -0)
+        if (e + c < A.d && (fabsf(q) * bound + dither_of(pick(words, c)) >= 1.0f || __float_as_uint(h[c]) == 0x80000000u))
+          cand |= 1u << c;
       }
     }
+  }
+  if (COMP == Q_QSGD) {
+    const double t = wave_tree_sum(mine ? lane_terms<Q_QSGD>(x - h, e, A.d) : 0.0);
+    if (lane == 0) A.chunk_sums[(int64_t)r * A.nchunks + tile_no] = t;
   }
   lds_store4(tile + r * kChunk + lane * 4, hn);
   __syncthreads();
@@ -127,7 +148,8 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_mix(Args A) {
   const bool open = total > kRecSlots;     // the same in every wave
   if (mine) {
     store4<true>(A.X + o, open ? x : xm);
-    if (kept && !open) store4<false>(A.Xhat + o, hn);
+    if (COMP == Q_TOPK && kept && !open) store4<false>(A.Xhat + o, hn);
+    if (COMP == Q_QSGD && A.codes) *reinterpret_cast<vi4*>(A.codes + o) = vi4{0, 0, 0, 0};
   }
   if (r == 0) {
     const uint32_t w = mask_word(open ? 0xFu : dirty, lane);
@@ -137,7 +159,7 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_mix(Args A) {
   if (open) {
 #pragma unroll
     for (int c = 0; c < 4; ++c)
-      if ((cand >> c) & 1u) {
+      if (COMP == Q_TOPK && ((cand >> c) & 1u)) {
         const int seg = tile_no % kSegs;
         const uint32_t at = atomicAdd(seg_counter(A, r, seg), 1u);
         if (at < A.seg_cap)
@@ -150,8 +172,12 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_mix(Args A) {
     for (int c = 0; c < 4; ++c) slot += __popcll(db[c] & below);
 #pragma unroll
     for (int c = 0; c < 4; ++c)
-      if ((dirty >> c) & 1u) record_of(A, tile_no, slot++)[r] = make_float2(x[c], h[c]);
+      if ((dirty >> c) & 1u) recs[slot++ * A.n + r] = make_float2(x[c], h[c]);
   }
+  if (open) return;
+  // (by way of LDS, whole records at a time: 616 against 623 us for gsgd at n = 8, d = 28 M, top_a 602 against 607)
+  __syncthreads();
+  for (int j = threadIdx.x; j < total * A.n; j += (int)blockDim.x) record_of(A, tile_no, 0)[j] = recs[j];
 }
 
 // The marked columns of the kRecTiles tiles from t0 on, to LDS as (tile of the sixteen x slots + slot,
@@ -204,6 +230,43 @@ __device__ __forceinline__ Recorded recorded(const Args& A, int t0, const ushort
   return R;
 }
 
+// Eight lanes to a record, lane i of them for worker i, with its row of W in registers.
+struct RecordLanes {
+  int i, grp, lane, deg;
+  uint32_t near;      // the workers that this one mixes with, itself among them
+  bool row;
+  int nc[kOnePassRows];
+  float nw[kOnePassRows];
+  __device__ __forceinline__ RecordLanes(const Args& A, int lane_) : i(lane_ & 7), grp(lane_ >> 3), lane(lane_) {
+    row = i < A.n;
+    const int pbeg = row ? A.row_ptr[i] : 0;
+    deg = row ? A.row_ptr[i + 1] - pbeg : 0;
+    near = 0;
+#pragma unroll
+    for (int j = 0; j < kOnePassRows; ++j) {
+      nc[j] = j < deg ? A.col[pbeg + j] : 0;
+      nw[j] = j < deg ? A.w[pbeg + j] : 0.0f;
+      if (j < deg) near |= 1u << nc[j];
+    }
+  }
+  // Does x of the lane's worker change with these lanes' xhat?  (A worker none of whose neighbours sent
+  // anything else than the pass went by has its x already: on a ring five of eight, and the scattered
+  // stores are what the last kernel takes its time for.)
+  __device__ __forceinline__ bool concerned(uint64_t lanes) const {
+    return (((uint32_t)(lanes >> (lane & ~7))) & near) != 0u;
+  }
+  // sum_p w_p (xhat_j - xhat_i) in a record whose lanes hold xhat; all lanes of the wave call it
+  __device__ __forceinline__ float mix_sum(float h) const {
+    float acc = 0.0f;
+#pragma unroll
+    for (int j = 0; j < kOnePassRows; ++j) {
+      const float other = __shfl(h, (lane & ~7) + nc[j], 64);
+      if (j < deg) acc = acc + nw[j] * (other - h);
+    }
+    return acc;
+  }
+};
+
 // The candidates among the recorded entries, to the rows' lists: each wave counts those of its sixteen
 // tiles row by row, takes room with one addition per row and writes them.  grid any, block 256.
 __global__ __launch_bounds__(256) void k_onepass_list(Args A, int32_t ntiles) {
@@ -246,6 +309,42 @@ __global__ __launch_bounds__(256) void k_onepass_list(Args A, int32_t ntiles) {
   }
 }
 
+// x' and xhat of the lane's 4-vector as they were before k_onepass_mix mixed tile t (not an open one).  All
+// waves of the workgroup call it, one row each; the LDS tile holds the old xhat afterwards.
+__device__ __forceinline__ void take_back(const Args& A, float* tile, int t, int r, int lane, const RowNbrs& nb, vf4& x,
+                                          vf4& h, bool& recorded_here) {
+  const int e = t * kChunk + lane * 4;
+  const bool mine = e < A.d;
+  const int64_t o = (int64_t)r * A.ld + e;
+  const uint32_t dirty = (A.rec_cols[(int64_t)t * 8 + (lane >> 3)] >> (4 * (lane & 7))) & 0xFu;
+  int slot = 0;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) slot += __popcll(__ballot((dirty >> c) & 1u) & ((1ull << lane) - 1ull));
+  vf4 xr = {0.f, 0.f, 0.f, 0.f};
+  x = h = xr;
+  if (mine) {
+    x = load4<true>(A.X + o);
+    h = load4<true>(A.Xhat + o);
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+      if ((dirty >> c) & 1u) {
+        const float2 v = record_of(A, t, slot++)[r];
+        xr[c] = v.x;
+        h[c] = v.y;
+      }
+  }
+  recorded_here = mine && dirty != 0u;
+  __syncthreads();                       // what the tile held before has been read
+  lds_store4(tile + r * kChunk + lane * 4, h);
+  __syncthreads();
+  const vf4 acc = mix_sum_staged<0>(A, tile, r, lane, nb);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const float step = A.gamma * acc[c];
+    x[c] = ((dirty >> c) & 1u) ? xr[c] : x[c] - step;
+  }
+}
+
 // Do all lists hold their row's k largest entries?  If not, what k_onepass_mix did to x and xhat is
 // undone, tile by tile, so that X is x' everywhere.  Normally a launch of workgroups that read the
 // lists' lengths and leave.  grid any, block 64 n, dynamic LDS n x 256 floats.
@@ -269,37 +368,12 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_restore(Args A, i
     const uint32_t* cols = A.rec_cols + (int64_t)t * 8;
     if (left_open(make_uint2(cols[0], cols[1]))) continue;
     const int e = t * kChunk + lane * 4;
-    const bool mine = e < A.d;
     const int64_t o = (int64_t)r * A.ld + e;
-    vf4 x = {0.f, 0.f, 0.f, 0.f}, h = x, xr = x;
-    const uint32_t dirty = (cols[lane >> 3] >> (4 * (lane & 7))) & 0xFu;
-    int slot = 0;
-#pragma unroll
-    for (int c = 0; c < 4; ++c) slot += __popcll(__ballot((dirty >> c) & 1u) & ((1ull << lane) - 1ull));
-    if (mine) {
-      x = load4<true>(A.X + o);
-      h = load4<true>(A.Xhat + o);
-#pragma unroll
-      for (int c = 0; c < 4; ++c)
-        if ((dirty >> c) & 1u) {
-          const float2 v = record_of(A, t, slot++)[r];
-          xr[c] = v.x;
-          h[c] = v.y;
-        }
-      if (dirty) store4<false>(A.Xhat + o, h);
-    }
-    __syncthreads();                       // the tile of the round before has been read
-    lds_store4(tile + r * kChunk + lane * 4, h);
-    __syncthreads();
-    const vf4 acc = mix_sum_staged<0>(A, tile, r, lane, nb);
-    if (mine) {
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const float step = A.gamma * acc[c];
-        x[c] = ((dirty >> c) & 1u) ? xr[c] : x[c] - step;
-      }
-      store4<true>(A.X + o, x);
-    }
+    vf4 x, h;
+    bool changed;
+    take_back(A, tile, t, r, lane, nb, x, h, changed);
+    if (changed) store4<false>(A.Xhat + o, h);
+    if (e < A.d) store4<true>(A.X + o, x);
   }
 }
 
@@ -348,19 +422,9 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_finish(Args A, in
     }
     if (all) return;
   }
-  // eight lanes to a record, lane i of them for worker i; W's row in registers
-  const int i = lane & 7, grp = lane >> 3;
-  const bool row = i < A.n;
-  const uint64_t kstar = A.ctl[row ? i : 0].kstar;
-  const uint32_t expected = A.ctl[row ? i : 0].expected_key;
-  const int pbeg = row ? A.row_ptr[i] : 0, deg = row ? A.row_ptr[i + 1] - pbeg : 0;
-  int nc[kOnePassRows];
-  float nw[kOnePassRows];
-#pragma unroll
-  for (int j = 0; j < kOnePassRows; ++j) {
-    nc[j] = j < deg ? A.col[pbeg + j] : 0;
-    nw[j] = j < deg ? A.w[pbeg + j] : 0.0f;
-  }
+  const RecordLanes L(A, lane);
+  const uint64_t kstar = A.ctl[L.row ? L.i : 0].kstar;
+  const uint32_t expected = A.ctl[L.row ? L.i : 0].expected_key;
   const int waves = (int)(blockDim.x >> 6), nwaves = (int)gridDim.x * waves;
   for (int t0 = ((int)blockIdx.x * waves + r) * kRecTiles; t0 < ntiles; t0 += nwaves * kRecTiles) {
     const uint32_t total = list_marked(A, t0, ntiles, lists[r]);
@@ -368,7 +432,7 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_finish(Args A, in
     for (uint32_t f0 = 0; f0 < total; f0 += 8 * U) {
       Recorded R[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) R[u] = recorded(A, t0, lists[r], f0 + 8u * u + (uint32_t)grp, total, i);
+      for (int u = 0; u < U; ++u) R[u] = recorded(A, t0, lists[r], f0 + 8u * u + (uint32_t)L.grp, total, L.i);
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const float q = R[u].x - R[u].h;
@@ -378,17 +442,131 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_finish(Args A, in
         const uint64_t wrong = __ballot(now != was);
         if (wrong != 0ull) {                                    // (every lane takes part in the exchange)
           const float hn = now ? R[u].h + q : R[u].h;
-          float acc = 0.0f;
-#pragma unroll
-          for (int j = 0; j < kOnePassRows; ++j) {
-            const float oth = __shfl(hn, (lane & ~7) + nc[j], 64);
-            if (j < deg) acc = acc + nw[j] * (oth - hn);
-          }
-          if (R[u].have && ((wrong >> (lane & ~7)) & 0xFFull) != 0ull) {
-            const int64_t o = (int64_t)i * A.ld + R[u].col;
+          const float acc = L.mix_sum(hn);
+          if (R[u].have && L.concerned(wrong)) {
+            const int64_t o = (int64_t)L.i * A.ld + R[u].col;
             A.X[o] = R[u].x + A.gamma * acc;
             if (now != was) A.Xhat[o] = hn;
           }
+        }
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+
+// Zeros to the bit planes of the kRecTiles tiles from t0 on, but for open ones: a piece of 512 bytes per row
+// and plane, two lanes to a tile.  (32 bytes per row, plane and tile out of k_onepass_mix
+// made that kernel 75 us longer at n = 8, d = 28 M, five planes; here they take 37.)  The words belong to this wave alone
+// until the kernel's end, so its bits need no more than the order among its own accesses.
+__device__ __forceinline__ void clear_planes(const Args& A, int t0, int ntiles, int lane) {
+  typedef uint32_t words4 __attribute__((ext_vector_type(4), aligned(4)));   // (a plane may have any number of words)
+  const int t = t0 + ((lane & 31) >> 1);
+  if (t >= ntiles) return;
+  const uint32_t* cols = A.rec_cols + (int64_t)t * 8;
+  if (left_open(make_uint2(cols[0], cols[1]))) return;
+  const int64_t word = (int64_t)t * 8 + 4 * (lane & 1), left = ((int64_t)A.d + 31) / 32 - word;
+  for (int q = lane >> 5; q < A.n * A.nplanes; q += 2) {
+    uint32_t* P = A.planes + (int64_t)q * A.plane_words + word;
+    if (left >= 4) *reinterpret_cast<words4*>(P) = words4{0u, 0u, 0u, 0u};
+    else
+      for (int j = 0; j < left; ++j) P[j] = 0u;
+  }
+}
+__device__ __forceinline__ void set_bits(uint32_t* word, uint32_t bits) {
+  (void)__hip_atomic_fetch_or(word, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// gsgd: the scales of every row are known.  Levels, xhat and bit planes of the recorded entries, and the mix
+// of the columns in which a level is not zero.  Tiles left unmixed are done as a whole; all tiles are where
+// the factor s / ||v|| came out above the bound that the pass went by, or ||v|| beyond fp32 (then even a
+// level of zero has a value).  grid any, block 64 n, dynamic LDS n x 256 floats.
+__global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_encode(Args A, int32_t ntiles) {
+  extern __shared__ float tile[];
+  __shared__ ushort2 lists[kOnePassRows][kRecTiles * kRecSlots];
+  const int r = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  bool all = false;
+  for (int j = 0; j < A.n; ++j)
+    all = all || !(A.ctl[j].scale_r <= A.ctl[j].bounded_r) || !(A.ctl[j].scale_step <= 3.402823466e38f);
+  if (all || A.onepass->open_step == A.t_lo) {
+    const RowNbrs nb = nbr_fetch(A, nbr_span<1, kOnePassRows>(A, r, lane), lane);
+    RowScale<Q_QSGD> sc;
+    sc.load(A.ctl + r);
+    for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
+      const uint32_t* cols = A.rec_cols + (int64_t)t * 8;
+      const bool open = left_open(make_uint2(cols[0], cols[1]));
+      if (!all && !open) continue;
+      const int e = t * kChunk + lane * 4;
+      const bool mine = e < A.d;
+      const int64_t o = (int64_t)r * A.ld + e;
+      vf4 x = {0.f, 0.f, 0.f, 0.f}, h = x;
+      if (!open) {
+        bool changed;
+        take_back(A, tile, t, r, lane, nb, x, h, changed);
+      } else if (mine) {
+        x = load4<true>(A.X + o);
+        h = load4<true>(A.Xhat + o);
+      }
+      vf4 nh = h;
+      vi4 code = {0, 0, 0, 0};
+      if (mine) {
+        nh = absorb<Q_QSGD>(x, h, sc, random_words(A, r, (uint32_t)(e >> 2), STREAM_DITHER), code);
+        mask_padding(A.d - e < 4 ? A.d - e : 4, h, nh, code);
+        store4<true>(A.Xhat + o, nh);
+        if (A.codes) *reinterpret_cast<vi4*>(A.codes + o) = code;
+      }
+      emit_code_planes<Q_QSGD>(A, r, e, lane, code, 0);
+      __syncthreads();
+      lds_store4(tile + r * kChunk + lane * 4, nh);
+      __syncthreads();
+      const vf4 acc = mix_sum_staged<0>(A, tile, r, lane, nb);
+      if (mine) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) x[c] = x[c] + A.gamma * acc[c];
+        store4<true>(A.X + o, x);
+      }
+    }
+    if (all) return;
+  }
+  const RecordLanes L(A, lane);
+  RowScale<Q_QSGD> sc;
+  sc.load(A.ctl + (L.row ? L.i : 0));
+  const int waves = (int)(blockDim.x >> 6), nwaves = (int)gridDim.x * waves;
+  for (int t0 = ((int)blockIdx.x * waves + r) * kRecTiles; t0 < ntiles; t0 += nwaves * kRecTiles) {
+    clear_planes(A, t0, ntiles, lane);
+    const uint32_t total = list_marked(A, t0, ntiles, lists[r]);
+    constexpr int U = 4;       // records of a group in flight
+    for (uint32_t f0 = 0; f0 < total; f0 += 8 * U) {
+      Recorded R[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) R[u] = recorded(A, t0, lists[r], f0 + 8u * u + (uint32_t)L.grp, total, L.i);
+      if (f0 == 0) __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");   // the zeros before the bits
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        int32_t code = 0;
+        float hn = R[u].h;
+        if (R[u].have) {
+          const uint4 words = random_words(A, L.i, (uint32_t)R[u].col >> 2, STREAM_DITHER);
+          hn = R[u].h + encode<Q_QSGD>(R[u].x - R[u].h, sc, pick(words, R[u].col & 3), code);
+        }
+        const bool changed = __float_as_uint(hn) != __float_as_uint(R[u].h);
+        const uint64_t any = __ballot(changed);
+        if (any == 0ull) continue;                               // (every lane takes part in the exchange)
+        const float acc = L.mix_sum(hn);
+        if (R[u].have && L.concerned(any)) {
+          const int64_t o = (int64_t)L.i * A.ld + R[u].col;
+          A.X[o] = R[u].x + A.gamma * acc;
+          if (changed) A.Xhat[o] = hn;
+        }
+        if (code != 0) {
+          if (A.codes) A.codes[(int64_t)L.i * A.ld + R[u].col] = code;
+          const uint32_t bit = 1u << (R[u].col & 31);
+          uint32_t* P = A.planes + (int64_t)L.i * A.nplanes * A.plane_words + ((uint32_t)R[u].col >> 5);
+          if (code < 0) set_bits(P, bit);
+          const int32_t mag = magnitude_sent(A, L.i, R[u].col, 0, code);
+          for (int p = 0; p < A.mb; ++p)
+            if ((mag >> p) & 1) set_bits(P + (int64_t)(1 + p) * A.plane_words, bit);
         }
       }
     }

@@ -1,4 +1,4 @@
-"""top_a in one pass over the state: every bit as the oracle has it, also where the pass went by a wrong
+"""top_a and gsgd in one pass over the state: every bit as the oracle has it, also where the pass went by a wrong
 threshold, left tiles unmixed, could not take its mix back without the records, or has to be undone."""
 import numpy as np
 import pytest
@@ -38,6 +38,30 @@ for name, n, d, kw in (
         else:
             assert not any(x.startswith("k_onepass") for x in a + b), name
     assert out["odd"][2] == ["12501x1x1", "512x1x1"] and out["n2"][2][1] == "128x1x1"
+
+
+def test_where_gsgd_takes_one_pass():
+    """Two to eight workers, whole vectors in the default order, more than 96 MiB per array, few levels above zero."""
+    out = recorded("""
+out = {}
+D = 3_200_000
+for name, n, d, kw in (
+        ("n8", 8, D, {}), ("n8 momentum", 8, D, {}), ("n2", 2, 4 * D + 1, dict(levels=64)), ("n9", 9, D, {}), ("n1", 1, 8 * D, {}),
+        ("96 MiB", 8, 96 * 2**20 // 32, {}), ("printed", 8, D, dict(order=1)), ("levels", 8, D, dict(levels=16)),
+        ("layers", 8, D, dict(layers=synth.layer_table([D // 2, D // 2])))):
+    c = Context(n, d, B.Q_QSGD, **{"levels": 8, **kw})
+    first = c.step()
+    l = c.step_momentum() if "momentum" in name else c.step()
+    out[name] = [[x[0].split("<")[0] for x in y] for y in (first, l)]
+    c.close()
+""")
+    for name, (first, later) in out.items():
+        assert not any(x.startswith("k_onepass") for x in first), name     # no norm to go by yet
+        if name in ("n8", "n8 momentum", "n2"):
+            assert first == ["k_dense_stat", "k_dense_finalise", "k_dense_apply_mix"], name
+            assert later == ["k_onepass_mix", "k_group_reduce", "k_dense_finalise", "k_onepass_encode"], name
+        else:
+            assert later == first, name
 
 
 def graph(name, n):
@@ -106,5 +130,62 @@ def test_one_pass_taken_back():
         pair.ref.X[:] = pair.ref.Xhat + np.round(X0 * 4) / np.float32(4)
         pair.force_state()
         steps(pair, grads, 0.0, "step", 2, "ties")
+    finally:
+        pair.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("n,d,levels,topo,mode,align,outlier", [
+    (8, 3_200_001, 8, "ring", "step", 4, False),
+    (7, 3_700_255, 4, "complete", "momentum", 64, False),
+    (3, 8_500_003, 16, "ring", "halves", 4, False),
+    (2, 12_800_000, 64, "ring", "step", 4, False),
+    (8, 3_200_000, 8, "ring", "step", 4, True),      # one entry carries a row's norm: the level s itself
+])
+def test_one_pass_gsgd(n, d, levels, topo, mode, align, outlier):
+    X0 = synth.normal_state(n, d, seed=n)
+    X0[:, 70_000:70_400] *= 100.0                    # tiles with more columns to record than there are slots
+    if outlier:
+        X0[2, 12_345], X0[0, d - 1] = 3e6, -5e5
+    pair = Pair(X0, graph(topo, n) if n > 2 else synth.complete_csr(2), 0.3, compressor=B.Q_QSGD, levels=levels, seed=9,
+                ld_align=align)
+    try:
+        steps(pair, synth.GradientStream(n, d, seed=2), 0.05, mode, 4, mode)
+        msgs = pair.gpu.pack_messages()              # the bit planes that the last step left
+        q = pair.gpu.unpack_messages(msgs)[:, :d].cpu().numpy()
+        codes = pair.codes[:, :d].cpu().numpy()
+        assert np.array_equal(np.sign(q), np.sign(codes))
+        assert not outlier or np.abs(codes).max() == levels
+    finally:
+        pair.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.timeout(300)
+def test_one_pass_gsgd_taken_back():
+    """Norms that shrink between two steps, of all workers or of one, beyond the bound that the pass went by; xhat of
+    its own in some columns of every tile (no exact inverse of the mix) and an xhat of minus zero."""
+    n, d = 8, 3_200_100
+    rng = np.random.default_rng(5)
+    pair = Pair(synth.normal_state(n, d, seed=3), synth.ring_csr(n), 0.7, compressor=B.Q_QSGD, levels=4, seed=2)
+    grads = synth.GradientStream(n, d, seed=4)
+    try:
+        steps(pair, grads, 0.05, "step", 2, "start")
+        for where in (slice(7, d, 256), slice(100, d, 256), slice(100_000, 120_000)):
+            pair.ref.Xhat[:, where] = pair.ref.X[:, where] + 1e-3 * rng.standard_normal(pair.ref.X[:, where].shape).astype(np.float32)
+        pair.ref.Xhat[:, 200_000:200_010] = -0.0
+        pair.force_state()
+        steps(pair, grads, 0.05, "step", 2, "lost")
+        pair.ref.X[:] = pair.ref.Xhat + (pair.ref.X - pair.ref.Xhat) * np.float32(0.1)
+        pair.force_state()
+        steps(pair, grads, 1e-6, "step", 2, "shrunk")
+        pair.ref.X[3] = pair.ref.Xhat[3] + (pair.ref.X[3] - pair.ref.Xhat[3]) * np.float32(0.5)
+        pair.force_state()
+        steps(pair, grads, 1e-6, "step", 2, "one row")
+        pair.ref.X[:] = pair.ref.Xhat                # nothing to send: a norm of zero, and one again after it
+        pair.force_state()
+        steps(pair, grads, 0.0, "step", 1, "zero")
+        steps(pair, grads, 0.05, "step", 2, "again")
     finally:
         pair.close()
