@@ -99,6 +99,7 @@ struct choco_ctx {
   bool fused_sparse_apply;   // ... whose update of xhat rides on the tile mix pass (direct form, compress-then-mix)
   bool one_pass;          // top_a, gsgd: one pass over the state (choco_onepass.h)
   bool one_pass_begun;    // ... and has taken a step (later ones have a threshold or a norm to go by)
+  bool short_rows;        // top_a: a workgroup selects a row out of its registers
   bool values_in_qv;      // random_a after such a step: the kept values are in Qv, not yet in the list
   int mix_form;           // resolved: CHOCO_MIX_INCREMENTAL_S or CHOCO_MIX_DIRECT
   bool tile_fits;         // the LDS tile of all rows exists (up to kMaxTileRows workers)
@@ -356,6 +357,18 @@ bool one_pass_topk(const choco_config& c) {
   return mib > 96.0 && marked <= (mib < 160.0 ? 8.0 : 16.0);
 }
 
+// top_a on rows that a workgroup selects out of its registers (k_row_compress)?  It saves a launch and the
+// way of the candidates through memory; the entries of a thread are worked through in turn, and every kept
+// one is marked in the map by an atomic.  us per step, candidate pass and select | out of registers:
+//   n = 8   d = 500 16.2 | 9.7   4,096, k = 41 16.7 | 12.1   6,000, k = 300 17.2 | 14.1   8,192, k = 81 17.0 | 14.5
+//           10,240, k = 10 16.6 | 14.4   k = 512 17.4 | 19.5
+//   n = 64  d = 1,000 18.0 | 13.0   4,096, k = 204 18.9 | 15.5   6,000, k = 300 19.6 | 18.0
+//           8,192, k = 81 18.4 | 17.4   k = 409 19.4 | 21.4
+bool short_rows(const choco_config& c) {
+  if (c.compressor != CHOCO_Q_TOPK || c.nlayers > 0 || !fused_sparse_apply(c)) return false;
+  return c.d <= 6144 || (c.d <= 8192 && c.k <= 80);
+}
+
 // gsgd in one pass over the state?  The entries whose level is not zero must be few: s ||v||_1 / ||v||_2 of a
 // row, 0.8 s sqrt(d) of a Gaussian one (at most a quarter more).  us per step, two passes | one (marked
 // columns of a tile expected):
@@ -483,7 +496,7 @@ Layout make_layout(const choco_config& c, int32_t nnz) {
   L.small_list = take(L.small_list_bytes * (size_t)L.select_sets);
   // kept entries: a bitmap per worker if it fits in the (single-block) select's LDS (40 KiB
   // beside its other arrays), else a bit per entry in global memory
-  L.bitmap_words = (guessed && !layered && !L.multipart && c.d <= 40 * 1024 * 8) ? (c.d + 31) / 32 : 0;
+  L.bitmap_words = (guessed && !layered && !L.multipart && !short_rows(c) && c.d <= 40 * 1024 * 8) ? (c.d + 31) / 32 : 0;
   const size_t map_bytes = (size_t)c.n * (size_t)((ld + 31) / 32) * sizeof(uint32_t);   // a bit per entry
   const bool one_pass = one_pass_topk(c) || one_pass_qsgd(c);
   L.keptmap = take(sparse && !L.bitmap_words && !one_pass ? map_bytes : 0);
@@ -697,7 +710,7 @@ int join_lookahead(choco_ctx* ctx) {
 enum KernelId {
   KID_SGD, KID_MOMENTUM, KID_DENSE_STAT, KID_GROUP_REDUCE, KID_DENSE_FINALISE, KID_DENSE_APPLY_MIX, KID_TILE_MIX,
   KID_DENSE_APPLY, KID_MIX_DIRECT_GLOBAL, KID_MIX_INCREMENTAL, KID_SEL_COMPACT, KID_SEL_FALLBACK,
-  KID_SEL_REFINE, KID_SCATTER_S, KID_XHAT_UPDATE, KID_GATHER_VALUES, KID_SEL_VALUES, KID_SEL_HIST_PARTS, KID_SEL_EMIT_PARTS, KID_SEL_FINISH, KID_DENSE_STAT_SGD, KID_DENSE_STAT_REDO, KID_DENSE_APPLY_MIX_SGD, KID_SEL_COMPACT_SGD, KID_SEL_COMPACT_REDO, KID_TILE_MIX_SGD, KID_MIX_INCREMENTAL_SGD, KID_LAYER_COMPRESS, KID_LAYER_COMPRESS_SGD, KID_LAYER_STAT, KID_LAYER_STAT_SGD, KID_LAYER_STAT_REDO, KID_LAYER_FINALISE, KID_WIRE, KID_ZERO_WORDS, KID_ONEPASS_MIX, KID_ONEPASS_MIX_SGD, KID_ONEPASS_LIST, KID_ONEPASS_RESTORE, KID_ONEPASS_FINISH, KID_ONEPASS_ENCODE, KID_COUNT
+  KID_SEL_REFINE, KID_SCATTER_S, KID_XHAT_UPDATE, KID_GATHER_VALUES, KID_SEL_VALUES, KID_SEL_HIST_PARTS, KID_SEL_EMIT_PARTS, KID_SEL_FINISH, KID_DENSE_STAT_SGD, KID_DENSE_STAT_REDO, KID_DENSE_APPLY_MIX_SGD, KID_SEL_COMPACT_SGD, KID_SEL_COMPACT_REDO, KID_TILE_MIX_SGD, KID_MIX_INCREMENTAL_SGD, KID_LAYER_COMPRESS, KID_LAYER_COMPRESS_SGD, KID_LAYER_STAT, KID_LAYER_STAT_SGD, KID_LAYER_STAT_REDO, KID_LAYER_FINALISE, KID_WIRE, KID_ZERO_WORDS, KID_ONEPASS_MIX, KID_ONEPASS_MIX_SGD, KID_ONEPASS_LIST, KID_ONEPASS_RESTORE, KID_ONEPASS_FINISH, KID_ONEPASS_ENCODE, KID_ROW_COMPRESS, KID_ROW_COMPRESS_SGD, KID_COUNT
 };
 const char* const kKernelNames[KID_COUNT] = {
   "k_sgd", "k_momentum", "k_dense_stat", "k_group_reduce", "k_dense_finalise", "k_dense_apply_mix", "k_tile_mix",
@@ -705,7 +718,7 @@ const char* const kKernelNames[KID_COUNT] = {
   "k_sel_refine", "k_scatter_s", "k_xhat_update", "k_gather_values", "k_sel_values", "k_sel_hist_parts", "k_sel_emit_parts", "k_sel_finish",
   "k_dense_stat_sgd", "k_dense_stat_redo", "k_dense_apply_mix_sgd", "k_sel_compact_sgd", "k_sel_compact_redo", "k_tile_mix_sgd", "k_mix_incremental_sgd",
   "k_layer_compress", "k_layer_compress_sgd", "k_layer_stat", "k_layer_stat_sgd", "k_layer_stat_redo", "k_layer_finalise", "k_wire",
-  "k_zero_words", "k_onepass_mix", "k_onepass_mix_sgd", "k_onepass_list", "k_onepass_restore", "k_onepass_finish", "k_onepass_encode"};
+  "k_zero_words", "k_onepass_mix", "k_onepass_mix_sgd", "k_onepass_list", "k_onepass_restore", "k_onepass_finish", "k_onepass_encode", "k_row_compress", "k_row_compress_sgd"};
 constexpr size_t kMaxProfiledLaunches = 16384;
 
 // Brackets one launch with two events when profiling is on (no-op otherwise).
@@ -1224,7 +1237,14 @@ int gossip_sparse(choco_ctx* ctx, const Args& F) {
     const int rc = look_ahead_begin(ctx, A, ahead, &selected);
     if (rc != CHOCO_OK) return rc;
   }
-  if (!selected) launch_select<COMP, NT>(ctx, C, A, kid_compact, fuse_mix);
+  if (COMP == Q_TOPK && ctx->short_rows) {
+    const int kid = C.G ? KID_ROW_COMPRESS_SGD : KID_ROW_COMPRESS;
+    // (a wave up to 768 entries: n = 8, d = 500 9.7 us per step, with 1024 threads 10.5)
+    if (A.d <= kWaveLayerLen) LAUNCH(ctx, kid, k_row_compress<64>, dim3((unsigned)A.n), dim3(64), 0, C);
+    else LAUNCH(ctx, kid, k_row_compress<1024>, dim3((unsigned)A.n), dim3(1024), 0, C);
+  } else if (!selected) {
+    launch_select<COMP, NT>(ctx, C, A, kid_compact, fuse_mix);
+  }
   const bool due = look_ahead_due(ctx, ahead);
   if (due) {
     const int rc = look_ahead_mark(ctx);
@@ -1762,6 +1782,7 @@ int choco_init(const choco_config* cfg, float* x_dev, void* workspace_dev, size_
   ctx->fused_sparse_apply = fused_sparse_apply(*cfg);
   ctx->one_pass = one_pass_topk(*cfg) || one_pass_qsgd(*cfg);
   ctx->one_pass_begun = false;
+  ctx->short_rows = short_rows(*cfg);
   ctx->values_in_qv = false;
   ctx->tile_fits = cfg->n <= kMaxTileRows;
   ctx->plan = SelectPlan{};

@@ -100,9 +100,11 @@ struct LayerShared {
   uint2* list;        // (key, index in the layer) of the keys in the bracket
 };
 
-template <int COMP, int THREADS, bool NT>
+// WHOLE: the layer is the whole vector of a configuration without layers; its guess and its figures are in
+// the worker's control block.
+template <int COMP, int THREADS, bool NT, bool WHOLE = false>
 __device__ __forceinline__ void layer_body(const Args& A, const int i, const LayerDesc L, const int tid,
-                                           const LayerShared sh) {
+                                           const LayerShared sh, unsigned long long* sh_kstar = nullptr) {
   static_assert(COMP == Q_TOPK || COMP == Q_RANDK, "sign and gsgd layers go through k_layer_stat");
   constexpr int NW = THREADS / 64;
   constexpr int kBatch = kLayerVecs;   // 4-vectors per thread whose loads are in flight together
@@ -116,7 +118,7 @@ __device__ __forceinline__ void layer_body(const Args& A, const int i, const Lay
   const int nit = (nvec + THREADS - 1) / THREADS;   // sweeps of the threads over the layer (<= kLayerVecs)
   const int lane = tid & 63, wave = tid >> 6;
   const int64_t row = (int64_t)i * A.ld + base;
-  double* scal = A.layer_scal + ((int64_t)i * A.nlayers + L.id) * 4;
+  double* scal = WHOLE ? nullptr : A.layer_scal + ((int64_t)i * A.nlayers + L.id) * 4;
   float* __restrict__ X = A.X;
   float* __restrict__ Xhat = A.Xhat;
   const float* __restrict__ G = A.G;
@@ -124,6 +126,7 @@ __device__ __forceinline__ void layer_body(const Args& A, const int i, const Lay
   if (tid == 0) {
     *sh.emit = 0;
     *sh.list_n = 0;
+    if (WHOLE) *sh_kstar = ~0ull;
   }
   layer_sync<THREADS>();   // no wave may count into the list before it is reset (waves start in any order)
 
@@ -181,7 +184,7 @@ __device__ __forceinline__ void layer_body(const Args& A, const int i, const Lay
   {
     // ---- top_a / random_a: exact k-th largest key ----
     const uint32_t k = (uint32_t)L.k;
-    if (k == 0) {
+    if (!WHOLE && k == 0) {
       if (tid == 0) scal[0] = scal[1] = scal[2] = scal[3] = 0.0;
       return;
     }
@@ -190,7 +193,7 @@ __device__ __forceinline__ void layer_body(const Args& A, const int i, const Lay
       else return __float_as_uint(v[it][c]) & 0x7FFFFFFFu;
     };
     constexpr int TOPBIT = COMP == Q_RANDK ? 31 : 30;
-    uint32_t* guess = A.layer_guess + (int64_t)i * A.nlayers + L.id;
+    uint32_t* guess = WHOLE ? &A.ctl[i].guess_key : A.layer_guess + (int64_t)i * A.nlayers + L.id;
     // a bracket that should hold the k-th largest key
     bool have = true;
     uint32_t lo, hi;
@@ -338,7 +341,7 @@ __device__ __forceinline__ void layer_body(const Args& A, const int i, const Lay
       equals = block_total<THREADS>(equals, sh.cnt, phase);
     }
     const uint32_t need = k - above;
-    if (tid == 0) {
+    if (!WHOLE && tid == 0) {
       scal[0] = (double)T;
       scal[1] = (double)need;
       scal[2] = (double)equals;
@@ -347,6 +350,7 @@ __device__ __forceinline__ void layer_body(const Args& A, const int i, const Lay
     const bool ties = equals > need;   // uniform over the layer's threads
     uint32_t running = 0;              // threshold-key entries in earlier sweeps (index order)
     uint32_t emitted = 0;              // one wave per layer: kept entries handed out so far
+    uint64_t least = ~0ull;            // WHOLE: the last of the lane's kept entries in the order of the selection
 #pragma unroll
     for (int it = 0; it < kLayerVecs; ++it) {
       if (it < nit) {
@@ -388,6 +392,8 @@ __device__ __forceinline__ void layer_body(const Args& A, const int i, const Lay
             keep = !ties || rank < need;
             ++rank;
           }
+          if (WHOLE && keep && Digits<COMP>::composite(key, (uint32_t)e) < least)
+            least = Digits<COMP>::composite(key, (uint32_t)e);
           const uint64_t kept = __ballot(keep);
           if (kept != 0) {   // uniform over the wave
             const uint32_t slot = claim<THREADS>(kept, emitted, sh.emit);
@@ -401,7 +407,37 @@ __device__ __forceinline__ void layer_body(const Args& A, const int i, const Lay
         }
       }
     }
+    if (WHOLE) {
+#pragma unroll
+      for (int off = 32; off >= 1; off >>= 1) {
+        const uint64_t other = __shfl_xor((unsigned long long)least, off, 64);
+        least = other < least ? other : least;
+      }
+      if (lane == 0) atomicMin(sh_kstar, (unsigned long long)least);
+      layer_sync<THREADS>();
+      if (tid == 0) {
+        WorkerCtl* ctl = A.ctl + i;
+        ctl->kstar = *sh_kstar;
+        ctl->kept = k;
+        ctl->mode = found ? 0u : 2u;
+        if (!found) ctl->fallbacks += 1;
+        ctl->last_candidates = have ? (THREADS == 64 ? listed_n : *sh.list_n) : 0u;
+      }
+    }
   }
+}
+
+// Short rows of top_a (the direct form, whose last pass applies the update of xhat): the select of a whole
+// vector out of one workgroup's registers, instead of a candidate pass and a select of the list.
+// grid n, block THREADS.
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void k_row_compress(Args A) {
+  __shared__ uint32_t sh_cnt[34], sh_emit, sh_list_n;
+  __shared__ unsigned long long sh_kstar;
+  __shared__ uint2 sh_list[2 * THREADS];
+  const LayerShared sh{sh_cnt, &sh_emit, &sh_list_n, sh_list};
+  const LayerDesc row{0, A.d, (int32_t)A.k, 0, 0, 0, {0, 0}};
+  layer_body<Q_TOPK, THREADS, false, true>(A, (int)blockIdx.x, row, (int)threadIdx.x, sh, &sh_kstar);
 }
 
 // A launch covers a piece of the work list A.layer_work (layers by falling length) from `first`

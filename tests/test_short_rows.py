@@ -1,0 +1,64 @@
+"""top_a on rows that one workgroup (or wave) selects out of its registers."""
+import numpy as np
+import pytest
+
+from paper_1907_09356_amd import binding as B
+from paper_1907_09356_amd import synth
+from tests.launches import recorded
+from tests.parity_util import Pair
+
+
+def test_which_rows_are_selected_out_of_registers():
+    out = recorded("""
+out = {}
+for d, k, kw in ((768, 7, {}), (769, 7, {}), (6144, 3000, {}), (6145, 80, {}), (6145, 81, {}), (8192, 80, {}), (8193, 8, {}),
+                 (1000, 10, dict(order=1)), (1000, 10, dict(mix_form=B.MIX_INCREMENTAL_S))):
+    c = Context(5, d, B.Q_TOPK, k=k, **kw)
+    out["%d %d %s" % (d, k, sorted(kw))] = [x[0] for x in c.step()][:-1]
+    c.close()
+c = Context(65, 1000, B.Q_TOPK, k=10)     # no tile of all rows
+out["n = 65"] = [x[0] for x in c.step()]
+""")
+    assert out["768 7 []"] == ["k_row_compress<64>"]
+    for case in ("769 7 []", "6144 3000 []", "6145 80 []", "8192 80 []"):
+        assert out[case] == ["k_row_compress<1024>"], case
+    assert sum(any(x.startswith("k_row_compress") for x in l) for l in out.values()) == 5
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,d,k,grid,mode", [
+    (3, 1, 1, 0, "step"), (4, 5, 2, 0, "halves"), (8, 767, 766, 0, "step"), (6, 768, 1, 0, "momentum"), (9, 769, 300, 0, "step"),
+    (2, 4097, 41, 0, "momentum"), (64, 1030, 50, 0, "step"), (5, 6144, 3000, 0, "halves"), (12, 8189, 80, 0, "step"),
+    (5, 700, 200, 3, "step"), (5, 3001, 900, 3, "step"), (3, 6144, 6144, 3, "step"),
+])
+def test_rows_selected_out_of_registers(n, d, k, grid, mode):
+    """Lengths around a wave's, a sweep's and the longest; ties (values on a grid); a scale that jumps, so that
+    the bracket around the last threshold misses.  The figures of the select are those of what was sent."""
+    X0 = synth.normal_state(n, d, seed=d)
+    if grid:
+        X0 = np.round(X0 * grid) / np.float32(grid)
+    pair = Pair(X0, synth.ring_csr(n) if n > 2 else synth.complete_csr(n), 0.2, compressor=B.Q_TOPK, k=k, ld_align=32 if n % 2 else 4)
+    grads = synth.GradientStream(n, d, seed=2)
+    missed = 0
+    try:
+        for t, lr in enumerate([0.0 if grid else 0.05, 0.0 if grid else 0.05, 500.0, 0.01, 0.01]):
+            g = grads.next()
+            if mode == "momentum":
+                det = pair.step_momentum(g, lr, 0.9, 1e-3)
+            elif mode == "halves":
+                pair.sgd_step(g, lr)
+                det = pair.gossip_step()
+            else:
+                det = pair.step(g, lr)
+            pair.check(det, tag="step %d" % t)
+            idx, val = (a.cpu().numpy() for a in pair.gpu.last_selection())
+            key = val.view(np.uint32) & 0x7FFFFFFF
+            scal = pair.gpu.last_scalars()
+            for i in range(n):
+                last = key[i].min()
+                assert scal[i, 0] == last and scal[i, 1] == idx[i][key[i] == last].max()
+            missed += int(np.all(scal[:, 3] == 2))
+            assert set(scal[:, 3]) <= {0.0, 2.0} and np.all(scal[:, 4] >= missed)
+        assert missed >= 1                               # (the first step has no threshold to go by)
+    finally:
+        pair.close()
