@@ -550,7 +550,7 @@ Layout make_layout(const choco_config& c, int32_t nnz) {
   L.qv = take(fused_sparse_apply(c) && c.compressor == CHOCO_Q_RANDK ? state : 0);
   L.recs = take(one_pass ? (size_t)L.nchunks * kRecSlots * (size_t)c.n * sizeof(float2) : 0);
   L.rec_cols = take(one_pass ? (size_t)L.nchunks * 8 * sizeof(uint32_t) : 0);
-  L.onepass = take(one_pass ? sizeof(OnePassState) : 0);
+  L.onepass = take(one_pass ? sizeof(OnePassState) + (size_t)c.n * sizeof(OnePassCtl) : 0);
   L.mpart = take(((size_t)kMetricsBlocks + 1) * 3 * sizeof(double));   // the blocks' sums, then the figures
   L.total = off;
   return L;
@@ -1878,6 +1878,7 @@ int choco_init(const choco_config* cfg, float* x_dev, void* workspace_dev, size_
   A.recs = ctx->one_pass ? (float2*)(base + L.recs) : nullptr;
   A.rec_cols = (uint32_t*)(base + L.rec_cols);
   A.onepass = (OnePassState*)(base + L.onepass);
+  A.onepass_ctl = (OnePassCtl*)(A.onepass + 1);
   A.Qv = (ctx->fused_sparse_apply && cfg->compressor == CHOCO_Q_RANDK) ? (float*)(base + L.qv) : nullptr;
   A.map_words = (A.ld + 31) / 32;
   A.bitmap = (uint32_t*)(base + L.bitmap);

@@ -75,14 +75,18 @@ struct WorkerCtl {
   // 'a workgroup gave up waiting: do not trust the list' (cleared when the next guess is placed)
   uint32_t fb_arrive, fb_go, fb_abort;
   uint64_t kstar;       // composite key of the k-th largest entry: kept <=> key >= kstar
-  // one-pass top_a: the threshold key that the next step's pass goes by, the one that this step's pass
-  // went by, and the rank among this step's entries at which the former was put
+};
+
+// ... and what one-pass top_a and gsgd (choco_onepass.h) keep beside it.
+struct OnePassCtl {
+  // top_a: the threshold key that the next step's pass goes by, the one that this step's pass went by, and
+  // the rank among this step's entries at which the former was put
   uint32_t expect_key, expected_key, expect_rank;
-  // one-pass gsgd: the bound on s / ||v||_2 that the next step's pass goes by, and the one that this step's did
+  // gsgd: the bound on s / ||v||_2 that the next step's pass goes by, and the one that this step's did
   float bound_r, bounded_r;
 };
 
-// What the kernels of one-pass top_a tell each other about a step (choco_onepass.h).
+// What their kernels tell each other about a step.
 struct OnePassState {
   uint32_t redo_all;    // X holds x - lr g everywhere: every tile is mixed by the last kernel
   uint32_t open_step;   // (low word of the) last step in which a tile was left unmixed
@@ -234,6 +238,7 @@ struct Args {
   float2* recs;            // tiles x kRecSlots x n: x' and xhat of all workers in the recorded columns
   uint32_t* rec_cols;      // tiles x 8: which columns of the tile are recorded; all bits: the tile was left unmixed
   OnePassState* onepass;
+  OnePassCtl* onepass_ctl; // n
   int32_t onepass_first;   // a context's first step
   // randomness
   uint32_t seed_lo, seed_hi, t_lo, t_hi;
@@ -798,8 +803,8 @@ __global__ __launch_bounds__(256) void k_dense_finalise(Args A) {
     scales_from_total<COMP>(A, sh[0], sc, ctl);
     if (ONEPASS) {
       const float change = before > 0.0f ? fminf(fabsf(sc.r / before - 1.0f), 1.0f) : 0.0f;
-      ctl->bounded_r = ctl->bound_r;
-      ctl->bound_r = sc.r * (1.02f + 2.0f * change);
+      A.onepass_ctl[i].bounded_r = A.onepass_ctl[i].bound_r;
+      A.onepass_ctl[i].bound_r = sc.r * (1.02f + 2.0f * change);
     }
   }
 }
@@ -2134,7 +2139,7 @@ __device__ __forceinline__ void emit_entry(const Args& A, int i, bool keep, uint
 // that rank is carried from step to step - with the rank at which this step's expectation was put and
 // the number c of entries that turned out above it, it moves by k - c.  Ranks become keys by the density
 // seen between the guess and the threshold T (total - k entries over `gap` keys).
-__device__ __forceinline__ void expect_threshold(const Args& A, WorkerCtl* ctl, uint32_t T, bool density, uint32_t gap,
+__device__ __forceinline__ void expect_threshold(const Args& A, OnePassCtl* ctl, uint32_t T, bool density, uint32_t gap,
                                                  uint32_t total, uint32_t guess) {
   const double k = (double)A.k;
   double key = (double)T, rank = 2.0 * k;
@@ -2170,7 +2175,7 @@ __device__ __forceinline__ void next_guess(const Args& A, WorkerCtl* ctl, uint64
   if (delta < 1) delta = 1;
   if (delta > 0xFFFFFFFFull) delta = 0xFFFFFFFFull;
   const uint32_t guess = delta >= (uint64_t)T ? 0u : T - (uint32_t)delta;
-  if (ONEPASS) expect_threshold(A, ctl, T, from_list && total > (uint32_t)A.k && T > G, T - G, total, guess);
+  if (ONEPASS) expect_threshold(A, A.onepass_ctl + (ctl - A.ctl), T, from_list && total > (uint32_t)A.k && T > G, T - G, total, guess);
   ctl->guess_key = guess;
   // 256-511 bins between the guess and where the threshold is expected: the 2048 bins then
   // still resolve a threshold that lands 4-8 times further above the guess than predicted

@@ -80,8 +80,8 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_mix(Args A) {
     if (mom) m = load4<true>(A.M + o);
   }
   const RowSpan span = nbr_span<1, kOnePassRows>(A, r, lane);
-  const uint32_t guess = A.ctl[r].guess_key, expect = A.ctl[r].expect_key;
-  const float bound = A.ctl[r].bound_r;
+  const uint32_t guess = A.ctl[r].guess_key, expect = A.onepass_ctl[r].expect_key;
+  const float bound = A.onepass_ctl[r].bound_r;
   if (r == 0) marks[lane] = 0u;    // (bytes of rows that there are not)
   uint4 words = make_uint4(0, 0, 0, 0);
   if (COMP == Q_QSGD) words = random_words(A, r, (uint32_t)(e >> 2), STREAM_DITHER);
@@ -424,7 +424,7 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_finish(Args A, in
   }
   const RecordLanes L(A, lane);
   const uint64_t kstar = A.ctl[L.row ? L.i : 0].kstar;
-  const uint32_t expected = A.ctl[L.row ? L.i : 0].expected_key;
+  const uint32_t expected = A.onepass_ctl[L.row ? L.i : 0].expected_key;
   const int waves = (int)(blockDim.x >> 6), nwaves = (int)gridDim.x * waves;
   for (int t0 = ((int)blockIdx.x * waves + r) * kRecTiles; t0 < ntiles; t0 += nwaves * kRecTiles) {
     const uint32_t total = list_marked(A, t0, ntiles, lists[r]);
@@ -488,7 +488,7 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_encode(Args A, in
   const int r = threadIdx.x >> 6, lane = threadIdx.x & 63;
   bool all = false;
   for (int j = 0; j < A.n; ++j)
-    all = all || !(A.ctl[j].scale_r <= A.ctl[j].bounded_r) || !(A.ctl[j].scale_step <= 3.402823466e38f);
+    all = all || !(A.ctl[j].scale_r <= A.onepass_ctl[j].bounded_r) || !(A.ctl[j].scale_step <= 3.402823466e38f);
   if (all || A.onepass->open_step == A.t_lo) {
     const RowNbrs nb = nbr_fetch(A, nbr_span<1, kOnePassRows>(A, r, lane), lane);
     RowScale<Q_QSGD> sc;
