@@ -98,6 +98,7 @@ struct choco_ctx {
   bool sparse;            // top_a / random_a
   bool fused_sparse_apply;   // ... whose update of xhat rides on the tile mix pass (direct form, compress-then-mix)
   bool one_pass;          // top_a, gsgd: one pass over the state (choco_onepass.h)
+  OnePass onepass;
   bool one_pass_begun;    // ... and has taken a step (later ones have a threshold or a norm to go by)
   bool short_rows;        // top_a: a workgroup selects a row out of its registers
   bool values_in_qv;      // random_a after such a step: the kept values are in Qv, not yet in the list
@@ -459,7 +460,8 @@ Layout make_layout(const choco_config& c, int32_t nnz) {
   L.row_ptr = take((size_t)(c.n + 1) * sizeof(int32_t));
   L.col = take((size_t)nnz * sizeof(int32_t));
   L.w = take((size_t)nnz * sizeof(float));
-  L.ctl = take((size_t)c.n * std::max<size_t>(1, longs.size()) * sizeof(WorkerCtl));
+  const bool one_pass = one_pass_topk(c) || one_pass_qsgd(c);
+  L.ctl = take((size_t)c.n * (std::max<size_t>(1, longs.size()) * sizeof(WorkerCtl) + (one_pass ? sizeof(OnePassCtl) : 0)));
   L.seg_counts = take(guessed ? (size_t)c.n * std::max<size_t>(1, longs.size()) * kSegs * kSegPad * sizeof(uint32_t) : 0);
   L.nchunks = (int32_t)((c.d + kChunk - 1) / kChunk);
   L.ngroups = (L.nchunks + kGroup - 1) / kGroup;
@@ -498,7 +500,6 @@ Layout make_layout(const choco_config& c, int32_t nnz) {
   // beside its other arrays), else a bit per entry in global memory
   L.bitmap_words = (guessed && !layered && !L.multipart && !short_rows(c) && c.d <= 40 * 1024 * 8) ? (c.d + 31) / 32 : 0;
   const size_t map_bytes = (size_t)c.n * (size_t)((ld + 31) / 32) * sizeof(uint32_t);   // a bit per entry
-  const bool one_pass = one_pass_topk(c) || one_pass_qsgd(c);
   L.keptmap = take(sparse && !L.bitmap_words && !one_pass ? map_bytes : 0);
   L.bitmap = take((size_t)c.n * (size_t)L.bitmap_words * sizeof(uint32_t));
   // further copies for the selections random_a makes ahead: the kept-index lists, the bitmap
@@ -550,7 +551,7 @@ Layout make_layout(const choco_config& c, int32_t nnz) {
   L.qv = take(fused_sparse_apply(c) && c.compressor == CHOCO_Q_RANDK ? state : 0);
   L.recs = take(one_pass ? (size_t)L.nchunks * kRecSlots * (size_t)c.n * sizeof(float2) : 0);
   L.rec_cols = take(one_pass ? (size_t)L.nchunks * 8 * sizeof(uint32_t) : 0);
-  L.onepass = take(one_pass ? sizeof(OnePassState) + (size_t)c.n * sizeof(OnePassCtl) : 0);
+  L.onepass = take(one_pass ? sizeof(OnePassState) : 0);
   L.mpart = take(((size_t)kMetricsBlocks + 1) * 3 * sizeof(double));   // the blocks' sums, then the figures
   L.total = off;
   return L;
@@ -959,10 +960,10 @@ int gossip_one_pass_qsgd(choco_ctx* ctx, const Args& F) {
   const size_t lds = (size_t)A.n * kChunk * sizeof(float);
   const dim3 block(64u * (unsigned)A.n);
   const int waves = (A.nchunks + kRecTiles - 1) / kRecTiles;
-  LAUNCH(ctx, F.G ? KID_ONEPASS_MIX_SGD : KID_ONEPASS_MIX, k_onepass_mix<Q_QSGD>, dim3((unsigned)A.nchunks), block, lds, F);
+  LAUNCH(ctx, F.G ? KID_ONEPASS_MIX_SGD : KID_ONEPASS_MIX, k_onepass_mix<Q_QSGD>, dim3((unsigned)A.nchunks), block, lds, F, ctx->onepass);
   LAUNCH(ctx, KID_GROUP_REDUCE, k_group_reduce, dim3((unsigned)((A.ngroups + 15) / 16), (unsigned)A.n), dim3(256), 0, A);
   LAUNCH(ctx, KID_DENSE_FINALISE, (k_dense_finalise<Q_QSGD, true>), dim3((unsigned)A.n), dim3(256), 0, A);
-  LAUNCH(ctx, KID_ONEPASS_ENCODE, k_onepass_encode, dim3((unsigned)std::min((waves + A.n - 1) / A.n, 1024)), block, lds, A, A.nchunks);
+  LAUNCH(ctx, KID_ONEPASS_ENCODE, k_onepass_encode, dim3((unsigned)std::min((waves + A.n - 1) / A.n, 1024)), block, lds, A, ctx->onepass, A.nchunks);
   LAUNCH_CHECK(ctx);
   return CHOCO_OK;
 }
@@ -1180,22 +1181,22 @@ int look_ahead_end(choco_ctx* ctx, const Args& A, uint64_t base) {
 
 // top_a in one pass (choco_onepass.h).  The kernels behind the pass have little or nothing to do as a
 // rule: workgroups to fill the chip once, which go through the tiles in turn.
-int gossip_one_pass_topk(choco_ctx* ctx, const Args& F0) {
-  Args F = F0;
-  F.onepass_first = ctx->one_pass_begun ? 0 : 1;
+int gossip_one_pass_topk(choco_ctx* ctx, const Args& F) {
+  OnePass P = ctx->onepass;
+  P.first = ctx->one_pass_begun ? 0 : 1;
   Args A = F;
   A.G = nullptr;
   const size_t lds = (size_t)A.n * kChunk * sizeof(float);
   const dim3 block(64u * (unsigned)A.n);
   const int waves = (A.nchunks + kRecTiles - 1) / kRecTiles;
-  LAUNCH(ctx, F.G ? KID_ONEPASS_MIX_SGD : KID_ONEPASS_MIX, k_onepass_mix<Q_TOPK>, dim3((unsigned)A.nchunks), block, lds, F);
-  if (!F.onepass_first) {
-    LAUNCH(ctx, KID_ONEPASS_LIST, k_onepass_list, dim3((unsigned)std::min((waves + 3) / 4, 2048)), dim3(256), 0, A, A.nchunks);
-    LAUNCH(ctx, KID_ONEPASS_RESTORE, k_onepass_restore, dim3((unsigned)std::min(A.nchunks, 512)), block, lds, A, A.nchunks);
+  LAUNCH(ctx, F.G ? KID_ONEPASS_MIX_SGD : KID_ONEPASS_MIX, k_onepass_mix<Q_TOPK>, dim3((unsigned)A.nchunks), block, lds, F, P);
+  if (!P.first) {
+    LAUNCH(ctx, KID_ONEPASS_LIST, k_onepass_list, dim3((unsigned)std::min((waves + 3) / 4, 2048)), dim3(256), 0, A, P, A.nchunks);
+    LAUNCH(ctx, KID_ONEPASS_RESTORE, k_onepass_restore, dim3((unsigned)std::min(A.nchunks, 512)), block, lds, A, P, A.nchunks);
   }
   launch_exact_select<Q_TOPK, true>(ctx, A);
   LAUNCH(ctx, KID_ONEPASS_FINISH, k_onepass_finish, dim3((unsigned)std::min((waves + A.n - 1) / A.n, 1024)), block, lds,
-         A, A.nchunks);
+         A, P, A.nchunks);
   LAUNCH_CHECK(ctx);
   ctx->one_pass_begun = true;
   return CHOCO_OK;
@@ -1455,7 +1456,7 @@ int gossip_layers_sparse(choco_ctx* ctx, const Args& F) {
                S, nlong, nmid + nsmall);
     } else {
       if (nmid > 0)
-        LAUNCH(ctx, kid, (k_layer_compress<COMP, 1024, NT>), dim3((unsigned)nmid, (unsigned)A.n), dim3(1024), 0, S,
+        LAUNCH(ctx, kid, (k_layer_compress<COMP, 1024, NT, true>), dim3((unsigned)nmid, (unsigned)A.n), dim3(1024), 0, S,
                nlong, nmid);
       if (nsmall + ntiny > 0)
         LAUNCH(ctx, kid, (k_layer_compress<COMP, 256, NT>), dim3((unsigned)(nsmall + (ntiny + 3) / 4), (unsigned)A.n),
@@ -1875,10 +1876,7 @@ int choco_init(const choco_config* cfg, float* x_dev, void* workspace_dev, size_
   A.sel_idx = (int32_t*)(base + L.sel_idx);
   A.sel_val = (float*)(base + L.sel_val);
   A.keptmap = ctx->one_pass ? nullptr : (uint32_t*)(base + L.keptmap);
-  A.recs = ctx->one_pass ? (float2*)(base + L.recs) : nullptr;
-  A.rec_cols = (uint32_t*)(base + L.rec_cols);
-  A.onepass = (OnePassState*)(base + L.onepass);
-  A.onepass_ctl = (OnePassCtl*)(A.onepass + 1);
+  ctx->onepass = OnePass{(float2*)(base + L.recs), (uint32_t*)(base + L.rec_cols), (OnePassState*)(base + L.onepass), 0};
   A.Qv = (ctx->fused_sparse_apply && cfg->compressor == CHOCO_Q_RANDK) ? (float*)(base + L.qv) : nullptr;
   A.map_words = (A.ld + 31) / 32;
   A.bitmap = (uint32_t*)(base + L.bitmap);

@@ -86,12 +86,6 @@ struct OnePassCtl {
   float bound_r, bounded_r;
 };
 
-// What their kernels tell each other about a step.
-struct OnePassState {
-  uint32_t redo_all;    // X holds x - lr g everywhere: every tile is mixed by the last kernel
-  uint32_t open_step;   // (low word of the) last step in which a tile was left unmixed
-};
-
 // One layer of a worker's vector when the operator is applied layer by layer.
 struct LayerDesc {
   int32_t start;     // first entry
@@ -234,15 +228,12 @@ struct Args {
   const int4* chunk_layer;   // per 256-entry chunk of a row: layer of its first entry, that layer's end, next layer's start
   double* layer_scal;        // n x nlayers x 4: norms and scales / threshold of the last step
   int32_t qsgd_biased;
-  // one-pass top_a and gsgd (choco_onepass.h)
-  float2* recs;            // tiles x kRecSlots x n: x' and xhat of all workers in the recorded columns
-  uint32_t* rec_cols;      // tiles x 8: which columns of the tile are recorded; all bits: the tile was left unmixed
-  OnePassState* onepass;
-  OnePassCtl* onepass_ctl; // n
-  int32_t onepass_first;   // a context's first step
   // randomness
   uint32_t seed_lo, seed_hi, t_lo, t_hi;
 };
+
+// The one-pass figures lie behind the control blocks.
+__device__ __forceinline__ OnePassCtl* onepass_ctl(const Args& A) { return reinterpret_cast<OnePassCtl*>(A.ctl + A.n); }
 
 // The select kernels' view of one long layer: the argument block of the whole-row select made
 // to point at the layer's piece of the rows, its slots of the kept lists, its control blocks
@@ -803,8 +794,8 @@ __global__ __launch_bounds__(256) void k_dense_finalise(Args A) {
     scales_from_total<COMP>(A, sh[0], sc, ctl);
     if (ONEPASS) {
       const float change = before > 0.0f ? fminf(fabsf(sc.r / before - 1.0f), 1.0f) : 0.0f;
-      A.onepass_ctl[i].bounded_r = A.onepass_ctl[i].bound_r;
-      A.onepass_ctl[i].bound_r = sc.r * (1.02f + 2.0f * change);
+      onepass_ctl(A)[i].bounded_r = onepass_ctl(A)[i].bound_r;
+      onepass_ctl(A)[i].bound_r = sc.r * (1.02f + 2.0f * change);
     }
   }
 }
@@ -2175,7 +2166,7 @@ __device__ __forceinline__ void next_guess(const Args& A, WorkerCtl* ctl, uint64
   if (delta < 1) delta = 1;
   if (delta > 0xFFFFFFFFull) delta = 0xFFFFFFFFull;
   const uint32_t guess = delta >= (uint64_t)T ? 0u : T - (uint32_t)delta;
-  if (ONEPASS) expect_threshold(A, A.onepass_ctl + (ctl - A.ctl), T, from_list && total > (uint32_t)A.k && T > G, T - G, total, guess);
+  if (ONEPASS) expect_threshold(A, onepass_ctl(A) + (ctl - A.ctl), T, from_list && total > (uint32_t)A.k && T > G, T - G, total, guess);
   ctl->guess_key = guess;
   // 256-511 bins between the guess and where the threshold is expected: the 2048 bins then
   // still resolve a threshold that lands 4-8 times further above the guess than predicted
@@ -2273,9 +2264,10 @@ __device__ void refine_and_emit(const Args& A, int i, const uint32_t* pre, uint3
 // stay in registers between the two sweeps).  If that bin is crowded (ties) the
 // digit-by-digit select runs on the list; if the list itself is not good, on the row.
 // grid n, block 1024, dynamic LDS = the worker's bitmap (short rows) or nothing.
-// BATCH: grid (n, long layers of A.long_tab).
+// BATCH: grid (n, long layers of A.long_tab); more workgroups than compute units as a rule, so 64 registers
+// for two to a unit (six layers, n = 64: 14.7 -> 10.6 us; a workgroup per worker is 0.7 us slower that way).
 template <int COMP, bool BATCH = false, bool ONEPASS = false>
-__global__ __launch_bounds__(1024) void k_sel_refine(Args A0) {
+__global__ __launch_bounds__(1024, BATCH ? 8 : 4) void k_sel_refine(Args A0) {
   const Args A = BATCH ? long_view(A0, A0.long_tab[blockIdx.y]) : A0;
   __shared__ uint32_t h[kBins];
   __shared__ uint32_t grp[256];

@@ -21,9 +21,11 @@
 // registers; if the k-th key provably lies inside, only the few keys in the bracket are
 // searched (bit by bit, in LDS); otherwise the whole layer is searched bit by bit (31 or 32
 // sweeps with block-wide counts).  Ties on the threshold key go to the lower index.  List
-// positions and kept-entry slots are handed out per wave from a ballot (a wave that has a
+// positions and kept-entry slots are handed out per wave from a scan over its lanes (a wave that has a
 // layer to itself counts in a register); no histogram, no global counters.
 #pragma once
+
+#include <type_traits>
 
 #include "choco_kernels.h"
 
@@ -63,6 +65,30 @@ __device__ __forceinline__ uint32_t wave_count_sum(uint32_t v) {
 // Lanes below this one whose bit is set in a ballot mask.
 __device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+}
+
+// Inclusive sum over the lanes up to this one, by data-parallel-primitive moves (rows of 16, then across).
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v) {
+  auto moved = [](uint32_t x, auto ctrl, auto rows) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, decltype(ctrl)::value, decltype(rows)::value, 0xF, false);
+  };
+  v += moved(v, std::integral_constant<int, 0x111>(), std::integral_constant<int, 0xF>());   // row_shr:1, 2, 4, 8
+  v += moved(v, std::integral_constant<int, 0x112>(), std::integral_constant<int, 0xF>());
+  v += moved(v, std::integral_constant<int, 0x114>(), std::integral_constant<int, 0xF>());
+  v += moved(v, std::integral_constant<int, 0x118>(), std::integral_constant<int, 0xF>());
+  v += moved(v, std::integral_constant<int, 0x142>(), std::integral_constant<int, 0xA>());   // row_bcast:15 to rows 1 and 3
+  v += moved(v, std::integral_constant<int, 0x143>(), std::integral_constant<int, 0xC>());   // row_bcast:31 to rows 2 and 3
+  return v;
+}
+
+// A place in a shared list for the `count` things of every lane: where the lane's own start.
+template <int THREADS>
+__device__ __forceinline__ uint32_t claim_counted(uint32_t count, uint32_t incl, uint32_t* shared_count) {
+  if (THREADS == 64) return incl - count;
+  const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+  uint32_t got = 0;
+  if ((threadIdx.x & 63) == 63 && total != 0u) got = atomicAdd(shared_count, total);
+  return (uint32_t)__builtin_amdgcn_readlane((int)got, 63) + incl - count;
 }
 
 // Positions for the lanes of `mask` (not empty, the same in every lane) in a list shared by
@@ -215,28 +241,44 @@ __device__ __forceinline__ void layer_body(const Args& A, const int i, const Lay
       lo = g > delta ? g - delta : 0u;
       hi = g < 0x7FFFFFFFu - delta ? g + delta : 0x7FFFFFFFu;
     }
+    if (lo == 0u) lo = 1u;   // (entries outside the layer have key 0)
     int phase = 0;
     uint32_t T = 0, at_or_above = 0xFFFFFFFFu;
     uint32_t listed_n = 0;   // one wave per layer: the length of its list
     bool found = false;
     if (have) {                                   // uniform
-      uint32_t nhi = 0, listed = 0;
+      // a thread counts its keys above the bracket and inside it, one scan over the wave and one LDS atomic
+      // place the latter (a ballot and an atomic for each of the thread's entries in turn, each waiting for
+      // the one before, and the same again for the kept entries: six layers of 4,608 to 9,216 entries, n = 64
+      // 21.6 against 20.0 us, the 59 shorter ones 15.7 against 14.1)
+      uint32_t mine = 0;                          // above | inside << 16
 #pragma unroll
       for (int it = 0; it < kLayerVecs; ++it)
         if (it < nit) {
-          const int m = it * THREADS + tid;
 #pragma unroll
           for (int c = 0; c < 4; ++c) {
             const uint32_t key = key_of(it, c);
-            nhi += wave_count(key >= hi);
-            const bool in = key >= lo && key < hi && inside(4 * m + c);
-            const uint64_t hits = __ballot(in);
-            if (hits != 0) {                      // uniform over the wave
-              const uint32_t pos = claim<THREADS>(hits, listed, sh.list_n);
-              if (in && pos < CAP) sh.list[pos] = make_uint2(key, (uint32_t)(4 * m + c));
-            }
+            mine += key >= hi ? 1u : key >= lo ? 65536u : 0u;
           }
         }
+      const uint32_t incl = wave_scan(mine);
+      uint32_t nhi = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63) & 0xFFFFu;
+      const uint32_t listed = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63) >> 16;
+      uint32_t pos = claim_counted<THREADS>(mine >> 16, incl >> 16, sh.list_n);
+      if (mine >> 16) {
+#pragma unroll
+        for (int it = 0; it < kLayerVecs; ++it)
+          if (it < nit) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+              const uint32_t key = key_of(it, c);
+              if (key >= lo && key < hi) {
+                if (pos < CAP) sh.list[pos] = make_uint2(key, (uint32_t)(4 * (it * THREADS + tid) + c));
+                ++pos;
+              }
+            }
+          }
+      }
       nhi = block_total<THREADS>(nhi, sh.cnt, phase);
       layer_sync<THREADS>();
       const uint32_t nin = THREADS == 64 ? listed : *sh.list_n;
@@ -348,9 +390,45 @@ __device__ __forceinline__ void layer_body(const Args& A, const int i, const Lay
       scal[3] = found ? 1.0 : 0.0;
     }
     const bool ties = equals > need;   // uniform over the layer's threads
+    auto keep_entry = [&](uint32_t slot, int it, int c) {
+      if (slot < k) {   // exactly k entries pass; the test only keeps a wrong count inside the layer's slots
+        const int e = 4 * (it * THREADS + tid) + c;
+        const int64_t dst = (int64_t)i * A.k + L.sel_base + slot;
+        A.sel_idx[dst] = base + e;
+        if constexpr (COMP == Q_TOPK) A.sel_val[dst] = v[it][c];
+        atomicOr(&A.keptmap[(int64_t)i * A.map_words + ((uint32_t)(base + e) >> 5)], 1u << ((uint32_t)(base + e) & 31u));
+      }
+    };
     uint32_t running = 0;              // threshold-key entries in earlier sweeps (index order)
     uint32_t emitted = 0;              // one wave per layer: kept entries handed out so far
     uint64_t least = ~0ull;            // WHOLE: the last of the lane's kept entries in the order of the selection
+    if (!ties && T != 0u) {            // all at or above the threshold (outside the layer the key is 0)
+      uint32_t mine = 0;
+#pragma unroll
+      for (int it = 0; it < kLayerVecs; ++it)
+        if (it < nit) {
+#pragma unroll
+          for (int c = 0; c < 4; ++c) mine += key_of(it, c) >= T ? 1u : 0u;
+        }
+      uint32_t slot = claim_counted<THREADS>(mine, wave_scan(mine), sh.emit);
+      if (mine) {
+#pragma unroll
+        for (int it = 0; it < kLayerVecs; ++it)
+          if (it < nit) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+              const uint32_t key = key_of(it, c);
+              if (key >= T) {
+                if (WHOLE) {
+                  const uint64_t K = Digits<COMP>::composite(key, (uint32_t)(4 * (it * THREADS + tid) + c));
+                  least = K < least ? K : least;
+                }
+                keep_entry(slot++, it, c);
+              }
+            }
+          }
+      }
+    } else
 #pragma unroll
     for (int it = 0; it < kLayerVecs; ++it) {
       if (it < nit) {
@@ -397,12 +475,7 @@ __device__ __forceinline__ void layer_body(const Args& A, const int i, const Lay
           const uint64_t kept = __ballot(keep);
           if (kept != 0) {   // uniform over the wave
             const uint32_t slot = claim<THREADS>(kept, emitted, sh.emit);
-            if (keep && slot < k) {   // exactly k entries pass; the test only keeps a wrong count inside the layer's slots
-              const int64_t dst = (int64_t)i * A.k + L.sel_base + slot;
-              A.sel_idx[dst] = base + e;
-              if (COMP == Q_TOPK) A.sel_val[dst] = v[it][c];
-              atomicOr(&A.keptmap[(int64_t)i * A.map_words + ((uint32_t)(base + e) >> 5)], 1u << ((uint32_t)(base + e) & 31u));
-            }
+            if (keep) keep_entry(slot, it, c);
           }
         }
       }
@@ -448,7 +521,8 @@ __global__ __launch_bounds__(THREADS) void k_row_compress(Args A) {
 // Few workers (the chip is not full either way): one launch of 1024-thread workgroups, one for
 // every layer above 768 entries and one for every sixteen smaller ones.
 // (64 registers: two 1024-thread workgroups share a compute unit.)
-template <int COMP, int THREADS, bool NT>
+// ONLY: every workgroup has a layer to itself (no wave-sized layers in the launch, and no code for them).
+template <int COMP, int THREADS, bool NT, bool ONLY = false>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8)))
 void k_layer_compress(Args A, int32_t first, int32_t nblock) {
   constexpr int NW = THREADS / 64;
@@ -457,7 +531,7 @@ void k_layer_compress(Args A, int32_t first, int32_t nblock) {
   __shared__ uint32_t sh_list_n[NW];
   __shared__ uint2 sh_list[2 * THREADS];
   const int i = blockIdx.y;
-  if ((int)blockIdx.x < nblock) {
+  if (ONLY || (int)blockIdx.x < nblock) {
     const LayerShared sh{sh_cnt, sh_emit, sh_list_n, sh_list};
     layer_body<COMP, THREADS, NT>(A, i, A.layer_work[first + (int)blockIdx.x], (int)threadIdx.x, sh);
   } else {

@@ -28,6 +28,18 @@
 
 namespace choco {
 
+// What the one-pass kernels need beside the argument block of all.
+struct OnePassState {
+  uint32_t redo_all;    // X holds x - lr g everywhere: every tile is mixed by the last kernel
+  uint32_t open_step;   // (low word of the) last step in which a tile was left unmixed
+};
+struct OnePass {
+  float2* recs;         // tiles x kRecSlots x n: x' and xhat of all workers in the recorded columns
+  uint32_t* cols;       // tiles x 8: which columns of the tile are recorded; all bits: the tile was left unmixed
+  OnePassState* state;
+  int32_t first;        // a context's first step
+};
+
 // Slots per tile of 256 columns.  A slot is 8 n bytes, so the records are a quarter of an array of the
 // state; at 5 expected columns per tile (n = 8, k / d = 0.001) no tile in 10^6 has more than 20.
 constexpr int kRecSlots = 32;
@@ -52,8 +64,8 @@ __device__ __forceinline__ uint32_t mask_word(uint32_t nibble, int lane) {
 }
 
 // (x', xhat) of worker 0 in a slot; worker i's is i further on.
-__device__ __forceinline__ float2* record_of(const Args& A, int64_t tile, int slot) {
-  return A.recs + (tile * kRecSlots + slot) * A.n;
+__device__ __forceinline__ float2* record_of(const Args& A, const OnePass& P, int64_t tile, int slot) {
+  return P.recs + (tile * kRecSlots + slot) * A.n;
 }
 
 // A tile that was left unmixed has all bits of its mask set (a recorded one no more than kRecSlots).
@@ -62,7 +74,7 @@ static_assert(kRecSlots < 64, "two full words of a mask mean an open tile");
 
 // grid ceil(d / 256), block 64 n (wave r: row r), dynamic LDS n x 256 floats.
 template <int COMP>
-__global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_mix(Args A) {
+__global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_mix(Args A, OnePass P) {
   extern __shared__ float tile[];
   __shared__ uint64_t marks[64];   // a byte per lane and wave
   __shared__ float2 recs[kRecSlots * kOnePassRows];
@@ -80,8 +92,8 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_mix(Args A) {
     if (mom) m = load4<true>(A.M + o);
   }
   const RowSpan span = nbr_span<1, kOnePassRows>(A, r, lane);
-  const uint32_t guess = A.ctl[r].guess_key, expect = A.onepass_ctl[r].expect_key;
-  const float bound = A.onepass_ctl[r].bound_r;
+  const uint32_t guess = A.ctl[r].guess_key, expect = onepass_ctl(A)[r].expect_key;
+  const float bound = onepass_ctl(A)[r].bound_r;
   if (r == 0) marks[lane] = 0u;    // (bytes of rows that there are not)
   uint4 words = make_uint4(0, 0, 0, 0);
   if (COMP == Q_QSGD) words = random_words(A, r, (uint32_t)(e >> 2), STREAM_DITHER);
@@ -90,7 +102,7 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_mix(Args A) {
     x = local_update_regs(A, x, g, m);
     if (mom) store4<true>(A.M + o, m);
   }
-  if (COMP == Q_TOPK && A.onepass_first) {   // no threshold to go by: the last kernel does all tiles
+  if (COMP == Q_TOPK && P.first) {   // no threshold to go by: the last kernel does all tiles
     if (mine && A.G) store4<true>(A.X + o, x);
     return;
   }
@@ -153,8 +165,8 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_mix(Args A) {
   }
   if (r == 0) {
     const uint32_t w = mask_word(open ? 0xFu : dirty, lane);
-    if ((lane & 7) == 0) A.rec_cols[(int64_t)tile_no * 8 + (lane >> 3)] = w;
-    if (open && lane == 0) A.onepass->open_step = A.t_lo;
+    if ((lane & 7) == 0) P.cols[(int64_t)tile_no * 8 + (lane >> 3)] = w;
+    if (open && lane == 0) P.state->open_step = A.t_lo;
   }
   if (open) {
 #pragma unroll
@@ -177,17 +189,17 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_mix(Args A) {
   if (open) return;
   // (by way of LDS, whole records at a time: 616 against 623 us for gsgd at n = 8, d = 28 M, top_a 602 against 607)
   __syncthreads();
-  for (int j = threadIdx.x; j < total * A.n; j += (int)blockDim.x) record_of(A, tile_no, 0)[j] = recs[j];
+  for (int j = threadIdx.x; j < total * A.n; j += (int)blockDim.x) record_of(A, P, tile_no, 0)[j] = recs[j];
 }
 
 // The marked columns of the kRecTiles tiles from t0 on, to LDS as (tile of the sixteen x slots + slot,
 // column in the tile); returns how many.  A whole wave calls it: four lanes to a tile, two words of its
 // mask each.
-__device__ __forceinline__ uint32_t list_marked(const Args& A, int t0, int ntiles, ushort2* out) {
+__device__ __forceinline__ uint32_t list_marked(const OnePass& P, int t0, int ntiles, ushort2* out) {
   const int lane = threadIdx.x & 63;
   const int t = t0 + (lane >> 2);
   uint2 w = make_uint2(0u, 0u);
-  if (t < ntiles) w = *reinterpret_cast<const uint2*>(A.rec_cols + (int64_t)t * 8 + 2 * (lane & 3));
+  if (t < ntiles) w = *reinterpret_cast<const uint2*>(P.cols + (int64_t)t * 8 + 2 * (lane & 3));
   if (left_open(w)) w = make_uint2(0u, 0u);
   const uint32_t cnt = (uint32_t)(__popc(w.x) + __popc(w.y));
   uint32_t incl = cnt;
@@ -215,14 +227,14 @@ struct Recorded {
   int col;
   bool have;    // there is such a record, and the lane stands for a worker in it
 };
-__device__ __forceinline__ Recorded recorded(const Args& A, int t0, const ushort2* list, uint32_t f, uint32_t total, int i) {
+__device__ __forceinline__ Recorded recorded(const Args& A, const OnePass& P, int t0, const ushort2* list, uint32_t f, uint32_t total, int i) {
   Recorded R{0.0f, 0.0f, 0, false};
   if (f < total) {
     const int ts = list[f].x, t = t0 + ts / kRecSlots;
     R.col = t * kChunk + list[f].y;
     R.have = i < A.n && R.col < A.d;
     if (R.have) {
-      const float2 v = record_of(A, t, ts % kRecSlots)[i];
+      const float2 v = record_of(A, P, t, ts % kRecSlots)[i];
       R.x = v.x;
       R.h = v.y;
     }
@@ -269,20 +281,20 @@ struct RecordLanes {
 
 // The candidates among the recorded entries, to the rows' lists: each wave counts those of its sixteen
 // tiles row by row, takes room with one addition per row and writes them.  grid any, block 256.
-__global__ __launch_bounds__(256) void k_onepass_list(Args A, int32_t ntiles) {
+__global__ __launch_bounds__(256) void k_onepass_list(Args A, OnePass P, int32_t ntiles) {
   __shared__ ushort2 lists[4][kRecTiles * kRecSlots];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, i = lane & 7, grp = lane >> 3;
   ushort2* list = lists[wave];
   const uint32_t guess = A.ctl[i < A.n ? i : 0].guess_key;
   const int w0 = (int)blockIdx.x * 4 + wave, nwaves = (int)gridDim.x * 4;
   for (int t0 = w0 * kRecTiles; t0 < ntiles; t0 += nwaves * kRecTiles) {
-    const uint32_t total = list_marked(A, t0, ntiles, list);
+    const uint32_t total = list_marked(P, t0, ntiles, list);
     auto is_candidate = [&](const Recorded& R) {
       return R.have && (__float_as_uint(R.x - R.h) & 0x7fffffffu) >= guess;
     };
     uint32_t mine = 0;
 #pragma unroll 4
-    for (uint32_t f = (uint32_t)grp; f < total; f += 8) mine += is_candidate(recorded(A, t0, list, f, total, i)) ? 1u : 0u;
+    for (uint32_t f = (uint32_t)grp; f < total; f += 8) mine += is_candidate(recorded(A, P, t0, list, f, total, i)) ? 1u : 0u;
     uint32_t incl = mine;     // over the eight lanes of a row
 #pragma unroll
     for (int off = 8; off < 64; off <<= 1) {
@@ -297,7 +309,7 @@ __global__ __launch_bounds__(256) void k_onepass_list(Args A, int32_t ntiles) {
       uint2* out = A.cand + ((int64_t)i * kSegs + seg) * A.seg_cap;
 #pragma unroll 4
       for (uint32_t f = (uint32_t)grp; f < total; f += 8) {
-        const Recorded R = recorded(A, t0, list, f, total, i);
+        const Recorded R = recorded(A, P, t0, list, f, total, i);
         if (is_candidate(R)) {
           if (base < A.seg_cap) out[base] = make_uint2(__float_as_uint(R.x - R.h), (uint32_t)R.col);
           ++base;
@@ -311,12 +323,12 @@ __global__ __launch_bounds__(256) void k_onepass_list(Args A, int32_t ntiles) {
 
 // x' and xhat of the lane's 4-vector as they were before k_onepass_mix mixed tile t (not an open one).  All
 // waves of the workgroup call it, one row each; the LDS tile holds the old xhat afterwards.
-__device__ __forceinline__ void take_back(const Args& A, float* tile, int t, int r, int lane, const RowNbrs& nb, vf4& x,
+__device__ __forceinline__ void take_back(const Args& A, const OnePass& P, float* tile, int t, int r, int lane, const RowNbrs& nb, vf4& x,
                                           vf4& h, bool& recorded_here) {
   const int e = t * kChunk + lane * 4;
   const bool mine = e < A.d;
   const int64_t o = (int64_t)r * A.ld + e;
-  const uint32_t dirty = (A.rec_cols[(int64_t)t * 8 + (lane >> 3)] >> (4 * (lane & 7))) & 0xFu;
+  const uint32_t dirty = (P.cols[(int64_t)t * 8 + (lane >> 3)] >> (4 * (lane & 7))) & 0xFu;
   int slot = 0;
 #pragma unroll
   for (int c = 0; c < 4; ++c) slot += __popcll(__ballot((dirty >> c) & 1u) & ((1ull << lane) - 1ull));
@@ -328,7 +340,7 @@ __device__ __forceinline__ void take_back(const Args& A, float* tile, int t, int
 #pragma unroll
     for (int c = 0; c < 4; ++c)
       if ((dirty >> c) & 1u) {
-        const float2 v = record_of(A, t, slot++)[r];
+        const float2 v = record_of(A, P, t, slot++)[r];
         xr[c] = v.x;
         h[c] = v.y;
       }
@@ -348,7 +360,7 @@ __device__ __forceinline__ void take_back(const Args& A, float* tile, int t, int
 // Do all lists hold their row's k largest entries?  If not, what k_onepass_mix did to x and xhat is
 // undone, tile by tile, so that X is x' everywhere.  Normally a launch of workgroups that read the
 // lists' lengths and leave.  grid any, block 64 n, dynamic LDS n x 256 floats.
-__global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_restore(Args A, int32_t ntiles) {
+__global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_restore(Args A, OnePass P, int32_t ntiles) {
   extern __shared__ float tile[];
   __shared__ uint32_t s_bad;
   const int r = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -361,17 +373,17 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_restore(Args A, i
   const bool fits = __ballot(raw > A.seg_cap) == 0ull;
   if (lane == 0 && (!fits || sum < (unsigned long long)A.k)) s_bad = 1u;
   __syncthreads();
-  if (blockIdx.x == 0 && threadIdx.x == 0) A.onepass->redo_all = s_bad;
+  if (blockIdx.x == 0 && threadIdx.x == 0) P.state->redo_all = s_bad;
   if (s_bad == 0u) return;
   const RowNbrs nb = nbr_fetch(A, nbr_span<1, kOnePassRows>(A, r, lane), lane);
   for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
-    const uint32_t* cols = A.rec_cols + (int64_t)t * 8;
+    const uint32_t* cols = P.cols + (int64_t)t * 8;
     if (left_open(make_uint2(cols[0], cols[1]))) continue;
     const int e = t * kChunk + lane * 4;
     const int64_t o = (int64_t)r * A.ld + e;
     vf4 x, h;
     bool changed;
-    take_back(A, tile, t, r, lane, nb, x, h, changed);
+    take_back(A, P, tile, t, r, lane, nb, x, h, changed);
     if (changed) store4<false>(A.Xhat + o, h);
     if (e < A.d) store4<true>(A.X + o, x);
   }
@@ -381,16 +393,16 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_restore(Args A, i
 // (all of them in a first step or after k_onepass_restore) get the update of xhat and the mix here; of
 // the others the recorded columns whose kept set is not the one that k_onepass_mix went by.
 // grid any, block 64 n, dynamic LDS n x 256 floats.
-__global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_finish(Args A, int32_t ntiles) {
+__global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_finish(Args A, OnePass P, int32_t ntiles) {
   extern __shared__ float tile[];
   __shared__ ushort2 lists[kOnePassRows][kRecTiles * kRecSlots];
   const int r = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const bool all = A.onepass_first || A.onepass->redo_all != 0u;
-  if (all || A.onepass->open_step == A.t_lo) {
+  const bool all = P.first || P.state->redo_all != 0u;
+  if (all || P.state->open_step == A.t_lo) {
     const RowNbrs nb = nbr_fetch(A, nbr_span<1, kOnePassRows>(A, r, lane), lane);
     const uint64_t kstar = A.ctl[r].kstar;
     for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
-      const uint32_t* cols = A.rec_cols + (int64_t)t * 8;
+      const uint32_t* cols = P.cols + (int64_t)t * 8;
       if (!all && !left_open(make_uint2(cols[0], cols[1]))) continue;
       const int e = t * kChunk + lane * 4;
       const bool mine = e < A.d;
@@ -424,15 +436,15 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_finish(Args A, in
   }
   const RecordLanes L(A, lane);
   const uint64_t kstar = A.ctl[L.row ? L.i : 0].kstar;
-  const uint32_t expected = A.onepass_ctl[L.row ? L.i : 0].expected_key;
+  const uint32_t expected = onepass_ctl(A)[L.row ? L.i : 0].expected_key;
   const int waves = (int)(blockDim.x >> 6), nwaves = (int)gridDim.x * waves;
   for (int t0 = ((int)blockIdx.x * waves + r) * kRecTiles; t0 < ntiles; t0 += nwaves * kRecTiles) {
-    const uint32_t total = list_marked(A, t0, ntiles, lists[r]);
+    const uint32_t total = list_marked(P, t0, ntiles, lists[r]);
     constexpr int U = 4;       // records of a group in flight
     for (uint32_t f0 = 0; f0 < total; f0 += 8 * U) {
       Recorded R[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) R[u] = recorded(A, t0, lists[r], f0 + 8u * u + (uint32_t)L.grp, total, L.i);
+      for (int u = 0; u < U; ++u) R[u] = recorded(A, P, t0, lists[r], f0 + 8u * u + (uint32_t)L.grp, total, L.i);
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const float q = R[u].x - R[u].h;
@@ -460,18 +472,18 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_finish(Args A, in
 // and plane, two lanes to a tile.  (32 bytes per row, plane and tile out of k_onepass_mix
 // made that kernel 75 us longer at n = 8, d = 28 M, five planes; here they take 37.)  The words belong to this wave alone
 // until the kernel's end, so its bits need no more than the order among its own accesses.
-__device__ __forceinline__ void clear_planes(const Args& A, int t0, int ntiles, int lane) {
+__device__ __forceinline__ void clear_planes(const Args& A, const OnePass& P, int t0, int ntiles, int lane) {
   typedef uint32_t words4 __attribute__((ext_vector_type(4), aligned(4)));   // (a plane may have any number of words)
   const int t = t0 + ((lane & 31) >> 1);
   if (t >= ntiles) return;
-  const uint32_t* cols = A.rec_cols + (int64_t)t * 8;
+  const uint32_t* cols = P.cols + (int64_t)t * 8;
   if (left_open(make_uint2(cols[0], cols[1]))) return;
   const int64_t word = (int64_t)t * 8 + 4 * (lane & 1), left = ((int64_t)A.d + 31) / 32 - word;
   for (int q = lane >> 5; q < A.n * A.nplanes; q += 2) {
-    uint32_t* P = A.planes + (int64_t)q * A.plane_words + word;
-    if (left >= 4) *reinterpret_cast<words4*>(P) = words4{0u, 0u, 0u, 0u};
+    uint32_t* plane = A.planes + (int64_t)q * A.plane_words + word;
+    if (left >= 4) *reinterpret_cast<words4*>(plane) = words4{0u, 0u, 0u, 0u};
     else
-      for (int j = 0; j < left; ++j) P[j] = 0u;
+      for (int j = 0; j < left; ++j) plane[j] = 0u;
   }
 }
 __device__ __forceinline__ void set_bits(uint32_t* word, uint32_t bits) {
@@ -482,19 +494,19 @@ __device__ __forceinline__ void set_bits(uint32_t* word, uint32_t bits) {
 // of the columns in which a level is not zero.  Tiles left unmixed are done as a whole; all tiles are where
 // the factor s / ||v|| came out above the bound that the pass went by, or ||v|| beyond fp32 (then even a
 // level of zero has a value).  grid any, block 64 n, dynamic LDS n x 256 floats.
-__global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_encode(Args A, int32_t ntiles) {
+__global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_encode(Args A, OnePass P, int32_t ntiles) {
   extern __shared__ float tile[];
   __shared__ ushort2 lists[kOnePassRows][kRecTiles * kRecSlots];
   const int r = threadIdx.x >> 6, lane = threadIdx.x & 63;
   bool all = false;
   for (int j = 0; j < A.n; ++j)
-    all = all || !(A.ctl[j].scale_r <= A.onepass_ctl[j].bounded_r) || !(A.ctl[j].scale_step <= 3.402823466e38f);
-  if (all || A.onepass->open_step == A.t_lo) {
+    all = all || !(A.ctl[j].scale_r <= onepass_ctl(A)[j].bounded_r) || !(A.ctl[j].scale_step <= 3.402823466e38f);
+  if (all || P.state->open_step == A.t_lo) {
     const RowNbrs nb = nbr_fetch(A, nbr_span<1, kOnePassRows>(A, r, lane), lane);
     RowScale<Q_QSGD> sc;
     sc.load(A.ctl + r);
     for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
-      const uint32_t* cols = A.rec_cols + (int64_t)t * 8;
+      const uint32_t* cols = P.cols + (int64_t)t * 8;
       const bool open = left_open(make_uint2(cols[0], cols[1]));
       if (!all && !open) continue;
       const int e = t * kChunk + lane * 4;
@@ -503,7 +515,7 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_encode(Args A, in
       vf4 x = {0.f, 0.f, 0.f, 0.f}, h = x;
       if (!open) {
         bool changed;
-        take_back(A, tile, t, r, lane, nb, x, h, changed);
+        take_back(A, P, tile, t, r, lane, nb, x, h, changed);
       } else if (mine) {
         x = load4<true>(A.X + o);
         h = load4<true>(A.Xhat + o);
@@ -534,13 +546,13 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_encode(Args A, in
   sc.load(A.ctl + (L.row ? L.i : 0));
   const int waves = (int)(blockDim.x >> 6), nwaves = (int)gridDim.x * waves;
   for (int t0 = ((int)blockIdx.x * waves + r) * kRecTiles; t0 < ntiles; t0 += nwaves * kRecTiles) {
-    clear_planes(A, t0, ntiles, lane);
-    const uint32_t total = list_marked(A, t0, ntiles, lists[r]);
+    clear_planes(A, P, t0, ntiles, lane);
+    const uint32_t total = list_marked(P, t0, ntiles, lists[r]);
     constexpr int U = 4;       // records of a group in flight
     for (uint32_t f0 = 0; f0 < total; f0 += 8 * U) {
       Recorded R[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) R[u] = recorded(A, t0, lists[r], f0 + 8u * u + (uint32_t)L.grp, total, L.i);
+      for (int u = 0; u < U; ++u) R[u] = recorded(A, P, t0, lists[r], f0 + 8u * u + (uint32_t)L.grp, total, L.i);
       if (f0 == 0) __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");   // the zeros before the bits
 #pragma unroll
       for (int u = 0; u < U; ++u) {
@@ -562,11 +574,11 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_encode(Args A, in
         if (code != 0) {
           if (A.codes) A.codes[(int64_t)L.i * A.ld + R[u].col] = code;
           const uint32_t bit = 1u << (R[u].col & 31);
-          uint32_t* P = A.planes + (int64_t)L.i * A.nplanes * A.plane_words + ((uint32_t)R[u].col >> 5);
-          if (code < 0) set_bits(P, bit);
+          uint32_t* plane = A.planes + (int64_t)L.i * A.nplanes * A.plane_words + ((uint32_t)R[u].col >> 5);
+          if (code < 0) set_bits(plane, bit);
           const int32_t mag = magnitude_sent(A, L.i, R[u].col, 0, code);
           for (int p = 0; p < A.mb; ++p)
-            if ((mag >> p) & 1) set_bits(P + (int64_t)(1 + p) * A.plane_words, bit);
+            if ((mag >> p) & 1) set_bits(plane + (int64_t)(1 + p) * A.plane_words, bit);
         }
       }
     }
