@@ -1026,13 +1026,20 @@ dim3 fallback_grid(int n) {
 }
 
 // A long pass that selects ahead generates Philox words (ALU work) while the caller's stream
-// runs the bandwidth-bound mix.  Left alone its workgroups fill every wave slot first and the
-// mix waits behind them; 48 KiB of LDS that it does not use hold it to two workgroups per
-// compute unit, so that both make progress (n = 8, 31.8 M entries in 14 layers, ms per step by
-// pad: 0 KiB 1.296, 16 KiB 1.267, 28 KiB 1.223, 48 KiB 1.189; a single workgroup per unit is
-// too slow to finish behind the mix: 1.316).
+// runs the bandwidth-bound mix.  Its workgroups must not fill the wave slots before the mix: there are
+// about 256 of them, and 72 KiB of LDS that they do not use keep two to a compute unit at most.
+//   us per step, a workgroup per chunk with 48 KiB | 256 that stay, 48 KiB | 72 KiB | 512 that stay, 72 KiB
+//   n = 8, 28 M 647 | 624 | 625 | 626    31.8 M in 14 layers 778 | 769 | 769 | 772   4 workers, 8 M 130 | 129 | 128 | 129
+//   64 workers, 2.2 M 529 | 540 | 530 | 531   32, 4 M 409 | 403 | 403 | 402   8, 12 M with momentum 414 | 407 | 408 | 411
 size_t ahead_lds_pad(const choco_ctx* ctx, int64_t row_len) {
-  return (ctx->launch_stream != ctx->stream && row_len > ((int64_t)1 << 21)) ? (size_t)48 << 10 : 0;
+  return (ctx->launch_stream != ctx->stream && row_len > ((int64_t)1 << 21)) ? (size_t)72 << 10 : 0;
+}
+
+// random_a's candidate pass over a long row beside a step (see k_sel_draw).
+void launch_draw(choco_ctx* ctx, const Args& A, int32_t nvec, size_t pad) {
+  const int chunks = (nvec + 256 * kCompactVecs - 1) / (256 * kCompactVecs);
+  const int per = std::min(std::max(256 / A.n / kSegs, 1) * kSegs, (chunks + kSegs - 1) / kSegs * kSegs);
+  LAUNCH(ctx, KID_SEL_COMPACT, k_sel_draw, dim3((unsigned)per, (unsigned)A.n), dim3(256), pad, A);
 }
 
 // The exact select on the candidate lists of whole rows.
@@ -1074,6 +1081,8 @@ void launch_select(choco_ctx* ctx, const Args& C, const Args& A, int kid_compact
     if (cvecs == 2) LAUNCH(ctx, kid_compact, (k_sel_compact<COMP, COMP == Q_TOPK, NT, 2>), cgrid, dim3(256), 0, C);
     else if (kWide) LAUNCH(ctx, kid_compact, (k_sel_compact<COMP, COMP == Q_TOPK, NT, 1, false, 1024>), cgrid, dim3(1024), 0, C);
     else LAUNCH(ctx, kid_compact, (k_sel_compact<COMP, COMP == Q_TOPK, NT, kCompactVecs>), cgrid, dim3(256), 0, C);
+  } else if (COMP == Q_RANDK && pad != 0) {
+    launch_draw(ctx, C, nvec, pad);
   } else {
     if (cvecs == 2)   // (top_a: one 4-vector per thread, n = 64, d = 65 k 33.8 -> 32.3 us per step, d = 270 k 96.0 -> 95.6)
       LAUNCH(ctx, kid_compact, (k_sel_compact<COMP, false, NT, COMP == Q_TOPK ? 1 : 2>), chunk_grid(nvec, A.n, COMP == Q_TOPK ? 1 : 2), dim3(256), pad, C);
@@ -1351,6 +1360,8 @@ void long_layer_pass(choco_ctx* ctx, const Args& C, int which) {
   if (B.plan.fallback_chain && COMP == Q_TOPK)   // (the shape of the whole-row pass on long rows)
     LAUNCH(ctx, kid_compact, (k_sel_compact<COMP, false, NT, 1, false, 1024>), chunk_grid(nvec, C.n, kCompactVecs),
            dim3(1024), 0, Cl);
+  else if (B.plan.fallback_chain && ahead_lds_pad(ctx, B.len) != 0)
+    launch_draw(ctx, Cl, nvec, ahead_lds_pad(ctx, B.len));
   else if (B.plan.fallback_chain)
     LAUNCH(ctx, kid_compact, (k_sel_compact<COMP, false, NT, kCompactVecs>), chunk_grid(nvec, C.n, kCompactVecs),
            dim3(256), ahead_lds_pad(ctx, B.len), Cl);

@@ -432,6 +432,46 @@ __device__ __forceinline__ uint4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_
   return make_uint4(c0, c1, c2, c3);
 }
 
+// U calls whose first counter words are m0, m0 + 64, ...: round by round side by side, so that a wave alone
+// on its SIMD has U independent chains to issue from (one after the other each waits for itself).
+template <int U>
+__device__ __forceinline__ void philox_side_by_side(uint32_t m0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0,
+                                                    uint32_t k1, uint4 (&out)[U]) {
+  uint32_t c[U][4];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    c[u][0] = m0 + 64u * (uint32_t)u;
+    c[u][1] = c1;
+    c[u][2] = c2;
+    c[u][3] = c3;
+  }
+#pragma unroll
+  for (int round = 0; round < 10; ++round) {
+    if (round > 0) {
+      k0 += 0x9E3779B9u;
+      k1 += 0xBB67AE85u;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint64_t p0 = (uint64_t)0xD2511F53u * (uint64_t)c[u][0];
+      const uint64_t p1 = (uint64_t)0xCD9E8D57u * (uint64_t)c[u][2];
+      const uint32_t n0 = xor3((uint32_t)(p1 >> 32), c[u][1], k0);
+      const uint32_t n2 = xor3((uint32_t)(p0 >> 32), c[u][3], k1);
+      c[u][0] = n0; c[u][1] = (uint32_t)p1; c[u][2] = n2; c[u][3] = (uint32_t)p0;
+    }
+    // (a round of all chains before the next round of any: the compiler would finish one chain after
+    // the other to save registers)
+#pragma unroll
+    for (int u = 0; u < U; u += 2)
+      if (u + 1 < U)
+        asm volatile("" : "+v"(c[u][0]), "+v"(c[u][1]), "+v"(c[u][2]), "+v"(c[u][3]), "+v"(c[u + 1][0]),
+                     "+v"(c[u + 1][1]), "+v"(c[u + 1][2]), "+v"(c[u + 1][3]));
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u) out[u] = make_uint4(c[u][0], c[u][1], c[u][2], c[u][3]);
+}
+
+
 // Four words for entries 4m .. 4m+3 of a worker on one stream.
 __device__ __forceinline__ uint4 random_words(const Args& A, int worker, uint32_t m, uint32_t stream) {
   return philox4x32_10(m, (uint32_t)worker, A.t_lo, stream | (A.t_hi << 8), A.seed_lo, A.seed_hi);
@@ -1727,10 +1767,12 @@ __device__ __forceinline__ void compact_chunk(const Args& A, int i, int chunk, u
       }
     }
   } else {
+    uint4 w[VECS];   // (also past the row's end, where nothing is listed: no branch between the chains)
+    philox_side_by_side<VECS>(A.vec_base + (uint32_t)m0, (uint32_t)i, A.t_lo, STREAM_RANDK | (A.t_hi << 8), A.seed_lo,
+                              A.seed_hi, w);
 #pragma unroll
     for (int u = 0; u < VECS; ++u) {
-      const int m = m0 + u * 64;
-      if (m < nvec) entry_bits<COMP, DO_MIX, NT, FIRST>(A, i, m, a[u]);
+      a[u][0] = ~w[u].x; a[u][1] = ~w[u].y; a[u][2] = ~w[u].z; a[u][3] = ~w[u].w;
     }
   }
 #pragma unroll
@@ -1796,6 +1838,61 @@ __global__ __launch_bounds__(THREADS) void k_sel_compact(Args A0) {
   }
   compact_chunk<COMP, DO_MIX, NT, true, VECS, THREADS, REDO>(A, row, chunk, stage, &s_count);
 }
+
+// random_a's candidate pass: Philox words only, no state.  Workgroups stay and go through the chunks of a row
+// in turn (gridDim.x is a multiple of kSegs, so that chunk c still appends to sub-list c % kSegs): it runs
+// beside a step's bandwidth-bound pass, whose waves fill the chip, and a workgroup per chunk spent more
+// time waiting for room than drawing (d = 21.6 M, n = 8: 395 us beside the pass, 77 alone; so 180).
+// grid (some, n), block 256.
+__global__ __launch_bounds__(256) void k_sel_draw(Args A) {
+  __shared__ uint2 stage[kStageCap];
+  __shared__ uint32_t s_count, s_base;
+  constexpr int VECS = kCompactVecs;
+  const int i = blockIdx.y, nvec = (A.d + 3) >> 2;
+  const uint32_t guess = A.ctl[i].guess_key;
+  const int seg = (int)blockIdx.x % kSegs;
+  uint2* cand = A.cand + ((int64_t)i * kSegs + seg) * A.seg_cap;
+  const int nchunk = (nvec + 256 * VECS - 1) / (256 * VECS);
+  if (threadIdx.x == 0) s_count = 0;
+  __syncthreads();
+  for (int chunk = blockIdx.x; chunk < nchunk; chunk += gridDim.x) {
+    const int m0 = chunk * (256 * VECS) + (threadIdx.x >> 6) * (64 * VECS) + (threadIdx.x & 63);
+    uint4 w[VECS];   // (also past the row's end, where nothing is listed: no branch between the chains)
+    philox_side_by_side<VECS>(A.vec_base + (uint32_t)m0, (uint32_t)i, A.t_lo, STREAM_RANDK | (A.t_hi << 8), A.seed_lo,
+                              A.seed_hi, w);
+#pragma unroll
+    for (int u = 0; u < VECS; ++u)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const int e = 4 * (m0 + 64 * u) + c;
+        const uint32_t key = ~pick(w[u], c);
+        if (key >= guess && e >= A.e_lo && e < A.d) {
+          const uint32_t slot = atomicAdd(&s_count, 1u);
+          if (slot < (uint32_t)kStageCap) {
+            stage[slot] = make_uint2(key, (uint32_t)e);
+          } else {   // more hits than the stage holds: append one by one
+            const uint32_t pos = atomicAdd(seg_counter(A, i, seg), 1u);
+            if (pos < A.seg_cap) cand[pos] = make_uint2(key, (uint32_t)e);
+          }
+        }
+      }
+    const bool last = chunk + (int)gridDim.x >= nchunk;
+    __syncthreads();
+    const uint32_t count = s_count < (uint32_t)kStageCap ? s_count : (uint32_t)kStageCap;
+    if (count > (uint32_t)kStageCap / 2 || last) {
+      __syncthreads();                       // (all have read the count)
+      if (threadIdx.x == 0) {
+        s_base = count != 0u ? atomicAdd(seg_counter(A, i, seg), count) : 0u;
+        s_count = 0;
+      }
+      __syncthreads();
+      for (uint32_t t = threadIdx.x; t < count; t += 256)
+        if (s_base + t < A.seg_cap) cand[s_base + t] = stage[t];
+    }
+    __syncthreads();
+  }
+}
+
 
 // The fallback of a failed guess on a long row, one launch.  A workgroup whose worker's list is
 // good leaves at once: a step whose guesses held pays for one launch of workgroups that read one
