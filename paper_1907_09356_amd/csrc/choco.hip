@@ -359,15 +359,17 @@ bool one_pass_topk(const choco_config& c) {
 }
 
 // top_a on rows that a workgroup selects out of its registers (k_row_compress)?  It saves a launch and the
-// way of the candidates through memory; the entries of a thread are worked through in turn, and every kept
-// one is marked in the map by an atomic.  us per step, candidate pass and select | out of registers:
-//   n = 8   d = 500 16.2 | 9.7   4,096, k = 41 16.7 | 12.1   6,000, k = 300 17.2 | 14.1   8,192, k = 81 17.0 | 14.5
-//           10,240, k = 10 16.6 | 14.4   k = 512 17.4 | 19.5
-//   n = 64  d = 1,000 18.0 | 13.0   4,096, k = 204 18.9 | 15.5   6,000, k = 300 19.6 | 18.0
-//           8,192, k = 81 18.4 | 17.4   k = 409 19.4 | 21.4
+// way of the candidates through memory; every kept entry costs a place in the map by an atomic.
+// us per step, candidate pass and select | out of registers:
+//   n = 8   d = 500, k = 25 16.2 | 9.9   1,000, k = 500 22.3 | 11.8   4,096, k = 41 16.7 | 11.5   k = 2,048 39 | 20   k = 4,096 25 | 56
+//           8,192, k = 163 16.5 | 13.1   k = 409 15.3-17.0 | 14.8   10,240, k = 102 16.7 | 13.6   k = 512 15.5-17.1 | 17.2
+//   n = 64  d = 1,000, k = 50 18.1 | 12.4   k = 1,000 44 | 29   2,000, k = 2,000 23 | 39   4,096, k = 204 18.9 | 14.6
+//           6,000, k = 1,800 23.4 | 20.3   8,192, k = 163 16.8-18.3 | 17.0   k = 245 17.1-18.7 | 18.5
+//           10,240, k = 102 18.1-19.3 | 17.4   k = 204 18.5-19.6 | 19.9
 bool short_rows(const choco_config& c) {
   if (c.compressor != CHOCO_Q_TOPK || c.nlayers > 0 || !fused_sparse_apply(c)) return false;
-  return c.d <= 6144 || (c.d <= 8192 && c.k <= 80);
+  if (c.d <= 6144) return 2 * c.k <= c.d || c.d <= 1024;
+  return c.d <= 8192 ? c.k <= 160 : c.d <= kMidLayerLen && c.k <= 128;
 }
 
 // gsgd in one pass over the state?  The entries whose level is not zero must be few: s ||v||_1 / ||v||_2 of a

@@ -11,7 +11,8 @@ from tests.parity_util import Pair
 def test_which_rows_are_selected_out_of_registers():
     out = recorded("""
 out = {}
-for d, k, kw in ((768, 7, {}), (769, 7, {}), (6144, 3000, {}), (6145, 80, {}), (6145, 81, {}), (8192, 80, {}), (8193, 8, {}),
+for d, k, kw in ((768, 7, {}), (769, 7, {}), (1024, 1024, {}), (1025, 1025, {}), (6144, 3072, {}), (6144, 3073, {}), (6145, 160, {}),
+                 (6145, 161, {}), (8192, 160, {}), (8193, 128, {}), (8193, 129, {}), (10240, 128, {}), (10241, 10, {}),
                  (1000, 10, dict(order=1)), (1000, 10, dict(mix_form=B.MIX_INCREMENTAL_S))):
     c = Context(5, d, B.Q_TOPK, k=k, **kw)
     out["%d %d %s" % (d, k, sorted(kw))] = [x[0] for x in c.step()][:-1]
@@ -20,16 +21,16 @@ c = Context(65, 1000, B.Q_TOPK, k=10)     # no tile of all rows
 out["n = 65"] = [x[0] for x in c.step()]
 """)
     assert out["768 7 []"] == ["k_row_compress<64>"]
-    for case in ("769 7 []", "6144 3000 []", "6145 80 []", "8192 80 []"):
-        assert out[case] == ["k_row_compress<1024>"], case
-    assert sum(any(x.startswith("k_row_compress") for x in l) for l in out.values()) == 5
+    rest = {"769 7 []", "1024 1024 []", "6144 3072 []", "6145 160 []", "8192 160 []", "8193 128 []", "10240 128 []"}
+    assert {c for c, l in out.items() if l == ["k_row_compress<1024>"]} == rest
+    assert sum(any(x.startswith("k_row_compress") for x in l) for l in out.values()) == 1 + len(rest)
 
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("n,d,k,grid,mode", [
     (3, 1, 1, 0, "step"), (4, 5, 2, 0, "halves"), (8, 767, 766, 0, "step"), (6, 768, 1, 0, "momentum"), (9, 769, 300, 0, "step"),
-    (2, 4097, 41, 0, "momentum"), (64, 1030, 50, 0, "step"), (5, 6144, 3000, 0, "halves"), (12, 8189, 80, 0, "step"),
-    (5, 700, 200, 3, "step"), (5, 3001, 900, 3, "step"), (3, 6144, 6144, 3, "step"),
+    (2, 4097, 41, 0, "momentum"), (64, 1030, 50, 0, "step"), (5, 6144, 3072, 0, "halves"), (12, 8189, 160, 0, "step"), (4, 10240, 128, 0, "step"),
+    (5, 700, 200, 3, "step"), (5, 3001, 900, 3, "step"), (3, 1024, 1024, 3, "step"),
 ])
 def test_rows_selected_out_of_registers(n, d, k, grid, mode):
     """Lengths around a wave's, a sweep's and the longest; ties (values on a grid); a scale that jumps, so that
