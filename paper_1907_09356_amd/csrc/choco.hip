@@ -155,7 +155,7 @@ size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 struct Layout {
   size_t xhat, s, row_ptr, col, w, ctl, seg_counts, chunk_sums, group_sums, hist16, cand, hist_parts, small_list, sel_idx, sel_val, keptmap, bitmap,
       layers, layer_work, long_tab, layer_guess, layer_scal, layer_groups, layer_group_first, layer_group_sums, layer_scale,
-      chunk_layer, planes, ovf_ring, ovf_pos, wire_rank, wire_word_off, wire_plane_off, sel_idx2, bitmap2, keptmap2, layer_scal2, qv, recs, rec_cols, onepass, mpart, total;
+      chunk_layer, planes, ovf_ring, ovf_pos, wire_rank, wire_word_off, wire_plane_off, sel_idx2, bitmap2, keptmap2, layer_scal2, qv, recs, rec_cols, ulps, uneven, onepass, mpart, total;
   int64_t wire_words, wire_plane_words;   // layer by layer: words of a worker's message / of one bit plane
   int32_t ngroup_items;
   uint32_t cand_cap, seg_cap;
@@ -553,6 +553,8 @@ Layout make_layout(const choco_config& c, int32_t nnz) {
   L.qv = take(fused_sparse_apply(c) && c.compressor == CHOCO_Q_RANDK ? state : 0);
   L.recs = take(one_pass ? (size_t)L.nchunks * kRecSlots * (size_t)c.n * sizeof(float2) : 0);
   L.rec_cols = take(one_pass ? (size_t)L.nchunks * 8 * sizeof(uint32_t) : 0);
+  L.ulps = take(one_pass ? (size_t)c.n * (size_t)ld : 0);
+  L.uneven = take(one_pass ? (size_t)L.nchunks : 0);
   L.onepass = take(one_pass ? sizeof(OnePassState) : 0);
   L.mpart = take(((size_t)kMetricsBlocks + 1) * 3 * sizeof(double));   // the blocks' sums, then the figures
   L.total = off;
@@ -1889,7 +1891,8 @@ int choco_init(const choco_config* cfg, float* x_dev, void* workspace_dev, size_
   A.sel_idx = (int32_t*)(base + L.sel_idx);
   A.sel_val = (float*)(base + L.sel_val);
   A.keptmap = ctx->one_pass ? nullptr : (uint32_t*)(base + L.keptmap);
-  ctx->onepass = OnePass{(float2*)(base + L.recs), (uint32_t*)(base + L.rec_cols), (OnePassState*)(base + L.onepass), 0};
+  ctx->onepass = OnePass{(float2*)(base + L.recs), (uint32_t*)(base + L.rec_cols), (int8_t*)(base + L.ulps), (uint8_t*)(base + L.uneven),
+                         (OnePassState*)(base + L.onepass), 0};
   A.Qv = (ctx->fused_sparse_apply && cfg->compressor == CHOCO_Q_RANDK) ? (float*)(base + L.qv) : nullptr;
   A.map_words = (A.ld + 31) / 32;
   A.bitmap = (uint32_t*)(base + L.bitmap);

@@ -18,9 +18,13 @@
 //   the norm trees)
 //   k_onepass_finish   top_a: the recorded columns whose kept set is not the expected one; tiles left unmixed
 //   k_onepass_encode   gsgd: the recorded columns; tiles left unmixed; everything where a bound did not hold
-// Every bit of the result is that of the two-pass form.  x' = x_mixed - gamma acc is exact for nearly all
-// entries (acc is formed again from the same xhat); the pass tries it, and records the columns where it
-// is not.  A tile with more than kRecSlots columns to record is left unmixed and done by the last kernel
+// Every bit of the result is that of the two-pass form.  x' is x_mixed - gamma acc (acc is formed again from
+// the same xhat) but for some units in the last place, in about |gamma acc / x'| of the entries; the pass
+// tries it and stores the difference, a byte per entry, for the rows of a tile that have one, and records
+// the columns where a byte does not hold it.  (n = 8, d = 28 M, xhat near x and apart by a few percent of it
+// between workers, us per step by gamma 0.002 | 0.02 | 0.1: top_a 681 | 885 | 1029, two passes 1059-1077; gsgd
+// 789 | 857 | 850, two passes 1182-1196.  Columns recorded instead filled the slots from gamma acc / x' of
+// a percent on.)  A tile with more than kRecSlots columns to record is left unmixed and done by the last kernel
 // (top_a: its candidates go to the lists one by one).
 #pragma once
 
@@ -36,6 +40,8 @@ struct OnePassState {
 struct OnePass {
   float2* recs;         // tiles x kRecSlots x n: x' and xhat of all workers in the recorded columns
   uint32_t* cols;       // tiles x 8: which columns of the tile are recorded; all bits: the tile was left unmixed
+  int8_t* ulps;         // n x ld: bits of x' less those of x_mixed - gamma acc, in the rows of tiles that are marked in
+  uint8_t* uneven;      // tiles: bit r: row r of the tile has such differences
   OnePassState* state;
   int32_t first;        // a context's first step
 };
@@ -136,7 +142,7 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_mix(Args A, OnePa
   lds_store4(tile + r * kChunk + lane * 4, hn);
   __syncthreads();
   vf4 xm = x;
-  uint32_t lost = 0u;
+  uint32_t lost = 0u, ulps = 0u;
   const vf4 acc = mix_sum_staged<0>(A, tile, r, lane, nb);
   if (mine) {
 #pragma unroll
@@ -144,10 +150,14 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_mix(Args A, OnePa
       const float step = A.gamma * acc[c];
       xm[c] = x[c] + step;
       const float back = xm[c] - step;
-      if (__float_as_uint(back) != __float_as_uint(x[c])) lost |= 1u << c;
+      const int32_t off = (int32_t)(__float_as_uint(x[c]) - __float_as_uint(back));
+      if (off != (int32_t)(int8_t)off) lost |= 1u << c;
+      else ulps |= (uint32_t)(off & 0xFF) << (8 * c);
     }
   }
-  reinterpret_cast<uint8_t*>(marks)[lane * 8 + r] = (uint8_t)(cand | lost);
+  const bool uneven = __ballot(ulps != 0u) != 0ull;
+  if (uneven && mine) *reinterpret_cast<uint32_t*>(P.ulps + o) = ulps;
+  reinterpret_cast<uint8_t*>(marks)[lane * 8 + r] = (uint8_t)(cand | lost | (uneven ? 0x10u : 0u));
   __syncthreads();
   const uint32_t dirty = fold_marks(marks[lane]);
   uint64_t db[4];
@@ -166,6 +176,8 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_mix(Args A, OnePa
   if (r == 0) {
     const uint32_t w = mask_word(open ? 0xFu : dirty, lane);
     if ((lane & 7) == 0) P.cols[(int64_t)tile_no * 8 + (lane >> 3)] = w;
+    if (lane == 0)   // (bit 4 of the rows' bytes, side by side)
+      P.uneven[tile_no] = (uint8_t)((((marks[0] >> 4) & 0x0101010101010101ull) * 0x0102040810204080ull) >> 56);
     if (open && lane == 0) P.state->open_step = A.t_lo;
   }
   if (open) {
@@ -350,10 +362,13 @@ __device__ __forceinline__ void take_back(const Args& A, const OnePass& P, float
   lds_store4(tile + r * kChunk + lane * 4, h);
   __syncthreads();
   const vf4 acc = mix_sum_staged<0>(A, tile, r, lane, nb);
+  uint32_t ulps = 0u;
+  if (mine && ((P.uneven[t] >> r) & 1u)) ulps = *reinterpret_cast<const uint32_t*>(P.ulps + o);
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
     const float step = A.gamma * acc[c];
-    x[c] = ((dirty >> c) & 1u) ? xr[c] : x[c] - step;
+    const int32_t off = (int32_t)(int8_t)(ulps >> (8 * c));
+    x[c] = ((dirty >> c) & 1u) ? xr[c] : __uint_as_float(__float_as_uint(x[c] - step) + (uint32_t)off);
   }
 }
 
