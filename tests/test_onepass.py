@@ -103,7 +103,8 @@ def test_one_pass_steps(n, d, k, topo, mode, align):
 @pytest.mark.timeout(300)
 def test_one_pass_taken_back():
     """Thresholds that fall by a factor between two steps (no list holds its k largest entries), with columns
-    whose mix has no exact inverse, tiles of such columns only, ties at the threshold, and NaN-free extremes."""
+    and whole tiles whose mix has no exact inverse (entries put right by units in the last place, or recorded), and
+    ties at the threshold."""
     n, d, k = 8, 3_150_336, 1500
     rng = np.random.default_rng(5)
     X0 = synth.normal_state(n, d, seed=3)
