@@ -579,14 +579,15 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_encode(Args A, On
         }
         const bool changed = __float_as_uint(hn) != __float_as_uint(R[u].h);
         const uint64_t any = __ballot(changed);
-        if (any == 0ull) continue;                               // (every lane takes part in the exchange)
-        const float acc = L.mix_sum(hn);
-        if (R[u].have && L.concerned(any)) {
-          const int64_t o = (int64_t)L.i * A.ld + R[u].col;
-          A.X[o] = R[u].x + A.gamma * acc;
-          if (changed) A.Xhat[o] = hn;
+        if (any != 0ull) {                                       // (every lane takes part in the exchange)
+          const float acc = L.mix_sum(hn);
+          if (R[u].have && L.concerned(any)) {
+            const int64_t o = (int64_t)L.i * A.ld + R[u].col;
+            A.X[o] = R[u].x + A.gamma * acc;
+            if (changed) A.Xhat[o] = hn;
+          }
         }
-        if (code != 0) {
+        if (code != 0) {   // (sent whether or not xhat is too large to show it)
           if (A.codes) A.codes[(int64_t)L.i * A.ld + R[u].col] = code;
           const uint32_t bit = 1u << (R[u].col & 31);
           uint32_t* plane = A.planes + (int64_t)L.i * A.nplanes * A.plane_words + ((uint32_t)R[u].col >> 5);

@@ -68,6 +68,15 @@ def graph(name, n):
     return synth.complete_csr(n) if name == "complete" else synth.ring_csr(n)
 
 
+def same_message(pair, det, tag):
+    """gsgd: the bit planes that the last step left decode to the oracle's levels times the step, every one."""
+    if pair.codes is None:
+        return
+    q = pair.gpu.unpack_messages(pair.gpu.pack_messages())[:, :pair.d].cpu().numpy()
+    step = np.float32(pair.gpu.last_scalars()[:, 3:4])
+    assert np.array_equal(q, det["codes"].astype(np.float32) * step), tag + ": messages differ"
+
+
 def steps(pair, grads, lr, mode, count, tag):
     for t in range(count):
         g = grads.next()
@@ -79,6 +88,8 @@ def steps(pair, grads, lr, mode, count, tag):
         else:
             det = pair.step(g, lr)
         pair.check(det, tag="%s step %d" % (tag, t))
+        same_message(pair, det, "%s step %d" % (tag, t))
+    return det
 
 
 @pytest.mark.gpu
@@ -152,12 +163,9 @@ def test_one_pass_gsgd(n, d, levels, topo, mode, align, outlier):
     pair = Pair(X0, graph(topo, n) if n > 2 else synth.complete_csr(2), 0.3, compressor=B.Q_QSGD, levels=levels, seed=9,
                 ld_align=align)
     try:
-        steps(pair, synth.GradientStream(n, d, seed=2), 0.05, mode, 4, mode)
-        msgs = pair.gpu.pack_messages()              # the bit planes that the last step left
-        q = pair.gpu.unpack_messages(msgs)[:, :d].cpu().numpy()
-        codes = pair.codes[:, :d].cpu().numpy()
-        assert np.array_equal(np.sign(q), np.sign(codes))
-        assert not outlier or np.abs(codes).max() == levels
+        det = steps(pair, synth.GradientStream(n, d, seed=2), 0.05, mode, 4, mode)
+        # (the columns that are 100 times as large hold s |v| / ||v|| up to 1.3 at eight levels, 0.65 at four)
+        assert np.abs(det["codes"]).max() >= (levels if outlier else 2 if levels >= 8 else 1)
     finally:
         pair.close()
 
@@ -188,5 +196,26 @@ def test_one_pass_gsgd_taken_back():
         pair.force_state()
         steps(pair, grads, 0.0, "step", 1, "zero")
         steps(pair, grads, 0.05, "step", 2, "again")
+    finally:
+        pair.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.timeout(300)
+def test_one_pass_gsgd_sends_what_xhat_cannot_show():
+    """Levels whose value is below half a unit in the last place of xhat: they are sent though xhat stays as it is."""
+    n, d, levels = 8, 3_200_000, 8
+    rng = np.random.default_rng(1)
+    X0 = np.tile(np.float32(1000.0) + rng.standard_normal(d).astype(np.float32), (n, 1))
+    pair = Pair(X0, synth.ring_csr(n), 0.3, compressor=B.Q_QSGD, levels=levels, seed=5)
+    zero = synth.GradientStream(n, d, seed=4)
+    try:
+        pair.ref.Xhat[:] = X0
+        for i in range(n):                                   # four entries per tile and row, one unit apart
+            pair.ref.X[i, i::64] = np.nextafter(X0[i, i::64], np.float32(0.0))
+        pair.force_state()
+        for t in range(3):
+            det = steps(pair, zero, 0.0, "step", 1, "unit %d" % t)
+            assert np.all(np.abs(det["codes"]).sum(axis=1) > 500) and np.array_equal(pair.ref.Xhat, X0)
     finally:
         pair.close()
