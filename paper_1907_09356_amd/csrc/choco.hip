@@ -99,7 +99,7 @@ struct choco_ctx {
   bool fused_sparse_apply;   // ... whose update of xhat rides on the tile mix pass (direct form, compress-then-mix)
   bool one_pass;          // top_a, gsgd: one pass over the state (choco_onepass.h)
   OnePass onepass;
-  bool one_pass_begun;    // ... and has taken a step (later ones have a threshold or a norm to go by)
+  bool one_pass_begun;    // gsgd: ... and has taken a step (later ones have a norm to go by)
   bool short_rows;        // top_a: a workgroup selects a row out of its registers
   bool values_in_qv;      // random_a after such a step: the kept values are in Qv, not yet in the list
   int mix_form;           // resolved: CHOCO_MIX_INCREMENTAL_S or CHOCO_MIX_DIRECT
@@ -1195,23 +1195,19 @@ int look_ahead_end(choco_ctx* ctx, const Args& A, uint64_t base) {
 // top_a in one pass (choco_onepass.h).  The kernels behind the pass have little or nothing to do as a
 // rule: workgroups to fill the chip once, which go through the tiles in turn.
 int gossip_one_pass_topk(choco_ctx* ctx, const Args& F) {
-  OnePass P = ctx->onepass;
-  P.first = ctx->one_pass_begun ? 0 : 1;
+  const OnePass& P = ctx->onepass;
   Args A = F;
   A.G = nullptr;
   const size_t lds = (size_t)A.n * kChunk * sizeof(float);
   const dim3 block(64u * (unsigned)A.n);
   const int waves = (A.nchunks + kRecTiles - 1) / kRecTiles;
   LAUNCH(ctx, F.G ? KID_ONEPASS_MIX_SGD : KID_ONEPASS_MIX, k_onepass_mix<Q_TOPK>, dim3((unsigned)A.nchunks), block, lds, F, P);
-  if (!P.first) {
-    LAUNCH(ctx, KID_ONEPASS_LIST, k_onepass_list, dim3((unsigned)std::min((waves + 3) / 4, 2048)), dim3(256), 0, A, P, A.nchunks);
-    LAUNCH(ctx, KID_ONEPASS_RESTORE, k_onepass_restore, dim3((unsigned)std::min(A.nchunks, 512)), block, lds, A, P, A.nchunks);
-  }
+  LAUNCH(ctx, KID_ONEPASS_LIST, k_onepass_list, dim3((unsigned)std::min((waves + 3) / 4, 2048)), dim3(256), 0, A, P, A.nchunks);
+  LAUNCH(ctx, KID_ONEPASS_RESTORE, k_onepass_restore, dim3((unsigned)std::min(A.nchunks, 512)), block, lds, A, P, A.nchunks);
   launch_exact_select<Q_TOPK, true>(ctx, A);
   LAUNCH(ctx, KID_ONEPASS_FINISH, k_onepass_finish, dim3((unsigned)std::min((waves + A.n - 1) / A.n, 1024)), block, lds,
          A, P, A.nchunks);
   LAUNCH_CHECK(ctx);
-  ctx->one_pass_begun = true;
   return CHOCO_OK;
 }
 
@@ -1892,7 +1888,7 @@ int choco_init(const choco_config* cfg, float* x_dev, void* workspace_dev, size_
   A.sel_val = (float*)(base + L.sel_val);
   A.keptmap = ctx->one_pass ? nullptr : (uint32_t*)(base + L.keptmap);
   ctx->onepass = OnePass{(float2*)(base + L.recs), (uint32_t*)(base + L.rec_cols), (int8_t*)(base + L.ulps), (uint8_t*)(base + L.uneven),
-                         (OnePassState*)(base + L.onepass), 0};
+                         (OnePassState*)(base + L.onepass)};
   A.Qv = (ctx->fused_sparse_apply && cfg->compressor == CHOCO_Q_RANDK) ? (float*)(base + L.qv) : nullptr;
   A.map_words = (A.ld + 31) / 32;
   A.bitmap = (uint32_t*)(base + L.bitmap);

@@ -34,7 +34,7 @@ namespace choco {
 
 // What the one-pass kernels need beside the argument block of all.
 struct OnePassState {
-  uint32_t redo_all;    // X holds x - lr g everywhere: every tile is mixed by the last kernel
+  uint32_t redo_all;    // top_a: X holds x - lr g everywhere: every tile is mixed by the last kernel
   uint32_t open_step;   // (low word of the) last step in which a tile was left unmixed
 };
 struct OnePass {
@@ -43,7 +43,6 @@ struct OnePass {
   int8_t* ulps;         // n x ld: bits of x' less those of x_mixed - gamma acc, in the rows of tiles that are marked in
   uint8_t* uneven;      // tiles: bit r: row r of the tile has such differences
   OnePassState* state;
-  int32_t first;        // a context's first step
 };
 
 // Slots per tile of 256 columns.  A slot is 8 n bytes, so the records are a quarter of an array of the
@@ -78,6 +77,12 @@ __device__ __forceinline__ float2* record_of(const Args& A, const OnePass& P, in
 __device__ __forceinline__ bool left_open(uint2 w) { return (w.x & w.y) == 0xFFFFFFFFu; }
 static_assert(kRecSlots < 64, "two full words of a mask mean an open tile");
 
+// top_a: the step is the first after choco_init, there is no threshold to go by (the guess lies above every key;
+// the rows get theirs all in the same step).  The device tells, not the host: a first step that was captured
+// into a graph is an ordinary one when it is replayed (n = 8, d = 12 M: 1616 us a replay when each went as a
+// first step, 361 as it is; two passes 478).
+__device__ __forceinline__ bool no_guess_yet(uint32_t guess_key) { return guess_key == 0xFFFFFFFFu; }
+
 // grid ceil(d / 256), block 64 n (wave r: row r), dynamic LDS n x 256 floats.
 template <int COMP>
 __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_mix(Args A, OnePass P) {
@@ -108,7 +113,7 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_mix(Args A, OnePa
     x = local_update_regs(A, x, g, m);
     if (mom) store4<true>(A.M + o, m);
   }
-  if (COMP == Q_TOPK && P.first) {   // no threshold to go by: the last kernel does all tiles
+  if (COMP == Q_TOPK && no_guess_yet(guess)) {   // the last kernel does all tiles
     if (mine && A.G) store4<true>(A.X + o, x);
     return;
   }
@@ -389,7 +394,7 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_restore(Args A, O
   if (lane == 0 && (!fits || sum < (unsigned long long)A.k)) s_bad = 1u;
   __syncthreads();
   if (blockIdx.x == 0 && threadIdx.x == 0) P.state->redo_all = s_bad;
-  if (s_bad == 0u) return;
+  if (s_bad == 0u || no_guess_yet(A.ctl[0].guess_key)) return;   // (the first step: nothing has been mixed)
   const RowNbrs nb = nbr_fetch(A, nbr_span<1, kOnePassRows>(A, r, lane), lane);
   for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
     const uint32_t* cols = P.cols + (int64_t)t * 8;
@@ -412,7 +417,7 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_finish(Args A, On
   extern __shared__ float tile[];
   __shared__ ushort2 lists[kOnePassRows][kRecTiles * kRecSlots];
   const int r = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const bool all = P.first || P.state->redo_all != 0u;
+  const bool all = P.state->redo_all != 0u;
   if (all || P.state->open_step == A.t_lo) {
     const RowNbrs nb = nbr_fetch(A, nbr_span<1, kOnePassRows>(A, r, lane), lane);
     const uint64_t kstar = A.ctl[r].kstar;

@@ -25,16 +25,14 @@ for name, n, d, kw in (
     out[name] = [[x[0].split("<")[0] for x in y] for y in (first, l)] + [l[0][1:3]]
     c.close()
 """)
-    # choco_init gives the first step no threshold to go by: nothing to list or to take back
-    select = ["k_sel_fallback", "k_sel_refine"]
-    first = ["k_onepass_mix"] + select + ["k_onepass_finish"]
-    later = ["k_onepass_mix", "k_onepass_list", "k_onepass_restore"] + select + ["k_onepass_finish"]
+    # (also the first step, which has no threshold to go by: it may be captured, and replayed as a later one)
+    launches = ["k_onepass_mix", "k_onepass_list", "k_onepass_restore", "k_sel_fallback", "k_sel_refine", "k_onepass_finish"]
     one = {"n8", "n8 momentum", "n2", "many kept, large", "odd"}
     for name, (a, b, shape) in out.items():
         if name in one:
             drop = {"k_sel_hist_parts", "k_sel_emit_parts"}
             norm = lambda l: ["k_sel_refine" if x == "k_sel_finish" else x for x in l if x not in drop]  # noqa: E731
-            assert (norm(a), norm(b)) == (first, later), name
+            assert norm(a) == norm(b) == launches, name
         else:
             assert not any(x.startswith("k_onepass") for x in a + b), name
     assert out["odd"][2] == ["12501x1x1", "512x1x1"] and out["n2"][2][1] == "128x1x1"
@@ -108,6 +106,38 @@ def test_one_pass_steps(n, d, k, topo, mode, align):
         steps(pair, synth.GradientStream(n, d, seed=2), 0.05, mode, 4, mode)
     finally:
         pair.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.timeout(300)
+def test_one_pass_captured_first_step():
+    """A first step that was captured: its replays go by the thresholds of those before, like eager steps."""
+    import torch
+    n, d, k = 8, 3_150_336, 2000
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        pair = Pair(synth.normal_state(n, d, seed=1), synth.ring_csr(n), 0.3, compressor=B.Q_TOPK, k=k)
+        grads = synth.GradientStream(n, d, seed=2)
+        try:
+            G = grads.next()
+            Gd = torch.zeros_like(pair.X)
+            Gd[:, :d] = torch.from_numpy(np.ascontiguousarray(G, dtype=np.float32)).to(pair.X.device)
+            pair.gpu.sync()
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=side):
+                pair.gpu.step(Gd, 0.05)
+            side.synchronize()
+            for t in range(6):
+                if t == 3:                                   # the program's own work between the replays
+                    steps(pair, grads, 0.05, "step", 1, "eager")
+                graph.replay()
+                side.synchronize()
+                pair.ref.sgd_step(G, 0.05)
+                pair.check(pair.ref.gossip_step(want_details=True), tag="replay %d" % t)
+            scal = pair.gpu.last_scalars()
+            assert np.all(scal[:, 3] == 0) and np.all(scal[:, 4] == 1), "only the first step has no threshold"
+        finally:
+            pair.close()
 
 
 @pytest.mark.gpu
