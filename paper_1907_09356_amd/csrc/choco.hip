@@ -372,6 +372,9 @@ bool short_rows(const choco_config& c) {
   return c.d <= 8192 ? c.k <= 160 : c.d <= kMidLayerLen && c.k <= 128;
 }
 
+// gsgd: of a tile's columns, those in which a row is expected to have a level above zero.
+float marked_per_row(const choco_config& c) { return (float)(kChunk * 0.8 * (double)c.levels / std::sqrt((double)c.d)); }
+
 // gsgd in one pass over the state?  The entries whose level is not zero must be few: s ||v||_1 / ||v||_2 of a
 // row, 0.8 s sqrt(d) of a Gaussian one (at most a quarter more).  us per step, two passes | one (marked
 // columns of a tile expected):
@@ -384,8 +387,7 @@ bool one_pass_qsgd(const choco_config& c) {
   if (c.compressor != CHOCO_Q_QSGD || c.nlayers > 0 || c.order != CHOCO_ORDER_COMPRESS_THEN_MIX) return false;
   if (c.n < 2 || c.n > kOnePassRows) return false;
   const double mib = (double)c.n * (double)resolve_ld(c) * sizeof(float) / 1048576.0;
-  const double marked = (double)kChunk * c.n * 0.8 * (double)c.levels / std::sqrt((double)c.d);
-  return mib > 96.0 && marked <= 14.0;
+  return mib > 96.0 && (double)c.n * marked_per_row(c) <= 14.0;
 }
 
 // The layers of a top_a / random_a configuration that are too long for the layer kernel.
@@ -967,7 +969,8 @@ int gossip_one_pass_qsgd(choco_ctx* ctx, const Args& F) {
   LAUNCH(ctx, F.G ? KID_ONEPASS_MIX_SGD : KID_ONEPASS_MIX, k_onepass_mix<Q_QSGD>, dim3((unsigned)A.nchunks), block, lds, F, ctx->onepass);
   LAUNCH(ctx, KID_GROUP_REDUCE, k_group_reduce, dim3((unsigned)((A.ngroups + 15) / 16), (unsigned)A.n), dim3(256), 0, A);
   LAUNCH(ctx, KID_DENSE_FINALISE, (k_dense_finalise<Q_QSGD, true>), dim3((unsigned)A.n), dim3(256), 0, A);
-  LAUNCH(ctx, KID_ONEPASS_ENCODE, k_onepass_encode, dim3((unsigned)std::min((waves + A.n - 1) / A.n, 1024)), block, lds, A, ctx->onepass, A.nchunks);
+  LAUNCH(ctx, KID_ONEPASS_ENCODE, k_onepass_encode, dim3((unsigned)std::max(std::min((waves + A.n - 1) / A.n, 1024), std::min(A.nchunks, 4096 / A.n))),
+         block, lds, A, ctx->onepass, A.nchunks);
   LAUNCH_CHECK(ctx);
   return CHOCO_OK;
 }
@@ -1205,7 +1208,7 @@ int gossip_one_pass_topk(choco_ctx* ctx, const Args& F) {
   LAUNCH(ctx, KID_ONEPASS_LIST, k_onepass_list, dim3((unsigned)std::min((waves + 3) / 4, 2048)), dim3(256), 0, A, P, A.nchunks);
   LAUNCH(ctx, KID_ONEPASS_RESTORE, k_onepass_restore, dim3((unsigned)std::min(A.nchunks, 512)), block, lds, A, P, A.nchunks);
   launch_exact_select<Q_TOPK, true>(ctx, A);
-  LAUNCH(ctx, KID_ONEPASS_FINISH, k_onepass_finish, dim3((unsigned)std::min((waves + A.n - 1) / A.n, 1024)), block, lds,
+  LAUNCH(ctx, KID_ONEPASS_FINISH, k_onepass_finish, dim3((unsigned)std::max(std::min((waves + A.n - 1) / A.n, 1024), std::min(A.nchunks, 8192 / A.n))), block, lds,
          A, P, A.nchunks);
   LAUNCH_CHECK(ctx);
   return CHOCO_OK;
@@ -1888,7 +1891,7 @@ int choco_init(const choco_config* cfg, float* x_dev, void* workspace_dev, size_
   A.sel_val = (float*)(base + L.sel_val);
   A.keptmap = ctx->one_pass ? nullptr : (uint32_t*)(base + L.keptmap);
   ctx->onepass = OnePass{(float2*)(base + L.recs), (uint32_t*)(base + L.rec_cols), (int8_t*)(base + L.ulps), (uint8_t*)(base + L.uneven),
-                         (OnePassState*)(base + L.onepass)};
+                         (OnePassState*)(base + L.onepass), marked_per_row(*cfg)};
   A.Qv = (ctx->fused_sparse_apply && cfg->compressor == CHOCO_Q_RANDK) ? (float*)(base + L.qv) : nullptr;
   A.map_words = (A.ld + 31) / 32;
   A.bitmap = (uint32_t*)(base + L.bitmap);

@@ -84,6 +84,7 @@ struct OnePassCtl {
   uint32_t expect_key, expected_key, expect_rank;
   // gsgd: the bound on s / ||v||_2 that the next step's pass goes by, and the one that this step's did
   float bound_r, bounded_r;
+  uint32_t held;   // not 0: the next step's pass leaves all tiles unmixed (the same in every row)
 };
 
 // One layer of a worker's vector when the operator is applied layer by layer.

@@ -36,13 +36,16 @@ namespace choco {
 struct OnePassState {
   uint32_t redo_all;    // top_a: X holds x - lr g everywhere: every tile is mixed by the last kernel
   uint32_t open_step;   // (low word of the) last step in which a tile was left unmixed
+  uint32_t failures;    // of what the pass went by, lately (judge_step)
 };
+constexpr uint32_t kHeldFailures = 1, kHeldWide = 2;   // OnePassCtl::held
 struct OnePass {
   float2* recs;         // tiles x kRecSlots x n: x' and xhat of all workers in the recorded columns
   uint32_t* cols;       // tiles x 8: which columns of the tile are recorded; all bits: the tile was left unmixed
   int8_t* ulps;         // n x ld: bits of x' less those of x_mixed - gamma acc, in the rows of tiles that are marked in
   uint8_t* uneven;      // tiles: bit r: row r of the tile has such differences
   OnePassState* state;
+  float marked_per_row; // gsgd: columns of a tile that a row is expected to mark where the bound is s / ||v|| itself
 };
 
 // Slots per tile of 256 columns.  A slot is 8 n bytes, so the records are a quarter of an array of the
@@ -50,6 +53,7 @@ struct OnePass {
 constexpr int kRecSlots = 32;
 constexpr int kOnePassRows = 8;     // a row per wave; n lanes of a group of eight where records are read
 constexpr int kRecTiles = 16;       // tiles whose records a wave goes through together
+constexpr float kWide = 24.0f;      // columns that a tile is expected to have marked above which all tiles are left open
 
 // Columns of the lane's 4-vector that some wave marked (a byte per wave).
 __device__ __forceinline__ uint32_t fold_marks(uint64_t m) {
@@ -83,6 +87,38 @@ static_assert(kRecSlots < 64, "two full words of a mask mean an open tile");
 // first step, 361 as it is; two passes 478).
 __device__ __forceinline__ bool no_guess_yet(uint32_t guess_key) { return guess_key == 0xFFFFFFFFu; }
 
+// top_a, a tile left open: the row's candidates in it (bits `cand` of the lane's 4-vector v) straight to the list.
+__device__ __forceinline__ void list_here(const Args& A, int r, int tile_no, uint32_t cand, vf4 v, int e) {
+  const int seg = tile_no % kSegs;
+#pragma unroll
+  for (int c = 0; c < 4; ++c)
+    if ((cand >> c) & 1u) {
+      const uint32_t at = atomicAdd(seg_counter(A, r, seg), 1u);
+      if (at < A.seg_cap) A.cand[((int64_t)r * kSegs + seg) * A.seg_cap + at] = make_uint2(__float_as_uint(v[c]), (uint32_t)(e + c));
+    }
+}
+
+// A step whose threshold or bound fails costs the pass, its undoing and the second form; where that happens to
+// about every other step it is better to leave all tiles unmixed and do them once (16 bytes per entry here and
+// 16 in the last kernel, as many as two passes take).  A failure counts two and a step that went well takes one
+// back, up to kHeldMost; tiles are left open from kHeldFrom on, down to kHeldTo.  gsgd and top_a also leave them for
+// one step when more columns are going to be marked than there are slots for.
+//   us per step, n = 8, d = 12 M: two passes | one pass always | as here
+//   gsgd, the gradient step to and fro (norms by 5)   503 | 788 | 590    every other pair of steps 503 | 517 | 473
+//         to or fro by chance                         503 | 384 | 374    a tenth of the entries moving 507 | 364 | 358
+//   top_a, the gradient step to and fro (all lists fail) 1773 | 1888 | 1657   by chance 1191 | 1317 | 1238
+// (The last kernel's whole tiles are bound by the encoding's arithmetic, with Philox, and by two workgroups of its 95
+// registers to a compute unit: 336 us for what k_dense_apply_mix does in 351 with the gradients to read again.)
+// One thread calls it, after k_onepass_mix has read the state and before the next step's does.
+constexpr int kHeldFrom = 6, kHeldTo = 2, kHeldMost = 12;
+__device__ __forceinline__ void judge_step(const Args& A, OnePassState* S, bool failed, bool wide) {
+  const int count = failed ? min((int)S->failures + 2, kHeldMost) : max((int)S->failures - 1, 0);
+  S->failures = (uint32_t)count;
+  const bool was = onepass_ctl(A)[0].held == kHeldFailures;
+  const uint32_t held = count >= kHeldFrom || (was && count > kHeldTo) ? kHeldFailures : wide ? kHeldWide : 0u;
+  for (int i = 0; i < A.n; ++i) onepass_ctl(A)[i].held = held;
+}
+
 // grid ceil(d / 256), block 64 n (wave r: row r), dynamic LDS n x 256 floats.
 template <int COMP>
 __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_mix(Args A, OnePass P) {
@@ -105,6 +141,7 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_mix(Args A, OnePa
   const RowSpan span = nbr_span<1, kOnePassRows>(A, r, lane);
   const uint32_t guess = A.ctl[r].guess_key, expect = onepass_ctl(A)[r].expect_key;
   const float bound = onepass_ctl(A)[r].bound_r;
+  const bool held = onepass_ctl(A)[r].held != 0u;
   if (r == 0) marks[lane] = 0u;    // (bytes of rows that there are not)
   uint4 words = make_uint4(0, 0, 0, 0);
   if (COMP == Q_QSGD) words = random_words(A, r, (uint32_t)(e >> 2), STREAM_DITHER);
@@ -143,6 +180,13 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_mix(Args A, OnePa
   if (COMP == Q_QSGD) {
     const double t = wave_tree_sum(mine ? lane_terms<Q_QSGD>(x - h, e, A.d) : 0.0);
     if (lane == 0) A.chunk_sums[(int64_t)r * A.nchunks + tile_no] = t;
+  }
+  if (held) {
+    if (mine && A.G) store4<true>(A.X + o, x);
+    if (COMP == Q_TOPK) list_here(A, r, tile_no, cand, x - h, e);
+    if (r == 0 && (lane & 7) == 0) P.cols[(int64_t)tile_no * 8 + (lane >> 3)] = 0xFFFFFFFFu;
+    if (tile_no == 0 && threadIdx.x == 0) P.state->open_step = A.t_lo;
+    return;
   }
   lds_store4(tile + r * kChunk + lane * 4, hn);
   __syncthreads();
@@ -186,14 +230,7 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_mix(Args A, OnePa
     if (open && lane == 0) P.state->open_step = A.t_lo;
   }
   if (open) {
-#pragma unroll
-    for (int c = 0; c < 4; ++c)
-      if (COMP == Q_TOPK && ((cand >> c) & 1u)) {
-        const int seg = tile_no % kSegs;
-        const uint32_t at = atomicAdd(seg_counter(A, r, seg), 1u);
-        if (at < A.seg_cap)
-          A.cand[((int64_t)r * kSegs + seg) * A.seg_cap + at] = make_uint2(__float_as_uint(x[c] - h[c]), (uint32_t)(e + c));
-      }
+    if (COMP == Q_TOPK) list_here(A, r, tile_no, cand, x - h, e);
   } else if (mine && dirty != 0u) {
     const uint64_t below = (1ull << lane) - 1ull;
     int slot = 0;
@@ -382,9 +419,10 @@ __device__ __forceinline__ void take_back(const Args& A, const OnePass& P, float
 // lists' lengths and leave.  grid any, block 64 n, dynamic LDS n x 256 floats.
 __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_restore(Args A, OnePass P, int32_t ntiles) {
   extern __shared__ float tile[];
-  __shared__ uint32_t s_bad;
+  __shared__ uint32_t s_bad, s_listed;
   const int r = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  if (threadIdx.x == 0) s_bad = 0u;
+  if (threadIdx.x == 0) s_bad = s_listed = 0u;
+  const bool first = no_guess_yet(A.ctl[0].guess_key);
   __syncthreads();
   const uint32_t raw = lane < kSegs ? *seg_counter(A, r, lane) : 0u;
   unsigned long long sum = raw;
@@ -392,9 +430,13 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_restore(Args A, O
   for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off, 64);
   const bool fits = __ballot(raw > A.seg_cap) == 0ull;
   if (lane == 0 && (!fits || sum < (unsigned long long)A.k)) s_bad = 1u;
+  if (lane == 0) atomicAdd(&s_listed, (uint32_t)(sum < (1u << 28) ? sum : (1u << 28)));
   __syncthreads();
-  if (blockIdx.x == 0 && threadIdx.x == 0) P.state->redo_all = s_bad;
-  if (s_bad == 0u || no_guess_yet(A.ctl[0].guess_key)) return;   // (the first step: nothing has been mixed)
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    P.state->redo_all = s_bad;
+    if (!first) judge_step(A, P.state, s_bad != 0u, (float)kChunk * (float)s_listed > kWide * (float)A.d);
+  }
+  if (s_bad == 0u || first) return;   // (in the first step nothing has been mixed)
   const RowNbrs nb = nbr_fetch(A, nbr_span<1, kOnePassRows>(A, r, lane), lane);
   for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
     const uint32_t* cols = P.cols + (int64_t)t * 8;
@@ -519,8 +561,13 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_encode(Args A, On
   __shared__ ushort2 lists[kOnePassRows][kRecTiles * kRecSlots];
   const int r = threadIdx.x >> 6, lane = threadIdx.x & 63;
   bool all = false;
-  for (int j = 0; j < A.n; ++j)
-    all = all || !(A.ctl[j].scale_r <= onepass_ctl(A)[j].bounded_r) || !(A.ctl[j].scale_step <= 3.402823466e38f);
+  float marked = 0.0f;   // columns of a tile that the next step is expected to mark
+  for (int j = 0; j < A.n; ++j) {
+    const float now = A.ctl[j].scale_r;
+    all = all || !(now <= onepass_ctl(A)[j].bounded_r) || !(A.ctl[j].scale_step <= 3.402823466e38f);
+    marked += P.marked_per_row * (now > 0.0f ? onepass_ctl(A)[j].bound_r / now : 0.0f);
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) judge_step(A, P.state, all, marked > kWide);
   if (all || P.state->open_step == A.t_lo) {
     const RowNbrs nb = nbr_fetch(A, nbr_span<1, kOnePassRows>(A, r, lane), lane);
     RowScale<Q_QSGD> sc;

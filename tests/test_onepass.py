@@ -249,3 +249,64 @@ def test_one_pass_gsgd_sends_what_xhat_cannot_show():
             assert np.all(np.abs(det["codes"]).sum(axis=1) > 500) and np.array_equal(pair.ref.Xhat, X0)
     finally:
         pair.close()
+
+
+def bounds_missed(r):
+    """gsgd, from s / ||v|| of each row step by step (the first is the two-pass step): which later steps fail."""
+    r = np.float32(r)
+    missed = []
+    for t in range(2, len(r) + 1):
+        before = r[t - 3] if t > 2 else np.zeros_like(r[0])
+        change = np.where(before > 0, np.minimum(np.abs(r[t - 2] / np.where(before > 0, before, 1) - 1), 1), 0)
+        missed.append(bool(t <= len(r) and np.any(r[t - 1] > r[t - 2] * (1.02 + 2 * change))))
+    return missed
+
+
+def held_back(missed):
+    """Two for a failure, one back for a step that went well; held from six on, down to two."""
+    count, held, out = 0, False, []
+    for m in missed:
+        out.append(held)
+        count = min(count + 2, 12) if m else max(count - 1, 0)
+        held = count >= 6 or (held and count > 2)
+    return out
+
+
+@pytest.mark.gpu
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("op", ["topk", "qsgd"])
+def test_one_pass_held_back(op):
+    """Failures in a row, after which the pass leaves all tiles unmixed (also through a further failure), and steps that
+    go well until it mixes again; gsgd then has norms that grow, with a bound too wide for the slots."""
+    n, d = 8, 3_200_100
+    kw = dict(compressor=B.Q_TOPK, k=1500) if op == "topk" else dict(compressor=B.Q_QSGD, levels=12)
+    X0 = synth.normal_state(n, d, seed=3)
+    pair = Pair(X0, synth.ring_csr(n), 0.2, seed=2, **kw)
+    grads = synth.GradientStream(n, d, seed=4)
+    figures = []
+
+    def go(lr, count, tag):
+        for _ in range(count):
+            steps(pair, grads, lr, "step", 1, "%s, step %d" % (tag, len(figures)))
+            figures.append(pair.gpu.last_scalars()[:, 4 if op == "topk" else 2].copy())
+
+    try:
+        go(1e-4, 2, "start")
+        for shrink in range(1, 5):
+            pair.ref.X[:] = X0 * np.float32(1e-3 ** shrink)
+            pair.ref.Xhat[:] = 0
+            pair.force_state()
+            go(0.0, 1, "failing")
+        go(0.0, 12, "well again")
+        if op == "topk":
+            missed = [bool(np.any(b > a)) for a, b in zip(figures, figures[1:])]
+        else:
+            missed = bounds_missed(figures)
+        held = held_back(missed)
+        assert missed[1:5] == [True] * 4 and held[4] and not held[-1], (missed, held)
+        if op == "qsgd":
+            pair.ref.X[:] = pair.ref.Xhat + (pair.ref.X - pair.ref.Xhat) * np.float32(5)
+            pair.force_state()
+            go(0.0, 3, "grown")
+    finally:
+        pair.close()
