@@ -359,17 +359,26 @@ bool one_pass_topk(const choco_config& c) {
 }
 
 // top_a on rows that a workgroup selects out of its registers (k_row_compress)?  It saves a launch and the
-// way of the candidates through memory; every kept entry costs a place in the map by an atomic.
-// us per step, candidate pass and select | out of registers:
-//   n = 8   d = 500, k = 25 16.2 | 9.9   1,000, k = 500 22.3 | 11.8   4,096, k = 41 16.7 | 11.5   k = 2,048 39 | 20   k = 4,096 25 | 56
-//           8,192, k = 163 16.5 | 13.1   k = 409 15.3-17.0 | 14.8   10,240, k = 102 16.7 | 13.6   k = 512 15.5-17.1 | 17.2
-//   n = 64  d = 1,000, k = 50 18.1 | 12.4   k = 1,000 44 | 29   2,000, k = 2,000 23 | 39   4,096, k = 204 18.9 | 14.6
-//           6,000, k = 1,800 23.4 | 20.3   8,192, k = 163 16.8-18.3 | 17.0   k = 245 17.1-18.7 | 18.5
-//           10,240, k = 102 18.1-19.3 | 17.4   k = 204 18.5-19.6 | 19.9
+// way of the candidates through memory, but one workgroup goes through the whole row whatever k is, and longer
+// where the threshold is not near the last one.
+// us per step, candidate pass and select | out of registers; gradient steps of one size, averaging from xhat = 0,
+// gradient steps whose size moves by half from one to the next:
+//   n = 8   d = 500, k = 25      17.6 | 13.4   17.4 | 12.3   17.6 | 13.7      1,000, k = 900    19.9 | 15.0   32.7 | 14.2   19.7 | 15.6
+//           4,096, k = 41        17.7 | 13.8   17.5 | 13.8   17.7 | 15.3      6,144, k = 1,200  20.4 | 15.0   32.8 | 19.8   20.4 | 19.2
+//           8,192, k = 160       17.7 | 15.6   17.6 | 16.5   17.8 | 18.3      10,240, k = 100   17.6 | 16.0   17.5 | 16.0   17.8 | 17.9
+//   n = 16  8,192, k = 160       17.9 | 16.0   17.9 | 17.8   17.9 | 18.9      10,240, k = 128   18.1 | 16.9   18.0 | 17.9   18.2 | 18.7
+//   n = 32  7,168, k = 160       18.7 | 16.5   18.5 | 18.4   18.8 | 19.3      8,192, k = 160    18.1 | 16.7   18.1 | 18.8   18.1 | 19.5
+//   n = 48  8,192, k = 160       19.2 | 18.1   19.0 | 20.2   19.2 | 20.9      10,240, k = 128   20.1 | 19.0   19.5 | 20.3   20.3 | 21.0
+//   n = 64  4,096, k = 204       20.4 | 17.0   19.9 | 18.2   20.3 | 19.5      6,144, k = 1,200  23.9 | 18.2   22.9 | 20.9   23.9 | 22.6
+//           8,192, k = 160       19.6 | 18.7   19.2 | 20.6   19.6 | 21.5      10,240, k = 128   21.0 | 19.7   20.0 | 20.9   21.1 | 21.8
+//           8,192, k = 40        19.3 | 17.4   18.9 | 17.0   19.3 | 18.7      10,240, k = 60    20.6 | 18.8   19.7 | 18.6   20.6 | 20.8
+//   k above half of d: n = 8, d = 4,096, k = 4,096 25 | 56, n = 64, d = 2,000, k = 2,000 23 | 39 (kept by atomics)
+// It loses up to 8 % at d = 10,240 where all values are a few units in the last place of x (19.7 | 21.2 at n = 64, k = 60).
 bool short_rows(const choco_config& c) {
   if (c.compressor != CHOCO_Q_TOPK || c.nlayers > 0 || !fused_sparse_apply(c)) return false;
   if (c.d <= 6144) return 2 * c.k <= c.d || c.d <= 1024;
-  return c.d <= 8192 ? c.k <= 160 : c.d <= kMidLayerLen && c.k <= 128;
+  if (c.d > kMidLayerLen) return false;
+  return c.k <= 64 || (c.n <= 32 && c.k <= (c.d <= 8192 ? 160 : 128));
 }
 
 // gsgd: of a tile's columns, those in which a row is expected to have a level above zero.
@@ -1254,6 +1263,9 @@ int gossip_sparse(choco_ctx* ctx, const Args& F) {
     const int kid = C.G ? KID_ROW_COMPRESS_SGD : KID_ROW_COMPRESS;
     // (a wave up to 768 entries: n = 8, d = 500 9.7 us per step, with 1024 threads 10.5)
     if (A.d <= kWaveLayerLen) LAUNCH(ctx, kid, k_row_compress<64>, dim3((unsigned)A.n), dim3(64), 0, C);
+    // (its kept entries marked by whole words of the map or by an atomic each: n = 8, d = 10,240, k = 20 15.5 | 15.4,
+    // 8,192, k = 40 14.8 | 14.8, k = 160 15.6 | 15.9; n = 64, d = 1,000, k = 900 17 | 25)
+    else if (A.k > 48) LAUNCH(ctx, kid, (k_row_compress<1024, true>), dim3((unsigned)A.n), dim3(1024), 0, C);
     else LAUNCH(ctx, kid, k_row_compress<1024>, dim3((unsigned)A.n), dim3(1024), 0, C);
   } else if (!selected) {
     launch_select<COMP, NT>(ctx, C, A, kid_compact, fuse_mix);

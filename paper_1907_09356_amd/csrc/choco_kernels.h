@@ -589,6 +589,15 @@ __device__ __forceinline__ int line_sharing_tile(int b, int ntiles) {
   return base + ((b & 7) << 2) + ((b >> 3) & 3);
 }
 
+// Bits `nibble` of the lane's 4-vector among the wave's 256 entries: word lane / 8 of their mask.
+__device__ __forceinline__ uint32_t mask_word(uint32_t nibble, int lane) {
+  uint32_t w = nibble << (4 * (lane & 7));
+  w |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0xB1, 0xF, 0xF, true);    // quad_perm [1,0,3,2]
+  w |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0x4E, 0xF, 0xF, true);    // quad_perm [2,3,0,1]
+  w |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0x141, 0xF, 0xF, true);   // row_half_mirror
+  return w;
+}
+
 // gsgd: the magnitude of entry e's code as its bit planes hold it.  The level s itself may not fit them (at
 // most four entries of a vector can reach it): such an entry is remembered in the ring beside them.
 __device__ __forceinline__ int32_t magnitude_sent(const Args& A, int r, int e, int lay, int32_t code) {

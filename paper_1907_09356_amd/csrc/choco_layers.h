@@ -128,7 +128,7 @@ struct LayerShared {
 
 // WHOLE: the layer is the whole vector of a configuration without layers; its guess and its figures are in
 // the worker's control block.
-template <int COMP, int THREADS, bool NT, bool WHOLE = false>
+template <int COMP, int THREADS, bool NT, bool WHOLE = false, bool WORDS = false>
 __device__ __forceinline__ void layer_body(const Args& A, const int i, const LayerDesc L, const int tid,
                                            const LayerShared sh, unsigned long long* sh_kstar = nullptr) {
   static_assert(COMP == Q_TOPK || COMP == Q_RANDK, "sign and gsgd layers go through k_layer_stat");
@@ -136,6 +136,8 @@ __device__ __forceinline__ void layer_body(const Args& A, const int i, const Lay
   constexpr int kBatch = kLayerVecs;   // 4-vectors per thread whose loads are in flight together
   constexpr int kBatches = (kLayerVecs + kBatch - 1) / kBatch;
   constexpr uint32_t CAP = 2 * THREADS;
+  constexpr uint32_t SOLO = 512;     // list lengths that one wave searches on its own
+  constexpr bool kNarrows = WHOLE && THREADS > 64;
   // local index e counts from the 4-vector boundary at or below the layer's first entry: the
   // layer's entries are head <= e < end (head = 0 unless the table is generic)
   const int head = L.head, end = L.head + L.len, base = L.start - L.head;
@@ -245,7 +247,13 @@ __device__ __forceinline__ void layer_body(const Args& A, const int i, const Lay
     int phase = 0;
     uint32_t T = 0, at_or_above = 0xFFFFFFFFu;
     uint32_t listed_n = 0;   // one wave per layer: the length of its list
-    bool found = false;
+    bool found = false, bracketed = false;   // bracketed: by the first bracket, not by a search of the whole layer
+    // a whole row: where the bracket misses or holds more than one wave can search, histograms narrow it down
+    // (gradient steps whose size moves by half from one to the next, us per step, bit by bit over the row | so:
+    // n = 8, d = 4,096, k = 41 16.0 | 15.3, 6,144, k = 1,200 22.4 | 19.2, n = 64, d = 8,192, k = 160 24.5 | 21.5)
+    uint32_t ties_at = 0;   // kNarrows: entries that hold T, where that is known without a list
+    for (int round = 0;; ++round) {
+    uint32_t nhi = 0, nin = 0;
     if (have) {                                   // uniform
       // a thread counts its keys above the bracket and inside it, one scan over the wave and one LDS atomic
       // place the latter (a ballot and an atomic for each of the thread's entries in turn, each waiting for
@@ -262,7 +270,7 @@ __device__ __forceinline__ void layer_body(const Args& A, const int i, const Lay
           }
         }
       const uint32_t incl = wave_scan(mine);
-      uint32_t nhi = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63) & 0xFFFFu;
+      nhi = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63) & 0xFFFFu;
       const uint32_t listed = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63) >> 16;
       uint32_t pos = claim_counted<THREADS>(mine >> 16, incl >> 16, sh.list_n);
       if (mine >> 16) {
@@ -281,15 +289,15 @@ __device__ __forceinline__ void layer_body(const Args& A, const int i, const Lay
       }
       nhi = block_total<THREADS>(nhi, sh.cnt, phase);
       layer_sync<THREADS>();
-      const uint32_t nin = THREADS == 64 ? listed : *sh.list_n;
+      nin = THREADS == 64 ? listed : *sh.list_n;
       listed_n = listed;
-      if (nhi < k && k - nhi <= nin && nin <= CAP) {
+      if (round == 0) bracketed = nhi < k && k - nhi <= nin;
+      if (nhi < k && k - nhi <= nin && nin <= (kNarrows ? SOLO : CAP)) {
         // the k-th largest key is the r-th largest of the list: bit by bit on key - lo
         found = true;
         const uint32_t r = k - nhi;
         const uint32_t span = hi - lo;            // >= 1: the list is not empty
         uint32_t Trel = 0, got = nin;
-        constexpr uint32_t SOLO = 512;     // list lengths that one wave searches on its own
         if (THREADS > 64 && nin <= SOLO) {
           // several waves: the first one searches the list on its own, eight keys per lane, and
           // the others wait once (a block-wide count per bit costs a barrier per bit)
@@ -335,7 +343,68 @@ __device__ __forceinline__ void layer_body(const Args& A, const int i, const Lay
         }
         T = lo + Trel;
         at_or_above = nhi + got;
+      } else if (lo == 1u && nhi + nin < k) {     // k includes zeros
+        bracketed = round == 0;
+        at_or_above = k;                          // (T = 0: nothing to search)
+        break;
       }
+    }
+    if (__builtin_expect(!kNarrows || found, 1)) break;
+    if constexpr (kNarrows) {
+      uint32_t* h = reinterpret_cast<uint32_t*>(sh.list);   // 2048 bins, find_digit's 256 sums, its answer
+      static_assert(CAP * 2 >= kBins + 256 + 2, "the histogram lies in the list's place");
+      uint32_t a = lo, b = hi, r = k - nhi;       // keys from a to b - 1, of which the r-th largest is wanted
+      if (!have || nhi >= k) {
+        a = have ? hi : 1u;
+        b = 0x80000000u;
+        r = k;
+      } else if (nhi + nin < k) {
+        a = 1u;
+        b = lo;
+        r = k - nhi - nin;
+      }
+      uint32_t inside_n = 0;
+      do {
+        const uint32_t span = b - a;
+        const int shift = span <= (uint32_t)kBins ? 0 : 21 - __clz((int)(span - 1u));
+        __syncthreads();                          // (the list or the last histogram has been read)
+        for (int j = tid; j < kBins; j += THREADS) h[j] = 0;
+        if (tid == 0) *sh.list_n = 0;
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < kLayerVecs; ++it)
+          if (it < nit) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+              const uint32_t key = key_of(it, c);
+              if (key >= a && key < b) atomicAdd(&h[(key - a) >> shift], 1u);
+            }
+          }
+        __syncthreads();
+        find_digit(h, h + kBins, r, h + kBins + 256, h + kBins + 257);
+        const uint32_t bin = h[kBins + 256], over = h[kBins + 257];
+        inside_n = h[bin];
+        if (over + inside_n < r) break;           // fewer than r of them: k includes zeros
+        a += bin << shift;
+        b = b - a < (1u << shift) ? b : a + (1u << shift);
+        r -= over;
+      } while (inside_n > SOLO && b - a > 1u);
+      if (inside_n < r) {
+        at_or_above = k;
+        break;
+      }
+      lo = a;
+      hi = b;
+      if (b - a == 1u) {                          // one key: it is the threshold
+        T = a;
+        ties_at = inside_n;
+        at_or_above = k - r + inside_n;
+        found = true;
+        break;
+      }
+      have = true;
+      __syncthreads();                            // (the histogram has been read)
+    }
     }
     if (!found) {
       // the whole layer, bit by bit: the largest T with count(key >= T) >= k; it may stop
@@ -360,7 +429,10 @@ __device__ __forceinline__ void layer_body(const Args& A, const int i, const Lay
     // entries above the threshold key are all kept; of those equal to it, the first `need`
     // by index (entries outside the layer carry key 0 and are told apart by their index)
     uint32_t above = 0, equals = 0;
-    if (found) {
+    if (kNarrows && ties_at != 0u) {
+      equals = ties_at;
+      above = at_or_above - equals;
+    } else if (found) {
       // the threshold lies in the bracket, so every entry that holds it is in the list
       const uint32_t nin = THREADS == 64 ? listed_n : *sh.list_n;
       for (uint32_t p = (uint32_t)tid; p < nin; p += THREADS) equals += sh.list[p].x == T ? 1u : 0u;
@@ -387,16 +459,18 @@ __device__ __forceinline__ void layer_body(const Args& A, const int i, const Lay
       scal[0] = (double)T;
       scal[1] = (double)need;
       scal[2] = (double)equals;
-      scal[3] = found ? 1.0 : 0.0;
+      scal[3] = bracketed ? 1.0 : 0.0;
     }
     const bool ties = equals > need;   // uniform over the layer's threads
+    uint32_t kept_bits = 0;   // WORDS: which of the lane's entries are kept
     auto keep_entry = [&](uint32_t slot, int it, int c) {
       if (slot < k) {   // exactly k entries pass; the test only keeps a wrong count inside the layer's slots
         const int e = 4 * (it * THREADS + tid) + c;
         const int64_t dst = (int64_t)i * A.k + L.sel_base + slot;
         A.sel_idx[dst] = base + e;
         if constexpr (COMP == Q_TOPK) A.sel_val[dst] = v[it][c];
-        atomicOr(&A.keptmap[(int64_t)i * A.map_words + ((uint32_t)(base + e) >> 5)], 1u << ((uint32_t)(base + e) & 31u));
+        if (WORDS) kept_bits |= 1u << (4 * it + c);
+        else atomicOr(&A.keptmap[(int64_t)i * A.map_words + ((uint32_t)(base + e) >> 5)], 1u << ((uint32_t)(base + e) & 31u));
       }
     };
     uint32_t running = 0;              // threshold-key entries in earlier sweeps (index order)
@@ -428,13 +502,38 @@ __device__ __forceinline__ void layer_body(const Args& A, const int i, const Lay
             }
           }
       }
-    } else
+    } else {
+    uint32_t last = 0xFFFFFFFFu;       // kNarrows: index of the last entry kept of those that hold T
+    const bool listed_ties = kNarrows && nit > 1 && found && ties_at == 0u && ties;
+    if (listed_ties) {
+      // all of them are in the list: the need-th by index, by one wave, instead of a block-wide scan per sweep
+      if (wave == 0) {
+        const uint32_t nin = *sh.list_n;
+        uint32_t at[SOLO / 64];
+#pragma unroll
+        for (int j = 0; j < (int)(SOLO / 64); ++j) {
+          const uint32_t p = (uint32_t)(lane + 64 * j);
+          at[j] = p < nin && sh.list[p].x == T ? sh.list[p].y : 0xFFFFFFFFu;
+        }
+        uint32_t upto = 0;                         // the largest index below which fewer than `need` of them lie
+        for (int bit = 31 - __clz(end); bit >= 0; --bit) {
+          const uint32_t cand = upto | (1u << bit);
+          uint32_t cnt = 0;
+#pragma unroll
+          for (int j = 0; j < (int)(SOLO / 64); ++j) cnt += wave_count(at[j] < cand);
+          if (cnt < need) upto = cand;
+        }
+        if (lane == 0) sh.cnt[32] = upto;
+      }
+      __syncthreads();
+      last = sh.cnt[32];
+    }
 #pragma unroll
     for (int it = 0; it < kLayerVecs; ++it) {
       if (it < nit) {
         const int m = it * THREADS + tid;
         uint32_t rank = 0;
-        if (ties) {
+        if (ties && !listed_ties) {
           uint32_t mine = 0;
 #pragma unroll
           for (int c = 0; c < 4; ++c) mine += (key_of(it, c) == T && inside(4 * m + c)) ? 1u : 0u;
@@ -467,7 +566,7 @@ __device__ __forceinline__ void layer_body(const Args& A, const int i, const Lay
           const uint32_t key = key_of(it, c);
           bool keep = key > T;
           if (key == T && inside(e)) {
-            keep = !ties || rank < need;
+            keep = !ties || (listed_ties ? (uint32_t)e <= last : rank < need);
             ++rank;
           }
           if (WHOLE && keep && Digits<COMP>::composite(key, (uint32_t)e) < least)
@@ -479,6 +578,15 @@ __device__ __forceinline__ void layer_body(const Args& A, const int i, const Lay
           }
         }
       }
+    }
+    }
+    if (WORDS) {   // to the map, whose words belong to eight lanes each
+#pragma unroll
+      for (int it = 0; it < kLayerVecs; ++it)
+        if (it < nit) {
+          const uint32_t w = mask_word((kept_bits >> (4 * it)) & 0xFu, lane);
+          if ((lane & 7) == 0 && w != 0u) A.keptmap[(int64_t)i * A.map_words + ((it * THREADS + tid) >> 3)] = w;
+        }
     }
     if (WHOLE) {
 #pragma unroll
@@ -492,8 +600,8 @@ __device__ __forceinline__ void layer_body(const Args& A, const int i, const Lay
         WorkerCtl* ctl = A.ctl + i;
         ctl->kstar = *sh_kstar;
         ctl->kept = k;
-        ctl->mode = found ? 0u : 2u;
-        if (!found) ctl->fallbacks += 1;
+        ctl->mode = bracketed ? 0u : 2u;
+        if (!bracketed) ctl->fallbacks += 1;
         ctl->last_candidates = have ? (THREADS == 64 ? listed_n : *sh.list_n) : 0u;
       }
     }
@@ -503,14 +611,14 @@ __device__ __forceinline__ void layer_body(const Args& A, const int i, const Lay
 // Short rows of top_a (the direct form, whose last pass applies the update of xhat): the select of a whole
 // vector out of one workgroup's registers, instead of a candidate pass and a select of the list.
 // grid n, block THREADS.
-template <int THREADS>
+template <int THREADS, bool WORDS = false>
 __global__ __launch_bounds__(THREADS) void k_row_compress(Args A) {
   __shared__ uint32_t sh_cnt[34], sh_emit, sh_list_n;
   __shared__ unsigned long long sh_kstar;
   __shared__ uint2 sh_list[2 * THREADS];
   const LayerShared sh{sh_cnt, &sh_emit, &sh_list_n, sh_list};
   const LayerDesc row{0, A.d, (int32_t)A.k, 0, 0, 0, {0, 0}};
-  layer_body<Q_TOPK, THREADS, false, true>(A, (int)blockIdx.x, row, (int)threadIdx.x, sh, &sh_kstar);
+  layer_body<Q_TOPK, THREADS, false, true, WORDS>(A, (int)blockIdx.x, row, (int)threadIdx.x, sh, &sh_kstar);
 }
 
 // A launch covers a piece of the work list A.layer_work (layers by falling length) from `first`

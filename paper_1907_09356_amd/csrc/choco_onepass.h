@@ -63,15 +63,6 @@ __device__ __forceinline__ uint32_t fold_marks(uint64_t m) {
   return (uint32_t)m & 0xFu;
 }
 
-// Bits `nibble` of the lane's 4-vector among the 256 columns of the tile: word lane / 8 of the tile's mask.
-__device__ __forceinline__ uint32_t mask_word(uint32_t nibble, int lane) {
-  uint32_t w = nibble << (4 * (lane & 7));
-  w |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0xB1, 0xF, 0xF, true);    // quad_perm [1,0,3,2]
-  w |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0x4E, 0xF, 0xF, true);    // quad_perm [2,3,0,1]
-  w |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0x141, 0xF, 0xF, true);   // row_half_mirror
-  return w;
-}
-
 // (x', xhat) of worker 0 in a slot; worker i's is i further on.
 __device__ __forceinline__ float2* record_of(const Args& A, const OnePass& P, int64_t tile, int slot) {
   return P.recs + (tile * kRecSlots + slot) * A.n;
