@@ -31,6 +31,7 @@ struct SelectPlan {
   uint32_t guess0, shift0;             // first guess and bin width (all ones: none, the first step falls back)
   uint32_t sample_stride, sample_need; // fallback histogram
   bool multipart;                      // long candidate lists: three multi-block launches instead of one block
+  uint32_t bin_cap;                    // ... which list the threshold bin's entries if they are no more than this
   bool fallback_chain;                 // long rows: histogram passes repair a failed guess (else a row scan)
 };
 
@@ -41,6 +42,7 @@ struct LongLayer {
   SelectPlan plan;
   LongSel sel;      // what the kernels need of it (filled by choco_init)
   bool batched;     // its pass and its select share a launch with those of the other such layers
+  int32_t part_set; // multi-block select: which of the copies of its scratch
 };
 
 // random_a selects ahead in batches of up to this many steps (two event operations on the
@@ -158,7 +160,7 @@ struct Layout {
       chunk_layer, planes, ovf_ring, ovf_pos, wire_rank, wire_word_off, wire_plane_off, sel_idx2, bitmap2, keptmap2, layer_scal2, qv, recs, rec_cols, ulps, uneven, onepass, mpart, total;
   int64_t wire_words, wire_plane_words;   // layer by layer: words of a worker's message / of one bit plane
   int32_t ngroup_items;
-  uint32_t cand_cap, seg_cap;
+  uint32_t cand_cap, seg_cap, bin_cap;
   int64_t bitmap_words;
   bool multipart;
   int32_t select_sets;   // copies of the select scratch (candidate lists, histograms, short list)
@@ -302,6 +304,9 @@ SelectPlan plan_select(int compressor, int64_t d, int64_t k) {
   seg_cap = std::min<int64_t>(seg_cap, feeders * per_block);
   P.seg_cap = (uint32_t)seg_cap;
   P.multipart = expected_candidates(compressor, k) > 16384.0;
+  // 256 to 511 bins lie between the guess and the expected threshold, with `want` entries in them: eight times the
+  // mean bin's
+  if (P.multipart) P.bin_cap = (uint32_t)std::min(std::max(want_candidates(compressor, k) / 32.0, (double)kSmallCap), (double)kBinCap);
   // A failed guess (first step, or the distribution moved) is repaired by three extra passes
   // (sampled histogram, new guess, rebuild) that are launched every step and normally exit at
   // once.  For short rows even those idle launches show, and the select kernel's own row scan
@@ -404,6 +409,7 @@ std::vector<LongLayer> long_layers_of(const choco_config& c) {
   std::vector<LongLayer> out;
   if (c.nlayers <= 0 || !is_sparse(c.compressor)) return out;
   int64_t sel_base = 0;
+  int32_t part_sets = 0;
   for (int32_t l = 0; l < c.nlayers; ++l) {
     const int64_t len = c.layer_len_host[l], k = c.layer_k_host[l];
     if (len + (c.layer_start_host[l] & 3) > kMidLayerLen) {   // (with the entries before it in its first 4-vector)
@@ -416,6 +422,7 @@ std::vector<LongLayer> long_layers_of(const choco_config& c) {
       B.plan = plan_select(c.compressor, len, std::max<int64_t>(k, 1));
       // one block per worker finishes the select, no histogram passes: such layers share launches
       B.batched = k > 0 && !B.plan.multipart && !B.plan.fallback_chain;
+      if (B.plan.multipart) B.part_set = part_sets++;
       out.push_back(B);
     }
     sel_base += k;
@@ -485,10 +492,13 @@ Layout make_layout(const choco_config& c, int32_t nnz) {
   L.group_sums = take(dense_stat ? (size_t)c.n * (size_t)L.ngroups * sizeof(double) : 0);
   int64_t cap = 0, seg_cap = 0;
   bool multipart = false;
+  size_t part_sets = 0;
   for (const SelectPlan& P : plans) {
     cap = std::max<int64_t>(cap, P.cand_cap);
     seg_cap = std::max<int64_t>(seg_cap, P.seg_cap);
     multipart = multipart || P.multipart;
+    part_sets += P.multipart ? 1 : 0;
+    L.bin_cap = std::max(L.bin_cap, P.bin_cap);
   }
   L.cand_cap = (uint32_t)cap;
   L.seg_cap = (uint32_t)seg_cap;
@@ -506,9 +516,9 @@ Layout make_layout(const choco_config& c, int32_t nnz) {
   L.sel_val = take(sparse ? (size_t)c.n * (size_t)kept * sizeof(float) : 0);
   L.multipart = guessed && multipart;
   L.hist_parts_bytes = align_up(L.multipart ? (size_t)c.n * kRefineParts * kBins * sizeof(uint32_t) : 0);
-  L.small_list_bytes = align_up(L.multipart ? (size_t)c.n * kBinCap * sizeof(uint2) : 0);
-  L.hist_parts = take(L.hist_parts_bytes * (size_t)L.select_sets);
-  L.small_list = take(L.small_list_bytes * (size_t)L.select_sets);
+  L.small_list_bytes = align_up(L.multipart ? (size_t)c.n * L.bin_cap * sizeof(uint2) : 0);
+  L.hist_parts = take(L.hist_parts_bytes * part_sets);
+  L.small_list = take(L.small_list_bytes * part_sets);
   // kept entries: a bitmap per worker if it fits in the (single-block) select's LDS (40 KiB
   // beside its other arrays), else a bit per entry in global memory
   L.bitmap_words = (guessed && !layered && !L.multipart && !short_rows(c) && c.d <= 40 * 1024 * 8) ? (c.d + 31) / 32 : 0;
@@ -1359,8 +1369,9 @@ Args long_layer_args(const choco_ctx* ctx, const Args& src, int which) {
   // entries before the layer in that 4-vector do not take part), the layer's own select scratch
   Args R = long_view(src, ctx->long_layers[(size_t)which].sel);
   R.hist16 = (uint32_t*)((char*)src.hist16 + (size_t)which * ctx->set_hist16);
-  R.hist_parts = (uint32_t*)((char*)src.hist_parts + (size_t)which * ctx->set_hist_parts);
-  R.small_list = (uint2*)((char*)src.small_list + (size_t)which * ctx->set_small_list);
+  const size_t part_set = (size_t)ctx->long_layers[(size_t)which].part_set;
+  R.hist_parts = (uint32_t*)((char*)src.hist_parts + part_set * ctx->set_hist_parts);
+  R.small_list = (uint2*)((char*)src.small_list + part_set * ctx->set_small_list);
   return R;
 }
 
@@ -1893,6 +1904,7 @@ int choco_init(const choco_config* cfg, float* x_dev, void* workspace_dev, size_
   A.cand = (uint2*)(base + L.cand);
   A.hist_parts = (uint32_t*)(base + L.hist_parts);
   A.small_list = (uint2*)(base + L.small_list);
+  A.bin_cap = L.bin_cap;
   ctx->multipart = ctx->plan.multipart;
   apply_plan(A, ctx->plan);
   const uint32_t guess0 = ctx->plan.guess0, shift0 = ctx->plan.shift0;

@@ -37,7 +37,7 @@ constexpr int kStreamVecs = 2;    // 4-vectors per thread in the streaming kerne
 constexpr int kCompactVecs = 4;   // 4-vectors per thread in the select pass of long rows and of random_a
 constexpr int kStageCap = 1024;   // candidates one block stages in LDS before its single append
 constexpr int kSmallCap = 1024;   // entries of the threshold bin the select ranks directly in LDS
-constexpr int kBinCap = 32768;    // entries of the threshold bin the multi-block select takes apart by a second histogram
+constexpr int kBinCap = 32768;    // entries of the threshold bin the multi-block select takes apart by a second histogram, at most
 // Chunks per wave in the norm passes (a workgroup takes a group of 16 chunks): one, in
 // 1024-thread workgroups, where the state is streamed past the caches (large states, and the
 // small ones that are latency-bound), two, in 512-thread workgroups, where it is read through
@@ -176,10 +176,11 @@ struct Args {
   uint32_t* hist16;    // n x kBins16 (fallback histogram)
   uint2* cand;         // n x kSegs x seg_cap  (a, index)
   uint32_t* hist_parts; // n x kRefineParts x kBins: per-block candidate histograms (multi-block select)
-  uint2* small_list;   // n x kBinCap: entries of the threshold bin (multi-block select)
+  uint2* small_list;   // n x bin_cap: entries of the threshold bin (multi-block select)
   uint32_t* seg_counts;  // n x kSegs x kSegPad: entries with key32 >= guess_key appended per sub-list (may exceed
                          // seg_cap), a cache line per counter
   uint32_t seg_cap;    // capacity of one sub-list
+  uint32_t bin_cap;    // capacity of a small_list: kSmallCap to kBinCap
   uint32_t cand_cap;   // largest total the fallback aims to stay under
   uint32_t sample_stride;  // the fallback histogram looks at every sample_stride-th 4-vector
   uint32_t sample_need;    // rank (within the sample) at which the fallback puts the guess
@@ -2622,7 +2623,7 @@ __global__ __launch_bounds__(1024) void k_sel_emit_parts(Args A) {
   __syncthreads();
   find_digit(h, grp, (uint32_t)A.k, &s_digit, &s_above);
   const uint32_t tbin = s_digit;
-  if (h[tbin] > (uint32_t)kBinCap) return;   // crowded threshold bin: k_sel_finish selects digit by digit
+  if (h[tbin] > A.bin_cap) return;   // crowded threshold bin: k_sel_finish selects digit by digit
   uint32_t lo, hi;
   part_slice(s_total, blockIdx.x, &lo, &hi);
   const uint32_t guess = ctl->guess_key, shift = ctl->bin_shift;
@@ -2667,7 +2668,7 @@ __global__ __launch_bounds__(1024) void k_sel_emit_parts(Args A) {
       if ((masks[u] >> lane) & 1ull)
         store_kept<COMP, ONEPASS>(A, i, running + (uint32_t)__popcll(masks[u] & below), c[u].x, c[u].y, nullptr);
       else if ((inside[u] >> lane) & 1ull)
-        A.small_list[(int64_t)i * kBinCap + pos + (uint32_t)__popcll(inside[u] & below)] = c[u];
+        A.small_list[(int64_t)i * A.bin_cap + pos + (uint32_t)__popcll(inside[u] & below)] = c[u];
       running += (uint32_t)__popcll(masks[u]);
       pos += (uint32_t)__popcll(inside[u]);
     }
@@ -2705,8 +2706,8 @@ __global__ __launch_bounds__(1024) void k_sel_finish(Args A) {
   const uint32_t in_bin = h[tbin];
   // the blocks of k_sel_emit_parts emitted `above` entries into slots 0..above-1 and collected
   // the in_bin entries of the threshold bin; rank those and emit the need_in_bin largest
-  const uint2* bin_list = A.small_list + (int64_t)i * kBinCap;
-  bool crowded = in_bin > (uint32_t)kBinCap;
+  const uint2* bin_list = A.small_list + (int64_t)i * A.bin_cap;
+  bool crowded = in_bin > A.bin_cap;
   uint32_t first = above, need = need_in_bin, m = in_bin;   // (slot of the best of `small`, kept of it, entries in it)
   if (!crowded && in_bin > (uint32_t)kSmallCap) {
     // more than can be ranked against each other: by the same steps again, one level down

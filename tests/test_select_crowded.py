@@ -8,6 +8,23 @@ from paper_1907_09356_amd import synth
 from tests.parity_util import Pair
 
 
+def test_room_for_the_bin():
+    """... is kept for as many entries as the bin is likely to hold, and for rows and layers that take it apart only."""
+    def workspace(n, d, k, **kw):
+        cfg, keep = B.make_config(n, d, *synth.ring_csr(n), 0.1, B.Q_TOPK, k=k, **kw)
+        return B.workspace_bytes(cfg)
+
+    # from one block to several per row (k of some 6,550 on): a histogram per block and 1,024 entries
+    assert workspace(1000, 20_000, 8000) - workspace(1000, 20_000, 6500) < 1000 * (16 * 2048 * 4 + 1024 * 8 + 1500 * 4 * 20)
+    # thirty layers that share launches cost the same beside a layer that is taken apart as without it
+    def layered(lengths, fraction):
+        t = synth.layer_table(lengths, fraction=fraction)
+        return workspace(64, synth.layers_dim(t), 1, layers=t)
+    alone, both = layered([300_000], 0.05), layered([300_000] + [11_000] * 30, 0.05)
+    lists = 64 * 31 * 32 * (2 * 4 * 15_000 // 32 + 1) * 8     # (every set's candidate lists are as long as the longest)
+    assert both - alone < lists + 64 * 30 * 11_000 * 6
+
+
 @pytest.mark.gpu
 @pytest.mark.timeout(200)
 @pytest.mark.parametrize("d,k,grid,order", [
