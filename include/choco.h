@@ -125,7 +125,12 @@ typedef struct {
 #define CHOCO_MAX_D (((int64_t)1 << 31) - ((int64_t)1 << 19)) /* rows are indexed in 32 bits with some headroom */
 
 /* Bytes of device workspace choco_init needs for this configuration (Xhat, S, the CSR
-   copy and scratch for the operators).  Validates the scalar fields of cfg only. */
+   copy and scratch for the operators).  Validates the scalar fields of cfg only.
+   For TOPK and QSGD of two to eight workers on rows that stream past the caches (more than
+   96 MiB per array, little sent, default order, no layer table) it holds nearly half an array of
+   the state more than two passes need (TOPK 1.55 arrays instead of 1.07, QSGD with 16 levels 1.67
+   instead of 1.16), with which a step goes over the state once instead of twice.  choco_init also
+   accepts a workspace without that part; the steps then take two passes.  Same results either way. */
 int choco_workspace_bytes(const choco_config *cfg, size_t *bytes_host);
 
 /* Algorithm 1, input line: takes X = x^(-1/2) as it stands in x_dev (n*ld floats, 16-byte
@@ -133,7 +138,7 @@ int choco_workspace_bytes(const choco_config *cfg, size_t *bytes_host);
    t = 0.  workspace_dev must be 256-byte aligned.  CHOCO_E_INVAL for n < 1, d out of
    range (above CHOCO_MAX_D), bad ld, k outside [1, d], levels < 1, gamma <= 0 or not finite, null pointers,
    malformed CSR, or a W that violates Assumption 1; CHOCO_E_NOMEM if the workspace is
-   too small.  On error *out is NULL.
+   too small (also for the two-pass form, see choco_workspace_bytes).  On error *out is NULL.
    Reads one environment variable, CHOCO_FALLBACK_SPIN_LIMIT (decimal; default 65536): TOPK /
    RANDK on rows above 2^21 entries repair a failed threshold guess in one launch whose
    workgroups wait for one of their number in a bounded poll; this is the bound.  A workgroup

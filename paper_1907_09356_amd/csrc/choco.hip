@@ -459,7 +459,13 @@ int64_t message_words(int compressor, int64_t d, int64_t k, int levels) {
   }
 }
 
-Layout make_layout(const choco_config& c, int32_t nnz) {
+// top_a / gsgd in one pass over the state, which takes half an array of the state more workspace: not
+// where x, xhat, gradients and momentum fill the card's 288 GB without it (above 48 GiB per array).
+bool one_pass_rule(const choco_config& c) {
+  return (one_pass_topk(c) || one_pass_qsgd(c)) && (double)c.n * (double)resolve_ld(c) * sizeof(float) <= 48.0 * 1073741824.0;
+}
+
+Layout make_layout(const choco_config& c, int32_t nnz, bool one_pass) {
   Layout L{};
   const int64_t ld = resolve_ld(c);
   const size_t state = (size_t)c.n * (size_t)ld * sizeof(float);
@@ -480,14 +486,13 @@ Layout make_layout(const choco_config& c, int32_t nnz) {
   L.row_ptr = take((size_t)(c.n + 1) * sizeof(int32_t));
   L.col = take((size_t)nnz * sizeof(int32_t));
   L.w = take((size_t)nnz * sizeof(float));
-  const bool one_pass = one_pass_topk(c) || one_pass_qsgd(c);
   L.ctl = take((size_t)c.n * (std::max<size_t>(1, longs.size()) * sizeof(WorkerCtl) + (one_pass ? sizeof(OnePassCtl) : 0)));
   L.seg_counts = take(guessed ? (size_t)c.n * std::max<size_t>(1, longs.size()) * kSegs * kSegPad * sizeof(uint32_t) : 0);
   L.nchunks = (int32_t)((c.d + kChunk - 1) / kChunk);
   L.ngroups = (L.nchunks + kGroup - 1) / kGroup;
   const bool dense_stat = c.compressor == CHOCO_Q_SIGN || c.compressor == CHOCO_Q_QSGD;
   // chunk sums are only materialised by the tile kernel of the printed order and by the one pass of gsgd
-  L.chunk_sums = take((dense_stat && c.order == CHOCO_ORDER_MIX_THEN_COMPRESS) || one_pass_qsgd(c)
+  L.chunk_sums = take(dense_stat && (c.order == CHOCO_ORDER_MIX_THEN_COMPRESS || one_pass)
                           ? (size_t)c.n * (size_t)L.nchunks * sizeof(double) : 0);
   L.group_sums = take(dense_stat ? (size_t)c.n * (size_t)L.ngroups * sizeof(double) : 0);
   int64_t cap = 0, seg_cap = 0;
@@ -1773,7 +1778,7 @@ int choco_workspace_bytes(const choco_config* cfg, size_t* bytes_host) {
   if (!cfg->row_ptr_host) return CHOCO_E_INVAL;
   const int32_t nnz = cfg->row_ptr_host[cfg->n];
   if (nnz < cfg->n) return CHOCO_E_INVAL;
-  *bytes_host = make_layout(*cfg, nnz).total;
+  *bytes_host = make_layout(*cfg, nnz, one_pass_rule(*cfg)).total;
   return CHOCO_OK;
 }
 
@@ -1787,7 +1792,12 @@ int choco_init(const choco_config* cfg, float* x_dev, void* workspace_dev, size_
   int32_t nnz = 0, maxdeg = 0;
   rc = check_csr(cfg, &nnz, &maxdeg);
   if (rc != CHOCO_OK) return rc;
-  const Layout L = make_layout(*cfg, nnz);
+  bool one_pass = one_pass_rule(*cfg);
+  Layout L = make_layout(*cfg, nnz, one_pass);
+  if (one_pass && workspace_bytes < L.total) {   // enough for two passes?
+    one_pass = false;
+    L = make_layout(*cfg, nnz, one_pass);
+  }
   if (workspace_bytes < L.total) return CHOCO_E_NOMEM;
 
   choco_ctx* ctx = new (std::nothrow) choco_ctx();
@@ -1818,7 +1828,7 @@ int choco_init(const choco_config* cfg, float* x_dev, void* workspace_dev, size_
   ctx->sparse = is_sparse(cfg->compressor);
   ctx->mix_form = resolve_mix_form(*cfg);
   ctx->fused_sparse_apply = fused_sparse_apply(*cfg);
-  ctx->one_pass = one_pass_topk(*cfg) || one_pass_qsgd(*cfg);
+  ctx->one_pass = one_pass;
   ctx->one_pass_begun = false;
   ctx->short_rows = short_rows(*cfg);
   ctx->values_in_qv = false;

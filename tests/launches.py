@@ -37,9 +37,10 @@ def load(path):
 
 
 class Context:
-    """A context on host memory.  `ld` 0: the shortest; x_off: bytes by which X is off a 256-byte boundary."""
+    """A context on host memory.  `ld` 0: the shortest; x_off: bytes by which X is off a 256-byte boundary; ws: bytes of
+    workspace handed over (default: all that are asked for)."""
 
-    def __init__(self, n, d, compressor, topo=None, x_off=0, align=4, **kw):
+    def __init__(self, n, d, compressor, topo=None, x_off=0, align=4, ws=None, **kw):
         import numpy as np
         from paper_1907_09356_amd import binding as B
         from paper_1907_09356_amd import synth
@@ -47,7 +48,8 @@ class Context:
         ld = (d + align - 1) // align * align
         topo = topo if topo is not None else synth.ring_csr(n)
         self.cfg, self.keep = B.make_config(n, d, *topo, 0.1, compressor, ld=ld, **kw)
-        nbytes = B.workspace_bytes(self.cfg)
+        self.asked = B.workspace_bytes(self.cfg)
+        nbytes = self.asked if ws is None else ws
         self.x, xp = self._buffer(4 * n * ld + x_off)
         self.ws, wp = self._buffer(nbytes)
         self.g, self.gp = self._buffer(4 * n * ld)

@@ -62,6 +62,49 @@ for name, n, d, kw in (
             assert later == first, name
 
 
+def test_a_workspace_for_two_passes_is_accepted():
+    """What choco_workspace_bytes asks for has room for one pass; without it the steps take two."""
+    out = recorded("""
+out = {}
+for name, comp, kw in (("topk", B.Q_TOPK, dict(k=4000)), ("qsgd", B.Q_QSGD, dict(levels=8))):
+    n, d = 8, 3_200_000
+    full = Context(n, d, comp, **kw)
+    lo, hi = 0, full.asked            # a size that is refused and one that is taken
+    while hi - lo > 256:
+        mid = (lo + hi) // 2
+        c = Context(n, d, comp, ws=mid, **kw)
+        if c.rc == B.OK:
+            hi = mid
+            c.close()
+        else:
+            assert c.rc == B.E_NOMEM, c.rc
+            lo = mid
+    steps = []
+    for ws in (hi, full.asked - 1, full.asked):
+        c = Context(n, d, comp, ws=ws, **kw)
+        c.step()
+        steps.append([x[0].split("<")[0] for x in c.step()])
+        c.close()
+    out[name] = [hi / (4 * n * d), full.asked / (4 * n * d), steps]
+    full.close()
+""")
+    two = {"topk": ["k_sel_compact", "k_sel_fallback", "k_sel_refine", "k_tile_mix"],
+           "qsgd": ["k_dense_stat", "k_dense_finalise", "k_dense_apply_mix"]}
+    for name, (least, asked, steps) in out.items():
+        assert least < 1.17 and 1.5 < asked < 1.75, name
+        assert steps[0] == steps[1] == two[name] and steps[2][0] == "k_onepass_mix", name
+
+
+def test_no_one_pass_where_the_state_fills_the_card():
+    """Above 48 GiB per array the workspace stays that of two passes."""
+    for comp, kw in ((B.Q_TOPK, dict(k=100_000)), (B.Q_QSGD, dict(levels=16))):
+        arrays = []
+        for d in (1_600_000_000, 1_620_000_000):
+            cfg, keep = B.make_config(8, d, *synth.ring_csr(8), 0.1, comp, **kw)
+            arrays.append(B.workspace_bytes(cfg) / (32 * d))
+        assert arrays[0] > 1.5 and arrays[1] < 1.17
+
+
 def graph(name, n):
     return synth.complete_csr(n) if name == "complete" else synth.ring_csr(n)
 
