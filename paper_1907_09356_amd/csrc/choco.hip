@@ -304,9 +304,6 @@ SelectPlan plan_select(int compressor, int64_t d, int64_t k) {
   seg_cap = std::min<int64_t>(seg_cap, feeders * per_block);
   P.seg_cap = (uint32_t)seg_cap;
   P.multipart = expected_candidates(compressor, k) > 16384.0;
-  // 256 to 511 bins lie between the guess and the expected threshold, with `want` entries in them: eight times the
-  // mean bin's
-  if (P.multipart) P.bin_cap = (uint32_t)std::min(std::max(want_candidates(compressor, k) / 32.0, (double)kSmallCap), (double)kBinCap);
   // A failed guess (first step, or the distribution moved) is repaired by three extra passes
   // (sampled histogram, new guess, rebuild) that are launched every step and normally exit at
   // once.  For short rows even those idle launches show, and the select kernel's own row scan
@@ -316,6 +313,7 @@ SelectPlan plan_select(int compressor, int64_t d, int64_t k) {
   const double extra = extra_candidates(k);
   P.extra = (uint32_t)extra;
   P.want = (uint32_t)std::min(want_candidates(compressor, k), 4294967295.0);
+  if (P.multipart) P.bin_cap = bin_capacity(P.seg_cap, k, (int32_t)d);
   P.guess0 = 0xFFFFFFFFu;   // top_a: no guess yet, the first step takes the fallback
   P.shift0 = 0;
   if (compressor == CHOCO_Q_RANDK) {
@@ -1914,7 +1912,6 @@ int choco_init(const choco_config* cfg, float* x_dev, void* workspace_dev, size_
   A.cand = (uint2*)(base + L.cand);
   A.hist_parts = (uint32_t*)(base + L.hist_parts);
   A.small_list = (uint2*)(base + L.small_list);
-  A.bin_cap = L.bin_cap;
   ctx->multipart = ctx->plan.multipart;
   apply_plan(A, ctx->plan);
   const uint32_t guess0 = ctx->plan.guess0, shift0 = ctx->plan.shift0;

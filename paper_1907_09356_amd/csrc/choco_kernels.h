@@ -176,11 +176,10 @@ struct Args {
   uint32_t* hist16;    // n x kBins16 (fallback histogram)
   uint2* cand;         // n x kSegs x seg_cap  (a, index)
   uint32_t* hist_parts; // n x kRefineParts x kBins: per-block candidate histograms (multi-block select)
-  uint2* small_list;   // n x bin_cap: entries of the threshold bin (multi-block select)
+  uint2* small_list;   // n x bin_capacity(): entries of the threshold bin (multi-block select)
   uint32_t* seg_counts;  // n x kSegs x kSegPad: entries with key32 >= guess_key appended per sub-list (may exceed
                          // seg_cap), a cache line per counter
   uint32_t seg_cap;    // capacity of one sub-list
-  uint32_t bin_cap;    // capacity of a small_list: kSmallCap to kBinCap
   uint32_t cand_cap;   // largest total the fallback aims to stay under
   uint32_t sample_stride;  // the fallback histogram looks at every sample_stride-th 4-vector
   uint32_t sample_need;    // rank (within the sample) at which the fallback puts the guess
@@ -233,6 +232,17 @@ struct Args {
   // randomness
   uint32_t seed_lo, seed_hi, t_lo, t_hi;
 };
+
+// Entries of the threshold bin that the multi-block select lists for each worker (small_list), from the capacity of
+// a sub-list, which is k / 4 or, where 4 k reaches the row, a sixteenth of it.  256 to 511 bins lie between the
+// guess and the expected threshold with 1.5 k entries in them: a quarter of a sub-list is ten mean bins.  But
+// where nearly all of the row is listed the guess may be zero and the bins as wide as half an octave around the
+// threshold: any share of the row (n = 12, d = 20,000, k = 8,000 43 us per step, 85 with room for 1,024; n = 64,
+// d = 15,000, k = 7,000 86 and 122).
+__host__ __device__ __forceinline__ uint32_t bin_capacity(uint32_t seg_cap, int64_t k, int32_t d) {
+  const uint32_t most = 4 * k >= d ? 16u * seg_cap : seg_cap / 4u;
+  return most < (uint32_t)kSmallCap ? (uint32_t)kSmallCap : most < (uint32_t)kBinCap ? most : (uint32_t)kBinCap;
+}
 
 // The one-pass figures lie behind the control blocks.
 __device__ __forceinline__ OnePassCtl* onepass_ctl(const Args& A) { return reinterpret_cast<OnePassCtl*>(A.ctl + A.n); }
@@ -2615,6 +2625,7 @@ __global__ __launch_bounds__(1024) void k_sel_emit_parts(Args A) {
   __shared__ uint32_t pre[kSegs + 1];
   __shared__ uint32_t s_total, s_good, s_digit, s_above, s_count, s_base, s_in, s_in_base;
   const int i = blockIdx.y;
+  const uint32_t cap = bin_capacity(A.seg_cap, A.k, A.d);
   WorkerCtl* ctl = A.ctl + i;
   if (threadIdx.x < 64) list_layout_wave(A, i, ctl, lens, pre, &s_total, &s_good);
   __syncthreads();
@@ -2623,7 +2634,7 @@ __global__ __launch_bounds__(1024) void k_sel_emit_parts(Args A) {
   __syncthreads();
   find_digit(h, grp, (uint32_t)A.k, &s_digit, &s_above);
   const uint32_t tbin = s_digit;
-  if (h[tbin] > A.bin_cap) return;   // crowded threshold bin: k_sel_finish selects digit by digit
+  if (h[tbin] > cap) return;   // crowded threshold bin: k_sel_finish selects digit by digit
   uint32_t lo, hi;
   part_slice(s_total, blockIdx.x, &lo, &hi);
   const uint32_t guess = ctl->guess_key, shift = ctl->bin_shift;
@@ -2668,7 +2679,7 @@ __global__ __launch_bounds__(1024) void k_sel_emit_parts(Args A) {
       if ((masks[u] >> lane) & 1ull)
         store_kept<COMP, ONEPASS>(A, i, running + (uint32_t)__popcll(masks[u] & below), c[u].x, c[u].y, nullptr);
       else if ((inside[u] >> lane) & 1ull)
-        A.small_list[(int64_t)i * A.bin_cap + pos + (uint32_t)__popcll(inside[u] & below)] = c[u];
+        A.small_list[(int64_t)i * cap + pos + (uint32_t)__popcll(inside[u] & below)] = c[u];
       running += (uint32_t)__popcll(masks[u]);
       pos += (uint32_t)__popcll(inside[u]);
     }
@@ -2685,6 +2696,7 @@ __global__ __launch_bounds__(1024) void k_sel_finish(Args A) {
   __shared__ uint64_t s_prefix, s_kstar;
   __shared__ uint32_t s_need, s_digit, s_above, s_emit, s_total, s_good, s_small;
   const int i = blockIdx.x;
+  const uint32_t cap = bin_capacity(A.seg_cap, A.k, A.d);
   WorkerCtl* ctl = A.ctl + i;
   if (threadIdx.x == 0) {
     s_prefix = 0;
@@ -2706,8 +2718,8 @@ __global__ __launch_bounds__(1024) void k_sel_finish(Args A) {
   const uint32_t in_bin = h[tbin];
   // the blocks of k_sel_emit_parts emitted `above` entries into slots 0..above-1 and collected
   // the in_bin entries of the threshold bin; rank those and emit the need_in_bin largest
-  const uint2* bin_list = A.small_list + (int64_t)i * A.bin_cap;
-  bool crowded = in_bin > A.bin_cap;
+  const uint2* bin_list = A.small_list + (int64_t)i * cap;
+  bool crowded = in_bin > cap;
   uint32_t first = above, need = need_in_bin, m = in_bin;   // (slot of the best of `small`, kept of it, entries in it)
   if (!crowded && in_bin > (uint32_t)kSmallCap) {
     // more than can be ranked against each other: by the same steps again, one level down

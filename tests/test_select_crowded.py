@@ -14,8 +14,9 @@ def test_room_for_the_bin():
         cfg, keep = B.make_config(n, d, *synth.ring_csr(n), 0.1, B.Q_TOPK, k=k, **kw)
         return B.workspace_bytes(cfg)
 
-    # from one block to several per row (k of some 6,550 on): a histogram per block and 1,024 entries
-    assert workspace(1000, 20_000, 8000) - workspace(1000, 20_000, 6500) < 1000 * (16 * 2048 * 4 + 1024 * 8 + 1500 * 4 * 20)
+    # from one block to several per row (k of some 6,550 on): a histogram per block and the row, where all of it may be listed
+    assert workspace(1000, 20_000, 8000) - workspace(1000, 20_000, 6500) < 1000 * (16 * 2048 * 4 + 20_000 * 8 + 1500 * 4 * 20)
+    assert workspace(1000, 40_000, 8000) - workspace(1000, 40_000, 6500) < 1000 * (16 * 2048 * 4 + 1024 * 8 + 1500 * 4 * 20)
     # thirty layers that share launches cost the same beside a layer that is taken apart as without it
     def layered(lengths, fraction):
         t = synth.layer_table(lengths, fraction=fraction)
@@ -39,6 +40,7 @@ def occupancy(keys, T, shift):
     (2_300_001, 700_000, 0, B.ORDER_COMPRESS_THEN_MIX, "histogram"),
     (2_300_001, 700_000, 0, B.ORDER_MIX_THEN_COMPRESS, None),
     (2_300_001, 2_299_999, 0, B.ORDER_COMPRESS_THEN_MIX, None),          # the list is the row
+    (20_001, 8000, 0, B.ORDER_COMPRESS_THEN_MIX, None),                  # ... and the bins as wide as half an octave
     (600_000, 300_000, 5000, B.ORDER_COMPRESS_THEN_MIX, None),           # about 1,000 entries in the bin
     (2_300_001, 700_000, 5000, B.ORDER_COMPRESS_THEN_MIX, "histogram"),  # a few hundred equal magnitudes in a sub-bin
     (2_300_001, 700_000, 200, B.ORDER_COMPRESS_THEN_MIX, "sub-bin"),     # thousands of them
