@@ -1055,13 +1055,19 @@ dim3 fallback_grid(int n) {
 }
 
 // A long pass that selects ahead generates Philox words (ALU work) while the caller's stream
-// runs the bandwidth-bound mix.  Its workgroups must not fill the wave slots before the mix: there are
-// about 256 of them, and 72 KiB of LDS that they do not use keep two to a compute unit at most.
-//   us per step, a workgroup per chunk with 48 KiB | 256 that stay, 48 KiB | 72 KiB | 512 that stay, 72 KiB
-//   n = 8, 28 M 647 | 624 | 625 | 626    31.8 M in 14 layers 778 | 769 | 769 | 772   4 workers, 8 M 130 | 129 | 128 | 129
-//   64 workers, 2.2 M 529 | 540 | 530 | 531   32, 4 M 409 | 403 | 403 | 402   8, 12 M with momentum 414 | 407 | 408 | 411
+// runs the bandwidth-bound mix.  Its workgroups stay (k_sel_draw: 256 or somewhat fewer up to eight rows, 32 a row
+// above) and must not fill the wave slots before the mix: 72 KiB of LDS that they do not use, beside the 8 that they
+// do, keep one to a compute unit, 48 KiB two.
+//   us per step, a workgroup per chunk with 48 KiB | staying, 48 KiB | staying, 72 KiB; and without gradients
+//   n = 8, 28 M      667 | 632 | 635     548 | 510 | 509       n = 4, 8 M       241 | 235 | 235     227 | 223 | 222
+//   n = 9, 2.2 M     118 | 104 | 132     114 | 102 | 131       n = 9, 6 M       202 | 189 | 188     177 | 162 | 174
+//   n = 12, 2.2 M, k = 100,000 196 | 193 | 197   181 | 173 | 191     n = 12, 3 M  152 | 131 | 130     130 | 109 | 113
+//   n = 14, 4 M      187 | 185 | 184     156 | 155 | 154       n = 16, 4 M      210 | 205 | 204     176 | 170 | 168
+//   n = 36, 3 M      347 | 347 | 344     282 | 278 | 274       n = 64, 2.2 M    484 | 430 | 428     406 | 341 | 337
+// (9 to 12 rows: at one to a compute unit a few workgroups are left for a second turn.)
 size_t ahead_lds_pad(const choco_ctx* ctx, int64_t row_len) {
-  return (ctx->launch_stream != ctx->stream && row_len > ((int64_t)1 << 21)) ? (size_t)72 << 10 : 0;
+  if (ctx->launch_stream == ctx->stream || row_len <= ((int64_t)1 << 21)) return 0;
+  return (size_t)(ctx->cfg.n > 8 && ctx->cfg.n <= 12 ? 48 : 72) << 10;
 }
 
 // random_a's candidate pass over a long row beside a step (see k_sel_draw).
@@ -1114,11 +1120,11 @@ void launch_select(choco_ctx* ctx, const Args& C, const Args& A, int kid_compact
     launch_draw(ctx, C, nvec, pad);
   } else {
     if (cvecs == 2)   // (top_a: one 4-vector per thread, n = 64, d = 65 k 33.8 -> 32.3 us per step, d = 270 k 96.0 -> 95.6)
-      LAUNCH(ctx, kid_compact, (k_sel_compact<COMP, false, NT, COMP == Q_TOPK ? 1 : 2>), chunk_grid(nvec, A.n, COMP == Q_TOPK ? 1 : 2), dim3(256), pad, C);
+      LAUNCH(ctx, kid_compact, (k_sel_compact<COMP, false, NT, COMP == Q_TOPK ? 1 : 2>), chunk_grid(nvec, A.n, COMP == Q_TOPK ? 1 : 2), dim3(256), 0, C);
     else if (kWide && NT && C.deferred_sgd)   // (1024 x 1 1066 us per step, 512 x 2 1035, 256 x 4 1030 at n = 8, d = 28 M)
       LAUNCH(ctx, kid_compact, (k_sel_compact<COMP, false, NT, kCompactVecs, false, 256, COMP == Q_TOPK && NT>), cgrid, dim3(256), 0, C);
-    else if (kWide) LAUNCH(ctx, kid_compact, (k_sel_compact<COMP, false, NT, 1, false, 1024>), cgrid, dim3(1024), pad, C);
-    else LAUNCH(ctx, kid_compact, (k_sel_compact<COMP, false, NT, kCompactVecs>), cgrid, dim3(256), pad, C);
+    else if (kWide) LAUNCH(ctx, kid_compact, (k_sel_compact<COMP, false, NT, 1, false, 1024>), cgrid, dim3(1024), 0, C);
+    else LAUNCH(ctx, kid_compact, (k_sel_compact<COMP, false, NT, kCompactVecs>), cgrid, dim3(256), 0, C);
   }
   launch_exact_select<COMP>(ctx, A);
 }
@@ -1393,7 +1399,7 @@ void long_layer_pass(choco_ctx* ctx, const Args& C, int which) {
     launch_draw(ctx, Cl, nvec, ahead_lds_pad(ctx, B.len));
   else if (B.plan.fallback_chain)
     LAUNCH(ctx, kid_compact, (k_sel_compact<COMP, false, NT, kCompactVecs>), chunk_grid(nvec, C.n, kCompactVecs),
-           dim3(256), ahead_lds_pad(ctx, B.len), Cl);
+           dim3(256), 0, Cl);
   else
     LAUNCH(ctx, kid_compact, (k_sel_compact<COMP, false, NT, 2>), chunk_grid(nvec, C.n, 2), dim3(256), 0, Cl);
 }

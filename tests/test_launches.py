@@ -200,3 +200,18 @@ for n, d in ((24, 60_000), (24, 100_000), (33, 20_000), (48, 20_000)):
     folded = {k for k, v in out.items() if len(v) == 2}
     assert folded == {"24 60000 ring", "24 100000 ring", "33 20000 ring", "48 20000 ring", "24 60000 complete"}
     assert all(v[-1] == ("k_dense_apply_mix" if k in folded else "k_dense_apply_mix_narrow") for k, v in out.items())
+
+
+def test_room_that_random_a_leaves_the_step():
+    """The draw beside a step: workgroups that stay, one to a compute unit, two where a few would be left over."""
+    out = recorded("""
+out = {}
+for n, d in ((2, 3_000_000), (8, 3_000_000), (9, 2_200_000), (12, 2_200_000), (13, 2_200_000), (64, 2_200_000), (8, 2_000_000)):
+    c = Context(n, d, B.Q_RANDK, k=d // 100)
+    out["%d %d" % (n, d)] = [l[1:] for l in c.step() if l[0] == "k_sel_draw"]
+    c.close()
+""")
+    assert out == {"2 3000000": [["128x2x1", "256x1x1", "73728"]], "8 3000000": [["32x8x1", "256x1x1", "73728"]],
+                   "9 2200000": [["32x9x1", "256x1x1", "49152"]], "12 2200000": [["32x12x1", "256x1x1", "49152"]],
+                   "13 2200000": [["32x13x1", "256x1x1", "73728"]], "64 2200000": [["32x64x1", "256x1x1", "73728"]],
+                   "8 2000000": []}
