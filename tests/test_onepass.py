@@ -106,6 +106,8 @@ def test_no_one_pass_where_the_state_fills_the_card():
 
 
 def graph(name, n):
+    if name == "irregular":                         # unequal degrees and weights
+        return synth.metropolis_csr(synth.irregular_graph(n, n - 2, seed=n))
     return synth.complete_csr(n) if name == "complete" else synth.ring_csr(n)
 
 
@@ -140,6 +142,8 @@ def steps(pair, grads, lr, mode, count, tag):
     (7, 3_600_255, 900, "complete", "momentum", 4),
     (3, 8_400_300, 12_000, "ring", "halves", 64),   # (multi-block select)
     (2, 12_600_000, 1, "ring", "step", 4),
+    (5, 5_100_001, 3000, "irregular", "step", 64),
+    (6, 4_300_002, 2000, "irregular", "halves", 4),
 ])
 def test_one_pass_steps(n, d, k, topo, mode, align):
     X0 = synth.normal_state(n, d, seed=n)
@@ -226,6 +230,8 @@ def test_one_pass_taken_back():
     (7, 3_700_255, 4, "complete", "momentum", 64, False),
     (3, 8_500_003, 16, "ring", "halves", 4, False),
     (2, 12_800_000, 64, "ring", "step", 4, False),
+    (4, 6_400_003, 16, "irregular", "step", 64, False),
+    (6, 4_300_001, 12, "irregular", "halves", 4, False),
     (8, 3_200_000, 8, "ring", "step", 4, True),      # one entry carries a row's norm: the level s itself
 ])
 def test_one_pass_gsgd(n, d, levels, topo, mode, align, outlier):
@@ -237,8 +243,15 @@ def test_one_pass_gsgd(n, d, levels, topo, mode, align, outlier):
                 ld_align=align)
     try:
         det = steps(pair, synth.GradientStream(n, d, seed=2), 0.05, mode, 4, mode)
-        # (the columns that are 100 times as large hold s |v| / ||v|| up to 1.3 at eight levels, 0.65 at four)
+        # (400 columns 100 times as large, |z| up to 4.5: s |v| / ||v|| = 100 s |z| / sqrt(d + 4e6) up to 1.3 with eight levels
+        # of 3.2 M, 2.2 with sixteen of 6.4 M, 0.65 with four)
         assert np.abs(det["codes"]).max() >= (levels if outlier else 2 if levels >= 8 else 1)
+        pair.gpu.set_step((1 << 33) + 2)             # a counter that is moved, back too: the dither follows it
+        pair.ref.t = (1 << 33) + 2
+        steps(pair, synth.GradientStream(n, d, seed=3), 0.05, "step", 1, "counter up")
+        pair.gpu.set_step(2)
+        pair.ref.t = 2
+        steps(pair, synth.GradientStream(n, d, seed=4), 0.05, "step", 1, "counter back")
     finally:
         pair.close()
 
@@ -351,5 +364,26 @@ def test_one_pass_held_back(op):
             pair.ref.X[:] = pair.ref.Xhat + (pair.ref.X - pair.ref.Xhat) * np.float32(5)
             pair.force_state()
             go(0.0, 3, "grown")
+    finally:
+        pair.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("op", ["topk", "qsgd"])
+def test_one_pass_extreme_values(op):
+    """Entries that carry a row by themselves (1e30), entries and a whole row below the normal range, zeros of both signs."""
+    n, d = 8, 3_200_000
+    X0 = synth.normal_state(n, d, seed=3)
+    X0[1] *= np.float32(1e-39)
+    X0[2, 5::1_000_000] = 1e30
+    X0[:, 100_000:100_040] = 1e-42
+    X0[:, 200_000:200_040] = -0.0
+    X0[3, 300_000:1_300_000] = 0.0
+    kw = dict(compressor=B.Q_TOPK, k=1500) if op == "topk" else dict(compressor=B.Q_QSGD, levels=8)
+    pair = Pair(X0, synth.ring_csr(n), 0.3, seed=2, **kw)
+    try:
+        steps(pair, synth.GradientStream(n, d, seed=4), 0.0, "step", 3, "no gradient")
+        steps(pair, synth.GradientStream(n, d, seed=4), 0.05, "step", 2, "gradient")
     finally:
         pair.close()
