@@ -423,27 +423,6 @@ __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
   return (uint32_t)__builtin_amdgcn_bitop3_b32((int)a, (int)b, (int)c, 0x96);
 }
 
-__device__ __forceinline__ uint4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
-                                               uint32_t k0, uint32_t k1) {
-#pragma unroll
-  for (int round = 0; round < 10; ++round) {
-    if (round > 0) {
-      k0 += 0x9E3779B9u;
-      k1 += 0xBB67AE85u;
-    }
-    // one 32 x 32 -> 64 bit product per counter word (a single multiply-add instruction on this
-    // target; written as two separate products it costs two quarter-rate multiplies)
-    const uint64_t p0 = (uint64_t)0xD2511F53u * (uint64_t)c0;
-    const uint64_t p1 = (uint64_t)0xCD9E8D57u * (uint64_t)c2;
-    const uint32_t hi0 = (uint32_t)(p0 >> 32), lo0 = (uint32_t)p0;
-    const uint32_t hi1 = (uint32_t)(p1 >> 32), lo1 = (uint32_t)p1;
-    const uint32_t n0 = xor3(hi1, c1, k0);
-    const uint32_t n2 = xor3(hi0, c3, k1);
-    c0 = n0; c1 = lo1; c2 = n2; c3 = lo0;
-  }
-  return make_uint4(c0, c1, c2, c3);
-}
-
 // U calls whose first counter words are m0, m0 + 64, ...: round by round side by side, so that a wave alone
 // on its SIMD has U independent chains to issue from (one after the other each waits for itself).
 template <int U>
@@ -463,6 +442,8 @@ __device__ __forceinline__ void philox_side_by_side(uint32_t m0, uint32_t c1, ui
       k0 += 0x9E3779B9u;
       k1 += 0xBB67AE85u;
     }
+    // one 32 x 32 -> 64 bit product per counter word (a single multiply-add instruction on this
+    // target; written as two separate products it costs two quarter-rate multiplies)
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const uint64_t p0 = (uint64_t)0xD2511F53u * (uint64_t)c[u][0];
@@ -483,6 +464,12 @@ __device__ __forceinline__ void philox_side_by_side(uint32_t m0, uint32_t c1, ui
   for (int u = 0; u < U; ++u) out[u] = make_uint4(c[u][0], c[u][1], c[u][2], c[u][3]);
 }
 
+__device__ __forceinline__ uint4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
+                                               uint32_t k0, uint32_t k1) {
+  uint4 out[1];
+  philox_side_by_side<1>(c0, c1, c2, c3, k0, k1, out);
+  return out[0];
+}
 
 // Four words for entries 4m .. 4m+3 of a worker on one stream.
 __device__ __forceinline__ uint4 random_words(const Args& A, int worker, uint32_t m, uint32_t stream) {
