@@ -134,9 +134,10 @@ KERNEL_BYTES_PER_ELEM = {
     "k_sel_compact_redo": 12,
     "k_dense_apply_mix_sgd": 20,  # read x, g, xhat; write x, xhat
     "k_tile_mix_sgd": 16,         # read x, g, xhat; write x
-    # top-k in one pass: candidates, update of xhat and mix (the records are not counted)
+    # top-k and qsgd in one pass: what is sent, update of xhat and mix (the records are not counted)
     "k_onepass_mix": 12,
     "k_onepass_mix_sgd": 16,
+    "k_onepass_encode": 0,        # qsgd: the message's bits (below)
     "k_mix_incremental_sgd": 20,  # read x, g, s, xhat; write x
     # layer-wise sign / gsgd: the norm pass over (layer, group) work items
     "k_layer_stat": 8,            # read x, xhat
@@ -328,7 +329,7 @@ def run_gpu(w, steps, warmup, profile=True, fused=True, mix_form=None, order=Non
                 bpe += 4 if name.endswith("_sgd") else 8   # the mix rides on this pass: + read s (+ write x)
             if bpe is not None and momentum and name.endswith("_sgd"):
                 bpe += 8                                   # + read and write the momentum memory
-            if bpe is not None and name in ("k_dense_apply_mix", "k_dense_apply_mix_sgd", "k_dense_apply"):
+            if bpe is not None and name in ("k_dense_apply_mix", "k_dense_apply_mix_sgd", "k_dense_apply", "k_onepass_encode"):
                 # + the message itself: one sign bit per entry (sign), b bits per entry (gsgd)
                 bpe += message_bits_per_entry(w) / 8.0
             if bpe is not None and not (w["comp"] == "randk" and name == "k_sel_compact"):
