@@ -214,8 +214,11 @@ int choco_nsum(choco_ctx *ctx, float **s_dev);
    gsgd: {sum v^2, ||v||_2, s/||v||_2, ||v||_2/(tau s), 0, 0} (the scales as rounded to fp32);
    TOPK/RANDK: {threshold key, tie cut-off index, kept count, select mode of the last step
    (0 = guessed threshold held, 1 = list rebuilt from the histogram, 2 = row scan), number of
-   steps so far that needed mode 1 or 2, length of the last candidate list}; for RANDK with the
-   look-ahead on (choco_set_lookahead) these are the figures of the selection made last, which
+   steps so far that needed mode 1 or 2, length of the last candidate list}; TOPK on rows up to
+   CHOCO_MAX_LAYER_LEN entries may be selected without such a list, out of one workgroup's
+   registers: mode 2 then says that the threshold lay outside the bracket around the last one
+   and the whole row was searched, and the length is that of the last bracket's list, which can
+   be below k or 0; for RANDK with the look-ahead on (choco_set_lookahead) these are the figures of the selection made last, which
    is a LATER step's (up to seven steps on).  Synchronises. */
 int choco_last_selection(choco_ctx *ctx, int32_t *idx_dev, float *val_dev);
 int choco_set_capture(choco_ctx *ctx, int32_t *codes_dev);
@@ -224,7 +227,7 @@ int choco_last_scalars(choco_ctx *ctx, double *scalars_host);
    (n * nlayers * 4, worker-major) from the last step.  SIGN: {||v_l||_1, scale, 0, 0};
    QSGD: {sum v_l^2, ||v_l||_2, s/||v_l||_2, ||v_l||_2/(tau_l s)}; TOPK/RANDK: {threshold
    key, entries kept at the threshold key, entries holding that key, 1 if the guessed
-   bracket held the threshold and 0 if the whole layer was searched}; for a layer above
+   bracket held the threshold (or k reaches its zeros) and 0 if the whole layer was searched}; for a layer above
    CHOCO_MAX_LAYER_LEN {threshold key, 0, 0, 0 if the select had to scan the layer itself
    and 1 otherwise}.  With
    layers, choco_last_selection returns sum(layer_k) pairs per worker, layer after layer,

@@ -1850,7 +1850,8 @@ __global__ __launch_bounds__(THREADS) void k_sel_compact(Args A0) {
 // random_a's candidate pass: Philox words only, no state.  Workgroups stay and go through the chunks of a row
 // in turn (gridDim.x is a multiple of kSegs, so that chunk c still appends to sub-list c % kSegs): it runs
 // beside a step's bandwidth-bound pass, whose waves fill the chip, and a workgroup per chunk spent more
-// time waiting for room than drawing (d = 21.6 M, n = 8: 395 us beside the pass, 77 alone; so 180).
+// time waiting for room than drawing (a layer of 21.6 M among 14, n = 8: 417 us beside the pass, 77 alone; so 252,
+// and the step takes as long as before: 772 us; a row of 28 M 667 -> 635).
 // grid (some, n), block 256.
 __global__ __launch_bounds__(256) void k_sel_draw(Args A) {
   __shared__ uint2 stage[kStageCap];

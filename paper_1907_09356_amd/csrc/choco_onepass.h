@@ -22,9 +22,9 @@
 // the same xhat) but for some units in the last place, in about |gamma acc / x'| of the entries; the pass
 // tries it and stores the difference, a byte per entry, for the rows of a tile that have one, and records
 // the columns where a byte does not hold it.  (n = 8, d = 28 M, xhat near x and apart by a few percent of it
-// between workers, us per step by gamma 0.002 | 0.02 | 0.1: top_a 681 | 885 | 1029, two passes 1059-1077; gsgd
-// 789 | 857 | 850, two passes 1182-1196.  Columns recorded instead filled the slots from gamma acc / x' of
-// a percent on.)  A tile with more than kRecSlots columns to record is left unmixed and done by the last kernel
+// between workers forty steps before, us per step by gamma 0.002 | 0.02 | 0.1 | 0.3: top_a 675 | 693 | 767 | 770, two
+// passes 1043-1049; gsgd 751 | 807 | 820 | 806, two passes 1168-1175.  Columns recorded instead filled the slots from
+// gamma acc / x' of a percent on.)  A tile with more than kRecSlots columns to record is left unmixed and done by the last kernel
 // (top_a: its candidates go to the lists one by one).
 #pragma once
 
@@ -51,7 +51,9 @@ struct OnePass {
 // Slots per tile of 256 columns.  A slot is 8 n bytes, so the records are a quarter of an array of the
 // state; at 5 expected columns per tile (n = 8, k / d = 0.001) no tile in 10^6 has more than 20.
 constexpr int kRecSlots = 32;
-constexpr int kOnePassRows = 8;     // a row per wave; n lanes of a group of eight where records are read
+// A row per wave, n lanes of a group of eight where records are read, a byte per row in a word of marks: the form ends
+// at eight workers by this layout (wider ones, where n k / d is as small, have not been built or measured).
+constexpr int kOnePassRows = 8;
 constexpr int kRecTiles = 16;       // tiles whose records a wave goes through together
 constexpr float kWide = 24.0f;      // columns that a tile is expected to have marked above which all tiles are left open
 
