@@ -55,7 +55,7 @@ constexpr int kRecSlots = 32;
 // at eight workers by this layout (wider ones, where n k / d is as small, have not been built or measured).
 constexpr int kOnePassRows = 8;
 constexpr int kRecTiles = 16;       // tiles whose records a wave goes through together
-constexpr float kWide = 24.0f;      // columns that a tile is expected to have marked above which all tiles are left open
+constexpr float kWide = 28.0f;      // gsgd: columns that a tile is expected to have marked above which all tiles are left open
 
 // Columns of the lane's 4-vector that some wave marked (a byte per wave).
 __device__ __forceinline__ uint32_t fold_marks(uint64_t m) {
@@ -94,8 +94,9 @@ __device__ __forceinline__ void list_here(const Args& A, int r, int tile_no, uin
 // A step whose threshold or bound fails costs the pass, its undoing and the second form; where that happens to
 // about every other step it is better to leave all tiles unmixed and do them once (16 bytes per entry here and
 // 16 in the last kernel, as many as two passes take).  A failure counts two and a step that went well takes one
-// back, up to kHeldMost; tiles are left open from kHeldFrom on, down to kHeldTo.  gsgd and top_a also leave them for
-// one step when more columns are going to be marked than there are slots for.
+// back, up to kHeldMost; tiles are left open from kHeldFrom on, down to kHeldTo.  gsgd also leaves them for one step
+// when its bound is so wide that nearly as many columns are going to be marked as there are slots for (top_a's next
+// list does not follow from this one's length).
 //   us per step, n = 8, d = 12 M: two passes | one pass always | as here
 //   gsgd, the gradient step to and fro (norms by 5)   503 | 788 | 590    every other pair of steps 503 | 517 | 473
 //         to or fro by chance                         503 | 384 | 374    a tenth of the entries moving 507 | 364 | 358
@@ -412,9 +413,9 @@ __device__ __forceinline__ void take_back(const Args& A, const OnePass& P, float
 // lists' lengths and leave.  grid any, block 64 n, dynamic LDS n x 256 floats.
 __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_restore(Args A, OnePass P, int32_t ntiles) {
   extern __shared__ float tile[];
-  __shared__ uint32_t s_bad, s_listed;
+  __shared__ uint32_t s_bad;
   const int r = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  if (threadIdx.x == 0) s_bad = s_listed = 0u;
+  if (threadIdx.x == 0) s_bad = 0u;
   const bool first = no_guess_yet(A.ctl[0].guess_key);
   __syncthreads();
   const uint32_t raw = lane < kSegs ? *seg_counter(A, r, lane) : 0u;
@@ -423,11 +424,10 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_restore(Args A, O
   for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off, 64);
   const bool fits = __ballot(raw > A.seg_cap) == 0ull;
   if (lane == 0 && (!fits || sum < (unsigned long long)A.k)) s_bad = 1u;
-  if (lane == 0) atomicAdd(&s_listed, (uint32_t)(sum < (1u << 28) ? sum : (1u << 28)));
   __syncthreads();
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     P.state->redo_all = s_bad;
-    if (!first) judge_step(A, P.state, s_bad != 0u, (float)kChunk * (float)s_listed > kWide * (float)A.d);
+    if (!first) judge_step(A, P.state, s_bad != 0u, false);
   }
   if (s_bad == 0u || first) return;   // (in the first step nothing has been mixed)
   const RowNbrs nb = nbr_fetch(A, nbr_span<1, kOnePassRows>(A, r, lane), lane);
