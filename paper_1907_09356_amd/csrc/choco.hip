@@ -1064,10 +1064,13 @@ dim3 fallback_grid(int n) {
 //   n = 12, 2.2 M, k = 100,000 196 | 193 | 197   181 | 173 | 191     n = 12, 3 M  152 | 131 | 130     130 | 109 | 113
 //   n = 14, 4 M      187 | 185 | 184     156 | 155 | 154       n = 16, 4 M      210 | 205 | 204     176 | 170 | 168
 //   n = 36, 3 M      347 | 347 | 344     282 | 278 | 274       n = 64, 2.2 M    484 | 430 | 428     406 | 341 | 337
-// (9 to 12 rows: at one to a compute unit a few workgroups are left for a second turn.)
+// (9 to 12 rows: at one to a compute unit a few workgroups are left for a second turn, which shows where the step is
+// short.  Longer rows and the long layers of a table keep 72 KiB: n = 12, 12 M, k = 120,000 48 KiB 595 | 72 KiB 589,
+// without gradients 486 | 510; 31.8 M in 14 layers, n = 10 931 | 924, without gradients 771 | 760.)
 size_t ahead_lds_pad(const choco_ctx* ctx, int64_t row_len) {
   if (ctx->launch_stream == ctx->stream || row_len <= ((int64_t)1 << 21)) return 0;
-  return (size_t)(ctx->cfg.n > 8 && ctx->cfg.n <= 12 ? 48 : 72) << 10;
+  const bool two = ctx->cfg.n > 8 && ctx->cfg.n <= 12 && ctx->nlayers == 0 && row_len <= ((int64_t)1 << 23);
+  return (size_t)(two ? 48 : 72) << 10;
 }
 
 // random_a's candidate pass over a long row beside a step (see k_sel_draw).

@@ -206,7 +206,7 @@ def test_room_that_random_a_leaves_the_step():
     """The draw beside a step: workgroups that stay, one to a compute unit, two where a few would be left over."""
     out = recorded("""
 out = {}
-for n, d in ((2, 3_000_000), (8, 3_000_000), (9, 2_200_000), (12, 2_200_000), (13, 2_200_000), (64, 2_200_000), (8, 2_000_000)):
+for n, d in ((2, 3_000_000), (8, 3_000_000), (9, 2_200_000), (12, 2_200_000), (13, 2_200_000), (64, 2_200_000), (8, 2_000_000), (9, 8_400_000)):
     c = Context(n, d, B.Q_RANDK, k=d // 100)
     out["%d %d" % (n, d)] = [l[1:] for l in c.step() if l[0] == "k_sel_draw"]
     c.close()
@@ -214,4 +214,4 @@ for n, d in ((2, 3_000_000), (8, 3_000_000), (9, 2_200_000), (12, 2_200_000), (1
     assert out == {"2 3000000": [["128x2x1", "256x1x1", "73728"]], "8 3000000": [["32x8x1", "256x1x1", "73728"]],
                    "9 2200000": [["32x9x1", "256x1x1", "49152"]], "12 2200000": [["32x12x1", "256x1x1", "49152"]],
                    "13 2200000": [["32x13x1", "256x1x1", "73728"]], "64 2200000": [["32x64x1", "256x1x1", "73728"]],
-                   "8 2000000": []}
+                   "8 2000000": [], "9 8400000": [["32x9x1", "256x1x1", "73728"]]}
