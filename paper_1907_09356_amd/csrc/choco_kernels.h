@@ -238,7 +238,8 @@ struct Args {
 // guess and the expected threshold with 1.5 k entries in them: a quarter of a sub-list is ten mean bins.  But
 // where nearly all of the row is listed the guess may be zero and the bins as wide as half an octave around the
 // threshold: any share of the row (n = 12, d = 20,000, k = 8,000 43 us per step, 85 with room for 1,024; n = 64,
-// d = 15,000, k = 7,000 86 and 122).
+// d = 15,000, k = 7,000 86 and 122).  (A capacity that the kernels work out costs the select 0.3 to 0.5 us against a
+// constant one, n = 8, d = 1 M, k = 7,000 65.7 -> 66.0 us per step; the constant 32,768 cost 256 KB per worker and set.)
 __host__ __device__ __forceinline__ uint32_t bin_capacity(uint32_t seg_cap, int64_t k, int32_t d) {
   const uint32_t most = 4 * k >= d ? 16u * seg_cap : seg_cap / 4u;
   return most < (uint32_t)kSmallCap ? (uint32_t)kSmallCap : most < (uint32_t)kBinCap ? most : (uint32_t)kBinCap;
