@@ -482,19 +482,54 @@ __device__ __forceinline__ uint32_t pick(const uint4& v, int c) {
 }
 
 // 64-lane butterfly sum in fp64; every lane ends with the halving-tree result
-// t[l] += t[l+off] for off = 32,16,...,1 (the sum is commutative, so the xor
-// exchange builds exactly that tree in every lane).
-__device__ __forceinline__ double wave_tree_sum(double t) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) t = t + __shfl_xor(t, off, 64);
-  return t;
+// t[l] += t[l+off] for off = 32,16,...,1 (the sum is commutative, so an exchange with
+// lane ^ off builds exactly that tree in every lane).  The exchanges are lane moves of the
+// vector unit - a swap of the halves, a swap of neighbouring rows of 16, and inside a row
+// rotations by 8 and 4 (after each step the values repeat, so a rotation by off reaches lane ^ off)
+// and quad permutations - instead of twelve trips through LDS, one waiting for the other: n = 8, d = 270 k,
+// sign 17.4 -> 17.0 us per step; 65 layers, n = 16, with momentum 37.4 -> 36.7.  (Where the vector unit is
+// what is short the trips through LDS are the better choice: wave_tree_sum_lds.)
+template <int CTRL>
+__device__ __forceinline__ double lane_move(double v) {
+  const uint64_t b = (uint64_t)__double_as_longlong(v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xF, 0xF, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xF, 0xF, true);
+  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
 
 // The same over aligned sub-groups of kGroup = 16 lanes (halving 8,4,2,1): lanes
 // 16q..16q+15 end with the tree sum of their own 16 values.
 __device__ __forceinline__ double group_tree_sum(double t) {
+  static_assert(kGroup == 16, "a row of the vector unit");
+  t = t + lane_move<0x128>(t);   // row_ror 8
+  t = t + lane_move<0x124>(t);   // row_ror 4
+  t = t + lane_move<0x4E>(t);    // quad_perm [2,3,0,1]
+  t = t + lane_move<0xB1>(t);    // quad_perm [1,0,3,2]
+  return t;
+}
+
+__device__ __forceinline__ double wave_tree_sum(double t) {
+  typedef uint32_t vu2 __attribute__((ext_vector_type(2)));
+  const auto joined = [](uint32_t lo, uint32_t hi) { return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo)); };
+  {
+    const uint64_t b = (uint64_t)__double_as_longlong(t);
+    const vu2 lo = __builtin_amdgcn_permlane32_swap((uint32_t)b, (uint32_t)b, false, false);
+    const vu2 hi = __builtin_amdgcn_permlane32_swap((uint32_t)(b >> 32), (uint32_t)(b >> 32), false, false);
+    t = joined(lo[0], hi[0]) + joined(lo[1], hi[1]);   // lower half everywhere + upper half everywhere
+  }
+  {
+    const uint64_t b = (uint64_t)__double_as_longlong(t);
+    const vu2 lo = __builtin_amdgcn_permlane16_swap((uint32_t)b, (uint32_t)b, false, false);
+    const vu2 hi = __builtin_amdgcn_permlane16_swap((uint32_t)(b >> 32), (uint32_t)(b >> 32), false, false);
+    t = joined(lo[0], hi[0]) + joined(lo[1], hi[1]);   // even rows + odd rows
+  }
+  return group_tree_sum(t);
+}
+
+// The same sum through LDS.  gsgd in one pass has Philox beside it: n = 8, d = 28 M 784 us per step, 786 with lane moves.
+__device__ __forceinline__ double wave_tree_sum_lds(double t) {
 #pragma unroll
-  for (int off = kGroup / 2; off >= 1; off >>= 1) t = t + __shfl_xor(t, off, 64);
+  for (int off = 32; off >= 1; off >>= 1) t = t + __shfl_xor(t, off, 64);
   return t;
 }
 

@@ -172,7 +172,7 @@ __global__ __launch_bounds__(64 * kOnePassRows) void k_onepass_mix(Args A, OnePa
     }
   }
   if (COMP == Q_QSGD) {
-    const double t = wave_tree_sum(mine ? lane_terms<Q_QSGD>(x - h, e, A.d) : 0.0);
+    const double t = wave_tree_sum_lds(mine ? lane_terms<Q_QSGD>(x - h, e, A.d) : 0.0);
     if (lane == 0) A.chunk_sums[(int64_t)r * A.nchunks + tile_no] = t;
   }
   if (held) {
