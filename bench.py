@@ -317,7 +317,7 @@ def run_gpu(w, steps, warmup, profile=True, fused=True, mix_form=None, order=Non
             entry = dict(launches_per_step=count / steps, avg_ms=avg_ms,
                          ms_per_step=total_ms / steps)
             bpe = KERNEL_BYTES_PER_ELEM.get(name)
-            if name.startswith("k_layer_compress"):
+            if name.startswith(("k_layer_compress", "k_layers_")):
                 # top-k: read x, xhat; random-k reads nothing; a pass that carries the local update
                 # also reads g and writes x
                 bpe = {"topk": 8, "randk": 0}[w["comp"]]
@@ -334,12 +334,15 @@ def run_gpu(w, steps, warmup, profile=True, fused=True, mix_form=None, order=Non
                 bpe += message_bits_per_entry(w) / 8.0
             if bpe is not None and not (w["comp"] == "randk" and name == "k_sel_compact"):
                 per_launch = bpe * elems
-                if "layers" in w and (name.startswith("k_layer_compress") or name.startswith("k_sel_compact")):
-                    # layers above 10,240 entries go through k_sel_compact, the others through
-                    # k_layer_compress; the launches of each share its part of one pass over the rows
+                if "layers" in w and name.startswith(("k_layer_compress", "k_layers_", "k_sel_compact")):
+                    # layers above 10,240 entries go through k_sel_compact, the others through k_layer_compress;
+                    # or k_layers_select takes those of 3,073 to 10,240 and k_layers_pass the rest.  The launches of
+                    # each share its part of one pass over the rows
                     lengths = layer_table_of(w)[1]
-                    long_part = float(lengths[lengths > 10240].sum()) / float(lengths.sum())
-                    per_launch *= long_part if name.startswith("k_sel_compact") else 1.0 - long_part
+                    part = ((lengths > 3072) & (lengths <= 10240) if name.startswith("k_layers_select") else
+                            (lengths <= 3072) | (lengths > 10240) if name.startswith("k_layers_pass") else
+                            lengths > 10240 if name.startswith("k_sel_compact") else lengths <= 10240)
+                    per_launch *= float(lengths[part].sum()) / float(lengths.sum())
                     per_launch /= entry["launches_per_step"]
                 entry["alg_bytes_per_launch"] = per_launch
                 entry["alg_GBps"] = per_launch / (avg_ms * 1e-3) / 1e9

@@ -739,7 +739,7 @@ int join_lookahead(choco_ctx* ctx) {
 enum KernelId {
   KID_SGD, KID_MOMENTUM, KID_DENSE_STAT, KID_GROUP_REDUCE, KID_DENSE_FINALISE, KID_DENSE_APPLY_MIX, KID_TILE_MIX,
   KID_DENSE_APPLY, KID_MIX_DIRECT_GLOBAL, KID_MIX_INCREMENTAL, KID_SEL_COMPACT, KID_SEL_FALLBACK,
-  KID_SEL_REFINE, KID_SCATTER_S, KID_XHAT_UPDATE, KID_GATHER_VALUES, KID_SEL_VALUES, KID_SEL_HIST_PARTS, KID_SEL_EMIT_PARTS, KID_SEL_FINISH, KID_DENSE_STAT_SGD, KID_DENSE_STAT_REDO, KID_DENSE_APPLY_MIX_SGD, KID_SEL_COMPACT_SGD, KID_SEL_COMPACT_REDO, KID_TILE_MIX_SGD, KID_MIX_INCREMENTAL_SGD, KID_LAYER_COMPRESS, KID_LAYER_COMPRESS_SGD, KID_LAYER_STAT, KID_LAYER_STAT_SGD, KID_LAYER_STAT_REDO, KID_LAYER_FINALISE, KID_WIRE, KID_ZERO_WORDS, KID_ONEPASS_MIX, KID_ONEPASS_MIX_SGD, KID_ONEPASS_LIST, KID_ONEPASS_RESTORE, KID_ONEPASS_FINISH, KID_ONEPASS_ENCODE, KID_ROW_COMPRESS, KID_ROW_COMPRESS_SGD, KID_COUNT
+  KID_SEL_REFINE, KID_SCATTER_S, KID_XHAT_UPDATE, KID_GATHER_VALUES, KID_SEL_VALUES, KID_SEL_HIST_PARTS, KID_SEL_EMIT_PARTS, KID_SEL_FINISH, KID_DENSE_STAT_SGD, KID_DENSE_STAT_REDO, KID_DENSE_APPLY_MIX_SGD, KID_SEL_COMPACT_SGD, KID_SEL_COMPACT_REDO, KID_TILE_MIX_SGD, KID_MIX_INCREMENTAL_SGD, KID_LAYER_COMPRESS, KID_LAYER_COMPRESS_SGD, KID_LAYER_STAT, KID_LAYER_STAT_SGD, KID_LAYER_STAT_REDO, KID_LAYER_FINALISE, KID_WIRE, KID_ZERO_WORDS, KID_ONEPASS_MIX, KID_ONEPASS_MIX_SGD, KID_ONEPASS_LIST, KID_ONEPASS_RESTORE, KID_ONEPASS_FINISH, KID_ONEPASS_ENCODE, KID_ROW_COMPRESS, KID_ROW_COMPRESS_SGD, KID_LAYERS_PASS, KID_LAYERS_PASS_SGD, KID_LAYERS_SELECT, KID_LAYERS_SELECT_SGD, KID_COUNT
 };
 const char* const kKernelNames[KID_COUNT] = {
   "k_sgd", "k_momentum", "k_dense_stat", "k_group_reduce", "k_dense_finalise", "k_dense_apply_mix", "k_tile_mix",
@@ -747,7 +747,8 @@ const char* const kKernelNames[KID_COUNT] = {
   "k_sel_refine", "k_scatter_s", "k_xhat_update", "k_gather_values", "k_sel_values", "k_sel_hist_parts", "k_sel_emit_parts", "k_sel_finish",
   "k_dense_stat_sgd", "k_dense_stat_redo", "k_dense_apply_mix_sgd", "k_sel_compact_sgd", "k_sel_compact_redo", "k_tile_mix_sgd", "k_mix_incremental_sgd",
   "k_layer_compress", "k_layer_compress_sgd", "k_layer_stat", "k_layer_stat_sgd", "k_layer_stat_redo", "k_layer_finalise", "k_wire",
-  "k_zero_words", "k_onepass_mix", "k_onepass_mix_sgd", "k_onepass_list", "k_onepass_restore", "k_onepass_finish", "k_onepass_encode", "k_row_compress", "k_row_compress_sgd"};
+  "k_zero_words", "k_onepass_mix", "k_onepass_mix_sgd", "k_onepass_list", "k_onepass_restore", "k_onepass_finish", "k_onepass_encode", "k_row_compress", "k_row_compress_sgd",
+  "k_layers_pass", "k_layers_pass_sgd", "k_layers_select", "k_layers_select_sgd"};
 constexpr size_t kMaxProfiledLaunches = 16384;
 
 // Brackets one launch with two events when profiling is on (no-op otherwise).
@@ -1446,10 +1447,17 @@ int gossip_layers_sparse(choco_ctx* ctx, const Args& F) {
   const int nlong = (int)ctx->long_layers.size();   // first in the work list, not for the layer kernel
   const int nmid = ctx->nmid, nsmall = ctx->nsmall, ntiny = A.nlayers - nlong - nmid - nsmall;
   const int wide_blocks = nmid + nsmall + (ntiny + 15) / 16;
+  // top_a with layers of every kind: two launches before the mix instead of four (see k_layers_pass).  Not where long
+  // rows' shape of the pass matters more, a 4-vector per thread of 1024: layers of up to 300,000 entries, n = 64, 250 MB
+  // 510 -> 457 us per step; of 1,690,000, n = 8, 1 GB 1241 -> 1247.
+  // (Workgroups are numbered in 31 bits there, and the grid has the layers in x.)
+  const int64_t pass_x = nsmall + (ntiny + 3) / 4 + (int64_t)((ctx->batched_nvec + 255) / 256) * ctx->nbatched;
+  const bool together = COMP == Q_TOPK && ctx->nbatched > 0 && nmid > 0 && nsmall + ntiny > 0 && ctx->batched_nvec <= (1 << 17) &&
+                        pass_x <= (1 << 22) && (pass_x + nmid) * A.n < ((int64_t)1 << 31);
   // few workers: with a 1024-thread workgroup for every layer above a wave's reach (and sixteen
   // waves' worth of smaller layers in each of the others) the chip still is not full, and one
   // launch does
-  const bool wide = (int64_t)wide_blocks * A.n <= 256;
+  const bool wide = !together && (int64_t)wide_blocks * A.n <= 256;
   // the long layers (those that share launches first, then the others one after the other), then
   // the layer kernel for the layers within its reach
   auto select_layers = [&](const Args& S) -> int {
@@ -1468,7 +1476,11 @@ int gossip_layers_sparse(choco_ctx* ctx, const Args& F) {
       if (split) ctx->launch_stream = yes ? ctx->aux_stream2 : ctx->aux_stream;
     };
     second(solo);
-    if (ctx->nbatched > 0 && NT && COMP == Q_TOPK) {
+    if (together) {
+      if constexpr (COMP == Q_TOPK)
+        LAUNCH(ctx, S.G ? KID_LAYERS_PASS_SGD : KID_LAYERS_PASS, (k_layers_pass<COMP, NT>), dim3((unsigned)pass_x, (unsigned)A.n),
+               dim3(256), 0, S, nlong + nmid, nsmall, nsmall + (ntiny + 3) / 4, (ctx->batched_nvec + 255) / 256);
+    } else if (ctx->nbatched > 0 && NT && COMP == Q_TOPK) {
       // (large states, streamed past the caches: the workgroup shape of the whole-row pass on long rows)
       const dim3 cgrid((unsigned)((ctx->batched_nvec + 1023) / 1024), (unsigned)A.n, (unsigned)ctx->nbatched);
       LAUNCH(ctx, S.G ? KID_SEL_COMPACT_SGD : KID_SEL_COMPACT, (k_sel_compact<COMP, false, NT, 1, true, 1024>), cgrid,
@@ -1479,7 +1491,11 @@ int gossip_layers_sparse(choco_ctx* ctx, const Args& F) {
       LAUNCH(ctx, S.G ? KID_SEL_COMPACT_SGD : KID_SEL_COMPACT, (k_sel_compact<COMP, false, NT, V, true>), cgrid,
              dim3(256), 0, S);
     }
-    if (ctx->nbatched > 0) {
+    if (together) {
+      if constexpr (COMP == Q_TOPK)
+        LAUNCH(ctx, S.G ? KID_LAYERS_SELECT_SGD : KID_LAYERS_SELECT, (k_layers_select<COMP, NT>),
+               dim3((unsigned)(nmid + ctx->nbatched), (unsigned)A.n), dim3(1024), 0, S, nlong, nmid);
+    } else if (ctx->nbatched > 0) {
       LAUNCH(ctx, KID_SEL_REFINE, (k_sel_refine<COMP, true>), dim3((unsigned)A.n, (unsigned)ctx->nbatched), dim3(1024),
              0, Q);
     }
@@ -1504,10 +1520,10 @@ int gossip_layers_sparse(choco_ctx* ctx, const Args& F) {
         LAUNCH(ctx, kid, (k_layer_compress<COMP, 1024, NT>), dim3((unsigned)wide_blocks, (unsigned)A.n), dim3(1024), 0,
                S, nlong, nmid + nsmall);
     } else {
-      if (nmid > 0)
+      if (nmid > 0 && !together)
         LAUNCH(ctx, kid, (k_layer_compress<COMP, 1024, NT, true>), dim3((unsigned)nmid, (unsigned)A.n), dim3(1024), 0, S,
                nlong, nmid);
-      if (nsmall + ntiny > 0)
+      if (nsmall + ntiny > 0 && !together)
         LAUNCH(ctx, kid, (k_layer_compress<COMP, 256, NT>), dim3((unsigned)(nsmall + (ntiny + 3) / 4), (unsigned)A.n),
                dim3(256), 0, S, nlong + nmid, nsmall);
     }

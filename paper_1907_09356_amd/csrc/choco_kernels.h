@@ -2408,18 +2408,22 @@ __device__ void refine_and_emit(const Args& A, int i, const uint32_t* pre, uint3
 // grid n, block 1024, dynamic LDS = the worker's bitmap (short rows) or nothing.
 // BATCH: grid (n, long layers of A.long_tab); more workgroups than compute units as a rule, so 64 registers
 // for two to a unit (six layers, n = 64: 14.7 -> 10.6 us; a workgroup per worker is 0.7 us slower that way).
-template <int COMP, bool BATCH = false, bool ONEPASS = false>
-__global__ __launch_bounds__(1024, BATCH ? 8 : 4) void k_sel_refine(Args A0) {
-  const Args A = BATCH ? long_view(A0, A0.long_tab[blockIdx.y]) : A0;
-  __shared__ uint32_t h[kBins];
-  __shared__ uint32_t grp[256];
-  __shared__ uint32_t lens[kSegs];
-  __shared__ uint32_t pre[kSegs + 1];
-  __shared__ uint2 small[kSmallCap];
-  __shared__ uint64_t s_prefix, s_kstar;
-  __shared__ uint32_t s_need, s_digit, s_above, s_emit, s_total, s_good, s_small, s_short;
-  extern __shared__ uint32_t lbits[];   // bitmap_words words: kept entries of this worker (short rows)
-  const int i = blockIdx.x;
+struct RefineShared {
+  uint32_t h[kBins];
+  uint32_t grp[256];
+  uint32_t lens[kSegs];
+  uint32_t pre[kSegs + 1];
+  uint2 small[kSmallCap];
+  uint64_t prefix, kstar;
+  uint32_t need, digit, above, emit, total, good, small_n, all_short;
+};
+template <int COMP, bool BATCH, bool ONEPASS>
+__device__ __forceinline__ void refine_row(const Args& A, int i, RefineShared& sh, uint32_t* lbits) {
+  uint32_t *const h = sh.h, *const grp = sh.grp, *const lens = sh.lens, *const pre = sh.pre;
+  uint2* const small = sh.small;
+  uint64_t &s_prefix = sh.prefix, &s_kstar = sh.kstar;
+  uint32_t &s_need = sh.need, &s_digit = sh.digit, &s_above = sh.above, &s_emit = sh.emit, &s_total = sh.total, &s_good = sh.good,
+           &s_small = sh.small_n, &s_short = sh.all_short;
   WorkerCtl* ctl = A.ctl + i;
   // The first kSpecPerSeg entries of every sub-list are fetched before the lengths are known (32
   // threads per sub-list, eight entries each; what lies beyond a list's end is old data inside
@@ -2573,6 +2577,14 @@ __global__ __launch_bounds__(1024, BATCH ? 8 : 4) void k_sel_refine(Args A0) {
   publish_bitmap(A, i, lbits);
   if (BATCH) reset_lists(A, i);
   if (threadIdx.x == 0) next_guess<ONEPASS>(A, ctl, s_kstar, total, true, s_emit, 0u);
+}
+
+template <int COMP, bool BATCH = false, bool ONEPASS = false>
+__global__ __launch_bounds__(1024, BATCH ? 8 : 4) void k_sel_refine(Args A0) {
+  __shared__ RefineShared sh;
+  extern __shared__ uint32_t lbits[];   // bitmap_words words: kept entries of this worker (short rows)
+  const Args A = BATCH ? long_view(A0, A0.long_tab[blockIdx.y]) : A0;
+  refine_row<COMP, BATCH, ONEPASS>(A, (int)blockIdx.x, sh, lbits);
 }
 
 // ---------------------------------------------------------------------------

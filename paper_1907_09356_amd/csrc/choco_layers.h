@@ -652,6 +652,82 @@ void k_layer_compress(Args A, int32_t first, int32_t nblock) {
   }
 }
 
+// top_a layer by layer, the launches above put together two by two where there are layers of each kind: a
+// launch whose workgroups last for a chain of barriers and look-ups, beside one that streams or beside another of its
+// kind that leaves slots free.  The longest chains of all workers come first in the grid.
+//   us per step on 65 layers: four launches before the mix (three up to n = 16) | two, a worker's chains first | all workers' first
+//   n = 64 123.4 | 113.5 | 107.4      n = 32 76.2 | 64.8 | 59.8      n = 20 62.2 | 48.5 | 44.9
+//   n = 16 46.7 | - | 39.8      n = 9 38.3 | - | 35.2      n = 4 32.3 | - | 28.7
+// Workgroup (x, y) of a grid of (own + other, n) as (worker, number) with the first `own` of every worker before all others.
+__device__ __forceinline__ int own_first(int own, int& worker) {
+  const int lin = (int)(blockIdx.y * gridDim.x + blockIdx.x), total = own * (int)gridDim.y;
+  if (lin < total) {
+    worker = lin / own;
+    return lin - worker * own;
+  }
+  const int other = (int)gridDim.x - own;
+  worker = (lin - total) / other;
+  return own + (lin - total) - worker * other;
+}
+
+// The pass over the long layers and the layers of up to 3,072 entries.
+// grid (nlayer + chunks x long layers, n), block 256; `first`, `nblock` as for k_layer_compress.
+template <int COMP, bool NT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8)))
+void k_layers_pass(Args A0, int32_t first, int32_t nblock, int32_t nlayer, int32_t chunks) {
+  __shared__ union {
+    struct {
+      uint32_t cnt[34], emit[4], list_n[4];
+      uint2 list[512];
+    } layer;
+    struct {
+      uint2 stage[kStageCap];
+      uint32_t count;
+    } pass;
+  } sh;
+  int i;
+  const int b = own_first(nlayer, i);
+  if (b >= nlayer) {
+    const int which = (b - nlayer) / chunks, chunk = (b - nlayer) - which * chunks;
+    const Args A = long_view(A0, A0.long_tab[which]);
+    if (chunk * 256 >= (A.d + 3) >> 2) return;
+    if (threadIdx.x == 0) sh.pass.count = 0;
+    __syncthreads();
+    compact_chunk<COMP, false, NT, true, 1>(A, i, chunk, sh.pass.stage, &sh.pass.count);
+  } else if (b < nblock) {
+    const LayerShared ls{sh.layer.cnt, sh.layer.emit, sh.layer.list_n, sh.layer.list};
+    layer_body<COMP, 256, NT>(A0, i, A0.layer_work[first + b], (int)threadIdx.x, ls);
+  } else {
+    const int wave = (int)threadIdx.x >> 6, idx = first + nblock + (b - nblock) * 4 + wave;
+    if (idx < A0.nlayers) {
+      const LayerShared ls{sh.layer.cnt, sh.layer.emit + wave, sh.layer.list_n + wave, sh.layer.list + 128 * wave};
+      layer_body<COMP, 64, NT>(A0, i, A0.layer_work[idx], (int)threadIdx.x & 63, ls);
+    }
+  }
+}
+
+// The layers above 3,072 entries and the exact select of the long ones.  grid (nmid + long layers, n), block 1024.
+template <int COMP, bool NT>
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8)))
+void k_layers_select(Args A0, int32_t first, int32_t nmid) {
+  __shared__ union {
+    struct {
+      uint32_t cnt[34], emit[16], list_n[16];
+      uint2 list[2048];
+    } layer;
+    RefineShared refine;
+  } sh;
+  int i;
+  const int b = own_first(nmid, i);
+  if (b >= nmid) {
+    const Args A = long_view(A0, A0.long_tab[b - nmid]);
+    refine_row<COMP, true, false>(A, i, sh.refine, nullptr);
+  } else {
+    const LayerShared ls{sh.layer.cnt, sh.layer.emit, sh.layer.list_n, sh.layer.list};
+    layer_body<COMP, 1024, NT>(A0, i, A0.layer_work[first + b], (int)threadIdx.x, ls);
+  }
+}
+
 // ---------------------------------------------------------------------------
 // sign / gsgd_b layer by layer: norm pass and scales.
 // ---------------------------------------------------------------------------
