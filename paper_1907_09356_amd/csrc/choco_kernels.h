@@ -429,26 +429,33 @@ __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
 template <int U>
 __device__ __forceinline__ void philox_side_by_side(uint32_t m0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0,
                                                     uint32_t k1, uint4 (&out)[U]) {
+  // The first two rounds by hand: of the counter words only the first differs between the calls, so one of
+  // each round's two products is the same for all of them (and for a worker known to the wave, scalar).
+  constexpr uint32_t kM0 = 0xD2511F53u, kM1 = 0xCD9E8D57u, kW0 = 0x9E3779B9u, kW1 = 0xBB67AE85u;
+  const uint64_t first = (uint64_t)kM1 * (uint64_t)c2;
+  const uint64_t second = (uint64_t)kM0 * (uint64_t)((uint32_t)(first >> 32) ^ c1 ^ k0);
   uint32_t c[U][4];
 #pragma unroll
   for (int u = 0; u < U; ++u) {
-    c[u][0] = m0 + 64u * (uint32_t)u;
-    c[u][1] = c1;
-    c[u][2] = c2;
-    c[u][3] = c3;
+    const uint64_t p0 = (uint64_t)kM0 * (uint64_t)(m0 + 64u * (uint32_t)u);
+    const uint64_t p1 = (uint64_t)kM1 * (uint64_t)xor3((uint32_t)(p0 >> 32), c3, k1);
+    c[u][0] = xor3((uint32_t)(p1 >> 32), (uint32_t)first, k0 + kW0);
+    c[u][1] = (uint32_t)p1;
+    c[u][2] = xor3((uint32_t)(second >> 32), (uint32_t)p0, k1 + kW1);
+    c[u][3] = (uint32_t)second;
   }
+  k0 += kW0;
+  k1 += kW1;
 #pragma unroll
-  for (int round = 0; round < 10; ++round) {
-    if (round > 0) {
-      k0 += 0x9E3779B9u;
-      k1 += 0xBB67AE85u;
-    }
+  for (int round = 2; round < 10; ++round) {
+    k0 += kW0;
+    k1 += kW1;
     // one 32 x 32 -> 64 bit product per counter word (a single multiply-add instruction on this
     // target; written as two separate products it costs two quarter-rate multiplies)
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const uint64_t p0 = (uint64_t)0xD2511F53u * (uint64_t)c[u][0];
-      const uint64_t p1 = (uint64_t)0xCD9E8D57u * (uint64_t)c[u][2];
+      const uint64_t p0 = (uint64_t)kM0 * (uint64_t)c[u][0];
+      const uint64_t p1 = (uint64_t)kM1 * (uint64_t)c[u][2];
       const uint32_t n0 = xor3((uint32_t)(p1 >> 32), c[u][1], k0);
       const uint32_t n2 = xor3((uint32_t)(p0 >> 32), c[u][3], k1);
       c[u][0] = n0; c[u][1] = (uint32_t)p1; c[u][2] = n2; c[u][3] = (uint32_t)p0;
