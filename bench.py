@@ -336,11 +336,12 @@ def run_gpu(w, steps, warmup, profile=True, fused=True, mix_form=None, order=Non
                 per_launch = bpe * elems
                 if "layers" in w and name.startswith(("k_layer_compress", "k_layers_", "k_sel_compact")):
                     # layers above 10,240 entries go through k_sel_compact, the others through k_layer_compress;
-                    # or k_layers_select takes those of 3,073 to 10,240 and k_layers_pass the rest.  The launches of
-                    # each share its part of one pass over the rows
+                    # or k_layers_pass takes them all, but for those of 3,073 to 10,240 where there is a
+                    # k_layers_select.  The launches of each share its part of one pass over the rows
                     lengths = layer_table_of(w)[1]
                     part = ((lengths > 3072) & (lengths <= 10240) if name.startswith("k_layers_select") else
-                            (lengths <= 3072) | (lengths > 10240) if name.startswith("k_layers_pass") else
+                            ((lengths <= 3072) | (lengths > 10240) if any(x.startswith("k_layers_select") for x in rep)
+                             else lengths > 0) if name.startswith("k_layers_pass") else
                             lengths > 10240 if name.startswith("k_sel_compact") else lengths <= 10240)
                     per_launch *= float(lengths[part].sum()) / float(lengths.sum())
                     per_launch /= entry["launches_per_step"]

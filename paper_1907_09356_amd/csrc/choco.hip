@@ -41,6 +41,7 @@ struct LongLayer {
   int32_t start, len, k, sel_base, id;
   SelectPlan plan;
   LongSel sel;      // what the kernels need of it (filled by choco_init)
+  bool mid;         // 3,073 to 10,240 entries
   bool batched;     // its pass and its select share a launch with those of the other such layers
   int32_t part_set; // multi-block select: which of the copies of its scratch
 };
@@ -121,9 +122,12 @@ struct choco_ctx {
   const LongSel* long_tab;   // device copy of the batched ones' LongSel, in the order of long_layers
   int nbatched;           // how many those are, and the 4-vectors of the longest of them
   int32_t batched_nvec;
+  int nbatched_mid;       // ... of which the last so many have 3,073 to 10,240 entries, and the 4-vectors of the longest of these
+  int32_t mid_nvec;
+  bool short_lists;       // all of them have lists of kShortList entries at most
   bool long_silent;       // one of them keeps nothing (its pass cannot carry the local update)
   bool overlap_long;      // top_a, several long layers with launches of their own: a layer's select runs on the second stream beside the next layer's pass
-  size_t set_hist16, set_cand, set_hist_parts, set_small_list;   // bytes from one long layer's select scratch to the next
+  size_t set_hist16, set_hist_parts, set_small_list;   // bytes from one long layer's select scratch to the next
   bool long_rows;         // d > 2^21: four 4-vectors per thread in the streaming kernels
   uint64_t t;             // step counter
   uint32_t* wire_rank;    // random_a without a bitmap: n x ceil(ld / 1024) chunk ranks of the message encoder
@@ -164,7 +168,7 @@ struct Layout {
   int64_t bitmap_words;
   bool multipart;
   int32_t select_sets;   // copies of the select scratch (candidate lists, histograms, short list)
-  size_t hist16_bytes, cand_bytes, hist_parts_bytes, small_list_bytes;   // size of one copy
+  size_t hist16_bytes, hist_parts_bytes, small_list_bytes;   // size of one copy
   size_t sel_idx_bytes, bitmap_bytes, keptmap_bytes, layer_scal_bytes;   // ... of what a selection made ahead writes
   int32_t nchunks, ngroups;
 };
@@ -402,15 +406,40 @@ bool one_pass_qsgd(const choco_config& c) {
   return mib > 96.0 && (double)c.n * marked_per_row(c) <= 14.0;
 }
 
-// The layers of a top_a / random_a configuration that are too long for the layer kernel.
+// top_a: do the layers of 3,073 to 10,240 entries go through candidate lists, as the longer ones of the table do,
+// instead of through a workgroup's registers?  Streamed, they cost their bytes and a short select; in registers every
+// (worker, layer) is a 1024-thread workgroup that waits for its loads and its bracket, all the more where thresholds
+// move.  Only with lists that a select of 512 or 256 threads holds.
+// us per step, registers | lists (steps of one size, 1 % | sizes that jump by five):
+//   65 layers of the 0.27 M model  n = 4 30.9 | 27.6   n = 8 36.2 | 31.9, jumps 47.8 | 34.7   n = 16 42.5 | 38.7
+//                                  n = 32 61.7 | 59.2  n = 64 108.8 | 105.4, jumps 118.8 | 105.3; 0.1 % 97.0 | 92.6
+//   1 of 20,000, 40 of 3,500 to 10,000  n = 8 35.8 | 29.5, jumps 46.3 | 30.0   n = 32 73.4 | 65.2   n = 64 126.6 | 120.8
+//   10 % (lists above 2,048): n = 8 47.3 | 59.9, n = 64 167.9 | 179.8
+constexpr double kShortList = 2048.0;
+bool mids_in_lists(const choco_config& c) {
+  if (c.nlayers <= 0 || c.nlayers > 65535 || c.compressor != CHOCO_Q_TOPK) return false;
+  bool any_long = false;
+  for (int32_t l = 0; l < c.nlayers; ++l) {
+    const int64_t k = c.layer_k_host[l], span = c.layer_len_host[l] + (c.layer_start_host[l] & 3);
+    if (span <= kSmallLayerLen) continue;
+    if (span > ((int64_t)1 << 19) || expected_candidates(c.compressor, k) > kShortList) return false;
+    if (span > kMidLayerLen) any_long = any_long || k > 0;
+    else if (k == 0) return false;   // (the layer kernel has what is left of the work list by falling length)
+  }
+  return any_long;
+}
+
+// The layers of a top_a / random_a configuration that do not go through the layer kernel; the longest class first.
 std::vector<LongLayer> long_layers_of(const choco_config& c) {
   std::vector<LongLayer> out;
   if (c.nlayers <= 0 || !is_sparse(c.compressor)) return out;
   int64_t sel_base = 0;
   int32_t part_sets = 0;
+  std::vector<LongLayer> mids;
+  const int64_t in_registers = mids_in_lists(c) ? kSmallLayerLen : kMidLayerLen;
   for (int32_t l = 0; l < c.nlayers; ++l) {
-    const int64_t len = c.layer_len_host[l], k = c.layer_k_host[l];
-    if (len + (c.layer_start_host[l] & 3) > kMidLayerLen) {   // (with the entries before it in its first 4-vector)
+    const int64_t len = c.layer_len_host[l], k = c.layer_k_host[l], span = len + (c.layer_start_host[l] & 3);
+    if (span > in_registers) {   // (with the entries before it in its first 4-vector)
       LongLayer B{};
       B.start = (int32_t)c.layer_start_host[l];
       B.len = (int32_t)len;
@@ -421,10 +450,17 @@ std::vector<LongLayer> long_layers_of(const choco_config& c) {
       // one block per worker finishes the select, no histogram passes: such layers share launches
       B.batched = k > 0 && !B.plan.multipart && !B.plan.fallback_chain;
       if (B.plan.multipart) B.part_set = part_sets++;
-      out.push_back(B);
+      B.mid = span <= kMidLayerLen;
+      if (B.mid) {
+        // a sub-list takes the hits of one 1024-entry chunk: room for four times an even share
+        const double share = 1024.0 * expected_candidates(c.compressor, k) / (double)len;
+        B.plan.seg_cap = (uint32_t)std::min(1024.0, std::max(64.0, std::ceil(4.0 * share)));
+      }
+      (B.mid ? mids : out).push_back(B);
     }
     sel_base += k;
   }
+  out.insert(out.end(), mids.begin(), mids.end());
   return out;
 }
 
@@ -461,6 +497,11 @@ int64_t message_words(int compressor, int64_t d, int64_t k, int levels) {
 // where x, xhat, gradients and momentum fill the card's 288 GB without it (above 48 GiB per array).
 bool one_pass_rule(const choco_config& c) {
   return (one_pass_topk(c) || one_pass_qsgd(c)) && (double)c.n * (double)resolve_ld(c) * sizeof(float) <= 48.0 * 1073741824.0;
+}
+
+// Bytes of the candidate lists of one selected piece of the rows.
+size_t candidate_bytes(int32_t n, const SelectPlan& P) {
+  return align_up((size_t)n * kSegs * (size_t)P.seg_cap * sizeof(uint2));
 }
 
 Layout make_layout(const choco_config& c, int32_t nnz, bool one_pass) {
@@ -512,9 +553,10 @@ Layout make_layout(const choco_config& c, int32_t nnz, bool one_pass) {
   bool chain = !layered;   // the histogram passes: long rows, whole-vector rows of any length
   for (const SelectPlan& P : plans) chain = chain || P.fallback_chain;
   L.hist16_bytes = align_up(guessed && chain ? (size_t)c.n * kBins16 * sizeof(uint32_t) : 0);
-  L.cand_bytes = align_up(guessed ? (size_t)c.n * kSegs * (size_t)seg_cap * sizeof(uint2) : 0);
   L.hist16 = take(L.hist16_bytes * (size_t)L.select_sets);
-  L.cand = take(L.cand_bytes * (size_t)L.select_sets);
+  size_t cand_bytes = 0;
+  for (const SelectPlan& P : plans) cand_bytes += candidate_bytes(c.n, P);
+  L.cand = take(guessed ? cand_bytes : 0);
   L.sel_idx = take(sparse ? (size_t)c.n * (size_t)kept * sizeof(int32_t) : 0);
   L.sel_val = take(sparse ? (size_t)c.n * (size_t)kept * sizeof(float) : 0);
   L.multipart = guessed && multipart;
@@ -1451,8 +1493,10 @@ int gossip_layers_sparse(choco_ctx* ctx, const Args& F) {
   // rows' shape of the pass matters more, a 4-vector per thread of 1024: layers of up to 300,000 entries, n = 64, 250 MB
   // 510 -> 457 us per step; of 1,690,000, n = 8, 1 GB 1241 -> 1247.
   // (Workgroups are numbered in 31 bits there, and the grid has the layers in x.)
-  const int64_t pass_x = nsmall + (ntiny + 3) / 4 + (int64_t)((ctx->batched_nvec + 255) / 256) * ctx->nbatched;
-  const bool together = COMP == Q_TOPK && ctx->nbatched > 0 && nmid > 0 && nsmall + ntiny > 0 && ctx->batched_nvec <= (1 << 17) &&
+  const LongGrid pass_long{ctx->nbatched - ctx->nbatched_mid, (ctx->batched_nvec + 255) / 256, (ctx->mid_nvec + 255) / 256};
+  const int64_t pass_x = nsmall + (ntiny + 3) / 4 + (int64_t)pass_long.long_chunks * pass_long.nlong +
+                         (int64_t)pass_long.mid_chunks * ctx->nbatched_mid;
+  const bool together = COMP == Q_TOPK && ctx->nbatched > 0 && nsmall + ntiny > 0 && ctx->batched_nvec <= (1 << 17) &&
                         pass_x <= (1 << 22) && (pass_x + nmid) * A.n < ((int64_t)1 << 31);
   // few workers: with a 1024-thread workgroup for every layer above a wave's reach (and sixteen
   // waves' worth of smaller layers in each of the others) the chip still is not full, and one
@@ -1479,7 +1523,7 @@ int gossip_layers_sparse(choco_ctx* ctx, const Args& F) {
     if (together) {
       if constexpr (COMP == Q_TOPK)
         LAUNCH(ctx, S.G ? KID_LAYERS_PASS_SGD : KID_LAYERS_PASS, (k_layers_pass<COMP, NT>), dim3((unsigned)pass_x, (unsigned)A.n),
-               dim3(256), 0, S, nlong + nmid, nsmall, nsmall + (ntiny + 3) / 4, (ctx->batched_nvec + 255) / 256);
+               dim3(256), 0, S, nlong + nmid, nsmall, nsmall + (ntiny + 3) / 4, pass_long);
     } else if (ctx->nbatched > 0 && NT && COMP == Q_TOPK) {
       // (large states, streamed past the caches: the workgroup shape of the whole-row pass on long rows)
       const dim3 cgrid((unsigned)((ctx->batched_nvec + 1023) / 1024), (unsigned)A.n, (unsigned)ctx->nbatched);
@@ -1491,10 +1535,21 @@ int gossip_layers_sparse(choco_ctx* ctx, const Args& F) {
       LAUNCH(ctx, S.G ? KID_SEL_COMPACT_SGD : KID_SEL_COMPACT, (k_sel_compact<COMP, false, NT, V, true>), cgrid,
              dim3(256), 0, S);
     }
-    if (together) {
+    if (together && nmid > 0) {
       if constexpr (COMP == Q_TOPK)
         LAUNCH(ctx, S.G ? KID_LAYERS_SELECT_SGD : KID_LAYERS_SELECT, (k_layers_select<COMP, NT>),
                dim3((unsigned)(nmid + ctx->nbatched), (unsigned)A.n), dim3(1024), 0, S, nlong, nmid);
+    } else if (together && ctx->short_lists && ctx->t != 0) {
+      // (a run's first step has no lists and goes through the layers themselves: 1024 threads)
+      // as many threads as let all workgroups be resident at once (n = 64: 768 of them 106.3 us per step with 256 threads,
+      // 105.4 with 512; 2,624 of them 120.8 with 256, 129.9 with 512; 1024 threads 110.6 and 147.1)
+      if constexpr (COMP == Q_TOPK) {
+        const dim3 rgrid((unsigned)A.n, (unsigned)ctx->nbatched);
+        if ((int64_t)A.n * ctx->nbatched > 1024)
+          LAUNCH(ctx, KID_SEL_REFINE, (k_sel_refine<COMP, true, false, 256>), rgrid, dim3(256), 0, Q);
+        else
+          LAUNCH(ctx, KID_SEL_REFINE, (k_sel_refine<COMP, true, false, 512>), rgrid, dim3(512), 0, Q);
+      }
     } else if (ctx->nbatched > 0) {
       LAUNCH(ctx, KID_SEL_REFINE, (k_sel_refine<COMP, true>), dim3((unsigned)A.n, (unsigned)ctx->nbatched), dim3(1024),
              0, Q);
@@ -1960,8 +2015,11 @@ int choco_init(const choco_config* cfg, float* x_dev, void* workspace_dev, size_
   // what the kernels need of each long layer; those that share launches go into a device table
   std::vector<LongSel> long_tab;
   ctx->nbatched = 0;
-  ctx->batched_nvec = 0;
+  ctx->batched_nvec = ctx->mid_nvec = 0;
+  ctx->nbatched_mid = 0;
+  ctx->short_lists = true;
   int nsolo = 0;
+  int64_t cand_first = 0;
   for (size_t b = 0; b < ctx->long_layers.size(); ++b) {
     LongLayer& B = ctx->long_layers[b];
     LongSel& Z = B.sel;
@@ -1978,10 +2036,17 @@ int choco_init(const choco_config* cfg, float* x_dev, void* workspace_dev, size_
     Z.delta0 = B.plan.delta0;
     Z.sample_stride = B.plan.sample_stride;
     Z.sample_need = B.plan.sample_need;
-    Z.set_cand = (int64_t)(L.cand_bytes / sizeof(uint2));
+    Z.scal_id = B.mid ? B.id : -1;
+    Z.cand_first = cand_first;
+    cand_first += (int64_t)(candidate_bytes(cfg->n, B.plan) / sizeof(uint2));
     if (B.batched && long_tab.size() < 65535) {   // (a grid has that many layers at most)
       long_tab.push_back(Z);
       ctx->batched_nvec = std::max(ctx->batched_nvec, (Z.d + 3) >> 2);
+      ctx->short_lists = ctx->short_lists && expected_candidates(cfg->compressor, B.k) <= kShortList;
+      if (B.mid) {
+        ctx->nbatched_mid += 1;
+        ctx->mid_nvec = std::max(ctx->mid_nvec, (Z.d + 3) >> 2);
+      }
     } else {
       B.batched = false;
       nsolo += B.k > 0 ? 1 : 0;
@@ -1992,7 +2057,6 @@ int choco_init(const choco_config* cfg, float* x_dev, void* workspace_dev, size_
   A.long_tab = ctx->long_tab;
   ctx->overlap_long = cfg->compressor == CHOCO_Q_TOPK && nsolo >= 2;
   ctx->set_hist16 = L.hist16_bytes;
-  ctx->set_cand = L.cand_bytes;
   ctx->set_hist_parts = L.hist_parts_bytes;
   ctx->set_small_list = L.small_list_bytes;
   if (ctx->overlap_long) {
@@ -2057,10 +2121,11 @@ int choco_init(const choco_config* cfg, float* x_dev, void* workspace_dev, size_
     std::stable_sort(work.begin(), work.end(),
                      [](const LayerDesc& a, const LayerDesc& b) { return a.len + a.head > b.len + b.head; });
     ctx->nmid = ctx->nsmall = 0;
+    const bool mids_listed = mids_in_lists(*cfg);
     for (const LayerDesc& D : work) {
       const int32_t span = D.len + D.head;   // what the layer kernel holds in registers
       // (long layers: first in the list, skipped by the layer kernel)
-      if (span <= kMidLayerLen && span > kSmallLayerLen) ctx->nmid += 1;
+      if (span <= kMidLayerLen && span > kSmallLayerLen && !mids_listed) ctx->nmid += 1;
       else if (span <= kSmallLayerLen && span > kWaveLayerLen) ctx->nsmall += 1;
     }
   }
@@ -2486,7 +2551,7 @@ int choco_layer_scalars(choco_ctx* ctx, double* scalars_host) {
     HIP_TRY(ctx, hipMemcpyAsync(ctl.data(), A.ctl, ctl.size() * sizeof(WorkerCtl), hipMemcpyDeviceToHost, ctx->stream));
   HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
   for (size_t b = 0; b < nlong; ++b)
-    for (int i = 0; i < A.n; ++i) {
+    for (int i = 0; i < A.n && !ctx->long_layers[b].mid; ++i) {
       const WorkerCtl& c = ctl[b * (size_t)A.n + (size_t)i];
       double* o = scalars_host + ((size_t)i * (size_t)A.nlayers + (size_t)ctx->long_layers[b].id) * 4;
       o[0] = (double)(uint32_t)(c.kstar >> 32);

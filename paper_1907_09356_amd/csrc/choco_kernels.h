@@ -123,7 +123,8 @@ struct LongSel {
   int32_t sel_base;    // the layer's first slot in a worker's kept lists
   int32_t set;         // which control blocks (n per layer) and which set of select scratch
   uint32_t cand_cap, seg_cap, extra, want, delta0, sample_stride, sample_need;   // see Args
-  int64_t set_cand;    // candidate entries from one set of lists to the next
+  int64_t cand_first;  // its candidate lists, in entries from the first layer's
+  int32_t scal_id;     // the layer whose scalars the select writes (those of the layer kernel), or -1
 };
 
 struct Args {
@@ -274,7 +275,7 @@ __host__ __device__ __forceinline__ Args long_view(const Args& src, const LongSe
   R.delta0 = L.delta0;
   R.sample_stride = L.sample_stride;
   R.sample_need = L.sample_need;
-  R.cand = src.cand + (int64_t)L.set * L.set_cand;
+  R.cand = src.cand + L.cand_first;
   return R;
 }
 
@@ -2339,13 +2340,33 @@ __device__ __forceinline__ void reset_lists(const Args& A, int i) {
   if (threadIdx.x < (unsigned)kSegs) *seg_counter(A, i, (int)threadIdx.x) = 0;
 }
 
+// The scalars of a layer that choco_layer_scalars gives for layers of up to 10,240 entries: the threshold key, the entries
+// kept of those that hold it, how many these are, and whether the guess held.
+struct TieCount {
+  unsigned long long least;   // the last kept entry in the order of the selection
+  uint32_t equal, kept;
+  template <int COMP>
+  __device__ __forceinline__ void add(uint32_t a, uint32_t idx, uint64_t kstar) {
+    if (Digits<COMP>::key32(a) != (uint32_t)(kstar >> 32)) return;
+    atomicAdd(&equal, 1u);
+    if (Digits<COMP>::composite(a, idx) >= kstar) atomicAdd(&kept, 1u);
+  }
+  __device__ __forceinline__ void publish(double* scal, uint64_t kstar, bool held) const {
+    scal[0] = (double)(uint32_t)(kstar >> 32);
+    scal[1] = (double)kept;
+    scal[2] = (double)equal;
+    scal[3] = held ? 1.0 : 0.0;
+  }
+};
+
 // Digit-by-digit radix select over the composite keys of the candidate list (ROW = false)
 // or of the row itself (ROW = true: the list is not good); emits the kept entries, marks
 // them and places the next guess.  All threads of a 1024-thread block.
 template <int COMP, bool ROW, bool ONEPASS>
 __device__ void refine_and_emit(const Args& A, int i, const uint32_t* pre, uint32_t total, uint32_t* h,
                                 uint32_t* grp, uint64_t* s_prefix, uint32_t* s_need, uint32_t* s_digit,
-                                uint32_t* s_above, uint32_t* s_emit, uint32_t* lbits) {
+                                uint32_t* s_above, uint32_t* s_emit, uint32_t* lbits, TieCount* tie = nullptr,
+                                double* scal = nullptr) {
   WorkerCtl* ctl = A.ctl + i;
   int last = 0;
   bool done = false;
@@ -2390,6 +2411,7 @@ __device__ void refine_and_emit(const Args& A, int i, const uint32_t* pre, uint3
   // emit every entry with composite >= kstar
   for_each_entry<COMP, ROW>(A, i, pre, total, [&](uint32_t a, uint32_t idx) {
     if (Digits<COMP>::composite(a, idx) >= kstar) {
+      if (scal) atomicMin(&tie->least, (unsigned long long)Digits<COMP>::composite(a, idx));
       const uint32_t slot = atomicAdd(s_emit, 1u);
       if (slot < (uint32_t)A.k) {
         A.sel_idx[(int64_t)i * A.sel_stride + slot] = A.idx_base + (int32_t)idx;
@@ -2400,6 +2422,11 @@ __device__ void refine_and_emit(const Args& A, int i, const uint32_t* pre, uint3
   });
   __syncthreads();
   publish_bitmap(A, i, lbits);
+  if (scal) {   // (kstar may lie below the k-th key where nothing lies between)
+    for_each_entry<COMP, ROW>(A, i, pre, total, [&](uint32_t a, uint32_t idx) { tie->add<COMP>(a, idx, tie->least); });
+    __syncthreads();
+    if (threadIdx.x == 0) tie->publish(scal, tie->least, !ROW);
+  }
   __syncthreads();
   reset_lists(A, i);
   if (threadIdx.x == 0) next_guess<ONEPASS>(A, ctl, kstar, total, !ROW, *s_emit, ROW ? 2u : 0u, ROW, floor_key);
@@ -2415,6 +2442,7 @@ __device__ void refine_and_emit(const Args& A, int i, const uint32_t* pre, uint3
 // grid n, block 1024, dynamic LDS = the worker's bitmap (short rows) or nothing.
 // BATCH: grid (n, long layers of A.long_tab); more workgroups than compute units as a rule, so 64 registers
 // for two to a unit (six layers, n = 64: 14.7 -> 10.6 us; a workgroup per worker is 0.7 us slower that way).
+// THREADS: the launch says how many and why; 256 at least (find_digit).  grid of whole rows: 1024.
 struct RefineShared {
   uint32_t h[kBins];
   uint32_t grp[256];
@@ -2423,9 +2451,10 @@ struct RefineShared {
   uint2 small[kSmallCap];
   uint64_t prefix, kstar;
   uint32_t need, digit, above, emit, total, good, small_n, all_short;
+  TieCount tie;
 };
-template <int COMP, bool BATCH, bool ONEPASS>
-__device__ __forceinline__ void refine_row(const Args& A, int i, RefineShared& sh, uint32_t* lbits) {
+template <int COMP, bool BATCH, bool ONEPASS, int THREADS>
+__device__ __forceinline__ void refine_row(const Args& A, int i, RefineShared& sh, uint32_t* lbits, double* scal = nullptr) {
   uint32_t *const h = sh.h, *const grp = sh.grp, *const lens = sh.lens, *const pre = sh.pre;
   uint2* const small = sh.small;
   uint64_t &s_prefix = sh.prefix, &s_kstar = sh.kstar;
@@ -2443,19 +2472,20 @@ __device__ __forceinline__ void refine_row(const Args& A, int i, RefineShared& s
   uint2 c[8];
   bool have[8];
   const int sseg = threadIdx.x >> 5, sj = threadIdx.x & 31;
-  static_assert(kSegs * 32 == 1024 && kSpecPerSeg == 8 * 32, "32 threads per sub-list, eight entries each");
+  static_assert(!SPECULATE || (kSegs * 32 == THREADS && kSpecPerSeg == 8 * 32), "32 threads per sub-list, eight entries each");
   if (SPECULATE) {
     const uint2* seg = A.cand + ((int64_t)i * kSegs + sseg) * A.seg_cap;
 #pragma unroll
     for (int u = 0; u < 8; ++u) c[u] = (uint32_t)(sj + 32 * u) < A.seg_cap ? seg[sj + 32 * u] : make_uint2(0u, 0u);
   }
-  for (int b = threadIdx.x; b < kBins; b += 1024) h[b] = 0;
-  for (int64_t wd = threadIdx.x; wd < A.bitmap_words; wd += 1024) lbits[wd] = 0;
+  for (int b = threadIdx.x; b < kBins; b += THREADS) h[b] = 0;
+  for (int64_t wd = threadIdx.x; wd < A.bitmap_words; wd += THREADS) lbits[wd] = 0;
   if (threadIdx.x == 0) {
     s_prefix = 0;
     s_need = (uint32_t)A.k;
     s_emit = 0;
     s_small = 0;
+    if (BATCH) sh.tie = TieCount{~0ull, 0u, 0u};
   }
   if (threadIdx.x < 64) {
     list_layout_wave(A, i, ctl, lens, pre, &s_total, &s_good, &s_short);
@@ -2464,7 +2494,8 @@ __device__ __forceinline__ void refine_row(const Args& A, int i, RefineShared& s
   __syncthreads();
   const uint32_t total = s_total;
   if (!s_good) {
-    refine_and_emit<COMP, true, ONEPASS>(A, i, pre, total, h, grp, &s_prefix, &s_need, &s_digit, &s_above, &s_emit, lbits);
+    refine_and_emit<COMP, true, ONEPASS>(A, i, pre, total, h, grp, &s_prefix, &s_need, &s_digit, &s_above, &s_emit, lbits, &sh.tie,
+                                       scal);
     return;
   }
   const uint32_t guess = ctl->guess_key, shift = ctl->bin_shift;
@@ -2473,7 +2504,7 @@ __device__ __forceinline__ void refine_row(const Args& A, int i, RefineShared& s
   // sweep 1: histogram of the candidates by their distance above the guess (eight
   // entries per thread in flight; a list of up to 8192 entries stays in registers)
   const bool fetched = SPECULATE && s_short != 0u;   // the entries fetched above are the whole list
-  const bool resident = fetched || total <= 1024u * 8u;
+  const bool resident = fetched || total <= THREADS * 8u;
   if (fetched) {
     const uint32_t len = lens[sseg];
 #pragma unroll
@@ -2482,10 +2513,10 @@ __device__ __forceinline__ void refine_row(const Args& A, int i, RefineShared& s
       if (have[u]) atomicAdd(&h[bin_of(c[u].x)], 1u);
     }
   } else {
-    for (uint32_t base = 0; base < total; base += 1024u * 8u) {
+    for (uint32_t base = 0; base < total; base += THREADS * 8u) {
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
-        const uint32_t f = base + (uint32_t)u * 1024u + threadIdx.x;
+        const uint32_t f = base + (uint32_t)u * THREADS + threadIdx.x;
         have[u] = f < total;
         if (have[u]) c[u] = entry_at(f);
       }
@@ -2501,7 +2532,8 @@ __device__ __forceinline__ void refine_row(const Args& A, int i, RefineShared& s
   const uint32_t in_bin = h[tbin];
   if (in_bin > (uint32_t)kSmallCap) {
     __syncthreads();
-    refine_and_emit<COMP, false, ONEPASS>(A, i, pre, total, h, grp, &s_prefix, &s_need, &s_digit, &s_above, &s_emit, lbits);
+    refine_and_emit<COMP, false, ONEPASS>(A, i, pre, total, h, grp, &s_prefix, &s_need, &s_digit, &s_above, &s_emit, lbits, &sh.tie,
+                                       scal);
     return;
   }
   // sweep 2: emit everything above the threshold bin, collect the bin itself
@@ -2538,11 +2570,11 @@ __device__ __forceinline__ void refine_row(const Args& A, int i, RefineShared& s
     for (int u = 0; u < 8; ++u)
       if (above[u]) store_kept<COMP, ONEPASS>(A, i, slot++, c[u].x, c[u].y, lbits);
   } else
-  for (uint32_t base = 0; base < total; base += 1024u * 8u) {
+  for (uint32_t base = 0; base < total; base += THREADS * 8u) {
     if (!resident) {
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
-        const uint32_t f = base + (uint32_t)u * 1024u + threadIdx.x;
+        const uint32_t f = base + (uint32_t)u * THREADS + threadIdx.x;
         have[u] = f < total;
         if (have[u]) c[u] = entry_at(f);
       }
@@ -2564,11 +2596,11 @@ __device__ __forceinline__ void refine_row(const Args& A, int i, RefineShared& s
   __syncthreads();
   // rank the entries of the threshold bin against each other; the need_in_bin largest are kept
   const uint32_t m = s_small < (uint32_t)kSmallCap ? s_small : (uint32_t)kSmallCap;
-  {
+  for (uint32_t at = threadIdx.x; (at & ~63u) < m; at += THREADS) {   // (whole waves: they emit together)
     bool keep = false;
     uint2 mine = make_uint2(0, 0);
-    if (threadIdx.x < m) {
-      mine = small[threadIdx.x];
+    if (at < m) {
+      mine = small[at];
       const uint64_t K = Digits<COMP>::composite(mine.x, mine.y);
       uint32_t rank = 0;
       for (uint32_t u = 0; u < m; ++u) {
@@ -2582,16 +2614,22 @@ __device__ __forceinline__ void refine_row(const Args& A, int i, RefineShared& s
   }
   __syncthreads();
   publish_bitmap(A, i, lbits);
+  if (BATCH && scal) {   // (all entries that hold the threshold key lie in its bin)
+    for (uint32_t at = threadIdx.x; at < m; at += THREADS) sh.tie.add<COMP>(small[at].x, small[at].y, s_kstar);
+    __syncthreads();
+    if (threadIdx.x == 0) sh.tie.publish(scal, s_kstar, true);
+  }
   if (BATCH) reset_lists(A, i);
   if (threadIdx.x == 0) next_guess<ONEPASS>(A, ctl, s_kstar, total, true, s_emit, 0u);
 }
 
-template <int COMP, bool BATCH = false, bool ONEPASS = false>
-__global__ __launch_bounds__(1024, BATCH ? 8 : 4) void k_sel_refine(Args A0) {
+template <int COMP, bool BATCH = false, bool ONEPASS = false, int THREADS = 1024>
+__global__ __launch_bounds__(THREADS, BATCH ? 8 : 4) void k_sel_refine(Args A0) {
   __shared__ RefineShared sh;
   extern __shared__ uint32_t lbits[];   // bitmap_words words: kept entries of this worker (short rows)
   const Args A = BATCH ? long_view(A0, A0.long_tab[blockIdx.y]) : A0;
-  refine_row<COMP, BATCH, ONEPASS>(A, (int)blockIdx.x, sh, lbits);
+  const int i = (int)blockIdx.x, id = BATCH ? A0.long_tab[blockIdx.y].scal_id : -1;
+  refine_row<COMP, BATCH, ONEPASS, THREADS>(A, i, sh, lbits, id >= 0 ? A0.layer_scal + ((int64_t)i * A0.nlayers + id) * 4 : nullptr);
 }
 
 // ---------------------------------------------------------------------------

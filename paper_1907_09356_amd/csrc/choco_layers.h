@@ -9,7 +9,8 @@
 //
 // top_a / random_a: k_layer_compress, for layers of up to kMidLayerLen = 10,240 entries (longer
 // ones stream through the guessed-threshold select of the whole-row path, all of them in one
-// launch of its pass over the rows and one of its exact select).  A layer of a worker is
+// launch of its pass over the rows and one of its exact select; so do top_a's layers above 3,072
+// entries in a table whose lists are short, see mids_in_lists).  A layer of a worker is
 // selected by one 1024-thread workgroup (above 3,072 entries), one 256-thread workgroup (above
 // 768) or one wave (smaller layers, four to a workgroup), with the layer's x - xhat (or its
 // random words) in registers: at most kLayerVecs = 3 4-vectors per thread, all loaded at once -
@@ -654,7 +655,9 @@ void k_layer_compress(Args A, int32_t first, int32_t nblock) {
 
 // top_a layer by layer, the launches above put together two by two where there are layers of each kind: a
 // launch whose workgroups last for a chain of barriers and look-ups, beside one that streams or beside another of its
-// kind that leaves slots free.  The longest chains of all workers come first in the grid.
+// kind that leaves slots free.  The longest chains of all workers come first in the grid.  (What follows was measured with
+// the layers of 3,073 to 10,240 entries in registers, in the second launch; where they go through lists that launch is
+// k_sel_refine and lasts 11 us instead of 28 at n = 64, the first 50 instead of 41.)
 //   us per step on 65 layers: four launches before the mix (three up to n = 16) | two, a worker's chains first | all workers' first
 //   n = 64 123.4 | 113.5 | 107.4      n = 32 76.2 | 64.8 | 59.8      n = 20 62.2 | 48.5 | 44.9
 //   n = 16 46.7 | - | 39.8      n = 9 38.3 | - | 35.2      n = 4 32.3 | - | 28.7
@@ -670,11 +673,16 @@ __device__ __forceinline__ int own_first(int own, int& worker) {
   return own + (lin - total) - worker * other;
 }
 
+// The workgroups of the streaming pass: so many for each of the first nlong layers of long_tab, so many for each other.
+struct LongGrid {
+  int32_t nlong, long_chunks, mid_chunks;
+};
+
 // The pass over the long layers and the layers of up to 3,072 entries.
 // grid (nlayer + chunks x long layers, n), block 256; `first`, `nblock` as for k_layer_compress.
 template <int COMP, bool NT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8)))
-void k_layers_pass(Args A0, int32_t first, int32_t nblock, int32_t nlayer, int32_t chunks) {
+void k_layers_pass(Args A0, int32_t first, int32_t nblock, int32_t nlayer, LongGrid grid) {
   __shared__ union {
     struct {
       uint32_t cnt[34], emit[4], list_n[4];
@@ -688,7 +696,9 @@ void k_layers_pass(Args A0, int32_t first, int32_t nblock, int32_t nlayer, int32
   int i;
   const int b = own_first(nlayer, i);
   if (b >= nlayer) {
-    const int which = (b - nlayer) / chunks, chunk = (b - nlayer) - which * chunks;
+    const int at = b - nlayer, lead = grid.nlong * grid.long_chunks;
+    const int which = at < lead ? at / grid.long_chunks : grid.nlong + (at - lead) / grid.mid_chunks;
+    const int chunk = at < lead ? at - which * grid.long_chunks : (at - lead) - (which - grid.nlong) * grid.mid_chunks;
     const Args A = long_view(A0, A0.long_tab[which]);
     if (chunk * 256 >= (A.d + 3) >> 2) return;
     if (threadIdx.x == 0) sh.pass.count = 0;
@@ -706,7 +716,8 @@ void k_layers_pass(Args A0, int32_t first, int32_t nblock, int32_t nlayer, int32
   }
 }
 
-// The layers above 3,072 entries and the exact select of the long ones.  grid (nmid + long layers, n), block 1024.
+// The layers above 3,072 entries and the exact select of the long ones, where the former stay in registers (mids_in_lists;
+// else k_sel_refine follows the pass).  grid (nmid + long layers, n), block 1024.
 template <int COMP, bool NT>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8)))
 void k_layers_select(Args A0, int32_t first, int32_t nmid) {
@@ -721,7 +732,7 @@ void k_layers_select(Args A0, int32_t first, int32_t nmid) {
   const int b = own_first(nmid, i);
   if (b >= nmid) {
     const Args A = long_view(A0, A0.long_tab[b - nmid]);
-    refine_row<COMP, true, false>(A, i, sh.refine, nullptr);
+    refine_row<COMP, true, false, 1024>(A, i, sh.refine, nullptr);
   } else {
     const LayerShared ls{sh.layer.cnt, sh.layer.emit, sh.layer.list_n, sh.layer.list};
     layer_body<COMP, 1024, NT>(A0, i, A0.layer_work[first + b], (int)threadIdx.x, ls);

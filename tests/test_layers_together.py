@@ -13,11 +13,12 @@ EDGES = [1, 768, 3072, 3073, 10240, 10241, 769, 5, 12288, 12289, 9216, 2304, 16,
 
 @pytest.mark.timeout(300)
 def test_which_tables_take_two_launches():
-    """Long layers of up to 2^19 entries, some of 3,073 to 10,240 and some shorter ones; whatever the workers and the order."""
+    """Long layers of up to 2^19 entries and some of up to 3,072; whatever the workers and the order.  Layers of 3,073 to
+    10,240 entries go through lists like the long ones where all lists are short, else through registers."""
     out = recorded("""
 out = {}
 for name, lengths in (("all", [20000, 4000, 100]), ("no long", [4000, 100]), ("no middle", [20000, 100]), ("no short", [20000, 4000]),
-                      ("longest", [1 << 19, 4000, 100]), ("longer", [(1 << 19) + 1, 4000, 100])):
+                      ("longest", [1 << 19, 4000, 100]), ("longer", [(1 << 19) + 1, 4000, 100]), ("many kept", [100000, 4000, 100])):
     for n in (2, 16, 64, 65):
         for order in (0, 1):
             for op, comp in (("topk", B.Q_TOPK), ("randk", B.Q_RANDK)):
@@ -25,26 +26,41 @@ for name, lengths in (("all", [20000, 4000, 100]), ("no long", [4000, 100]), ("n
                     continue
                 t = synth.layer_table(lengths, fraction=0.01)
                 c = Context(n, synth.layers_dim(t), comp, layers=t, order=order)
+                c.step()
                 out["%s %s %d %d" % (op, name, n, order)] = [x[0].split("<")[0] + " " + x[1] for x in c.step()]
                 c.close()
 """)
     for key, launches in out.items():
-        together = [x for x in launches if x.startswith("k_layers")]
-        assert [x.split()[0] for x in together] == (
-            ["k_layers_pass", "k_layers_select"] if key.startswith("topk") and ("all" in key or "longest" in key) else []), key
-        assert not together or not any(x.startswith(("k_sel", "k_layer_")) for x in launches), key
-    assert out["topk all 64 0"][:2] == ["k_layers_pass %dx64x1" % (1 + (20000 // 4 + 255) // 256), "k_layers_select 2x64x1"]
+        first = [x.split()[0] for x in launches if x.startswith(("k_layer", "k_sel"))]
+        op, name = key.rsplit(" ", 2)[0].split(" ", 1)
+        if op == "randk":
+            assert not any(x.startswith("k_layers") for x in first), key
+        elif name in ("all", "no middle"):
+            assert first == ["k_layers_pass", "k_sel_refine"], key
+        elif name in ("longest", "many kept"):
+            assert first == ["k_layers_pass", "k_layers_select"], key
+        else:
+            assert not any(x.startswith("k_layers") for x in first), key
+            assert ("k_layer_compress" in first) == (name != "no short"), key
+    assert out["topk all 64 0"][:2] == ["k_layers_pass %dx64x1" % (1 + (20000 // 4 + 255) // 256 + (4000 // 4 + 255) // 256),
+                                        "k_sel_refine 64x2x1"]
+    assert out["topk many kept 64 0"][:2] == ["k_layers_pass %dx64x1" % (1 + (100000 // 4 + 255) // 256), "k_layers_select 2x64x1"]
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("n,table,form", [
-    (2, "aligned", "step"), (5, "generic", "step"), (12, "aligned", "step"), (12, "aligned", "momentum"),
-    (33, "aligned", "step"), (33, "aligned", "printed"), (17, "generic", "printed"), (70, "aligned", "step")])
-def test_parity_where_the_kinds_meet(n, table, form):
-    start, length, k = synth.layer_table(EDGES, fraction=0.02)
+@pytest.mark.parametrize("n,table,form,fraction", [
+    (2, "aligned", "step", 0.02), (5, "generic", "step", 0.02), (12, "aligned", "step", 0.02), (12, "aligned", "momentum", 0.02),
+    (33, "aligned", "step", 0.02), (33, "aligned", "printed", 0.02), (17, "generic", "printed", 0.02), (70, "aligned", "step", 0.02),
+    (5, "generic", "step", 0.06), (33, "aligned", "momentum", 0.06), (12, "aligned", "printed", 0.06), (64, "many", "step", 0.01),
+    (64, "many", "printed", 0.002)])
+def test_parity_where_the_kinds_meet(n, table, form, fraction):
+    """Lists of 512 threads (256 with more than 1,024 of them), at 6 % registers."""
+    edges = EDGES if table != "many" else EDGES + [3073, 3074, 3500, 4000, 4096, 4097, 5000, 6144, 7000, 8191]
+    start, length, k = synth.layer_table(edges, fraction=fraction)
     if table == "generic":      # layers that start anywhere, with gaps
         start = np.cumsum([3] + [int(a) + 1 + (j % 3) for j, a in enumerate(length)])[:-1]
     k[1], k[7] = 0, length[7]   # a silent layer, a layer sent whole
+    k[2], k[5] = 1, max(k[5], 1)
     layers = (np.asarray(start, dtype=np.int64), length, k)
     d = int(layers[0][-1] + length[-1])
     order = binding.ORDER_MIX_THEN_COMPRESS if form == "printed" else binding.ORDER_COMPRESS_THEN_MIX
@@ -52,9 +68,44 @@ def test_parity_where_the_kinds_meet(n, table, form):
     g = synth.GradientStream(n, d, seed=4)
     for t in range(4):
         det = pair.step_momentum(g.next(), 0.05, 0.9, 1e-4) if form == "momentum" else pair.step(g.next(), 0.05)
-        pair.check(det, tag="%d workers, %s table, %s, step %d" % (n, table, form, t))
+        pair.check(det, tag="%d workers, %s table, %s, %g, step %d" % (n, table, form, fraction, t))
     pair.gpu.set_profiling(True)
     pair.step(g.next(), 0.05)
     names = pair.gpu.profile_report()
-    assert any(x.startswith("k_layers_pass") for x in names) and any(x.startswith("k_layers_select") for x in names), names
+    assert any(x.startswith("k_layers_pass") for x in names), names
+    assert any(x.startswith("k_layers_select") for x in names) == (fraction == 0.06), names
     pair.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("spread", [2.0 ** -3, 2.0 ** -12])
+def test_layer_scalars_are_those_of_the_register_form(spread):
+    """Layers of 3,073 to 10,240 entries, many entries of one magnitude: x, and where ties are cut threshold key, entries kept
+    of those that hold it and how many these are, by lists (a long layer behind them) and by registers (none)."""
+    import torch
+    lengths, n = [3073, 5000, 10240, 100, 9216], 6
+    common = synth.layers_dim(synth.layer_table(lengths))
+    got = []
+    for more in ([], [20000]):
+        layers = synth.layer_table(lengths + more, fraction=0.01)
+        d = synth.layers_dim(layers)
+        ld = (d + 63) // 64 * 64
+        x = torch.from_numpy(synth.normal_state(n, 1 << 16, seed=5))[:, :ld].div(spread).round().mul(spread).contiguous().cuda()
+        ctx = binding.Choco(x, d, *synth.ring_csr(n), 0.25, binding.Q_TOPK, seed=3, layers=layers)
+        g = torch.from_numpy(synth.normal_state(n, 1 << 16, seed=6)).div(spread).round().mul(spread).cuda()
+        scal, sel = [], []
+        for t in range(6):
+            ctx.step(g[:, 64 * t:64 * t + ld].contiguous(), 0.5 if t != 4 else 20.0)
+            scal.append(ctx.layer_scalars()[:, :len(lengths), :3])
+            sel.append(x[:, :common].cpu().numpy())
+        got.append((np.array(scal), np.array(sel)))
+        ctx.close()
+    np.testing.assert_array_equal(got[0][1], got[1][1])
+    registers, lists = (a[:, :, [0, 1, 2, 4]] for a in (got[0][0], got[1][0]))
+    tied = registers[:, :, :, 2] > registers[:, :, :, 1]
+    np.testing.assert_array_equal(registers[tied], lists[tied])
+    # all that hold the threshold key are kept: the search of the register form may end below the last kept key
+    np.testing.assert_array_equal(lists[~tied][:, 1], lists[~tied][:, 2])
+    assert np.all(lists[~tied][:, 1] >= 1) and np.all(lists[~tied][:, 0] >= registers[~tied][:, 0])
+    if spread == 2.0 ** -3:
+        assert np.any(tied)
