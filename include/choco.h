@@ -113,7 +113,7 @@ typedef struct {
      of its registers and longer layers take the whole-vector select, in launches that they
      share (they cost workspace for its candidate lists, a set per such layer); so do TOPK's
      layers of 3,073 entries on in a table that has longer ones than CHOCO_MAX_LAYER_LEN, none
-     above 2^19, and keeps no more than 819 entries of any.  With
+     above 2^19, and keeps no more than 819 entries of any, up to 4 GiB per state array.  With
      layers, IDENTITY is CHOCO_E_UNSUPPORTED, SIGN and QSGD take CHOCO_MIX_AUTO only, and
      TOPK / RANDK take CHOCO_MIX_DIRECT in the default order and up to 64 workers only.
      layer_k_host may be NULL for SIGN and QSGD.     */

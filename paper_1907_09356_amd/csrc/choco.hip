@@ -415,9 +415,11 @@ bool one_pass_qsgd(const choco_config& c) {
 //                                  n = 32 61.7 | 59.2  n = 64 108.8 | 105.4, jumps 118.8 | 105.3; 0.1 % 97.0 | 92.6
 //   1 of 20,000, 40 of 3,500 to 10,000  n = 8 35.8 | 29.5, jumps 46.3 | 30.0   n = 32 73.4 | 65.2   n = 64 126.6 | 120.8
 //   10 % (lists above 2,048): n = 8 47.3 | 59.9, n = 64 167.9 | 179.8
+// The lists of these layers take one to three times one array of the state: not above 4 GiB per array.
 constexpr double kShortList = 2048.0;
 bool mids_in_lists(const choco_config& c) {
   if (c.nlayers <= 0 || c.nlayers > 65535 || c.compressor != CHOCO_Q_TOPK) return false;
+  if ((double)c.n * (double)resolve_ld(c) * sizeof(float) > 4.0 * 1073741824.0) return false;
   bool any_long = false;
   for (int32_t l = 0; l < c.nlayers; ++l) {
     const int64_t k = c.layer_k_host[l], span = c.layer_len_host[l] + (c.layer_start_host[l] & 3);
@@ -452,9 +454,10 @@ std::vector<LongLayer> long_layers_of(const choco_config& c) {
       if (B.plan.multipart) B.part_set = part_sets++;
       B.mid = span <= kMidLayerLen;
       if (B.mid) {
-        // a sub-list takes the hits of one 1024-entry chunk: room for four times an even share
-        const double share = 1024.0 * expected_candidates(c.compressor, k) / (double)len;
-        B.plan.seg_cap = (uint32_t)std::min(1024.0, std::max(64.0, std::ceil(4.0 * share)));
+        // a sub-list takes the hits of one 1024-entry chunk: room for all that are expected in the layer (large
+        // entries may lie together) and for four times an even share
+        const double expected = expected_candidates(c.compressor, k), share = 1024.0 * expected / (double)len;
+        B.plan.seg_cap = (uint32_t)std::min(1024.0, std::max(64.0, std::ceil(std::max(4.0 * share, 1.25 * expected))));
       }
       (B.mid ? mids : out).push_back(B);
     }

@@ -109,3 +109,27 @@ def test_layer_scalars_are_those_of_the_register_form(spread):
     assert np.all(lists[~tied][:, 1] >= 1) and np.all(lists[~tied][:, 0] >= registers[~tied][:, 0])
     if spread == 2.0 ** -3:
         assert np.any(tied)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("fraction", [0.001, 0.01, 0.03])
+def test_large_entries_that_lie_together_stay_in_the_lists(fraction):
+    """All of a layer's large entries in one chunk of 1,024: its sub-list holds them."""
+    lengths, n = [20000, 9216, 5000, 100, 10240], 5
+    start, length, k = layers = synth.layer_table(lengths, fraction=fraction)
+    d = int(start[-1] + length[-1])
+    where = np.zeros(d, dtype=np.float32)
+    for a, m in zip(start, length):
+        where[a + min(1024, m // 2):a + min(2048, m)] = 1.0
+
+    def clustered(v):
+        return (np.asarray(v) * (0.001 + where)).astype(np.float32)
+
+    pair = Pair(clustered(synth.normal_state(n, d, seed=8)), synth.ring_csr(n), 0.05, seed=3, compressor=binding.Q_TOPK, layers=layers)
+    g = synth.GradientStream(n, d, seed=9)
+    for t in range(8):
+        det = pair.step(clustered(g.next()), 0.5)
+        pair.check(det, tag="clustered, %g, step %d" % (fraction, t))
+        if t > 2:
+            assert np.all(pair.gpu.layer_scalars()[:, [1, 2, 4], 3] == 1), t
+    pair.close()
