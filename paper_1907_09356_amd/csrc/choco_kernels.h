@@ -18,6 +18,7 @@
 // the group sums and a halving tree).
 #pragma once
 
+#include <type_traits>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -534,7 +535,24 @@ __device__ __forceinline__ double wave_tree_sum(double t) {
   return group_tree_sum(t);
 }
 
-// The same sum through LDS.  gsgd in one pass has Philox beside it: n = 8, d = 28 M 784 us per step, 786 with lane moves.
+// Inclusive sum over the lanes up to this one, by data-parallel-primitive moves (rows of 16, then across); all 64
+// lanes call it.  (Six steps of the vector unit; through LDS each step is a trip that waits for the one before, and the
+// select waits for several scans in a row: n = 64, d = 270 k, 1 % kept 95.7 -> 93.0 us per step, n = 32, d = 3 M in the
+// printed order 382.8 -> 382.1, n = 8, d = 28 M 675.6 -> 673.2.)
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v) {
+  auto moved = [](uint32_t x, auto ctrl, auto rows) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, decltype(ctrl)::value, decltype(rows)::value, 0xF, false);
+  };
+  v += moved(v, std::integral_constant<int, 0x111>(), std::integral_constant<int, 0xF>());   // row_shr:1, 2, 4, 8
+  v += moved(v, std::integral_constant<int, 0x112>(), std::integral_constant<int, 0xF>());
+  v += moved(v, std::integral_constant<int, 0x114>(), std::integral_constant<int, 0xF>());
+  v += moved(v, std::integral_constant<int, 0x118>(), std::integral_constant<int, 0xF>());
+  v += moved(v, std::integral_constant<int, 0x142>(), std::integral_constant<int, 0xA>());   // row_bcast:15 to rows 1 and 3
+  v += moved(v, std::integral_constant<int, 0x143>(), std::integral_constant<int, 0xC>());   // row_bcast:31 to rows 2 and 3
+  return v;
+}
+
+// The 64-lane sum through LDS.  gsgd in one pass has Philox beside it: n = 8, d = 28 M 784 us per step, 786 with lane moves.
 __device__ __forceinline__ double wave_tree_sum_lds(double t) {
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) t = t + __shfl_xor(t, off, 64);
@@ -2100,14 +2118,7 @@ __device__ __forceinline__ void list_layout_wave(const Args& A, int i, const Wor
   const int lane = threadIdx.x & 63;
   const uint32_t raw = lane < kSegs ? *seg_counter(A, i, lane) : 0u;
   const uint32_t len = raw < A.seg_cap ? raw : A.seg_cap;
-  uint32_t incl = len;
-  unsigned long long rawsum = raw;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint32_t up = __shfl_up(incl, off, 64);
-    if (lane >= off) incl += up;
-    rawsum += __shfl_xor(rawsum, off, 64);
-  }
+  const uint32_t incl = wave_scan(len);
   if (lane < kSegs) {
     lens[lane] = len;
     pre[lane] = incl - len;
@@ -2116,10 +2127,12 @@ __device__ __forceinline__ void list_layout_wave(const Args& A, int i, const Wor
     pre[kSegs] = incl;
     *total_out = incl;
   }
+  const uint32_t listed = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
   const bool fits = __ballot(raw > A.seg_cap) == 0ull;
   const bool all_short = __ballot(raw > kSpecPerSeg) == 0ull;
   if (lane == 0) {
-    *good_out = (fits && rawsum >= (unsigned long long)A.k && ctl->fb_abort == 0u) ? 1u : 0u;
+    // (where none overflowed the lengths are the counts, d of them at most)
+    *good_out = (fits && (int64_t)listed >= A.k && ctl->fb_abort == 0u) ? 1u : 0u;
     if (short_out) *short_out = all_short ? 1u : 0u;
   }
 }
@@ -2177,8 +2190,8 @@ __device__ __forceinline__ void for_each_entry(const Args& A, int i, const uint3
 // the running count first reaches `need` (the last digit if it never does).  All
 // threads of a block with >= 256 threads call it; grp is 256 words of LDS
 // scratch.  Wave 0 does the search: lane l owns bins 32l..32l+31, a suffix scan
-// over the lane totals finds the lane in which the count is reached, and that
-// lane walks its 32 bins.
+// over the lane totals finds the lane in which the count is reached, and a scan over
+// that lane's 32 bins the bin.
 __device__ __forceinline__ void find_digit(const uint32_t* h, uint32_t* grp, uint32_t need,
                                            uint32_t* out_digit, uint32_t* out_above) {
   const int t = threadIdx.x;
@@ -2192,26 +2205,22 @@ __device__ __forceinline__ void find_digit(const uint32_t* h, uint32_t* grp, uin
   if (t < 64) {
     const uint32_t mine = grp[4 * t] + grp[4 * t + 1] + grp[4 * t + 2] + grp[4 * t + 3];
     // inclusive suffix sum over lanes: incl = sum of lane totals of lanes >= t
-    uint32_t incl = mine;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const uint32_t other = __shfl_down(incl, off, 64);
-      if (t + off < 64) incl += other;
-    }
+    const uint32_t upto = wave_scan(mine);
+    const uint32_t incl = (uint32_t)__builtin_amdgcn_readlane((int)upto, 63) - upto + mine;
     const uint32_t above_lane = incl - mine;          // entries in bins above this lane's range
     const bool here = above_lane < need && incl >= need;
     const uint64_t found = __ballot(here);
     if (found == 0) {                                 // fewer than `need` entries in total
       if (t == 0) { *out_digit = 0; *out_above = incl - h[0]; }
-    } else if (here) {
-      uint32_t cum = above_lane;
-      int b = 32 * t + 31;
-      for (; b > 32 * t; --b) {
-        if (cum + h[b] >= need) break;
-        cum += h[b];
+    } else {
+      const int owner = __ffsll((unsigned long long)found) - 1;
+      const uint32_t above = (uint32_t)__builtin_amdgcn_readlane((int)above_lane, owner);
+      const uint32_t own = t < 32 ? h[32 * owner + 31 - t] : 0u;
+      const uint32_t upto_bin = above + wave_scan(own);
+      if (t == __ffsll((unsigned long long)__ballot(upto_bin >= need)) - 1) {
+        *out_digit = (uint32_t)(32 * owner + 31 - t);
+        *out_above = upto_bin - own;
       }
-      *out_digit = (uint32_t)b;
-      *out_above = cum;
     }
   }
   __syncthreads();
@@ -2556,12 +2565,7 @@ __device__ __forceinline__ void refine_row(const Args& A, int i, RefineShared& s
       mine += above[u] ? 1u : 0u;
     }
     const int lane = threadIdx.x & 63;
-    uint32_t incl = mine;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const uint32_t up = __shfl_up(incl, off, 64);
-      if (lane >= off) incl += up;
-    }
+    const uint32_t incl = wave_scan(mine);
     uint32_t wave_base = 0;
     if (lane == 63 && incl != 0u) wave_base = atomicAdd(&s_emit, incl);
     wave_base = __shfl(wave_base, 63, 64);

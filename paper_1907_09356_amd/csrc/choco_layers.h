@@ -68,20 +68,6 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
-// Inclusive sum over the lanes up to this one, by data-parallel-primitive moves (rows of 16, then across).
-__device__ __forceinline__ uint32_t wave_scan(uint32_t v) {
-  auto moved = [](uint32_t x, auto ctrl, auto rows) {
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, decltype(ctrl)::value, decltype(rows)::value, 0xF, false);
-  };
-  v += moved(v, std::integral_constant<int, 0x111>(), std::integral_constant<int, 0xF>());   // row_shr:1, 2, 4, 8
-  v += moved(v, std::integral_constant<int, 0x112>(), std::integral_constant<int, 0xF>());
-  v += moved(v, std::integral_constant<int, 0x114>(), std::integral_constant<int, 0xF>());
-  v += moved(v, std::integral_constant<int, 0x118>(), std::integral_constant<int, 0xF>());
-  v += moved(v, std::integral_constant<int, 0x142>(), std::integral_constant<int, 0xA>());   // row_bcast:15 to rows 1 and 3
-  v += moved(v, std::integral_constant<int, 0x143>(), std::integral_constant<int, 0xC>());   // row_bcast:31 to rows 2 and 3
-  return v;
-}
-
 // A place in a shared list for the `count` things of every lane: where the lane's own start.
 template <int THREADS>
 __device__ __forceinline__ uint32_t claim_counted(uint32_t count, uint32_t incl, uint32_t* shared_count) {
@@ -538,13 +524,8 @@ __device__ __forceinline__ void layer_body(const Args& A, const int i, const Lay
           uint32_t mine = 0;
 #pragma unroll
           for (int c = 0; c < 4; ++c) mine += (key_of(it, c) == T && inside(4 * m + c)) ? 1u : 0u;
-          uint32_t incl = mine;
-#pragma unroll
-          for (int off = 1; off < 64; off <<= 1) {
-            const uint32_t up = __shfl_up(incl, off, 64);
-            if (lane >= off) incl += up;
-          }
-          uint32_t base = 0, total = __shfl(incl, 63, 64);
+          const uint32_t incl = wave_scan(mine);
+          uint32_t base = 0, total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
           if (THREADS > 64) {
             uint32_t* buf = sh.cnt + 16 * phase;
             phase ^= 1;

@@ -250,12 +250,7 @@ __device__ __forceinline__ uint32_t list_marked(const OnePass& P, int t0, int nt
   if (t < ntiles) w = *reinterpret_cast<const uint2*>(P.cols + (int64_t)t * 8 + 2 * (lane & 3));
   if (left_open(w)) w = make_uint2(0u, 0u);
   const uint32_t cnt = (uint32_t)(__popc(w.x) + __popc(w.y));
-  uint32_t incl = cnt;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint32_t up = __shfl_up(incl, off, 64);
-    if (lane >= off) incl += up;
-  }
+  const uint32_t incl = wave_scan(cnt);
   uint32_t at = incl - cnt;
   uint32_t slot = at - __shfl(at, lane & ~3, 64);
   uint64_t bits = ((uint64_t)w.y << 32) | w.x;
