@@ -2114,7 +2114,7 @@ constexpr uint32_t kSpecPerSeg = 256;   // entries of a sub-list that k_sel_refi
 
 __device__ __forceinline__ void list_layout_wave(const Args& A, int i, const WorkerCtl* ctl, uint32_t* lens, uint32_t* pre,
                                                  uint32_t* total_out, uint32_t* good_out,
-                                                 uint32_t* short_out = nullptr) {
+                                                 uint32_t* short_out = nullptr, uint32_t* nonzeros_out = nullptr) {
   const int lane = threadIdx.x & 63;
   const uint32_t raw = lane < kSegs ? *seg_counter(A, i, lane) : 0u;
   const uint32_t len = raw < A.seg_cap ? raw : A.seg_cap;
@@ -2134,6 +2134,8 @@ __device__ __forceinline__ void list_layout_wave(const Args& A, int i, const Wor
     // (where none overflowed the lengths are the counts, d of them at most)
     *good_out = (fits && (int64_t)listed >= A.k && ctl->fb_abort == 0u) ? 1u : 0u;
     if (short_out) *short_out = all_short ? 1u : 0u;
+    // (top_a: whatever is not zero is at or above a guess of 1)
+    if (nonzeros_out) *nonzeros_out = (fits && ctl->guess_key == 1u && ctl->fb_abort == 0u) ? 1u : 0u;
   }
 }
 
@@ -2310,11 +2312,11 @@ __device__ __forceinline__ void expect_threshold(const Args& A, OnePassCtl* ctl,
 // Place the guess (and the bin width) for the next step below this step's
 // threshold key T: by the distance that, at the key density seen between the old
 // guess and T, holds `want` entries (for top_a the k entries kept now leave the
-// race, so want includes k).  Also resets the per-step counters (the lists': reset_lists).
+// race, so want includes k).  Not below `lowest`.  Also resets the per-step counters (the lists': reset_lists).
 template <bool ONEPASS>
 __device__ __forceinline__ void next_guess(const Args& A, WorkerCtl* ctl, uint64_t kstar, uint32_t total,
                                            bool from_list, uint32_t emitted, uint32_t mode,
-                                           bool have_floor = false, uint32_t floor_key = 0) {
+                                           bool have_floor = false, uint32_t floor_key = 0, uint32_t lowest = 0) {
   const uint32_t T = (uint32_t)(kstar >> 32);
   const uint32_t G = ctl->guess_key;
   uint64_t delta = A.delta0;
@@ -2324,7 +2326,8 @@ __device__ __forceinline__ void next_guess(const Args& A, WorkerCtl* ctl, uint64
     delta = (uint64_t)(T - floor_key);   // row scan: the first-digit histogram located rank k + want
   if (delta < 1) delta = 1;
   if (delta > 0xFFFFFFFFull) delta = 0xFFFFFFFFull;
-  const uint32_t guess = delta >= (uint64_t)T ? 0u : T - (uint32_t)delta;
+  const uint32_t below = delta >= (uint64_t)T ? 0u : T - (uint32_t)delta;
+  const uint32_t guess = below < lowest ? lowest : below;
   if (ONEPASS) expect_threshold(A, onepass_ctl(A) + (ctl - A.ctl), T, from_list && total > (uint32_t)A.k && T > G, T - G, total, guess);
   ctl->guess_key = guess;
   // 256-511 bins between the guess and where the threshold is expected: the 2048 bins then
@@ -2368,10 +2371,66 @@ struct TieCount {
   }
 };
 
+// The long layers of a table: no guess of top_a lies below 1.  A layer of which fewer than k entries are not zero - it
+// gets no gradients, or few of its entries do, and it has been sent - then lists those and nothing else, and emit_with_zeros
+// has the rest.  With a guess of 0 it lists its zeros too, which the sub-lists do not hold, and is scanned in every step.
+template <int COMP, bool BATCH>
+constexpr uint32_t kLowestGuess = COMP == Q_TOPK && BATCH ? 1u : 0u;
+constexpr int kZeroFillK = 32 * 256;   // a bit per entry kept in 256 words
+
+// All `total` < k listed entries and the first k - total of the others, which are zeros.  They lie among the first k
+// entries, of which at most `total` are listed.  bits: 256 words of LDS, zero; before: 256 words of LDS; all threads of a
+// block of 256 at least.
+// us per step, every other layer without gradients, with layers of 3,073 to 10,240 entries in registers and the longer ones
+// scanned | all scanned | so (the same tables with gradients everywhere 127, 104 | 257, 227 | 38.5, 30.3):
+//   65 layers n = 64 335 | 356 | 97      2 of 200,000, 40 of 5,000, 20 of 100 n = 64 1263 | 2407 | 234      65 layers n = 8 225 | 225 | 29.5
+template <int COMP>
+__device__ __forceinline__ void emit_with_zeros(const Args& A, int i, const uint32_t* pre, uint32_t total, uint32_t* bits,
+                                                uint32_t* before, uint64_t* s_kstar, double* scal) {
+  const uint32_t k = (uint32_t)A.k, fill = k - total, first = (uint32_t)A.e_lo;
+  for (uint32_t f = threadIdx.x; f < total; f += blockDim.x) {
+    const uint2 c = list_entry(A, i, pre, f);
+    store_kept<COMP>(A, i, f, c.x, c.y, nullptr);
+    if (c.y - first < k) atomicOr(&bits[(c.y - first) >> 5], 1u << ((c.y - first) & 31u));
+  }
+  __syncthreads();
+  if (threadIdx.x < 64) {   // the zeros before each word, four words per lane
+    uint32_t n[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) n[j] = 32u - (uint32_t)__popc(bits[4 * threadIdx.x + j]);
+    const uint32_t mine = n[0] + n[1] + n[2] + n[3];
+    uint32_t at = wave_scan(mine) - mine;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      before[4 * threadIdx.x + j] = at;
+      at += n[j];
+    }
+  }
+  __syncthreads();
+  for (uint32_t j = threadIdx.x; j < k; j += blockDim.x) {
+    const uint32_t w = bits[j >> 5], bit = 1u << (j & 31u);
+    const uint32_t rank = before[j >> 5] + (uint32_t)__popc(~w & (bit - 1u));
+    if ((w & bit) != 0u || rank >= fill) continue;
+    uint32_t a, idx;
+    row_entry<COMP>(A, i, first + j, a, idx);
+    store_kept<COMP>(A, i, total + rank, a, idx, nullptr);
+    if (rank + 1u == fill) *s_kstar = Digits<COMP>::composite(a, idx);
+  }
+  __syncthreads();
+  if (scal && threadIdx.x == 0) {
+    scal[0] = 0.0;
+    scal[1] = (double)fill;
+    scal[2] = (double)((uint32_t)A.d - first - total);
+    scal[3] = 1.0;
+  }
+  reset_lists(A, i);
+  if (threadIdx.x == 0) next_guess<false>(A, A.ctl + i, *s_kstar, total, true, k, 0u, false, 0u, kLowestGuess<COMP, true>);
+}
+
 // Digit-by-digit radix select over the composite keys of the candidate list (ROW = false)
 // or of the row itself (ROW = true: the list is not good); emits the kept entries, marks
 // them and places the next guess.  All threads of a 1024-thread block.
-template <int COMP, bool ROW, bool ONEPASS>
+template <int COMP, bool ROW, bool ONEPASS, bool BATCH>
 __device__ void refine_and_emit(const Args& A, int i, const uint32_t* pre, uint32_t total, uint32_t* h,
                                 uint32_t* grp, uint64_t* s_prefix, uint32_t* s_need, uint32_t* s_digit,
                                 uint32_t* s_above, uint32_t* s_emit, uint32_t* lbits, TieCount* tie = nullptr,
@@ -2438,7 +2497,7 @@ __device__ void refine_and_emit(const Args& A, int i, const uint32_t* pre, uint3
   }
   __syncthreads();
   reset_lists(A, i);
-  if (threadIdx.x == 0) next_guess<ONEPASS>(A, ctl, kstar, total, !ROW, *s_emit, ROW ? 2u : 0u, ROW, floor_key);
+  if (threadIdx.x == 0) next_guess<ONEPASS>(A, ctl, kstar, total, !ROW, *s_emit, ROW ? 2u : 0u, ROW, floor_key, kLowestGuess<COMP, BATCH>);
 }
 
 // Exact selection from the candidates by one block per worker: emission of the kept
@@ -2459,7 +2518,7 @@ struct RefineShared {
   uint32_t pre[kSegs + 1];
   uint2 small[kSmallCap];
   uint64_t prefix, kstar;
-  uint32_t need, digit, above, emit, total, good, small_n, all_short;
+  uint32_t need, digit, above, emit, total, good, small_n, all_short, nonzeros;
   TieCount tie;
 };
 template <int COMP, bool BATCH, bool ONEPASS, int THREADS>
@@ -2497,13 +2556,19 @@ __device__ __forceinline__ void refine_row(const Args& A, int i, RefineShared& s
     if (BATCH) sh.tie = TieCount{~0ull, 0u, 0u};
   }
   if (threadIdx.x < 64) {
-    list_layout_wave(A, i, ctl, lens, pre, &s_total, &s_good, &s_short);
+    list_layout_wave(A, i, ctl, lens, pre, &s_total, &s_good, &s_short, BATCH ? &sh.nonzeros : nullptr);
     if (!BATCH) reset_lists(A, i);
   }
   __syncthreads();
   const uint32_t total = s_total;
   if (!s_good) {
-    refine_and_emit<COMP, true, ONEPASS>(A, i, pre, total, h, grp, &s_prefix, &s_need, &s_digit, &s_above, &s_emit, lbits, &sh.tie,
+    if constexpr (COMP == Q_TOPK && BATCH) {
+      if (sh.nonzeros && total < (uint32_t)A.k && A.k <= kZeroFillK) {
+        emit_with_zeros<COMP>(A, i, pre, total, h, grp, &s_kstar, scal);
+        return;
+      }
+    }
+    refine_and_emit<COMP, true, ONEPASS, BATCH>(A, i, pre, total, h, grp, &s_prefix, &s_need, &s_digit, &s_above, &s_emit, lbits, &sh.tie,
                                        scal);
     return;
   }
@@ -2541,7 +2606,7 @@ __device__ __forceinline__ void refine_row(const Args& A, int i, RefineShared& s
   const uint32_t in_bin = h[tbin];
   if (in_bin > (uint32_t)kSmallCap) {
     __syncthreads();
-    refine_and_emit<COMP, false, ONEPASS>(A, i, pre, total, h, grp, &s_prefix, &s_need, &s_digit, &s_above, &s_emit, lbits, &sh.tie,
+    refine_and_emit<COMP, false, ONEPASS, BATCH>(A, i, pre, total, h, grp, &s_prefix, &s_need, &s_digit, &s_above, &s_emit, lbits, &sh.tie,
                                        scal);
     return;
   }
@@ -2624,7 +2689,7 @@ __device__ __forceinline__ void refine_row(const Args& A, int i, RefineShared& s
     if (threadIdx.x == 0) sh.tie.publish(scal, s_kstar, true);
   }
   if (BATCH) reset_lists(A, i);
-  if (threadIdx.x == 0) next_guess<ONEPASS>(A, ctl, s_kstar, total, true, s_emit, 0u);
+  if (threadIdx.x == 0) next_guess<ONEPASS>(A, ctl, s_kstar, total, true, s_emit, 0u, false, 0u, kLowestGuess<COMP, BATCH>);
 }
 
 template <int COMP, bool BATCH = false, bool ONEPASS = false, int THREADS = 1024>
@@ -2792,7 +2857,7 @@ __global__ __launch_bounds__(1024) void k_sel_finish(Args A) {
   __syncthreads();
   const uint32_t total = s_total;
   if (!s_good) {
-    refine_and_emit<COMP, true, ONEPASS>(A, i, pre, total, h, grp, &s_prefix, &s_need, &s_digit, &s_above, &s_emit, nullptr);
+    refine_and_emit<COMP, true, ONEPASS, false>(A, i, pre, total, h, grp, &s_prefix, &s_need, &s_digit, &s_above, &s_emit, nullptr);
     return;
   }
   sum_hist_parts(A, i, h);
@@ -2838,7 +2903,7 @@ __global__ __launch_bounds__(1024) void k_sel_finish(Args A) {
   }
   __syncthreads();
   if (crowded) {
-    refine_and_emit<COMP, false, ONEPASS>(A, i, pre, total, h, grp, &s_prefix, &s_need, &s_digit, &s_above, &s_emit, nullptr);
+    refine_and_emit<COMP, false, ONEPASS, false>(A, i, pre, total, h, grp, &s_prefix, &s_need, &s_digit, &s_above, &s_emit, nullptr);
     return;
   }
   if (threadIdx.x < m) {

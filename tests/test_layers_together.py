@@ -133,3 +133,50 @@ def test_large_entries_that_lie_together_stay_in_the_lists(fraction):
         if t > 2:
             assert np.all(pair.gpu.layer_scalars()[:, [1, 2, 4], 3] == 1), t
     pair.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,table", [(5, "aligned"), (5, "generic"), (64, "aligned")])
+def test_layers_with_fewer_values_than_are_kept(n, table):
+    """Layers without gradients whose values have all been sent, and such of which few entries get one: the zeros that are
+    kept with the others are the first, and once the layer has come to that its lists say so (no scan)."""
+    lengths = [20000, 4000, 3500, 9216, 100, 10240, 5000, 3073, 2500, 12000, 7000, 3100, 6000, 8000, 3300, 9999, 4097, 30000]
+    start, length, k = synth.layer_table(lengths, fraction=0.01)
+    if table == "generic":
+        start = np.cumsum([3] + [int(a) + 1 + (j % 3) for j, a in enumerate(length)])[:-1]
+    k[2], k[9], k[13] = 819, 700, 1
+    layers = (np.asarray(start, dtype=np.int64), length, k)
+    d = int(layers[0][-1] + length[-1])
+    rng = np.random.default_rng(n)
+    # values left to be sent (the same of all workers, so that the mix adds none), entries that get a gradient
+    left = [3.5, 0.5, 0.3, 0, 1.5, 2.2, 9, 0.9, 1.7, 0.6, 0, 2, 1, 1, 0.2, 0, 1.1, 0.4]
+    moving = [0, 0, 0.7, 0, 0, 0.5, 3, 0, 0, 0.9, 0.4, 0.97, 0, 0, 1, 0, 0, 0.3]
+    X0, at = np.zeros((n, d), dtype=np.float32), []
+    for l, (a, m, kk) in enumerate(zip(layers[0], length, k)):
+        places = a + rng.permutation(m if l % 2 else min(m, 2 * kk))[:int(np.ceil(left[l] * kk))]
+        X0[:, places] = rng.standard_normal(len(places)).astype(np.float32)
+        # among the first entries, about the k-th, anywhere
+        near = [min(m, 2 * kk), min(m, kk + 40), m][l % 3]
+        at.append(a + rng.permutation(near)[:min(near, int(moving[l] * kk))])
+    at = np.concatenate(at)
+    pair = Pair(X0, synth.ring_csr(n), 0.02, seed=3, compressor=binding.Q_TOPK, layers=layers)
+    before = np.zeros((n, len(lengths)), dtype=bool)
+    seen = 0
+    for t in range(14):
+        g = np.zeros((n, d), dtype=np.float32)
+        g[:, at] = rng.standard_normal((1 if t < 11 else n, len(at))).astype(np.float32)
+        v = (pair.ref.X - np.float32(0.25) * g) - pair.ref.Xhat
+        pair.check(pair.step(g, 0.25), tag="%d workers, %s, step %d" % (n, table, t))
+        scal = pair.gpu.layer_scalars()
+        for l, (a, m, kk) in enumerate(zip(layers[0], length, k)):
+            some = np.count_nonzero(v[:, a:a + m], axis=1)
+            now = some < kk
+            if m <= 10240:
+                np.testing.assert_array_equal(scal[now, l, :3], np.stack([0 * some, kk - some, m - some], axis=1)[now])
+            else:
+                assert np.all(scal[now, l, 0] == 0)
+            assert np.all(scal[now & before[:, l], l, 3] == 1), (t, l)
+            seen += int((now & before[:, l]).sum())
+            before[:, l] = now
+    assert seen > 50 * n
+    pair.close()
