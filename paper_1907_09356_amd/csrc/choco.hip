@@ -406,6 +406,26 @@ bool one_pass_qsgd(const choco_config& c) {
   return mib > 96.0 && (double)c.n * marked_per_row(c) <= 14.0;
 }
 
+// What a launch of k_layers_pass covers: so many layers that are streamed, above 10,240 entries and of 3,073 to 10,240, the
+// longest of each, and so many that a 256-thread workgroup or a wave selects.
+struct PassCount {
+  int64_t nlong, nmid, nsmall, ntiny, longest, longest_mid;
+  LongGrid grid() const { return LongGrid{(int32_t)nlong, (int32_t)((longest + 1023) / 1024), (int32_t)((longest_mid + 1023) / 1024)}; }
+  int64_t blocks() const {   // of one worker
+    const LongGrid g = grid();
+    return nsmall + (ntiny + 3) / 4 + (int64_t)g.long_chunks * nlong + (int64_t)g.mid_chunks * nmid;
+  }
+};
+
+// top_a with long layers: one launch for the pass over all of them (and the short layers, see k_layers_pass)?  Not where long
+// rows' shape of the pass matters more, a 4-vector per thread of 1024: layers of up to 300,000 entries, n = 64, 250 MB
+// 510 -> 457 us per step; of 1,690,000, n = 8, 1 GB 1241 -> 1247.  (Workgroups are numbered in 31 bits, `others` per worker
+// in the launch after it, and the grid has the layers in x.)
+bool fits_one_pass_launch(const PassCount& c, int64_t others, int64_t n) {
+  const int64_t x = c.blocks();
+  return c.longest <= ((int64_t)1 << 19) && x <= (1 << 22) && (x + others) * n < ((int64_t)1 << 31);
+}
+
 // top_a: do the layers of 3,073 to 10,240 entries go through candidate lists, as the longer ones of the table do,
 // instead of through a workgroup's registers?  Streamed, they cost their bytes and a short select; in registers every
 // (worker, layer) is a 1024-thread workgroup that waits for its loads and its bracket, all the more where thresholds
@@ -414,21 +434,31 @@ bool one_pass_qsgd(const choco_config& c) {
 //   65 layers of the 0.27 M model  n = 4 30.9 | 27.6   n = 8 36.2 | 31.9, jumps 47.8 | 34.7   n = 16 42.5 | 38.7
 //                                  n = 32 61.7 | 59.2  n = 64 108.8 | 105.4, jumps 118.8 | 105.3; 0.1 % 97.0 | 92.6
 //   1 of 20,000, 40 of 3,500 to 10,000  n = 8 35.8 | 29.5, jumps 46.3 | 30.0   n = 32 73.4 | 65.2   n = 64 126.6 | 120.8
+//   no layer of up to 3,072: 1 of 20,000, 40 of 4,000  n = 4 30.2 | 19.9   n = 8 33.5 | 22.4, jumps 38.7 | 22.8   n = 64 94.2 | 80.0
+//                            1 of 500,000, 200 of 5,000  n = 8 87 | 77   n = 64 526 | 514, jumps 547 | 515
 //   10 % (lists above 2,048): n = 8 47.3 | 59.9, n = 64 167.9 | 179.8
 // The lists of these layers take one to three times one array of the state: not above 4 GiB per array.
 constexpr double kShortList = 2048.0;
 bool mids_in_lists(const choco_config& c) {
   if (c.nlayers <= 0 || c.nlayers > 65535 || c.compressor != CHOCO_Q_TOPK) return false;
   if ((double)c.n * (double)resolve_ld(c) * sizeof(float) > 4.0 * 1073741824.0) return false;
-  bool any_long = false;
+  PassCount count{};
   for (int32_t l = 0; l < c.nlayers; ++l) {
     const int64_t k = c.layer_k_host[l], span = c.layer_len_host[l] + (c.layer_start_host[l] & 3);
-    if (span <= kSmallLayerLen) continue;
-    if (span > ((int64_t)1 << 19) || expected_candidates(c.compressor, k) > kShortList) return false;
-    if (span > kMidLayerLen) any_long = any_long || k > 0;
-    else if (k == 0) return false;   // (the layer kernel has what is left of the work list by falling length)
+    if (span > kSmallLayerLen && expected_candidates(c.compressor, k) > kShortList) return false;
+    if (span > kMidLayerLen) {
+      if (span > ((int64_t)1 << 19)) return false;
+      count.nlong += k > 0 ? 1 : 0;
+      count.longest = std::max(count.longest, k > 0 ? span : 0);
+    } else if (span > kSmallLayerLen) {
+      if (k == 0) return false;   // (the layer kernel has what is left of the work list by falling length)
+      count.nmid += 1;
+      count.longest_mid = std::max(count.longest_mid, span);
+    } else {
+      (span > kWaveLayerLen ? count.nsmall : count.ntiny) += 1;
+    }
   }
-  return any_long;
+  return count.nlong > 0 && fits_one_pass_launch(count, 0, c.n);
 }
 
 // The layers of a top_a / random_a configuration that do not go through the layer kernel; the longest class first.
@@ -1492,15 +1522,15 @@ int gossip_layers_sparse(choco_ctx* ctx, const Args& F) {
   const int nlong = (int)ctx->long_layers.size();   // first in the work list, not for the layer kernel
   const int nmid = ctx->nmid, nsmall = ctx->nsmall, ntiny = A.nlayers - nlong - nmid - nsmall;
   const int wide_blocks = nmid + nsmall + (ntiny + 15) / 16;
-  // top_a with layers of every kind: two launches before the mix instead of four (see k_layers_pass).  Not where long
-  // rows' shape of the pass matters more, a 4-vector per thread of 1024: layers of up to 300,000 entries, n = 64, 250 MB
-  // 510 -> 457 us per step; of 1,690,000, n = 8, 1 GB 1241 -> 1247.
-  // (Workgroups are numbered in 31 bits there, and the grid has the layers in x.)
-  const LongGrid pass_long{ctx->nbatched - ctx->nbatched_mid, (ctx->batched_nvec + 255) / 256, (ctx->mid_nvec + 255) / 256};
-  const int64_t pass_x = nsmall + (ntiny + 3) / 4 + (int64_t)pass_long.long_chunks * pass_long.nlong +
-                         (int64_t)pass_long.mid_chunks * ctx->nbatched_mid;
-  const bool together = COMP == Q_TOPK && ctx->nbatched > 0 && nsmall + ntiny > 0 && ctx->batched_nvec <= (1 << 17) &&
-                        pass_x <= (1 << 22) && (pass_x + nmid) * A.n < ((int64_t)1 << 31);
+  // top_a: two launches before the mix instead of four (see k_layers_pass), where there is something to put together: the
+  // layers of 3,073 to 10,240 entries in lists (mids_in_lists has seen to it that it is possible) or shorter ones beside the
+  // long.  us per step before | so: 6 layers of 36,864, 12 of 2,304, 20 of 64 n = 8 34.6 | 28.3, n = 64 103.9 | 91.3; 3 of
+  // 300,000, 20 of 1,000 n = 8 56.6 | 49.6, n = 64 330 | 313.
+  const PassCount pass{ctx->nbatched - ctx->nbatched_mid, ctx->nbatched_mid, nsmall, ntiny, 4 * (int64_t)ctx->batched_nvec, 4 * (int64_t)ctx->mid_nvec};
+  const LongGrid pass_long = pass.grid();
+  const int64_t pass_x = pass.blocks();
+  const bool together = COMP == Q_TOPK && ctx->nbatched > 0 &&
+                        (ctx->nbatched_mid > 0 || (nsmall + ntiny > 0 && fits_one_pass_launch(pass, nmid, A.n)));
   // few workers: with a 1024-thread workgroup for every layer above a wave's reach (and sixteen
   // waves' worth of smaller layers in each of the others) the chip still is not full, and one
   // launch does

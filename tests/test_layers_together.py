@@ -14,7 +14,8 @@ EDGES = [1, 768, 3072, 3073, 10240, 10241, 769, 5, 12288, 12289, 9216, 2304, 16,
 @pytest.mark.timeout(300)
 def test_which_tables_take_two_launches():
     """Long layers of up to 2^19 entries and some of up to 3,072; whatever the workers and the order.  Layers of 3,073 to
-    10,240 entries go through lists like the long ones where all lists are short, else through registers."""
+    10,240 entries go through lists like the long ones where all lists are short, else through registers; in lists they
+    take the same launches without any of up to 3,072."""
     out = recorded("""
 out = {}
 for name, lengths in (("all", [20000, 4000, 100]), ("no long", [4000, 100]), ("no middle", [20000, 100]), ("no short", [20000, 4000]),
@@ -35,16 +36,35 @@ for name, lengths in (("all", [20000, 4000, 100]), ("no long", [4000, 100]), ("n
         op, name = key.rsplit(" ", 2)[0].split(" ", 1)
         if op == "randk":
             assert not any(x.startswith("k_layers") for x in first), key
-        elif name in ("all", "no middle"):
+        elif name in ("all", "no middle", "no short"):
             assert first == ["k_layers_pass", "k_sel_refine"], key
         elif name in ("longest", "many kept"):
             assert first == ["k_layers_pass", "k_layers_select"], key
         else:
             assert not any(x.startswith("k_layers") for x in first), key
-            assert ("k_layer_compress" in first) == (name != "no short"), key
+            assert "k_layer_compress" in first, key
     assert out["topk all 64 0"][:2] == ["k_layers_pass %dx64x1" % (1 + (20000 // 4 + 255) // 256 + (4000 // 4 + 255) // 256),
                                         "k_sel_refine 64x2x1"]
+    assert out["topk no short 64 0"][:2] == ["k_layers_pass %dx64x1" % ((20000 // 4 + 255) // 256 + (4000 // 4 + 255) // 256),
+                                             "k_sel_refine 64x2x1"]
     assert out["topk many kept 64 0"][:2] == ["k_layers_pass %dx64x1" % (1 + (100000 // 4 + 255) // 256), "k_layers_select 2x64x1"]
+
+
+def test_no_launch_covers_more_chunks_than_the_layers_have():
+    """200 layers of 5,000 entries beside a long one, with and without a short one: the streaming pass launches their chunks
+    of 1,024 entries and one workgroup for the short layer."""
+    out = recorded("""
+out = {}
+for name, n, more in (("short", 8, [100]), ("none", 8, []), ("none", 64, [])):
+    t = synth.layer_table([1 << 19] + [5000] * 200 + more, fraction=0.0015)
+    c = Context(n, synth.layers_dim(t), B.Q_TOPK, layers=t)
+    out["%s %d" % (name, n)] = [x[:3] for x in c.step() + c.step()]
+    c.close()
+""")
+    for name, launches in out.items():
+        assert not any(x[0].startswith(("k_sel_compact", "k_layer_compress")) for x in launches), name
+        grid = "%dx%dx1" % (512 + 5 * 200 + name.startswith("short"), int(name.split()[1]))
+        assert [x[1:] for x in launches if x[0].startswith("k_layers_pass")] == [[grid, "256x1x1"]] * 2, name
 
 
 @pytest.mark.gpu
@@ -52,15 +72,18 @@ for name, lengths in (("all", [20000, 4000, 100]), ("no long", [4000, 100]), ("n
     (2, "aligned", "step", 0.02), (5, "generic", "step", 0.02), (12, "aligned", "step", 0.02), (12, "aligned", "momentum", 0.02),
     (33, "aligned", "step", 0.02), (33, "aligned", "printed", 0.02), (17, "generic", "printed", 0.02), (70, "aligned", "step", 0.02),
     (5, "generic", "step", 0.06), (33, "aligned", "momentum", 0.06), (12, "aligned", "printed", 0.06), (64, "many", "step", 0.01),
-    (64, "many", "printed", 0.002)])
+    (64, "many", "printed", 0.002), (5, "no short", "step", 0.02), (33, "no short", "momentum", 0.01), (64, "no short", "printed", 0.02)])
 def test_parity_where_the_kinds_meet(n, table, form, fraction):
     """Lists of 512 threads (256 with more than 1,024 of them), at 6 % registers."""
     edges = EDGES if table != "many" else EDGES + [3073, 3074, 3500, 4000, 4096, 4097, 5000, 6144, 7000, 8191]
+    if table == "no short":
+        edges = [x for x in EDGES if x > 3072] + [3073, 3074, 4096, 4097, 7168]
     start, length, k = synth.layer_table(edges, fraction=fraction)
     if table == "generic":      # layers that start anywhere, with gaps
         start = np.cumsum([3] + [int(a) + 1 + (j % 3) for j, a in enumerate(length)])[:-1]
-    k[1], k[7] = 0, length[7]   # a silent layer, a layer sent whole
-    k[2], k[5] = 1, max(k[5], 1)
+    if table != "no short":
+        k[1], k[7] = 0, length[7]   # a silent layer, a layer sent whole
+        k[2], k[5] = 1, max(k[5], 1)
     layers = (np.asarray(start, dtype=np.int64), length, k)
     d = int(layers[0][-1] + length[-1])
     order = binding.ORDER_MIX_THEN_COMPRESS if form == "printed" else binding.ORDER_COMPRESS_THEN_MIX
