@@ -42,6 +42,7 @@ struct LongLayer {
   SelectPlan plan;
   LongSel sel;      // what the kernels need of it (filled by choco_init)
   bool mid;         // 3,073 to 10,240 entries
+  int64_t cand_first;   // its candidate lists, in entries from the first layer's
   bool batched;     // its pass and its select share a launch with those of the other such layers
   int32_t part_set; // multi-block select: which of the copies of its scratch
 };
@@ -406,6 +407,50 @@ bool one_pass_qsgd(const choco_config& c) {
   return mib > 96.0 && (double)c.n * marked_per_row(c) <= 14.0;
 }
 
+// A layer of top_a of 3,073 to 10,240 entries that goes through lists.
+SelectPlan plan_mid(int64_t len, int64_t k) {
+  SelectPlan P = plan_select(CHOCO_Q_TOPK, len, k);
+  // a sub-list takes the hits of one 1024-entry chunk: room for all that are expected in the layer (large
+  // entries may lie together) and for four times an even share
+  const double expected = expected_candidates(CHOCO_Q_TOPK, k), share = 1024.0 * expected / (double)len;
+  P.seg_cap = (uint32_t)std::min(1024.0, std::max(64.0, std::ceil(std::max(4.0 * share, 1.25 * expected))));
+  return P;
+}
+
+// Entries of the candidate lists of one selected piece of the rows, on the workspace's alignment.
+int64_t list_entries(int32_t n, uint32_t seg_cap) {
+  return (int64_t)(align_up((size_t)n * kSegs * (size_t)seg_cap * sizeof(uint2)) / sizeof(uint2));
+}
+
+// Such a layer has a sub-list per chunk, ten at most: several share the kSegs sub-lists of one piece, those of like capacity,
+// and all get the largest capacity among them.  The entries all of them take; a layer's first sub-list goes to first_of.
+// (Workspace of 40 layers of 4,000 beside one of 20,000, 1 % kept, n = 64, a state array of 46 MB: 165 MB with kSegs each, 92 so.)
+struct MidLists {
+  int64_t span;
+  uint32_t seg_cap;
+  int64_t first;   // the layer's first sub-list, in entries from the first of all
+};
+int64_t share_lists(int32_t n, std::vector<MidLists>& mids) {
+  std::vector<size_t> order(mids.size());
+  for (size_t j = 0; j < order.size(); ++j) order[j] = j;
+  std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t b) { return mids[a].seg_cap > mids[b].seg_cap; });
+  int64_t piece = 0, end = 0, used = kSegs;
+  uint32_t cap = 0;
+  for (size_t j : order) {
+    const int64_t chunks = (mids[j].span + 1023) / 1024;
+    if (used + chunks > kSegs) {
+      piece = end;
+      used = 0;
+      cap = mids[j].seg_cap;
+      end += list_entries(n, cap);
+    }
+    mids[j].seg_cap = cap;
+    mids[j].first = piece + used * (int64_t)cap;
+    used += chunks;
+  }
+  return end;
+}
+
 // What a launch of k_layers_pass covers: so many layers that are streamed, above 10,240 entries and of 3,073 to 10,240, the
 // longest of each, and so many that a 256-thread workgroup or a wave selects.
 struct PassCount {
@@ -437,11 +482,14 @@ bool fits_one_pass_launch(const PassCount& c, int64_t others, int64_t n) {
 //   no layer of up to 3,072: 1 of 20,000, 40 of 4,000  n = 4 30.2 | 19.9   n = 8 33.5 | 22.4, jumps 38.7 | 22.8   n = 64 94.2 | 80.0
 //                            1 of 500,000, 200 of 5,000  n = 8 87 | 77   n = 64 526 | 514, jumps 547 | 515
 //   10 % (lists above 2,048): n = 8 47.3 | 59.9, n = 64 167.9 | 179.8
-// The lists of these layers take one to three times one array of the state: not above 4 GiB per array.
+// The lists of these layers and their counters take half an array of the state (0.1 % kept) to three (819 of 3,100 entries):
+// not above 4 GiB per array, nor more than two arrays.
 constexpr double kShortList = 2048.0;
 bool mids_in_lists(const choco_config& c) {
   if (c.nlayers <= 0 || c.nlayers > 65535 || c.compressor != CHOCO_Q_TOPK) return false;
-  if ((double)c.n * (double)resolve_ld(c) * sizeof(float) > 4.0 * 1073741824.0) return false;
+  const double state = (double)c.n * (double)resolve_ld(c) * sizeof(float);
+  if (state > 4.0 * 1073741824.0) return false;
+  std::vector<MidLists> mids;
   PassCount count{};
   for (int32_t l = 0; l < c.nlayers; ++l) {
     const int64_t k = c.layer_k_host[l], span = c.layer_len_host[l] + (c.layer_start_host[l] & 3);
@@ -454,15 +502,20 @@ bool mids_in_lists(const choco_config& c) {
       if (k == 0) return false;   // (the layer kernel has what is left of the work list by falling length)
       count.nmid += 1;
       count.longest_mid = std::max(count.longest_mid, span);
+      mids.push_back(MidLists{span, plan_mid(c.layer_len_host[l], k).seg_cap, 0});
     } else {
       (span > kWaveLayerLen ? count.nsmall : count.ntiny) += 1;
     }
   }
-  return count.nlong > 0 && fits_one_pass_launch(count, 0, c.n);
+  const double counters = (double)c.n * (double)mids.size() * kSegs * kSegPad * sizeof(uint32_t);
+  return count.nlong > 0 && (double)share_lists(c.n, mids) * sizeof(uint2) + counters <= 2.0 * state &&
+         fits_one_pass_launch(count, 0, c.n);
 }
 
 // The layers of a top_a / random_a configuration that do not go through the layer kernel; the longest class first.
-std::vector<LongLayer> long_layers_of(const choco_config& c) {
+// list_end: what their candidate lists take, in entries.
+std::vector<LongLayer> long_layers_of(const choco_config& c, int64_t* list_end = nullptr) {
+  if (list_end) *list_end = 0;
   std::vector<LongLayer> out;
   if (c.nlayers <= 0 || !is_sparse(c.compressor)) return out;
   int64_t sel_base = 0;
@@ -478,22 +531,29 @@ std::vector<LongLayer> long_layers_of(const choco_config& c) {
       B.k = (int32_t)k;
       B.sel_base = (int32_t)sel_base;
       B.id = l;
-      B.plan = plan_select(c.compressor, len, std::max<int64_t>(k, 1));
+      B.mid = span <= kMidLayerLen;
+      B.plan = B.mid ? plan_mid(len, k) : plan_select(c.compressor, len, std::max<int64_t>(k, 1));
       // one block per worker finishes the select, no histogram passes: such layers share launches
       B.batched = k > 0 && !B.plan.multipart && !B.plan.fallback_chain;
       if (B.plan.multipart) B.part_set = part_sets++;
-      B.mid = span <= kMidLayerLen;
-      if (B.mid) {
-        // a sub-list takes the hits of one 1024-entry chunk: room for all that are expected in the layer (large
-        // entries may lie together) and for four times an even share
-        const double expected = expected_candidates(c.compressor, k), share = 1024.0 * expected / (double)len;
-        B.plan.seg_cap = (uint32_t)std::min(1024.0, std::max(64.0, std::ceil(std::max(4.0 * share, 1.25 * expected))));
-      }
       (B.mid ? mids : out).push_back(B);
     }
     sel_base += k;
   }
+  int64_t end = 0;
+  for (LongLayer& B : out) {
+    B.cand_first = end;
+    end += list_entries(c.n, B.plan.seg_cap);
+  }
+  std::vector<MidLists> lists;
+  for (const LongLayer& B : mids) lists.push_back(MidLists{B.len + (B.start & 3), B.plan.seg_cap, 0});
+  const int64_t mids_end = end + share_lists(c.n, lists);
+  for (size_t j = 0; j < mids.size(); ++j) {
+    mids[j].plan.seg_cap = lists[j].seg_cap;
+    mids[j].cand_first = end + lists[j].first;
+  }
   out.insert(out.end(), mids.begin(), mids.end());
+  if (list_end) *list_end = mids_end;
   return out;
 }
 
@@ -532,11 +592,6 @@ bool one_pass_rule(const choco_config& c) {
   return (one_pass_topk(c) || one_pass_qsgd(c)) && (double)c.n * (double)resolve_ld(c) * sizeof(float) <= 48.0 * 1073741824.0;
 }
 
-// Bytes of the candidate lists of one selected piece of the rows.
-size_t candidate_bytes(int32_t n, const SelectPlan& P) {
-  return align_up((size_t)n * kSegs * (size_t)P.seg_cap * sizeof(uint2));
-}
-
 Layout make_layout(const choco_config& c, int32_t nnz, bool one_pass) {
   Layout L{};
   const int64_t ld = resolve_ld(c);
@@ -545,7 +600,8 @@ Layout make_layout(const choco_config& c, int32_t nnz, bool one_pass) {
   const bool layered = c.nlayers > 0;
   // selects by guessed threshold: the whole row, or every long layer in turn (they share the
   // candidate lists and histograms, each has control blocks of its own)
-  const std::vector<LongLayer> longs = long_layers_of(c);
+  int64_t list_end = 0;
+  const std::vector<LongLayer> longs = long_layers_of(c, &list_end);
   const bool guessed = sparse && (!layered || !longs.empty());
   std::vector<SelectPlan> plans;
   if (sparse && !layered) plans.push_back(plan_select(c.compressor, c.d, c.k));
@@ -587,9 +643,8 @@ Layout make_layout(const choco_config& c, int32_t nnz, bool one_pass) {
   for (const SelectPlan& P : plans) chain = chain || P.fallback_chain;
   L.hist16_bytes = align_up(guessed && chain ? (size_t)c.n * kBins16 * sizeof(uint32_t) : 0);
   L.hist16 = take(L.hist16_bytes * (size_t)L.select_sets);
-  size_t cand_bytes = 0;
-  for (const SelectPlan& P : plans) cand_bytes += candidate_bytes(c.n, P);
-  L.cand = take(guessed ? cand_bytes : 0);
+  if (sparse && !layered) list_end = list_entries(c.n, plans[0].seg_cap);
+  L.cand = take((size_t)list_end * sizeof(uint2));
   L.sel_idx = take(sparse ? (size_t)c.n * (size_t)kept * sizeof(int32_t) : 0);
   L.sel_val = take(sparse ? (size_t)c.n * (size_t)kept * sizeof(float) : 0);
   L.multipart = guessed && multipart;
@@ -2052,7 +2107,6 @@ int choco_init(const choco_config* cfg, float* x_dev, void* workspace_dev, size_
   ctx->nbatched_mid = 0;
   ctx->short_lists = true;
   int nsolo = 0;
-  int64_t cand_first = 0;
   for (size_t b = 0; b < ctx->long_layers.size(); ++b) {
     LongLayer& B = ctx->long_layers[b];
     LongSel& Z = B.sel;
@@ -2070,8 +2124,7 @@ int choco_init(const choco_config* cfg, float* x_dev, void* workspace_dev, size_
     Z.sample_stride = B.plan.sample_stride;
     Z.sample_need = B.plan.sample_need;
     Z.scal_id = B.mid ? B.id : -1;
-    Z.cand_first = cand_first;
-    cand_first += (int64_t)(candidate_bytes(cfg->n, B.plan) / sizeof(uint2));
+    Z.cand_first = B.cand_first;
     if (B.batched && long_tab.size() < 65535) {   // (a grid has that many layers at most)
       long_tab.push_back(Z);
       ctx->batched_nvec = std::max(ctx->batched_nvec, (Z.d + 3) >> 2);

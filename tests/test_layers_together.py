@@ -67,6 +67,30 @@ for name, n, more in (("short", 8, [100]), ("none", 8, []), ("none", 64, [])):
         assert [x[1:] for x in launches if x[0].startswith("k_layers_pass")] == [[grid, "256x1x1"]] * 2, name
 
 
+def workspace(n, lengths, fraction, silent=()):
+    start, length, k = synth.layer_table(lengths, fraction=fraction)
+    k[list(silent)] = 0
+    d = int(start[-1] + length[-1])
+    cfg, keep = binding.make_config(n, d, *synth.ring_csr(n), 0.1, binding.Q_TOPK, layers=(start, length, k))
+    return binding.workspace_bytes(cfg), 4 * n * d
+
+
+@pytest.mark.parametrize("n,lengths,fraction,listed", [
+    (64, [20000] + [4000] * 40, 0.01, True), (64, [20000] + [3100] * 1000, 0.01, True), (8, [1 << 19] + [5000] * 200, 0.0015, True),
+    (64, [16000] + [3100] * 1000, 0.05, True), (64, [10300] + [3100] * 5000, 0.079, False), (64, [11000] + [3100] * 1000, 0.19, False)])
+def test_lists_take_no_more_than_two_arrays(n, lengths, fraction, listed):
+    """What the layers of 3,073 to 10,240 entries add to the workspace: their sub-lists, as many as a layer has chunks, and the
+    counters; a silent one takes the table to registers."""
+    lists, state = workspace(n, lengths, fraction)
+    registers, _ = workspace(n, lengths, fraction, silent=[1])
+    assert (lists > registers + state // 20) == listed
+    assert lists <= registers + 2 * state
+    if listed:
+        chunks = sum((m + 1023) // 1024 for m in lengths[1:])
+        room = min(1024, max(64, int(2.5 * lengths[1] * fraction + 120) * 2))   # of a sub-list, generously
+        assert lists <= registers + n * (8 * room * chunks + 4 * 32 * 32 * len(lengths[1:])) + 4096 * len(lengths)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("n,table,form,fraction", [
     (2, "aligned", "step", 0.02), (5, "generic", "step", 0.02), (12, "aligned", "step", 0.02), (12, "aligned", "momentum", 0.02),
