@@ -113,7 +113,9 @@ typedef struct {
      of its registers and longer layers take the whole-vector select, in launches that they
      share (they cost workspace for its candidate lists, a set per such layer); so do TOPK's
      layers of 3,073 entries on in a table that has longer ones than CHOCO_MAX_LAYER_LEN, none
-     above 2^19, and keeps no more than 819 entries of any, up to 4 GiB per state array.  With
+     above 2^19, and of whose layers above 3,072 entries none keeps more than 819 and none of up to
+     CHOCO_MAX_LAYER_LEN keeps nothing, up to 4 GiB per state array and where their lists take two
+     such arrays at most (choco_init also accepts a workspace without those lists).  With
      layers, IDENTITY is CHOCO_E_UNSUPPORTED, SIGN and QSGD take CHOCO_MIX_AUTO only, and
      TOPK / RANDK take CHOCO_MIX_DIRECT in the default order and up to 64 workers only.
      layer_k_host may be NULL for SIGN and QSGD.     */
@@ -131,8 +133,10 @@ typedef struct {
    For TOPK and QSGD of two to eight workers on rows that stream past the caches (more than
    96 MiB per array, little sent, default order, no layer table) it holds nearly half an array of
    the state more than two passes need (TOPK 1.55 arrays instead of 1.07, QSGD with 16 levels 1.67
-   instead of 1.16), with which a step goes over the state once instead of twice.  choco_init also
-   accepts a workspace without that part; the steps then take two passes.  Same results either way. */
+   instead of 1.16), with which a step goes over the state once instead of twice.  For TOPK on a layer
+   table it may hold lists for the layers of 3,073 to CHOCO_MAX_LAYER_LEN entries (see there), a half to
+   two arrays.  choco_init also accepts a workspace without that part; the steps then take two passes,
+   those layers are selected in registers.  Same results either way. */
 int choco_workspace_bytes(const choco_config *cfg, size_t *bytes_host);
 
 /* Algorithm 1, input line: takes X = x^(-1/2) as it stands in x_dev (n*ld floats, 16-byte
@@ -140,7 +144,7 @@ int choco_workspace_bytes(const choco_config *cfg, size_t *bytes_host);
    t = 0.  workspace_dev must be 256-byte aligned.  CHOCO_E_INVAL for n < 1, d out of
    range (above CHOCO_MAX_D), bad ld, k outside [1, d], levels < 1, gamma <= 0 or not finite, null pointers,
    malformed CSR, or a W that violates Assumption 1; CHOCO_E_NOMEM if the workspace is
-   too small (also for the two-pass form, see choco_workspace_bytes).  On error *out is NULL.
+   too small (also without that part, see choco_workspace_bytes).  On error *out is NULL.
    Reads one environment variable, CHOCO_FALLBACK_SPIN_LIMIT (decimal; default 65536): TOPK /
    RANDK on rows above 2^21 entries repair a failed threshold guess in one launch whose
    workgroups wait for one of their number in a bounded poll; this is the bound.  A workgroup

@@ -513,15 +513,15 @@ bool mids_in_lists(const choco_config& c) {
 }
 
 // The layers of a top_a / random_a configuration that do not go through the layer kernel; the longest class first.
-// list_end: what their candidate lists take, in entries.
-std::vector<LongLayer> long_layers_of(const choco_config& c, int64_t* list_end = nullptr) {
+// list_mids: those of mids_in_lists too.  list_end: what their candidate lists take, in entries.
+std::vector<LongLayer> long_layers_of(const choco_config& c, bool list_mids, int64_t* list_end = nullptr) {
   if (list_end) *list_end = 0;
   std::vector<LongLayer> out;
   if (c.nlayers <= 0 || !is_sparse(c.compressor)) return out;
   int64_t sel_base = 0;
   int32_t part_sets = 0;
   std::vector<LongLayer> mids;
-  const int64_t in_registers = mids_in_lists(c) ? kSmallLayerLen : kMidLayerLen;
+  const int64_t in_registers = list_mids ? kSmallLayerLen : kMidLayerLen;
   for (int32_t l = 0; l < c.nlayers; ++l) {
     const int64_t len = c.layer_len_host[l], k = c.layer_k_host[l], span = len + (c.layer_start_host[l] & 3);
     if (span > in_registers) {   // (with the entries before it in its first 4-vector)
@@ -592,7 +592,7 @@ bool one_pass_rule(const choco_config& c) {
   return (one_pass_topk(c) || one_pass_qsgd(c)) && (double)c.n * (double)resolve_ld(c) * sizeof(float) <= 48.0 * 1073741824.0;
 }
 
-Layout make_layout(const choco_config& c, int32_t nnz, bool one_pass) {
+Layout make_layout(const choco_config& c, int32_t nnz, bool one_pass, bool list_mids) {
   Layout L{};
   const int64_t ld = resolve_ld(c);
   const size_t state = (size_t)c.n * (size_t)ld * sizeof(float);
@@ -601,7 +601,7 @@ Layout make_layout(const choco_config& c, int32_t nnz, bool one_pass) {
   // selects by guessed threshold: the whole row, or every long layer in turn (they share the
   // candidate lists and histograms, each has control blocks of its own)
   int64_t list_end = 0;
-  const std::vector<LongLayer> longs = long_layers_of(c, &list_end);
+  const std::vector<LongLayer> longs = long_layers_of(c, list_mids, &list_end);
   const bool guessed = sparse && (!layered || !longs.empty());
   std::vector<SelectPlan> plans;
   if (sparse && !layered) plans.push_back(plan_select(c.compressor, c.d, c.k));
@@ -1944,7 +1944,7 @@ int choco_workspace_bytes(const choco_config* cfg, size_t* bytes_host) {
   if (!cfg->row_ptr_host) return CHOCO_E_INVAL;
   const int32_t nnz = cfg->row_ptr_host[cfg->n];
   if (nnz < cfg->n) return CHOCO_E_INVAL;
-  *bytes_host = make_layout(*cfg, nnz, one_pass_rule(*cfg)).total;
+  *bytes_host = make_layout(*cfg, nnz, one_pass_rule(*cfg), mids_in_lists(*cfg)).total;
   return CHOCO_OK;
 }
 
@@ -1958,11 +1958,11 @@ int choco_init(const choco_config* cfg, float* x_dev, void* workspace_dev, size_
   int32_t nnz = 0, maxdeg = 0;
   rc = check_csr(cfg, &nnz, &maxdeg);
   if (rc != CHOCO_OK) return rc;
-  bool one_pass = one_pass_rule(*cfg);
-  Layout L = make_layout(*cfg, nnz, one_pass);
-  if (one_pass && workspace_bytes < L.total) {   // enough for two passes?
-    one_pass = false;
-    L = make_layout(*cfg, nnz, one_pass);
+  bool one_pass = one_pass_rule(*cfg), list_mids = mids_in_lists(*cfg);
+  Layout L = make_layout(*cfg, nnz, one_pass, list_mids);
+  if ((one_pass || list_mids) && workspace_bytes < L.total) {   // enough for two passes, or for fewer lists?
+    one_pass = list_mids = false;
+    L = make_layout(*cfg, nnz, one_pass, list_mids);
   }
   if (workspace_bytes < L.total) return CHOCO_E_NOMEM;
 
@@ -2004,7 +2004,7 @@ int choco_init(const choco_config* cfg, float* x_dev, void* workspace_dev, size_
   if (ctx->sparse && cfg->nlayers == 0) ctx->plan = plan_select(cfg->compressor, cfg->d, cfg->k);
   ctx->fallback_chain = ctx->plan.fallback_chain;
   ctx->long_rows = cfg->d > ((int64_t)1 << 21);
-  ctx->long_layers = long_layers_of(*cfg);
+  ctx->long_layers = long_layers_of(*cfg, list_mids);
   ctx->long_silent = false;
   for (const LongLayer& B : ctx->long_layers) ctx->long_silent = ctx->long_silent || B.k == 0;
   ctx->nlayers = cfg->nlayers;
@@ -2207,11 +2207,10 @@ int choco_init(const choco_config* cfg, float* x_dev, void* workspace_dev, size_
     std::stable_sort(work.begin(), work.end(),
                      [](const LayerDesc& a, const LayerDesc& b) { return a.len + a.head > b.len + b.head; });
     ctx->nmid = ctx->nsmall = 0;
-    const bool mids_listed = mids_in_lists(*cfg);
     for (const LayerDesc& D : work) {
       const int32_t span = D.len + D.head;   // what the layer kernel holds in registers
       // (long layers: first in the list, skipped by the layer kernel)
-      if (span <= kMidLayerLen && span > kSmallLayerLen && !mids_listed) ctx->nmid += 1;
+      if (span <= kMidLayerLen && span > kSmallLayerLen && !list_mids) ctx->nmid += 1;
       else if (span <= kSmallLayerLen && span > kWaveLayerLen) ctx->nsmall += 1;
     }
   }

@@ -124,9 +124,10 @@ struct LongSel {
   int32_t sel_base;    // the layer's first slot in a worker's kept lists
   int32_t set;         // which control blocks (n per layer) and which set of select scratch
   uint32_t cand_cap, seg_cap, extra, want, delta0, sample_stride, sample_need;   // see Args
-  int64_t cand_first;  // its candidate lists, in entries from the first layer's
   int32_t scal_id;     // the layer whose scalars the select writes (those of the layer kernel), or -1
+  int64_t cand_first;  // its candidate lists, in entries from the first layer's
 };
+static_assert(sizeof(LongSel) == 64, "a workspace that was enough for the table stays so");
 
 struct Args {
   int32_t n;

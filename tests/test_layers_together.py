@@ -91,6 +91,50 @@ def test_lists_take_no_more_than_two_arrays(n, lengths, fraction, listed):
         assert lists <= registers + n * (8 * room * chunks + 4 * 32 * 32 * len(lengths[1:])) + 4096 * len(lengths)
 
 
+def test_a_workspace_that_was_enough_is_accepted():
+    """Bytes that were asked for before layers of 3,073 to 10,240 entries went through lists: enough for the register form, and
+    for a table without such layers."""
+    out = recorded("""
+out = {}
+for name, n, lengths, fraction, ws in (("41", 64, [20000] + [4000] * 40, 0.01, 65611264), ("201", 8, [1 << 19] + [5000] * 200, 0.0015, 52669952),
+                                       ("image", 64, list(synth.resnet20_like_lengths()), 0.01, 175791360),
+                                       ("long", 8, [12000] * 40, 0.01, 101414400)):
+    t = synth.layer_table(lengths, fraction=fraction)
+    out[name] = []
+    for given in (ws, None):
+        c = Context(n, synth.layers_dim(t), B.Q_TOPK, layers=t, ws=given)
+        assert c.rc == B.OK, (name, given, c.asked)
+        c.step()
+        out[name].append([x[0].split("<")[0] for x in c.step()])
+        c.close()
+    assert name == "long" or Context(n, synth.layers_dim(t), B.Q_TOPK, layers=t, ws=ws // 2).rc == B.E_NOMEM
+""")
+    for name, (before, asked) in out.items():
+        if name == "long":
+            assert before == asked, name
+        else:
+            assert any(x in ("k_layers_select", "k_layer_compress") for x in before), name
+            assert asked[:2] == ["k_layers_pass", "k_sel_refine"], name
+
+
+@pytest.mark.gpu
+def test_parity_in_a_workspace_without_the_lists(monkeypatch):
+    lengths, n = [20000, 4000, 100, 9216, 3073, 10240], 9
+    layers = synth.layer_table(lengths, fraction=0.01)
+    d = synth.layers_dim(layers)
+    least = workspace(n, lengths, 0.01, silent=[1])[0] + (1 << 16)    # registers, what the silent layer keeps, longer rows
+    assert least < workspace(n, lengths, 0.01)[0]
+    monkeypatch.setattr(binding, "workspace_bytes", lambda cfg: least)
+    pair = Pair(synth.normal_state(n, d, seed=8), synth.ring_csr(n), 0.05, seed=3, compressor=binding.Q_TOPK, layers=layers)
+    g = synth.GradientStream(n, d, seed=9)
+    for t in range(4):
+        pair.check(pair.step(g.next(), 0.05), tag="registers, step %d" % t)
+    pair.gpu.set_profiling(True)
+    pair.step(g.next(), 0.05)
+    assert any(x.startswith("k_layers_select") for x in pair.gpu.profile_report())
+    pair.close()
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("n,table,form,fraction", [
     (2, "aligned", "step", 0.02), (5, "generic", "step", 0.02), (12, "aligned", "step", 0.02), (12, "aligned", "momentum", 0.02),
