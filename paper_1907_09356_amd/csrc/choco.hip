@@ -126,6 +126,7 @@ struct choco_ctx {
   int nbatched_mid;       // ... of which the last so many have 3,073 to 10,240 entries, and the 4-vectors of the longest of these
   int32_t mid_nvec;
   bool short_lists;       // all of them have lists of kShortList entries at most
+  bool lists_begun;       // a step has been enqueued: later ones find lists
   bool long_silent;       // one of them keeps nothing (its pass cannot carry the local update)
   bool overlap_long;      // top_a, several long layers with launches of their own: a layer's select runs on the second stream beside the next layer's pass
   size_t set_hist16, set_hist_parts, set_small_list;   // bytes from one long layer's select scratch to the next
@@ -479,7 +480,7 @@ bool fits_one_pass_launch(const PassCount& c, int64_t others, int64_t n) {
 //   65 layers of the 0.27 M model  n = 4 30.9 | 27.6   n = 8 36.2 | 31.9, jumps 47.8 | 34.7   n = 16 42.5 | 38.7
 //                                  n = 32 61.7 | 59.2  n = 64 108.8 | 105.4, jumps 118.8 | 105.3; 0.1 % 97.0 | 92.6
 //   1 of 20,000, 40 of 3,500 to 10,000  n = 8 35.8 | 29.5, jumps 46.3 | 30.0   n = 32 73.4 | 65.2   n = 64 126.6 | 120.8
-//   no layer of up to 3,072: 1 of 20,000, 40 of 4,000  n = 4 30.2 | 19.9   n = 8 33.5 | 22.4, jumps 38.7 | 22.8   n = 64 94.2 | 80.0
+//   no layer of up to 3,072: 1 of 20,000, 40 of 4,000  n = 4 30.2 | 19.9   n = 8 33.5 | 22.4, jumps 38.7 | 22.8   n = 64 94.2 | 87
 //                            1 of 500,000, 200 of 5,000  n = 8 87 | 77   n = 64 526 | 514, jumps 547 | 515
 //   10 % (lists above 2,048): n = 8 47.3 | 59.9, n = 64 167.9 | 179.8
 // The lists of these layers and their counters take half an array of the state (0.1 % kept) to three (819 of 3,100 entries):
@@ -1627,13 +1628,25 @@ int gossip_layers_sparse(choco_ctx* ctx, const Args& F) {
       if constexpr (COMP == Q_TOPK)
         LAUNCH(ctx, S.G ? KID_LAYERS_SELECT_SGD : KID_LAYERS_SELECT, (k_layers_select<COMP, NT>),
                dim3((unsigned)(nmid + ctx->nbatched), (unsigned)A.n), dim3(1024), 0, S, nlong, nmid);
-    } else if (together && ctx->short_lists && ctx->t != 0) {
-      // (a run's first step has no lists and goes through the layers themselves: 1024 threads)
-      // as many threads as let all workgroups be resident at once (n = 64: 768 of them 106.3 us per step with 256 threads,
-      // 105.4 with 512; 2,624 of them 120.8 with 256, 129.9 with 512; 1024 threads 110.6 and 147.1)
+    } else if (together && ctx->short_lists && ctx->lists_begun && (int64_t)A.n * ctx->nbatched > 512) {
+      // (a context's first step has no lists and goes through the layers themselves: 1024 threads)
+      // 1024 threads where the chip holds all of them at once (512), then 512 where it holds them in three turns (1,024 at
+      // once), then 256.  A step whose guesses fail scans the layers with those threads: fewer make the select of a list
+      // cheaper and that step dearer.  us per step | such a step; layers up to 10,240 in registers and longer ones scanned
+      // by 1024 threads, an entry at a time; and lists with 256, 512, 1024 threads:
+      //   n = 64, 1 of 20,000, 40 of 4,000 (2,624)              88 | 173    75 | 239    83 | 165    94 | 140
+      //   n = 64, 1 of 20,000, 40 of 3,500 to 10,000 (2,624)   125 | 226   111 | 293   118 | 215   129 | 191
+      //   n = 64, 40 of 36,864 (2,560)                         559 | 1034  499 | 1143  500 | 1022  508 | 990
+      //   n = 64, 10 of 100,000, 50 of 5,000 (3,840)           452 | 975   428 | 884   441 | 847   455 | 814
+      //   n = 64, 1 of 500,000, 200 of 5,000 (12,864)          521 | 1719  501 | 1605  544 | 1076  602 | 894
+      //   n = 8, the same (1,608)                               83 | 606    76 | 817    73 | 468    82 | 324
+      //   n = 64, 65 layers (768)                              123 | 229   102 | 281   102 | 219   106 | 184
+      //   n = 8, 65 layers (96)                                 37 | 102    30 | 152    29 | 102    28 | 79
+      //   n = 64, 3 of 300,000 (192)                           331 | 1054  314 | 966   314 | 696   313 | 603
+      //   n = 8, 1 of 20,000, 40 of 4,000 (328)                 31 | 67     21 | 154    21 | 99     21 | 72
       if constexpr (COMP == Q_TOPK) {
         const dim3 rgrid((unsigned)A.n, (unsigned)ctx->nbatched);
-        if ((int64_t)A.n * ctx->nbatched > 1024)
+        if ((int64_t)A.n * ctx->nbatched > 3072)
           LAUNCH(ctx, KID_SEL_REFINE, (k_sel_refine<COMP, true, false, 256>), rgrid, dim3(256), 0, Q);
         else
           LAUNCH(ctx, KID_SEL_REFINE, (k_sel_refine<COMP, true, false, 512>), rgrid, dim3(512), 0, Q);
@@ -1642,6 +1655,7 @@ int gossip_layers_sparse(choco_ctx* ctx, const Args& F) {
       LAUNCH(ctx, KID_SEL_REFINE, (k_sel_refine<COMP, true>), dim3((unsigned)A.n, (unsigned)ctx->nbatched), dim3(1024),
              0, Q);
     }
+    ctx->lists_begun = true;
     // top_a with several long layers: a layer's select (a few small launches that wait on
     // memory) goes to the second stream and runs beside the next layer's pass over the rows
     const bool overlap = COMP == Q_TOPK && ctx->overlap_long && !ctx->profiling && ctx->launch_stream == ctx->stream;
@@ -2106,6 +2120,7 @@ int choco_init(const choco_config* cfg, float* x_dev, void* workspace_dev, size_
   ctx->batched_nvec = ctx->mid_nvec = 0;
   ctx->nbatched_mid = 0;
   ctx->short_lists = true;
+  ctx->lists_begun = false;
   int nsolo = 0;
   for (size_t b = 0; b < ctx->long_layers.size(); ++b) {
     LongLayer& B = ctx->long_layers[b];

@@ -2163,10 +2163,30 @@ __device__ __forceinline__ void row_entry(const Args& A, int i, uint32_t t, uint
 
 // Visit every entry of the domain (ROW: the whole row; else the concatenated candidate
 // sub-lists, pre = their prefix offsets in LDS, total entries) with f(a, idx).  All threads
-// of the block take part; list entries are fetched eight per thread at a time.
-template <int COMP, bool ROW, class F>
+// of the block take part; list entries are fetched eight per thread at a time, and so are those of a long layer (BATCH),
+// whose select has 256 or 512 threads where there are many (us of a step whose guesses fail, one at a time | eight: 2^19
+// entries, n = 8, 1024 threads 672 | 297; 1 of 500,000 and 200 of 5,000, n = 64, 256 threads 4081 | 1596, 512 2409 | 1076;
+// a workgroup's 256-entry turns cost 80 ns each, in issue: more in flight would not help).
+template <int COMP, bool ROW, bool BATCH, class F>
 __device__ __forceinline__ void for_each_entry(const Args& A, int i, const uint32_t* pre, uint32_t total, F f) {
-  if (ROW) {
+  if (ROW && COMP == Q_TOPK && BATCH) {   // (no layer table defers the local update of top_a)
+    const float *const x = A.X + (int64_t)i * A.ld, *const xhat = A.Xhat + (int64_t)i * A.ld;
+    const uint32_t d = (uint32_t)A.d;
+    for (uint32_t base = (uint32_t)A.e_lo; base < d; base += blockDim.x * 8u) {
+      float v[8], h[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const uint32_t p = base + (uint32_t)u * blockDim.x + threadIdx.x, at = p < d ? p : d - 1u;
+        v[u] = x[at];
+        h[u] = xhat[at];
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const uint32_t p = base + (uint32_t)u * blockDim.x + threadIdx.x;
+        if (p < d) f(__float_as_uint(v[u] - h[u]), p);
+      }
+    }
+  } else if (ROW) {
     for (uint32_t t = (uint32_t)A.e_lo + threadIdx.x; t < (uint32_t)A.d; t += blockDim.x) {
       uint32_t a, idx;
       row_entry<COMP>(A, i, t, a, idx);
@@ -2430,7 +2450,7 @@ __device__ __forceinline__ void emit_with_zeros(const Args& A, int i, const uint
 
 // Digit-by-digit radix select over the composite keys of the candidate list (ROW = false)
 // or of the row itself (ROW = true: the list is not good); emits the kept entries, marks
-// them and places the next guess.  All threads of a 1024-thread block.
+// them and places the next guess.  All threads of a block of 256 at least.
 template <int COMP, bool ROW, bool ONEPASS, bool BATCH>
 __device__ void refine_and_emit(const Args& A, int i, const uint32_t* pre, uint32_t total, uint32_t* h,
                                 uint32_t* grp, uint64_t* s_prefix, uint32_t* s_need, uint32_t* s_digit,
@@ -2440,6 +2460,7 @@ __device__ void refine_and_emit(const Args& A, int i, const uint32_t* pre, uint3
   int last = 0;
   bool done = false;
   uint32_t floor_key = 0;
+  uint32_t tied = 0, tied_kept = 0;   // entries that hold the threshold key, and how many of them are kept
   for (int level = 0; level < 6 && !done; ++level) {
     for (int b = threadIdx.x; b < kBins; b += blockDim.x) h[b] = 0;
     __syncthreads();
@@ -2447,7 +2468,7 @@ __device__ void refine_and_emit(const Args& A, int i, const uint32_t* pre, uint3
     const int scur = Digits<COMP>::shift(level);
     const int sprev = level > 0 ? Digits<COMP>::shift(level - 1) : 63;
     const uint32_t mask = (1u << Digits<COMP>::bits(level)) - 1u;
-    for_each_entry<COMP, ROW>(A, i, pre, total, [&](uint32_t a, uint32_t idx) {
+    for_each_entry<COMP, ROW, BATCH>(A, i, pre, total, [&](uint32_t a, uint32_t idx) {
       const uint64_t K = Digits<COMP>::composite(a, idx);
       // level 0: every entry takes part (nothing of the composite lies above digit 0)
       const bool match = level == 0 ? true : ((K >> sprev) == prefix);
@@ -2467,6 +2488,10 @@ __device__ void refine_and_emit(const Args& A, int i, const uint32_t* pre, uint3
     const uint32_t digit = *s_digit, above = *s_above;
     const uint32_t in_digit = h[digit];
     const uint32_t need = *s_need - above;
+    if (level == 2) {   // (the third digit ends the key)
+      tied = in_digit;
+      tied_kept = need;
+    }
     __syncthreads();
     if (threadIdx.x == 0) {
       *s_prefix = (level == 0 ? 0ull : (prefix << Digits<COMP>::bits(level))) | (uint64_t)digit;
@@ -2478,9 +2503,9 @@ __device__ void refine_and_emit(const Args& A, int i, const uint32_t* pre, uint3
   }
   const uint64_t kstar = *s_prefix << Digits<COMP>::shift(last);
   // emit every entry with composite >= kstar
-  for_each_entry<COMP, ROW>(A, i, pre, total, [&](uint32_t a, uint32_t idx) {
+  for_each_entry<COMP, ROW, BATCH>(A, i, pre, total, [&](uint32_t a, uint32_t idx) {
     if (Digits<COMP>::composite(a, idx) >= kstar) {
-      if (scal) atomicMin(&tie->least, (unsigned long long)Digits<COMP>::composite(a, idx));
+      if (scal && last < 2) atomicMin(&tie->least, (unsigned long long)Digits<COMP>::composite(a, idx));
       const uint32_t slot = atomicAdd(s_emit, 1u);
       if (slot < (uint32_t)A.k) {
         A.sel_idx[(int64_t)i * A.sel_stride + slot] = A.idx_base + (int32_t)idx;
@@ -2491,10 +2516,19 @@ __device__ void refine_and_emit(const Args& A, int i, const uint32_t* pre, uint3
   });
   __syncthreads();
   publish_bitmap(A, i, lbits);
-  if (scal) {   // (kstar may lie below the k-th key where nothing lies between)
-    for_each_entry<COMP, ROW>(A, i, pre, total, [&](uint32_t a, uint32_t idx) { tie->add<COMP>(a, idx, tie->least); });
-    __syncthreads();
-    if (threadIdx.x == 0) tie->publish(scal, tie->least, !ROW);
+  if (COMP == Q_TOPK && scal) {
+    if (last < 2) {   // all that share the digits found are kept, and kstar may lie below the least key of them
+      for (uint32_t slot = threadIdx.x; slot < (uint32_t)A.k; slot += blockDim.x)
+        if (Digits<COMP>::key32(__float_as_uint(A.sel_val[(int64_t)i * A.sel_stride + slot])) == (uint32_t)(tie->least >> 32))
+          atomicAdd(&tie->kept, 1u);
+      __syncthreads();
+      tied = tied_kept = tie->kept;
+    }
+    if (threadIdx.x == 0) {
+      tie->equal = tied;
+      tie->kept = tied_kept;
+      tie->publish(scal, last < 2 ? tie->least : kstar, !ROW);
+    }
   }
   __syncthreads();
   reset_lists(A, i);

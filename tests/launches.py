@@ -70,6 +70,9 @@ class Context:
         _stub.stub_clear()
         return self._launches(self.B.lib().choco_step(self.ctx, self.gp, 0.1))
 
+    def set_step(self, t):
+        assert self.B.lib().choco_set_step(self.ctx, t) == self.B.OK
+
     def step_momentum(self):
         _stub.stub_clear()
         return self._launches(self.B.lib().choco_step_momentum(self.ctx, self.gp, self.mp, 0.1, 0.9, 1e-4))

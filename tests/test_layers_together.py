@@ -67,6 +67,47 @@ for name, n, more in (("short", 8, [100]), ("none", 8, []), ("none", 64, [])):
         assert [x[1:] for x in launches if x[0].startswith("k_layers_pass")] == [[grid, "256x1x1"]] * 2, name
 
 
+def test_threads_of_the_select():
+    """1024 in a context's first step, whatever its step counter, and for up to 512 workgroups; 512 for up to 3,072, then 256."""
+    out = recorded("""
+out = {}
+for name, n, mids, t0 in (("512", 64, 7, 0), ("513", 27, 18, 0), ("3072", 64, 47, 0), ("3073", 7, 438, 0), ("resumed", 64, 47, 1000)):
+    t = synth.layer_table([300000] + [3100] * mids, fraction=0.0015)
+    c = Context(n, synth.layers_dim(t), B.Q_TOPK, layers=t)
+    c.set_step(t0)
+    out[name] = [[x[1:3] for x in c.step() if x[0].startswith("k_sel_refine")] for _ in range(3)]
+    c.close()
+""")
+    for name, threads, grid in (("512", 1024, "64x8x1"), ("513", 512, "27x19x1"), ("3072", 512, "64x48x1"), ("3073", 256, "7x439x1"),
+                                ("resumed", 512, "64x48x1")):
+        assert out[name] == [[[grid, "%dx1x1" % t]] for t in (1024, threads, threads)], (name, out[name])
+
+
+@pytest.mark.gpu
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("n,spread", [(64, 2.0 ** -1), (64, 2.0 ** -5), (64, 0.0), (20, 2.0 ** -3)])
+def test_failed_guesses_and_ties_with_few_threads(n, spread):
+    """Selects of 256 threads (512 with 20 workers): values of few magnitudes, steps whose size jumps (layers scanned, lists
+    beyond what the threads hold), and a run that is resumed at another step."""
+    lengths = [20000, 12000] + [3073, 3100, 3074, 3200] * 11 + [10240, 5000, 4096, 9216, 100]
+    layers = synth.layer_table(lengths, fraction=0.015)
+    d, rng = synth.layers_dim(layers), np.random.default_rng(5)
+
+    def values():
+        v = rng.standard_normal((n, d)).astype(np.float32)
+        return np.round(v / np.float32(spread)) * np.float32(spread) if spread else v
+
+    pair = Pair(values(), synth.ring_csr(n), 0.25, seed=3, compressor=binding.Q_TOPK, layers=layers)
+    pair.gpu.set_step(1000)
+    pair.ref.t = 1000
+    scanned = []
+    for t, lr in enumerate((0.5, 0.5, 0.25, 2.0, 0.5, 64.0, 0.5, 0.0)):
+        pair.check(pair.step(values(), lr), tag="%d workers, %g, step %d" % (n, spread, t))
+        scanned.append(pair.gpu.layer_scalars()[:, :-1, 3] == 0)
+    assert scanned[0].all() and scanned[5].mean() > 0.5 and any(0 < s.mean() < 0.5 for s in scanned[1:5])
+    pair.close()
+
+
 def workspace(n, lengths, fraction, silent=()):
     start, length, k = synth.layer_table(lengths, fraction=fraction)
     k[list(silent)] = 0
