@@ -233,7 +233,9 @@ int choco_last_scalars(choco_ctx *ctx, double *scalars_host);
    (n * nlayers * 4, worker-major) from the last step.  SIGN: {||v_l||_1, scale, 0, 0};
    QSGD: {sum v_l^2, ||v_l||_2, s/||v_l||_2, ||v_l||_2/(tau_l s)}; TOPK/RANDK: {threshold
    key, entries kept at the threshold key, entries holding that key, 1 if the guessed
-   bracket held the threshold (or k reaches its zeros) and 0 if the whole layer was searched}; for a layer above
+   bracket or list held the threshold (or k reaches its zeros) and 0 if the whole layer was searched}; the key is
+   that of the last kept entry, but where all entries that hold it are kept and the layer is selected in
+   registers it may lie lower, above that of any entry not kept (the counts are of that key); for a layer above
    CHOCO_MAX_LAYER_LEN {threshold key, 0, 0, 0 if the select had to scan the layer itself
    and 1 otherwise}.  With
    layers, choco_last_selection returns sum(layer_k) pairs per worker, layer after layer,

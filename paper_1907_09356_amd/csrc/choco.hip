@@ -35,8 +35,8 @@ struct SelectPlan {
   bool fallback_chain;                 // long rows: histogram passes repair a failed guess (else a row scan)
 };
 
-// A layer too long for the register-resident layer kernel: it takes the select chain of the
-// whole-vector path on its own piece of the rows.
+// A layer too long for the register-resident layer kernel, or one that goes through lists all the same (mids_in_lists):
+// it takes the select chain of the whole-vector path on its own piece of the rows.
 struct LongLayer {
   int32_t start, len, k, sel_base, id;
   SelectPlan plan;
@@ -119,7 +119,7 @@ struct choco_ctx {
   bool layers_generic;    // ... on a table that is not aligned (see layers_aligned): no pass carries the local update
   int nmid, nsmall;       // layers (by falling length, after the long ones) that take a 1024- / a 256-thread workgroup
   SelectPlan plan;        // whole-vector top_a / random_a
-  std::vector<LongLayer> long_layers;   // top_a / random_a layer by layer: layers above CHOCO_MAX_LAYER_LEN
+  std::vector<LongLayer> long_layers;   // top_a / random_a layer by layer: see LongLayer
   const LongSel* long_tab;   // device copy of the batched ones' LongSel, in the order of long_layers
   int nbatched;           // how many those are, and the 4-vectors of the longest of them
   int32_t batched_nvec;
@@ -166,7 +166,7 @@ struct Layout {
       chunk_layer, planes, ovf_ring, ovf_pos, wire_rank, wire_word_off, wire_plane_off, sel_idx2, bitmap2, keptmap2, layer_scal2, qv, recs, rec_cols, ulps, uneven, onepass, mpart, total;
   int64_t wire_words, wire_plane_words;   // layer by layer: words of a worker's message / of one bit plane
   int32_t ngroup_items;
-  uint32_t cand_cap, seg_cap, bin_cap;
+  uint32_t bin_cap;
   int64_t bitmap_words;
   bool multipart;
   int32_t select_sets;   // copies of the select scratch (candidate lists, histograms, short list)
@@ -599,8 +599,8 @@ Layout make_layout(const choco_config& c, int32_t nnz, bool one_pass, bool list_
   const size_t state = (size_t)c.n * (size_t)ld * sizeof(float);
   const bool sparse = is_sparse(c.compressor);
   const bool layered = c.nlayers > 0;
-  // selects by guessed threshold: the whole row, or every long layer in turn (they share the
-  // candidate lists and histograms, each has control blocks of its own)
+  // selects by guessed threshold: the whole row, or every long layer (each with candidate lists and
+  // control blocks of its own)
   int64_t list_end = 0;
   const std::vector<LongLayer> longs = long_layers_of(c, list_mids, &list_end);
   const bool guessed = sparse && (!layered || !longs.empty());
@@ -624,18 +624,13 @@ Layout make_layout(const choco_config& c, int32_t nnz, bool one_pass, bool list_
   L.chunk_sums = take(dense_stat && (c.order == CHOCO_ORDER_MIX_THEN_COMPRESS || one_pass)
                           ? (size_t)c.n * (size_t)L.nchunks * sizeof(double) : 0);
   L.group_sums = take(dense_stat ? (size_t)c.n * (size_t)L.ngroups * sizeof(double) : 0);
-  int64_t cap = 0, seg_cap = 0;
   bool multipart = false;
   size_t part_sets = 0;
   for (const SelectPlan& P : plans) {
-    cap = std::max<int64_t>(cap, P.cand_cap);
-    seg_cap = std::max<int64_t>(seg_cap, P.seg_cap);
     multipart = multipart || P.multipart;
     part_sets += P.multipart ? 1 : 0;
     L.bin_cap = std::max(L.bin_cap, P.bin_cap);
   }
-  L.cand_cap = (uint32_t)cap;
-  L.seg_cap = (uint32_t)seg_cap;
   // a set of select scratch per long layer: the layers that share launches are selected at the
   // same time, and the select of one that has launches of its own can run (top_a, on the
   // library's second stream) beside the next layer's pass over the rows

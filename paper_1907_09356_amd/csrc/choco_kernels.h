@@ -538,8 +538,8 @@ __device__ __forceinline__ double wave_tree_sum(double t) {
 
 // Inclusive sum over the lanes up to this one, by data-parallel-primitive moves (rows of 16, then across); all 64
 // lanes call it.  (Six steps of the vector unit; through LDS each step is a trip that waits for the one before, and the
-// select waits for several scans in a row: n = 64, d = 270 k, 1 % kept 95.7 -> 93.0 us per step, n = 32, d = 3 M in the
-// printed order 382.8 -> 382.1, n = 8, d = 28 M 675.6 -> 673.2.)
+// select waits for several scans in a row: n = 64, d = 270 k, 1 % kept 95.7 -> 93.0 us per step; n = 32, d = 3 M in the
+// printed order 382 and n = 8, d = 28 M 674 either way.)
 __device__ __forceinline__ uint32_t wave_scan(uint32_t v) {
   auto moved = [](uint32_t x, auto ctrl, auto rows) {
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, decltype(ctrl)::value, decltype(rows)::value, 0xF, false);
@@ -2539,7 +2539,7 @@ __device__ void refine_and_emit(const Args& A, int i, const uint32_t* pre, uint3
 // (index, value) pairs and of the kept-entry map, next guess.  Fast path: an LDS
 // histogram of the candidates by their distance above the guess tells which bin holds
 // the k-th largest key; everything above that bin is emitted as it is and the few
-// entries inside it are ranked against each other in LDS (lists of up to 8192 entries
+// entries inside it are ranked against each other in LDS (lists of up to eight entries per thread
 // stay in registers between the two sweeps).  If that bin is crowded (ties) the
 // digit-by-digit select runs on the list; if the list itself is not good, on the row.
 // grid n, block 1024, dynamic LDS = the worker's bitmap (short rows) or nothing.
@@ -2611,7 +2611,7 @@ __device__ __forceinline__ void refine_row(const Args& A, int i, RefineShared& s
   auto entry_at = [&](uint32_t f) -> uint2 { return list_entry(A, i, pre, f); };
   auto bin_of = [&](uint32_t a) -> uint32_t { return cand_bin<COMP>(a, guess, shift); };
   // sweep 1: histogram of the candidates by their distance above the guess (eight
-  // entries per thread in flight; a list of up to 8192 entries stays in registers)
+  // entries per thread in flight; a list of up to that many stays in registers)
   const bool fetched = SPECULATE && s_short != 0u;   // the entries fetched above are the whole list
   const bool resident = fetched || total <= THREADS * 8u;
   if (fetched) {
