@@ -183,7 +183,7 @@ def test_parity_in_a_workspace_without_the_lists(monkeypatch):
     (5, "generic", "step", 0.06), (33, "aligned", "momentum", 0.06), (12, "aligned", "printed", 0.06), (64, "many", "step", 0.01),
     (64, "many", "printed", 0.002), (5, "no short", "step", 0.02), (33, "no short", "momentum", 0.01), (64, "no short", "printed", 0.02)])
 def test_parity_where_the_kinds_meet(n, table, form, fraction):
-    """Lists of 512 threads (256 with more than 1,024 of them), at 6 % registers."""
+    """Lists through selects of 1024 threads (512 with more than 512 of them), at 6 % registers."""
     edges = EDGES if table != "many" else EDGES + [3073, 3074, 3500, 4000, 4096, 4097, 5000, 6144, 7000, 8191]
     if table == "no short":
         edges = [x for x in EDGES if x > 3072] + [3073, 3074, 4096, 4097, 7168]
