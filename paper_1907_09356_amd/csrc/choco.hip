@@ -1634,7 +1634,7 @@ int gossip_layers_sparse(choco_ctx* ctx, const Args& F) {
       //   n = 64, 40 of 36,864 (2,560)                         559 | 1034  499 | 1143  500 | 1022  508 | 990
       //   n = 64, 10 of 100,000, 50 of 5,000 (3,840)           452 | 975   428 | 884   441 | 847   455 | 814
       //   n = 64, 1 of 500,000, 200 of 5,000 (12,864)          521 | 1719  501 | 1605  544 | 1076  602 | 894
-      //   n = 8, the same (1,608)                               83 | 606    76 | 817    73 | 468    82 | 324
+      //   n = 8, the same (1,608)                               83 | 606    76 | 817    73 | 504    82 | 324
       //   n = 64, 65 layers (768)                              123 | 229   102 | 281   102 | 219   106 | 184
       //   n = 8, 65 layers (96)                                 37 | 102    30 | 152    29 | 102    28 | 79
       //   n = 64, 3 of 300,000 (192)                           331 | 1054  314 | 966   314 | 696   313 | 603

@@ -108,6 +108,30 @@ def test_failed_guesses_and_ties_with_few_threads(n, spread):
     pair.close()
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,lengths,start0", [(9, [20000, 3073, 4096, 10240, 9216, 100, 1 << 19], 0), (33, [12000, 4096, 5000, 3333], 0),
+                                              (2, [1 << 21, 700000], 3), (2, [1 << 21, 5000], 0)])
+def test_layers_of_one_magnitude(n, lengths, start0):
+    """Constant layers that get no gradients: every step scans them, all entries in one bin of each digit, and the cut is by the
+    index; long layers up to the 2^21 entries (and three before them) below which the index's first digit is known."""
+    start, length, k = synth.layer_table(lengths, fraction=0.01)
+    k = np.minimum(k, 700)
+    layers = (np.asarray(start) + start0, length, k)
+    d = int(layers[0][-1] + length[-1])
+    rng = np.random.default_rng(n)
+    X0 = np.ones((n, d), dtype=np.float32)
+    X0[:, ::3] = -1.0
+    X0[0, rng.integers(0, d, 7)] = 1.5
+    pair = Pair(X0, synth.ring_csr(n), 0.05, seed=3, compressor=binding.Q_TOPK, layers=layers)
+    g = np.zeros((n, d), dtype=np.float32)
+    for t in range(5):
+        if t == 3:
+            g[:, rng.integers(0, d, 50)] = 2.0
+        pair.check(pair.step(g, 0.25), tag="%d workers, %s, step %d" % (n, lengths, t))
+    assert np.any(pair.gpu.layer_scalars()[:, :, 3] == 0)
+    pair.close()
+
+
 def workspace(n, lengths, fraction, silent=()):
     start, length, k = synth.layer_table(lengths, fraction=fraction)
     k[list(silent)] = 0
