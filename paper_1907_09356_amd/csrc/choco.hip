@@ -424,7 +424,7 @@ int64_t list_entries(int32_t n, uint32_t seg_cap) {
 }
 
 // Such a layer has a sub-list per chunk, ten at most: several share the kSegs sub-lists of one piece, those of like capacity,
-// and all get the largest capacity among them.  The entries all of them take; a layer's first sub-list goes to first_of.
+// and all get the largest capacity among them.  Returns the entries all of them take.
 // (Workspace of 40 layers of 4,000 beside one of 20,000, 1 % kept, n = 64, a state array of 46 MB: 165 MB with kSegs each, 92 so.)
 struct MidLists {
   int64_t span;
